@@ -154,16 +154,24 @@ __global__ __launch_bounds__(16 * R) void bn_finalize_kernel(const S *__restrict
 }
 
 // evaluation mode: the affine map from the running statistics, times a scalar `s` (the test-time
-// scaling of a residual branch): scale = s*gamma/sqrt(rvar+eps), shift = s*(beta - rmean*gamma/sqrt(rvar+eps))
-__global__ __launch_bounds__(kThreads) void bn_eval_affine_kernel(const float *__restrict__ gamma, const float *__restrict__ beta,
-                                                                  const float *__restrict__ rmean, const float *__restrict__ rvar,
-                                                                  float eps, float s, float *__restrict__ scale,
-                                                                  float *__restrict__ shift, int C) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
-  const double k = (double)gamma[c] / sqrt((double)rvar[c] + (double)eps);
-  scale[c] = (float)((double)s * k);
-  shift[c] = (float)((double)s * ((double)beta[c] - (double)rmean[c] * k));
+// scaling of a residual branch): scale = s*gamma/sqrt(rvar+eps), shift = s*(beta - rmean*gamma/sqrt(rvar+eps)).
+// Every BN of a network in one launch (the table travels in the kernel arguments): one launch per BN, a few hundred
+// threads each, cost 4.7 us apiece at 70 BNs.
+constexpr int kEvalSegs = 56;
+struct EvalTable {
+  BnEval seg[kEvalSegs];
+  int first_wg[kEvalSegs + 1];
+  int nseg;
+};
+__global__ __launch_bounds__(kThreads) void bn_eval_affine_kernel(EvalTable t, float eps) {
+  int i = 0;
+  while (i + 1 < t.nseg && (int)blockIdx.x >= t.first_wg[i + 1]) ++i;
+  const BnEval &b = t.seg[i];
+  const int c = ((int)blockIdx.x - t.first_wg[i]) * kThreads + threadIdx.x;
+  if (c >= b.C) return;
+  const double k = (double)b.gamma[c] / sqrt((double)b.rvar[c] + (double)eps);
+  b.scale[c] = (float)((double)b.s * k);
+  b.shift[c] = (float)((double)b.s * ((double)b.beta[c] - (double)b.rmean[c] * k));
 }
 
 // ---- forward apply -------------------------------------------------------------------------------
@@ -478,12 +486,23 @@ int bn_finalize(const float *stats, StatParts sp, int64_t M, int C, const BnBufs
   return RESIST_OK;
 }
 
-int bn_eval_affine(int C, const BnBufs &b, float eps, float s, hipStream_t st) {
-  if (C < 1) return set_error(RESIST_ESHAPE, "bn_eval_affine: C=%d", C);
-  prof::Scope ps("bn_eval_affine", 0, 24.0 * C, st);
-  hipLaunchKernelGGL(bn_eval_affine_kernel, dim3((C + kThreads - 1) / kThreads), dim3(kThreads), 0, st, b.gamma, b.beta, b.rmean,
-                     b.rvar, eps, s, b.scale, b.shift, C);
-  RESIST_CHECK_LAUNCH("bn_eval_affine");
+int bn_eval_affine(const std::vector<BnEval> &items, float eps, hipStream_t st) {
+  for (size_t i = 0; i < items.size(); i += kEvalSegs) {
+    EvalTable t{};
+    int wg = 0, channels = 0;
+    for (size_t j = i; j < items.size() && t.nseg < kEvalSegs; ++j) {
+      const BnEval &b = items[j];
+      if (b.C < 1) return set_error(RESIST_ESHAPE, "bn_eval_affine: C=%d", b.C);
+      t.first_wg[t.nseg] = wg;
+      t.seg[t.nseg++] = b;
+      wg += (b.C + kThreads - 1) / kThreads;
+      channels += b.C;
+    }
+    t.first_wg[t.nseg] = wg;
+    prof::Scope ps("bn_eval_affine", 0, 24.0 * channels, st);
+    hipLaunchKernelGGL(bn_eval_affine_kernel, dim3(wg), dim3(kThreads), 0, st, t, eps);
+    RESIST_CHECK_LAUNCH("bn_eval_affine");
+  }
   return RESIST_OK;
 }
 

@@ -131,8 +131,12 @@ int conv_check(const ConvGeom &g, int dt);
 // floats (capacity conv_stats_floats(g)); input of bn_finalize
 struct StatParts { int parts = 0; int rows = 0; };
 int64_t conv_stats_floats(const ConvGeom &g);
+// act (optional, test time): the value v as stored in y (y may then be NULL: nothing is stored there) goes on to
+// act->out = max(scale*v + shift [+ BN(res)], 0), the arithmetic of bn_apply, with the shortcut's own affine map
+// rscale, rshift (NULL: res is added as it is).  No statistics are taken then.
+struct EvalAct { void *out; const float *scale, *shift; const void *res = nullptr; const float *rscale = nullptr, *rshift = nullptr; };
 int conv_fwd(const ConvGeom &g, int dt, const void *x, const void *w, void *y, const void *addend, float *stats,
-             StatParts *stat_parts, hipStream_t st);
+             StatParts *stat_parts, hipStream_t st, const EvalAct *act = nullptr);
 // dx = dgrad(dy, wT) [+ addend]; wT is the [C][R][S][K] transpose made by prepare_filter.  relu_mask
 // (optional, indexed like dx): the output of the ReLU that produced the convolution's input; dx is set
 // to zero where it is not positive, i.e. the gradient leaves this kernel already taken through that ReLU
@@ -164,8 +168,10 @@ int conv_wgrad_static(const ConvGeom &g, int dt, const void *dy, const void *x, 
 // scratch of stem_wgrad_scratch_floats floats.  Limits: C <= 4, K a multiple of 16 up to 128, kpad <= 160.
 StatParts stem_stat_parts(int N, int C, int H, int W, int K, int R, int stride, int pad, int P, int Q, int kpad);
 int64_t stem_wgrad_scratch_floats(int N, int C, int H, int W, int K, int R, int stride, int pad, int P, int Q, int kpad);
+// act (test time): as for conv_fwd, without res
 int stem_conv_fwd(int dt, const float *x_nchw, const void *wpad, void *y, float *stats, StatParts *stat_parts, int N, int C,
-                  int H, int W, int K, int R, int stride, int pad, int P, int Q, int kpad, hipStream_t st);
+                  int H, int W, int K, int R, int stride, int pad, int P, int Q, int kpad, hipStream_t st,
+                  const EvalAct *act = nullptr);
 int stem_conv_wgrad(int dt, const void *dy, const float *x_nchw, float *dwpad, float *partial, int N, int C, int H, int W,
                     int K, int R, int stride, int pad, int P, int Q, int kpad, hipStream_t st);
 // out[i] = sum over z < splits of part[z*n4 + i] (float4 elements), fixed order (conv.hip)
@@ -186,8 +192,10 @@ int64_t bn_scratch_doubles(int C);   // partial-sum scratch for one bn_finalize 
 // affine map of bn_apply, and the running statistics
 int bn_finalize(const float *stats, StatParts parts, int64_t M, int C, const BnBufs &b, float eps, float momentum,
                 double *scratch, hipStream_t st);
-// evaluation mode: scale/shift from the running statistics, both multiplied by s
-int bn_eval_affine(int C, const BnBufs &b, float eps, float s, hipStream_t st);
+// evaluation mode, all BNs of a network in one launch (or a few): scale/shift from the running statistics, both
+// multiplied by s
+struct BnEval { int C; const float *gamma, *beta, *rmean, *rvar; float s; float *scale, *shift; };
+int bn_eval_affine(const std::vector<BnEval> &items, float eps, hipStream_t st);
 // a = [relu]( scale*y + shift [+ res] )            res: raw tensor, or BN(res_y) if res_bn given
 int bn_apply(int dt, const void *y, int64_t M, int C, const BnBufs &b, const void *res,
              const BnBufs *res_bn, bool relu, void *a, hipStream_t st);

@@ -30,6 +30,8 @@ struct StemArgs {
   const float *x;      // [N][C][H][W]
   const void *wpad;    // forward: filter [K][kpad] in the compute type (zero columns past taps)
   void *y;             // forward: output [N][P][Q][K]
+  void *act;           // forward, test time: max(act_scale * y + act_shift, 0); y may then be NULL
+  const float *act_scale, *act_shift;
   float *stats;        // forward: [3][parts][K] shift, sum(y - shift), sum((y - shift)^2) per tile
   const void *dy;      // weight gradient: [N][P][Q][K]
   float *partial;      // weight gradient: [workgroups][K][kpad] partial sums
@@ -272,6 +274,11 @@ __global__ __launch_bounds__(256) void stem_fwd_kernel(StemArgs a) {
   const int rps = 256 / cvn;                 // pixels per pass
   const int cv = (threadIdx.x % cvn) * VEC, r0 = threadIdx.x / cvn;
   const int valid = a.RB * a.QB;
+  float asc[VEC], ash[VEC];
+  if (a.act) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) { asc[e] = a.act_scale[cv + e]; ash[e] = a.act_shift[cv + e]; }
+  }
   if (r0 < rps)
     for (int r = r0; r < valid; r += rps) {
       const int pr = r / a.QB, qc = r - pr * a.QB;
@@ -279,7 +286,16 @@ __global__ __launch_bounds__(256) void stem_fwd_kernel(StemArgs a) {
       float v[VEC];
 #pragma unroll
       for (int e = 0; e < VEC; ++e) v[e] = Cs[r * ldc + cv + e];
-      Vec<T>::store(y + pix * a.K + cv, v);
+      if (y) Vec<T>::store(y + pix * a.K + cv, v);
+      if (a.act) {   // the arithmetic of bn_apply_kernel on the value as stored
+        float o[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          o[e] = fmaf(as_stored<T>(v[e]), asc[e], ash[e]);
+          o[e] = o[e] > 0.f ? o[e] : 0.f;
+        }
+        Vec<T>::store(static_cast<T *>(a.act) + pix * a.K + cv, o);
+      }
     }
   if (!a.stats) return;
   // BN statistics of the tile: per channel a shift k (the tile's first pixel) and the sums of (y - k), (y - k)^2
@@ -517,11 +533,12 @@ int64_t stem_wgrad_scratch_floats(int N, int C, int H, int W, int K, int R, int 
 }
 
 int stem_conv_fwd(int dt, const float *x, const void *wpad, void *y, float *stats, StatParts *stat_parts, int N, int C, int H,
-                  int W, int K, int R, int stride, int pad, int P, int Q, int kpad, hipStream_t st) {
+                  int W, int K, int R, int stride, int pad, int P, int Q, int kpad, hipStream_t st, const EvalAct *act) {
   StemArgs a;
   RESIST_TRY(stem_args(N, C, H, W, K, R, stride, pad, P, Q, kpad, &a));
   if (stats && !stat_parts) return set_error(RESIST_EINVAL, "stem_conv_fwd: stats without stat_parts");
   a.x = x; a.wpad = wpad; a.y = y; a.stats = stats; a.parts = a.tiles;
+  if (act) { a.act = act->out; a.act_scale = act->scale; a.act_shift = act->shift; }
   stem_set_mode(a);
   if (stat_parts) { stat_parts->parts = a.tiles; stat_parts->rows = a.RB * a.QB; }
   int lds = dt == DT_BF16 ? stem_lds<__bf16>(a, false).total : stem_lds<float>(a, false).total;
@@ -532,7 +549,7 @@ int stem_conv_fwd(int dt, const float *x, const void *wpad, void *y, float *stat
   if (lds > kStemLdsLimit) return set_error(RESIST_ESHAPE, "stem convolution: tile needs %d bytes of LDS", lds);
   const double flops = 2.0 * N * P * Q * K * a.taps;
   prof::Scope ps(dt == DT_BF16 ? "stem_conv_bf16_fwd" : "stem_conv_f32_fwd", flops,
-                 4.0 * N * C * H * W + (double)esize(dt) * ((double)N * P * Q * K + (double)K * kpad), st);
+                 4.0 * N * C * H * W + (double)esize(dt) * ((double)N * P * Q * K * ((y ? 1 : 0) + (act ? 1 : 0)) + (double)K * kpad), st);
   const int ntiles = (a.K + 31) / 32;        // 1..4: K <= 128 was checked above
 #define RESIST_STEM_FWD(NTILES)                                                                                  \
   do {                                                                                                           \

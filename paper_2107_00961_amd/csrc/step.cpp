@@ -160,9 +160,9 @@ int64_t stem_stats_floats(const Net &net, int N, int kpad) {
   return (int64_t)3 * sp.parts * net.d.width[0];
 }
 int stem_forward(const Net &net, int dt, int N, int kpad, const float *x, const void *wpad, void *y, float *stats,
-                 StatParts *parts, hipStream_t st) {
+                 StatParts *parts, hipStream_t st, const EvalAct *act = nullptr) {
   return stem_conv_fwd(dt, x, wpad, y, stats, parts, N, net.d.in_c, net.d.in_h, net.d.in_w, net.d.width[0], net.stem_rs,
-                       net.stem_stride, net.stem_pad, net.stem_h, net.stem_w, kpad, st);
+                       net.stem_stride, net.stem_pad, net.stem_h, net.stem_w, kpad, st, act);
 }
 
 ConvLayer make_conv(const BlockLayout &L, int layer, int N, int H, int W, int C, int K, int R, int stride, int pad) {
@@ -332,8 +332,9 @@ int build_plan(const resist_model_desc *desc, const int32_t *blocks, int32_t nbl
   return RESIST_OK;
 }
 
-// ---- test-time forward: nothing is kept, so every convolution output goes to one shared buffer and
-// the activations alternate between two
+// ---- test-time forward: nothing is kept, so the activations alternate between two buffers.  Every convolution
+// applies the BN behind it (and the shortcut and the ReLU) to its tile before it is stored, so of the convolution
+// outputs only a shortcut's exists in memory; the affine maps of all BNs are made by one launch up front.
 struct ForwardPlan {
   Net net;
   std::vector<BlockLayout> layouts;
@@ -342,7 +343,6 @@ struct ForwardPlan {
   void *wpad = nullptr, *stem_pool = nullptr;
   uint8_t *stem_argmax = nullptr;
   std::vector<BlockPlan> blocks;
-  float *affine[2] = {nullptr, nullptr};   // scale/shift scratch of the branch BN and the shortcut BN: [2][max_c] each
   float *pooled = nullptr, *dz = nullptr, *row_loss = nullptr;
   const void *feat = nullptr;
   int feat_hw = 0;
@@ -369,7 +369,6 @@ int build_forward_plan(const resist_model_desc *desc, const int32_t *blocks, int
   P->stem = make_conv(P->layouts[0], 0, N, net.stem_h, net.stem_w, P->kpad, K0, 1, 1, 0);
   if (stem_scratch_floats(net, N, P->kpad) == 0) return RESIST_ESHAPE;
   int64_t max_act = P->stem.M() * K0;
-  int max_c = K0;
   P->blocks.resize(nblocks);
   for (int i = 0; i < nblocks; ++i) {
     const BlockShape &bs = net.blocks[blocks[i]];
@@ -389,16 +388,19 @@ int build_forward_plan(const resist_model_desc *desc, const int32_t *blocks, int
     for (const ConvLayer &c : bp.convs) {
       RESIST_TRY(conv_check(c.g, net.d.compute_dtype));
       max_act = std::max<int64_t>(max_act, c.M() * c.g.K);
-      max_c = std::max(max_c, c.g.K);
     }
     if (bs.has_ds) RESIST_TRY(conv_check(bp.ds.g, net.d.compute_dtype));
     bp.out_elems = (int64_t)N * bs.h_out * bs.w_out * bs.c_out;
   }
   P->wpad = A.take_act((int64_t)K0 * P->kpad, es);
-  void *ybuf = A.take_act(max_act, es), *ydsbuf = A.take_act(max_act, es);
+  void *ydsbuf = A.take_act(max_act, es);
+  auto take_affine = [&](ConvLayer &c) {
+    c.scale = A.take<float>((int64_t)2 * c.g.K);
+    c.shift = c.scale + c.g.K;
+  };
   void *abuf[2] = {A.take_act(max_act, es), A.take_act(max_act, es)};
   void *obuf[2] = {A.take_act(max_act, es), A.take_act(max_act, es)};
-  P->stem.y = ybuf;
+  take_affine(P->stem);
   P->stem.a = obuf[0];
   const void *cur = obuf[0];
   int oi = 1;
@@ -415,13 +417,14 @@ int build_forward_plan(const resist_model_desc *desc, const int32_t *blocks, int
     for (size_t j = 0; j < bp.convs.size(); ++j) {
       ConvLayer &c = bp.convs[j];
       c.in = x;
-      c.y = ybuf;
+      take_affine(c);
       if (net.d.compute_dtype == DT_BF16) c.wlp = A.take_act((int64_t)c.g.K * c.g.R * c.g.S * c.g.C, es);
       if (j + 1 < bp.convs.size()) { c.a = abuf[j & 1]; x = c.a; }
     }
     if (bp.has_ds) {
       bp.ds.in = bp.in;
       bp.ds.y = ydsbuf;
+      take_affine(bp.ds);
       if (net.d.compute_dtype == DT_BF16) bp.ds.wlp = A.take_act((int64_t)bp.ds.g.K * bp.ds.g.C, es);
     }
     bp.out = obuf[oi];
@@ -431,8 +434,6 @@ int build_forward_plan(const resist_model_desc *desc, const int32_t *blocks, int
   P->feat = cur;
   const BlockShape &last = net.blocks[blocks[nblocks - 1]];
   P->feat_hw = last.h_out * last.w_out;
-  P->affine[0] = A.take<float>((int64_t)2 * max_c);
-  P->affine[1] = A.take<float>((int64_t)2 * max_c);
   P->pooled = A.take<float>((int64_t)N * net.head_c);
   P->dz = A.take<float>((int64_t)N * net.d.num_classes);
   P->row_loss = A.take<float>(N);
@@ -440,16 +441,9 @@ int build_forward_plan(const resist_model_desc *desc, const int32_t *blocks, int
   return RESIST_OK;
 }
 
-// running statistics and affine parameters of a BN inside a block buffer, scale/shift in `affine`
-BnBufs bn_eval_bufs(const ConvLayer &c, float *params, float *affine) {
-  BnBufs b{};
-  b.gamma = params + c.gamma_off;
-  b.beta = params + c.beta_off;
-  b.rmean = params + c.rmean_off;
-  b.rvar = params + c.rvar_off;
-  b.scale = affine;
-  b.shift = affine + c.g.K;
-  return b;
+// the evaluation-mode affine map of the BN behind a convolution, times s
+BnEval bn_eval_item(const ConvLayer &c, const float *params, float s) {
+  return BnEval{c.g.K, params + c.gamma_off, params + c.beta_off, params + c.rmean_off, params + c.rvar_off, s, c.scale, c.shift};
 }
 
 // ---- pre-activation networks (block_kind 2, 3) -------------------------------------------------------
@@ -1015,9 +1009,10 @@ struct PreForwardPlan {
   ConvGeom stem;
   void *wpad = nullptr;
   std::vector<PreBlock> blocks;
-  void *abuf = nullptr, *sc = nullptr;
-  float *affine = nullptr, *pooled = nullptr, *dz = nullptr, *row_loss = nullptr;
-  const void *feat_in = nullptr;
+  void *abuf[2] = {nullptr, nullptr}, *sc = nullptr;   // what the next convolution reads; a shortcut convolution's output
+  float *hscale = nullptr, *hshift = nullptr;          // affine map of the head's BN
+  float *pooled = nullptr, *dz = nullptr, *row_loss = nullptr;
+  void *feat = nullptr;
   int feat_hw = 0;
   int64_t bytes = 0;
 };
@@ -1040,7 +1035,6 @@ int build_preact_forward_plan(const resist_model_desc *desc, const int32_t *bloc
   P->stem = make_geom(N, net.stem_h, net.stem_w, P->kpad, K0, 1, 1, 0);
   if (stem_scratch_floats(net, N, P->kpad) == 0) return RESIST_ESHAPE;
   int64_t max_act = (int64_t)N * net.stem_h * net.stem_w * K0;
-  int max_c = std::max(K0, net.head_c);
   P->blocks.resize(nblocks);
   for (int i = 0; i < nblocks; ++i) {
     const BlockShape &bs = net.blocks[blocks[i]];
@@ -1067,10 +1061,11 @@ int build_preact_forward_plan(const resist_model_desc *desc, const int32_t *bloc
       // a copy of the filter in the compute type; the last unit's always (it carries the branch scale)
       if (net.d.compute_dtype == DT_BF16 || j + 1 == gs.size())
         un.wlp = A.take_act((int64_t)un.g.K * un.g.R * un.g.S * un.g.C, es);
+      un.scale = A.take<float>((int64_t)2 * un.g.C);
+      un.shift = un.scale + un.g.C;
       RESIST_TRY(conv_check(un.g, net.d.compute_dtype));
       max_act = std::max<int64_t>(max_act, (int64_t)N * un.g.P * un.g.Q * un.g.K);
       max_act = std::max<int64_t>(max_act, un.rows() * un.g.C);
-      max_c = std::max(max_c, std::max(un.g.C, un.g.K));
       pb.units.push_back(un);
     }
     pb.has_ds = bs.has_ds;
@@ -1081,31 +1076,29 @@ int build_preact_forward_plan(const resist_model_desc *desc, const int32_t *bloc
     }
   }
   P->wpad = A.take_act((int64_t)K0 * P->kpad, es);
-  // the residual stream alternates between two buffers, the branch between two more
+  // the residual stream alternates between two buffers, the activations the convolutions read between two more
+  // (every convolution applies the next BN and ReLU to its tile; a branch's inner outputs exist in that form only)
   void *ubuf[2] = {A.take_act(max_act, es), A.take_act(max_act, es)};
-  void *hbuf[2] = {A.take_act(max_act, es), A.take_act(max_act, es)};
-  P->abuf = A.take_act(max_act, es);
+  for (void *&p : P->abuf) p = A.take_act(max_act, es);
   P->sc = A.take_act(max_act, es);
   const void *cur = ubuf[0];
-  int ui = 1;
+  int ui = 1, ai = 0;
   for (PreBlock &pb : P->blocks) {
     pb.x = cur;
-    const void *u = cur;
-    for (size_t j = 0; j < pb.units.size(); ++j) {
-      PreUnit &un = pb.units[j];
-      un.u = u;
-      un.a = P->abuf;
-      un.h = j + 1 == pb.units.size() ? ubuf[ui] : hbuf[j & 1];
-      u = un.h;
+    for (PreUnit &un : pb.units) {
+      un.a = P->abuf[ai];
+      ai ^= 1;
     }
+    pb.units.back().h = ubuf[ui];
     pb.out = ubuf[ui];
     cur = pb.out;
     ui ^= 1;
   }
-  P->feat_in = cur;
+  P->feat = P->abuf[ai];
   const BlockShape &last = net.blocks[blocks[nblocks - 1]];
   P->feat_hw = last.h_out * last.w_out;
-  P->affine = A.take<float>((int64_t)2 * max_c);
+  P->hscale = A.take<float>((int64_t)2 * net.head_c);
+  P->hshift = P->hscale + net.head_c;
   P->pooled = A.take<float>((int64_t)N * net.head_c);
   P->dz = A.take<float>((int64_t)N * net.d.num_classes);
   P->row_loss = A.take<float>(N);
@@ -1139,39 +1132,45 @@ int forward_preact(const resist_model_desc *desc, const int32_t *blocks, int32_t
     }
     RESIST_TRY(prepare_filters(prep, dt, st));
   }
+  const int J = net.d.num_classes, CH = net.head_c;
+  const BlockLayout &HL = P.layouts[nslots - 1];
+  float *hp = params(nslots - 1);
+  std::vector<BnEval> affine;
+  for (PreBlock &pb : P.blocks)
+    for (PreUnit &un : pb.units) {
+      const float *pp = params(pb.slot);
+      affine.push_back(BnEval{un.g.C, pp + un.gamma_off, pp + un.beta_off, pp + un.rmean_off, pp + un.rvar_off, 1.f, un.scale, un.shift});
+    }
+  affine.push_back(BnEval{CH, hp + HL.off(T_GAMMA, 0), hp + HL.off(T_BETA, 0), hp + HL.off(T_RMEAN, 0), hp + HL.off(T_RVAR, 0), 1.f,
+                          P.hscale, P.hshift});
+  RESIST_TRY(bn_eval_affine(affine, eps, st));
   const int K0 = net.d.width[0];
   const int taps = net.stem_rs * net.stem_rs * net.d.in_c;
   RESIST_TRY(pad_rows(dt, params(0) + P.layouts[0].off(T_CONVW, 0), P.wpad, K0, taps, P.kpad, st));
-  RESIST_TRY(stem_forward(net, dt, N, P.kpad, x, P.wpad, const_cast<void *>(P.blocks[0].x), nullptr, nullptr, st));
-  for (PreBlock &pb : P.blocks) {
+  {
+    const PreUnit &first = P.blocks[0].units[0];
+    const EvalAct act{first.a, first.scale, first.shift};
+    RESIST_TRY(stem_forward(net, dt, N, P.kpad, x, P.wpad, const_cast<void *>(P.blocks[0].x), nullptr, nullptr, st, &act));
+  }
+  for (size_t bi = 0; bi < P.blocks.size(); ++bi) {
+    PreBlock &pb = P.blocks[bi];
     float *pp = params(pb.slot);
     const size_t n = pb.units.size();
     for (size_t j = 0; j < n; ++j) {
       PreUnit &un = pb.units[j];
-      BnBufs b{};
-      b.gamma = pp + un.gamma_off; b.beta = pp + un.beta_off; b.rmean = pp + un.rmean_off; b.rvar = pp + un.rvar_off;
-      b.scale = P.affine; b.shift = P.affine + un.g.C;
-      RESIST_TRY(bn_eval_affine(un.g.C, b, eps, 1.f, st));
-      RESIST_TRY(bn_apply(dt, un.u, un.rows(), un.g.C, b, nullptr, nullptr, true, un.a, st));
       if (j == 0 && pb.has_ds) {
         const void *wd = dt == DT_F32 ? (const void *)(pp + pb.ds_w_off) : pb.ds_wlp;
         RESIST_TRY(conv_fwd(pb.dsg, dt, un.a, wd, P.sc, nullptr, nullptr, nullptr, st));
       }
       const void *wf = un.wlp ? un.wlp : (const void *)(pp + un.w_off);
       const void *addend = j + 1 == n ? (pb.has_ds ? (const void *)P.sc : pb.x) : nullptr;
-      RESIST_TRY(conv_fwd(un.g, dt, un.a, wf, un.h, addend, nullptr, nullptr, st));
+      // the BN-ReLU of whoever reads this output: the next unit, the next block's first, or the head
+      const PreUnit *next = j + 1 < n ? &pb.units[j + 1] : bi + 1 < P.blocks.size() ? &P.blocks[bi + 1].units[0] : nullptr;
+      const EvalAct act{next ? next->a : P.feat, next ? next->scale : P.hscale, next ? next->shift : P.hshift};
+      RESIST_TRY(conv_fwd(un.g, dt, un.a, wf, un.h, addend, nullptr, nullptr, st, &act));
     }
   }
-  const int J = net.d.num_classes, CH = net.head_c;
-  const BlockLayout &HL = P.layouts[nslots - 1];
-  float *hp = params(nslots - 1);
-  BnBufs hb{};
-  hb.gamma = hp + HL.off(T_GAMMA, 0); hb.beta = hp + HL.off(T_BETA, 0);
-  hb.rmean = hp + HL.off(T_RMEAN, 0); hb.rvar = hp + HL.off(T_RVAR, 0);
-  hb.scale = P.affine; hb.shift = P.affine + CH;
-  RESIST_TRY(bn_eval_affine(CH, hb, eps, 1.f, st));
-  RESIST_TRY(bn_apply(dt, P.feat_in, (int64_t)N * P.feat_hw, CH, hb, nullptr, nullptr, true, P.abuf, st));
-  RESIST_TRY(avgpool_fwd(dt, P.abuf, P.pooled, N, P.feat_hw, CH, st));
+  RESIST_TRY(avgpool_fwd(dt, P.feat, P.pooled, N, P.feat_hw, CH, st));
   RESIST_TRY(fc_fwd_f32(P.pooled, hp + HL.off(T_FCW, 0), hp + HL.off(T_FCB, 0), logits_out, N, CH, J, st));
   if (labels) {
     RESIST_TRY(softmax_ce_f32(logits_out, labels, P.dz, P.row_loss, N, J, st));
@@ -1235,40 +1234,37 @@ extern "C" int resist_forward(const resist_model_desc *desc, const int32_t *bloc
   }
   auto filter = [&](const ConvLayer &c, const float *w) -> const void * { return dt == DT_F32 ? (const void *)w : c.wlp; };
   {
+    std::vector<BnEval> affine{bn_eval_item(P.stem, params(0), 1.f)};
+    for (size_t bi = 0; bi < P.blocks.size(); ++bi) {
+      BlockPlan &bp = P.blocks[bi];
+      for (size_t j = 0; j < bp.convs.size(); ++j)
+        affine.push_back(bn_eval_item(bp.convs[j], params(bp.slot), branch_scale && j + 1 == bp.convs.size() ? branch_scale[bi] : 1.f));
+      if (bp.has_ds) affine.push_back(bn_eval_item(bp.ds, params(bp.slot), 1.f));
+    }
+    RESIST_TRY(bn_eval_affine(affine, eps, st));
+  }
+  {
     ConvLayer &s = P.stem;
     const int K0 = net.d.width[0];
     const int taps = net.stem_rs * net.stem_rs * net.d.in_c;
     RESIST_TRY(pad_rows(dt, params(0) + s.w_off, P.wpad, K0, taps, P.kpad, st));
-    RESIST_TRY(stem_forward(net, dt, N, P.kpad, x, P.wpad, s.y, nullptr, nullptr, st));
-    BnBufs b = bn_eval_bufs(s, params(0), P.affine[0]);
-    RESIST_TRY(bn_eval_affine(K0, b, eps, 1.f, st));
-    RESIST_TRY(bn_apply(dt, s.y, s.M(), K0, b, nullptr, nullptr, true, s.a, st));
+    const EvalAct act{s.a, s.scale, s.shift};
+    RESIST_TRY(stem_forward(net, dt, N, P.kpad, x, P.wpad, nullptr, nullptr, nullptr, st, &act));
     if (net.d.stem_kind == 1)
       RESIST_TRY(maxpool_fwd(dt, s.a, P.stem_pool, P.stem_argmax, N, net.stem_h, net.stem_w, K0, net.body_h, net.body_w, st));
   }
-  for (size_t bi = 0; bi < P.blocks.size(); ++bi) {
-    BlockPlan &bp = P.blocks[bi];
+  for (BlockPlan &bp : P.blocks) {
     float *pp = params(bp.slot);
-    const float scale = branch_scale ? branch_scale[bi] : 1.f;
-    const size_t nc = bp.convs.size();
-    BnBufs bl{};
-    for (size_t j = 0; j < nc; ++j) {
-      ConvLayer &c = bp.convs[j];
-      RESIST_TRY(conv_fwd(c.g, dt, c.in, filter(c, pp + c.w_off), c.y, nullptr, nullptr, nullptr, st));
-      BnBufs b = bn_eval_bufs(c, pp, P.affine[0]);
-      RESIST_TRY(bn_eval_affine(c.g.K, b, eps, j + 1 == nc ? scale : 1.f, st));
-      if (c.a) RESIST_TRY(bn_apply(dt, c.y, c.M(), c.g.K, b, nullptr, nullptr, true, c.a, st));
-      else bl = b;
-    }
-    ConvLayer &last = bp.convs.back();
-    if (bp.has_ds) {
-      ConvLayer &d = bp.ds;
-      RESIST_TRY(conv_fwd(d.g, dt, d.in, filter(d, pp + d.w_off), d.y, nullptr, nullptr, nullptr, st));
-      BnBufs bd = bn_eval_bufs(d, pp, P.affine[1]);
-      RESIST_TRY(bn_eval_affine(d.g.K, bd, eps, 1.f, st));
-      RESIST_TRY(bn_apply(dt, last.y, last.M(), last.g.K, bl, d.y, &bd, true, bp.out, st));
-    } else {
-      RESIST_TRY(bn_apply(dt, last.y, last.M(), last.g.K, bl, bp.in, nullptr, true, bp.out, st));
+    const ConvLayer &d = bp.ds;
+    if (bp.has_ds) RESIST_TRY(conv_fwd(d.g, dt, d.in, filter(d, pp + d.w_off), d.y, nullptr, nullptr, nullptr, st));
+    for (ConvLayer &c : bp.convs) {
+      EvalAct act{c.a, c.scale, c.shift};
+      if (!c.a) {   // the last one: the shortcut joins, and the block's output is written
+        act.out = bp.out;
+        act.res = bp.has_ds ? d.y : bp.in;
+        if (bp.has_ds) { act.rscale = d.scale; act.rshift = d.shift; }
+      }
+      RESIST_TRY(conv_fwd(c.g, dt, c.in, filter(c, pp + c.w_off), nullptr, nullptr, nullptr, nullptr, st, &act));
     }
   }
   const int J = net.d.num_classes, CH = net.head_c;

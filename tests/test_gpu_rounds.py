@@ -145,3 +145,23 @@ def test_forward_eval_with_branch_scaling(kind):
     # nothing was written to the parameters
     for k, p in zip(glob.keys, glob.params):
         assert np.array_equal(p.cpu().numpy(), R.pack_block(model, k, params[k]))
+
+
+@pytest.mark.parametrize("kind,dtype", [(0, 0), (0, 1), (2, 0), (2, 1), (1, 0)])
+def test_forward_eval_epilogue_ragged(kind, dtype):
+    """The BN, shortcut and ReLU of the test-time forward are applied by the convolutions themselves: channel counts that
+    fill no tile, row tiles that end in mid-image, a branch scale per block.  Bounds: as in the test above (the fp32
+    element-wise bound; bf16 storage, 2^-9 per activation)."""
+    from oracle import resnet as OR
+    model = dict(get_config("cfg1")["model"], block_kind=kind, widths=[48, 80, 144], blocks=[2, 1, 2], in_h=12, in_w=20, num_classes=7,
+                 compute_dtype=dtype)
+    nb = R.num_blocks(model)
+    params = make_params(model, 11, perturb_bn=True)
+    x, _ = make_batch(model, 5, 4)
+    scale = [1.0, 0.25, 1.0, 1.0, 0.5]
+    got = DeviceModel(model, list(range(nb)), params).predict(to_device_batch(x, np.zeros(5))[0], branch_scale=scale).cpu().numpy()
+    want = OR.forward_eval(model, list(range(nb)), params, x, branch_scale=scale)
+    if dtype == 1:
+        assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 2e-2
+    else:
+        assert_close(got, want, f"kind {kind} logits")
