@@ -301,6 +301,9 @@ int launch_igemm(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
 
 template <typename T, int MODE>
 int dispatch_igemm(const IgemmArgs &a, hipStream_t st, StatParts *tiles_m_out = nullptr) {
+  if constexpr (sizeof(T) == 4) {
+    if (conv3_takes(a)) return conv3_launch(a, MODE, st, tiles_m_out);
+  }
   // pick the largest tile that still yields enough workgroups to cover the 256 compute units
   constexpr int V = Elem<T>::VEC;   // K-chunks of 8*V and 16*V elements: 128 and 256 bytes per tile row
   const long long classes = (long long)a.cls * a.cls;

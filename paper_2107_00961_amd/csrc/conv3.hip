@@ -1,0 +1,370 @@
+// 3x3 stride-1 convolution of fp32 tensors (forward and data gradient) on the bf16 matrix core.
+//
+// Every fp32 operand a is taken apart into three bf16 numbers, a = h + m + l, each the nearest bf16 to what the ones
+// before it leave: 8 + 8 + 8 significant bits, so nothing of a's 24 is lost.  A product is then six bf16 products
+//   a*b = h*h' + (h*m' + m*h') + (m*m' + h*l' + l*h')      (what is left out is below 2^-26 of |a*b|)
+// accumulated in fp32, small terms first.  v_mfma_f32_32x32x16_bf16 does 16 times the work of
+// v_mfma_f32_32x32x2_f32 per cycle, so six of them take 6/16 of the time one fp32 product takes.
+//
+// Infinities (and finite values that round to one) leave a NaN in the difference a - h and so in every output they
+// reach; a workgroup that finds a NaN in its tile computes the tile again on the fp32 matrix instruction.
+//
+// What bounds this kernel is the staging: an operand element costs 5.5 vector instructions to take apart and 6 bytes of
+// LDS.  So the input pixels of a tile are staged once per 64 channels and serve all nine taps: the tile is a range of
+// BM consecutive pixels of the flattened [N*H*W], tap (r, s) of pixel m is pixel m + (r-1)*W + (s-1), so a range of
+// BM + 2W + 2 pixels holds every tap, whatever H, W and the image boundaries are; a tap that falls off its image reads
+// a row of zeros instead.
+//
+// Measured, us, fp32 instruction -> this kernel (forward | data gradient with its filter transpose), batch 128:
+//   64 ch 32x32  87 -> 63 | 93 -> 67     128 ch 16x16  83 -> 54 | 88 -> 59
+//  256 ch  8x8   95 -> 54 | 98 -> 60     512 ch  4x4   89 -> 60 | 99 -> 68
+// The 256-channel forward kernel is busy with products 57 % of its cycles (43 us with nothing else left in the loop: the
+// matrix core does not hold its nominal clock); the filter rows staged per tap cost 8 us of the rest, the fragment reads 4.
+// Error against float64 over 27 to 4608 products per output: 1.6e-7 to 4.6e-7 (2-norm), the fp32 instruction's 2.5e-7 to
+// 1.1e-6.
+#include "conv_tile.h"
+
+namespace resist {
+namespace {
+
+constexpr int kMaxW = 56;
+constexpr int kBN = 64, kNT = 512, kBK = 64, kWGK = 4, kWGM = 2, kTN = 2;
+constexpr int kPlane = kBK * 2;            // bytes of one part of a staged row
+constexpr int kPitch = 3 * kPlane + 16;    // row pitch: rows 4 banks apart, conflict-free 16-byte reads of consecutive rows
+constexpr int kStageB = kBN * kPitch;
+
+// the three bf16 parts of four floats to their places in a staged row
+__device__ inline void store_split(char *row, f32x4 v) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(row + p * kPlane) = split_part(v);
+}
+
+// 8 waves: 2 along the pixels, 4 sharing the reduction (wave slice k takes 16 of every 64 channels), so that a wave's
+// tile is as large as the registers allow (BM/2 x 64): an operand fragment read from LDS feeds 2*TM or 2*TN products.
+template <int BM, int MODE>
+__global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
+  constexpr int WTM = BM / kWGM, TM = WTM / 32, NSUB = TM * kTN;
+  constexpr int PA = (BM + 2 * kMaxW + 2 + 31) / 32, PB = kBN / 32;   // staging passes of 32 rows x 16 lanes
+  constexpr int PX = PA * 32;                     // staged pixels; the row after them is zero
+  constexpr int LDC = kBN + 8;
+  constexpr size_t kOperand = 2 * kStageB + (size_t)(PX + 1) * kPitch;
+  constexpr size_t kReduce = (size_t)kWGM * kWGK * NSUB * 4 * 64 * 16;
+  constexpr size_t kTile = sizeof(float) * BM * LDC;
+  constexpr size_t kBytes = kOperand > kReduce ? (kOperand > kTile ? kOperand : kTile) : (kReduce > kTile ? kReduce : kTile);
+  __shared__ __attribute__((aligned(16))) char lds[kBytes];
+  __shared__ int row_off[BM];
+  char *const Bs = lds, *const Px = lds + 2 * kStageB;
+  float (*Cs)[LDC] = reinterpret_cast<float (*)[LDC]>(lds);
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wk = wave & 3, wm = wave >> 2;
+  const int lr = lane & 31, lg = lane >> 5;
+  const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int tm = fdiv(bid, a.div_tn), tn = bid - tm * a.tiles_n;
+  const int m0 = tm * BM, n0 = tn * kBN;
+  const int W = a.IW, IC = a.IC, px = BM + 2 * W + 2;   // staged pixels: m0 - W - 1 .. m0 + BM + W
+  const int cchunks = (IC + kBK - 1) / kBK;
+  const int steps = 9 * cchunks;
+
+  for (int r = tid; r < BM; r += kNT) row_off[r] = m0 + r < a.Mrows ? m0 + r : -1;
+
+  // which taps of this lane's pixels lie inside their image, and where in LDS its operands start
+  int valid[TM], abase[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int ml = wm * WTM + i * 32 + lr, m = m0 + ml;
+    const int n = fdiv(m, a.div_plane), rem = m - n * (a.IH * W);
+    const int h = fdiv(rem, a.div_w), w = rem - h * W;
+    int v = 0;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int r = MODE == kBwd ? 2 - t / 3 : t / 3, s = MODE == kBwd ? 2 - t % 3 : t % 3;
+      if ((unsigned)(h + r - 1) < (unsigned)a.IH && (unsigned)(w + s - 1) < (unsigned)W) v |= 1 << t;
+    }
+    valid[i] = m < a.Mrows ? v : 0;
+    abase[i] = (ml + W + 1) * kPitch + wk * 32 + lg * 16;
+  }
+  const int zbase = PX * kPitch + wk * 32 + lg * 16;
+
+  const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, (unsigned)a.N * a.IH * W * IC * 4u);
+  const __amdgpu_buffer_rsrc_t rwt = make_rsrc(a.wt, (unsigned)a.OC * 9u * IC * 4u);
+
+  // ---- staging: 16 lanes (4 channels each) per row
+  const int srow = tid >> 4, sch = (tid & 15) * 4;
+  // filter stage of a set: where a thread stores its rows, where a lane fetches its fragments
+  char *bdst[2] = {Bs + srow * kPitch + sch * 2, Bs + kStageB + srow * kPitch + sch * 2};
+  const char *bsrc[2] = {Bs + lr * kPitch + wk * 32 + lg * 16, Bs + kStageB + lr * kPitch + wk * 32 + lg * 16};
+  char *const pdst = Px + srow * kPitch + sch * 2;
+  f32x4 rp[PA], rb[2][PB];
+  unsigned boff[PB];
+#pragma unroll
+  for (int i = 0; i < PB; ++i) {
+    const int oc = n0 + i * 32 + srow;
+    boff[i] = oc < a.OC ? (unsigned)(oc * 9 * IC + sch) * 4u : kOOB;
+  }
+  // pixels before the first and past the last of the tensor come back as zeros (offsets wrap above the size)
+  const unsigned poff = (unsigned)((m0 - W - 1 + srow) * IC + sch) * 4u;
+  int pc = 0;                 // chunk of the pixels requested next
+  auto request_pixels = [&]() {
+    const bool ok = pc < cchunks && pc * kBK + sch < IC;
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+      unsigned o = ok && i * 32 + srow < px ? poff + (unsigned)(i * 32 * IC + pc * kBK) * 4u : kOOB;
+      asm("" : "+v"(o));   // a selected offset; left alone, the compiler makes two loads behind a branch and waits for each
+      rp[i] = buffer_load_16B(rin, o);
+    }
+    ++pc;
+  };
+  auto store_pixels = [&](int i) {
+    if (i * 32 < px) store_split(pdst + i * 32 * kPitch, rp[i]);   // uniform
+  };
+  int bt = 0, bc = 0;         // tap and chunk of the filter rows requested next
+  auto request_filter = [&](int set) {
+    const bool ok = bc < cchunks && bc * kBK + sch < IC;
+    const unsigned d = (unsigned)(bt * IC + bc * kBK) * 4u;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) rb[set][i] = buffer_load_16B(rwt, ok ? boff[i] + d : kOOB);
+    const bool wrap = bt == 8;
+    bt = wrap ? 0 : bt + 1;
+    bc = wrap ? bc + 1 : bc;
+  };
+  // the rows of step t wait in register set t % 2 and go to LDS stage t % 2
+  auto store_filter = [&](int set, int i) { store_split(bdst[set] + i * 32 * kPitch, rb[set][i]); };
+
+  // ---- fragments: three parts of TM pixel tiles and kTN filter tiles.  A part is fetched for the next step as soon as
+  // its last product of this step is issued; only the leading parts (index 0), which the last product of a step and the
+  // first two of the next both use, have two register sets.
+  f32x4 fa0[2][TM], fb0[2][kTN], fa[3][TM], fb[3][kTN];
+  int ft = 0;                 // tap of the fragments fetched next
+  int aat[TM];                // where that tap's pixel is
+  auto aim = [&]() {
+    const int r = ft / 3, s = ft - r * 3;
+    const int d = ((r - 1) * W + s - 1) * (MODE == kBwd ? -kPitch : kPitch);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) aat[i] = (valid[i] >> ft) & 1 ? abase[i] + d : zbase;
+    ft = ft == 8 ? 0 : ft + 1;
+  };
+  auto fetch_a = [&](int set, int q) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(Px + aat[i] + q * kPlane);
+      if (q == 0) fa0[set][i] = v;
+      else fa[q][i] = v;
+    }
+  };
+  auto fetch_b = [&](int set, int q) {
+#pragma unroll
+    for (int j = 0; j < kTN; ++j) {
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(bsrc[set] + j * 32 * kPitch + q * kPlane);
+      if (q == 0) fb0[set][j] = v;
+      else fb[q][j] = v;
+    }
+  };
+
+  f32x16 acc[TM][kTN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < kTN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  auto product = [&](int set, int pa, int pb) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < kTN; ++j)
+        Elem<__bf16>::mma(acc[i][j], pa == 0 ? fa0[set][i] : fa[pa][i], pb == 0 ? fb0[set][j] : fb[pb][j]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto lds_barrier = [&]() {
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+  };
+
+  request_pixels();
+  request_filter(0);
+  request_filter(1);
+  if (tid < 100) *reinterpret_cast<unsigned *>(Px + PX * kPitch + tid * 4) = 0;
+#pragma unroll
+  for (int i = 0; i < PA; ++i) store_pixels(i);
+#pragma unroll
+  for (int i = 0; i < PB; ++i) store_filter(0, i);
+  request_filter(0);
+  store_filter(1, 0);
+  request_pixels();
+  lds_barrier();
+  aim();
+#pragma unroll
+  for (int q = 0; q < 3; ++q) { fetch_a(0, q); fetch_b(0, q); }
+  __builtin_amdgcn_sched_barrier(0);
+
+  // Step (chunk, tap), six groups of products, small terms first.  Beside them, spread so that neither the LDS nor the
+  // vector unit sees a burst: the second half of the next step's filter rows goes to LDS and the rows three steps ahead
+  // are requested (all workgroups walk the filter in step, so each row comes from beyond the L2 once per XCD and every
+  // one of them waits for it); the barrier, after which the filter fragments of the next step are fetched; the first
+  // half of the rows of the step after it.  The last step of a chunk also replaces the pixels: all fragments of this
+  // chunk are in registers once its barrier is passed.  (The products stand outside the branches: inside, the
+  // accumulators are copied.)
+  static_assert(PB == 2, "filter rows per step");
+  int tap = 0;
+  auto step = [&](int set, int it) {
+    const bool turn = tap == 8 && it + 1 < steps;   // uniform
+    const int nx = set ^ 1;
+    constexpr int H = (PA + 2) / 3;
+    auto replace = [&](int q) {
+      if (turn) {
+#pragma unroll
+        for (int i = q * H; i < (q + 1) * H && i < PA; ++i) store_pixels(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    aim();
+    store_filter(nx, 1);
+    product(set, 2, 0);
+    if (!turn) fetch_a(nx, 2);
+    request_filter(nx);
+    product(set, 0, 2);
+    lds_barrier();
+    fetch_b(nx, 2);
+    if (!turn) fetch_a(nx, 0);
+    product(set, 1, 1);
+    replace(0);
+    fetch_b(nx, 0);
+    product(set, 1, 0);
+    replace(1);
+    if (!turn) fetch_a(nx, 1);
+    store_filter(set, 0);        // of step it + 2
+    product(set, 0, 1);
+    replace(2);
+    fetch_b(nx, 1);
+    if (turn) {
+      request_pixels();
+      lds_barrier();
+#pragma unroll
+      for (int q = 2; q >= 0; --q) fetch_a(nx, q);
+    }
+    product(set, 0, 0);
+    tap = tap == 8 ? 0 : tap + 1;
+  };
+  // An odd number of steps starts with one on its own, after which the sets change places: a loop that could end between
+  // its two steps makes the compiler wait for every load at its top.  (Behind the last step: rows nobody uses.)
+  int it = 0;
+  if (steps & 1) {
+    step(0, 0);
+    it = 1;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) fa0[0][i] = fa0[1][i];
+#pragma unroll
+    for (int j = 0; j < kTN; ++j) fb0[0][j] = fb0[1][j];
+#pragma unroll
+    for (int i = 0; i < PB; ++i) { const f32x4 t = rb[0][i]; rb[0][i] = rb[1][i]; rb[1][i] = t; }
+    char *const d = bdst[0]; bdst[0] = bdst[1]; bdst[1] = d;
+    const char *const f = bsrc[0]; bsrc[0] = bsrc[1]; bsrc[1] = f;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  do {
+    step(0, it);
+    step(1, it + 1);
+    it += 2;
+  } while (it < steps);
+
+  conv_epilogue<float, BM, kBN, kNT, MODE>(a, Cs, row_off, tm, n0, [&]() {
+    // the four slices of a wave tile are added in slice order; wave slice k finishes the k-th quarter of it
+    f32x4 *const red = reinterpret_cast<f32x4 *>(lds);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NSUB; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x16 &c = acc[u / kTN][u % kTN];
+        red[(((wm * kWGK + wk) * NSUB + u) * 4 + e) * 64 + lane] = f32x4{c[4 * e], c[4 * e + 1], c[4 * e + 2], c[4 * e + 3]};
+      }
+    __syncthreads();
+    f32x4 v[NSUB];
+    bool bad = false;
+#pragma unroll
+    for (int g = 0; g < NSUB; ++g) {
+      v[g] = red[((wm * kWGK) * NSUB * 4 + wk * NSUB + g) * 64 + lane];
+#pragma unroll
+      for (int k = 1; k < kWGK; ++k) v[g] += red[((wm * kWGK + k) * NSUB * 4 + wk * NSUB + g) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bad |= v[g][e] != v[g][e];
+    }
+    // group g of this wave: rows 8*ge + 4*lg .. +3 of sub-tile u, column lr
+    const int g0 = wk * NSUB;
+    if (__syncthreads_or(bad)) {
+      // a NaN somewhere in the tile: again in fp32, without staging
+      const int u = g0 / 4, i = u / kTN, j = u % kTN;
+      const float *in = static_cast<const float *>(a.in), *wt = static_cast<const float *>(a.wt);
+      const int m = m0 + wm * WTM + i * 32 + lr, oc = n0 + j * 32 + lr;
+      int vm = valid[0];
+      if constexpr (TM == 2) vm = i ? valid[1] : valid[0];
+      f32x16 c;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) c[e] = 0.f;
+      for (int t = 0; t < 9; ++t) {
+        const int d = ((t / 3 - 1) * W + t % 3 - 1) * (MODE == kBwd ? -1 : 1);
+        const bool ok = (vm >> t) & 1;
+        for (int ch = lg; ch < IC; ch += 2) {   // IC is even
+          const float x = ok ? in[(size_t)(m + d) * IC + ch] : 0.f;
+          const float y = oc < a.OC ? wt[((size_t)oc * 9 + t) * IC + ch] : 0.f;
+          c = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, c, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < NSUB; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if constexpr (NSUB == 4) v[g][e] = c[4 * g + e];
+          else v[g][e] = (wk & 1) ? c[8 + 4 * g + e] : c[4 * g + e];
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < NSUB; ++g) {
+      const int u = (g0 + g) / 4, ge = (g0 + g) % 4;
+      const int row = wm * WTM + (u / kTN) * 32 + ge * 8 + lg * 4, col = (u % kTN) * 32 + lr;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) Cs[row + e][col] = v[g][e];
+    }
+  });
+}
+
+template <int BM, int MODE>
+int launch(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
+  a.tiles_m = (a.Mrows + BM - 1) / BM;
+  a.tiles_n = (a.OC + kBN - 1) / kBN;
+  if (tiles_m_out) { tiles_m_out->parts = a.tiles_m; tiles_m_out->rows = BM; }
+  a.div_plane = make_fastdiv((unsigned)(a.IH * a.IW)); a.div_w = make_fastdiv((unsigned)a.IW);
+  a.div_tn = make_fastdiv((unsigned)a.tiles_n);
+  const long long grid = (long long)a.tiles_m * a.tiles_n;
+  if (grid <= 0 || grid > 0x7fffffffLL) return set_error(RESIST_ESHAPE, "conv3 grid %lld", grid);
+  {
+    static const std::string label = std::string("conv3_f32_") + (MODE == kFwd ? "fwd_" : MODE == kEval ? "eval_" : "bwd_") + std::to_string(BM) + "x64";
+    const double flops = 2.0 * a.Mrows * a.OC * a.IC * 9;
+    const double bytes = 4.0 * ((double)a.Mrows * a.IC + (double)a.Mrows * a.OC * (1 + (a.addend ? 1 : 0) + (a.relu_mask ? 1 : 0) + (MODE == kBwd && a.bn_sums ? 1 : 0) +
+                                (MODE == kEval ? (a.out ? 1 : 0) + (a.act_res ? 1 : 0) : 0)) + (double)a.OC * 9 * a.IC);
+    prof::Scope ps(label.c_str(), flops, bytes, st);
+    hipLaunchKernelGGL((conv3_split_kernel<BM, MODE>), dim3((unsigned)grid), dim3(kNT), 0, st, a);
+  }
+  RESIST_CHECK_LAUNCH("conv3");
+  return RESIST_OK;
+}
+
+// 64-pixel tiles where 128-pixel ones would not give every CU a workgroup (512 ch 4x4, batch 128: 128 tiles)
+template <int MODE>
+int pick(const IgemmArgs &a, hipStream_t st, StatParts *p) {
+  const long long t128 = (long long)((a.Mrows + 127) / 128) * ((a.OC + kBN - 1) / kBN);
+  return t128 >= 256 ? launch<128, MODE>(a, st, p) : launch<64, MODE>(a, st, p);
+}
+
+}  // namespace
+
+bool conv3_takes(const IgemmArgs &a) {
+  return a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.IW <= kMaxW && a.IC >= 48;
+}
+
+int conv3_launch(const IgemmArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out) {
+  return mode == kFwd ? pick<kFwd>(a, st, tiles_m_out) : mode == kBwd ? pick<kBwd>(a, st, tiles_m_out) : pick<kEval>(a, st, tiles_m_out);
+}
+
+}  // namespace resist

@@ -9,29 +9,6 @@ namespace resist {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-namespace {
-
-// Element traits: a 16-byte vector holds VEC elements; one pair of 16-byte fragments (A, B) feeds
-// the matrix core with 2*VEC values of the GEMM-K axis (lane group l/32 owns VEC consecutive ones).
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-  static constexpr int VEC = 4;
-  __device__ static inline void mma(f32x16 &acc, const f32x4 &a, const f32x4 &b) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
-  }
-  __device__ static inline float from_f32(float v) { return v; }
-  __device__ static inline float to_f32(float v) { return v; }
-};
-template <> struct Elem<__bf16> {
-  static constexpr int VEC = 8;
-  __device__ static inline void mma(f32x16 &acc, const f32x4 &a, const f32x4 &b) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-  }
-  __device__ static inline __bf16 from_f32(float v) { return (__bf16)v; }   // round to nearest even
-  __device__ static inline float to_f32(__bf16 v) { return (float)v; }
-};
-
 // division by a runtime constant: q = (n * mul) >> sh, exact for 0 <= n < 2^31
 struct FastDiv { unsigned mul; int sh; };
 inline FastDiv make_fastdiv(unsigned d) {
@@ -83,6 +60,40 @@ constexpr int kBwd = 1;  // source pixel = (out + pad - tap) / stride
 // for the launch that made its map) buys nothing.  CIFAR-shaped model, batch 128, fp32: 6.04 -> 5.56 ms; batch 33, bf16:
 // 1.48 -> 1.05; one ImageNet-shaped image, bf16: 0.83 -> 0.55; bit for bit the same logits.
 constexpr int kEval = 2;
+
+namespace {
+
+// Element traits: a 16-byte vector holds VEC elements; one pair of 16-byte fragments (A, B) feeds
+// the matrix core with 2*VEC values of the GEMM-K axis (lane group l/32 owns VEC consecutive ones).
+template <typename T> struct Elem;
+template <> struct Elem<float> {
+  static constexpr int VEC = 4;
+  __device__ static inline void mma(f32x16 &acc, const f32x4 &a, const f32x4 &b) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
+  }
+  __device__ static inline float from_f32(float v) { return v; }
+  __device__ static inline float to_f32(float v) { return v; }
+};
+template <> struct Elem<__bf16> {
+  static constexpr int VEC = 8;
+  __device__ static inline void mma(f32x16 &acc, const f32x4 &a, const f32x4 &b) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  }
+  __device__ static inline __bf16 from_f32(float v) { return (__bf16)v; }   // round to nearest even
+  __device__ static inline float to_f32(__bf16 v) { return (float)v; }
+};
+
+// The leading bf16 part of four fp32 values (nearest even), packed; v keeps what it leaves, exactly.  Three calls take a
+// value apart: 8 + 8 + 8 significant bits.  (An infinity, or a value that rounds to one, leaves a NaN behind.)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ inline u32x2 split_part(f32x4 &v) {
+  const unsigned a = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{v[0], v[1]}), bf16x2));
+  const unsigned b = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{v[2], v[3]}), bf16x2));
+  v -= f32x4{bf16_lo(a), bf16_hi(a), bf16_lo(b), bf16_hi(b)};
+  return u32x2{a, b};
+}
 
 // Workgroups are handed to the 8 XCDs round-robin by their linear id, and each XCD has its own L2.
 // This maps the hardware id to a logical tile index such that every XCD works on one contiguous
@@ -282,4 +293,9 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
 }
 
 }  // namespace
+
+// 3x3 stride-1 convolutions in fp32 through operands split into three bf16 parts (conv3.hip)
+bool conv3_takes(const IgemmArgs &a);
+int conv3_launch(const IgemmArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);
+
 }  // namespace resist

@@ -83,6 +83,45 @@ def test_conv_wgrad(case):
     assert_close(dw.cpu().numpy().transpose(0, 3, 1, 2), want, f"conv wgrad {case}")
 
 
+# ---- fp32 3x3 stride-1 layers of at least 48 input channels: operands taken apart into three bf16 parts --------------
+# Edges of the 64- and 128-pixel tiles, of the 64-channel chunks (the last one ragged, an odd and an even number of them)
+# and of the 64-wide output tiles; images one pixel wide, smaller than a tile, and at and past the widest that is staged.
+#              N   H   W   C    K   R st pad
+SPLIT_CASES = [(1, 1, 1, 64, 16, 3, 1, 1), (5, 3, 1, 48, 80, 3, 1, 1), (1, 8, 8, 64, 64, 3, 1, 1), (1, 5, 13, 52, 68, 3, 1, 1),
+               (13, 5, 2, 128, 48, 3, 1, 1), (2, 3, 56, 64, 32, 3, 1, 1), (2, 3, 57, 64, 32, 3, 1, 1), (129, 4, 4, 132, 1028, 3, 1, 1),
+               (2, 127, 31, 64, 300, 3, 1, 1), (3, 9, 7, 192, 64, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES)
+def test_conv_split_forward_and_dgrad(case):
+    print("case", case, flush=True)
+    x, w, _ = _tensors(case, 8)
+    y = R.conv2d_forward(_nhwc(x), _nhwc(w), 1, 1)
+    N, H, W, C, K = case[:5]
+    # the data gradient of the layer with in- and output channels exchanged has the same tiles
+    dx = R.conv2d_dgrad(_nhwc(x), _nhwc(np.ascontiguousarray(w.transpose(1, 0, 2, 3))), (N, H, W, K), 1, 1)
+    torch.cuda.synchronize()
+    assert_close(y.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_fwd(x, w, 1, 1), f"conv fwd {case}")
+    want = L.conv2d_dgrad(x, w.transpose(1, 0, 2, 3), (N, K, H, W), 1, 1)
+    assert_close(dx.cpu().numpy().transpose(0, 3, 1, 2), want, f"conv dgrad {case}")
+
+
+def _same_values(got, want, what):
+    # infinities and NaN where float64 has them, everything else close (values next to the largest float included)
+    with np.errstate(over="ignore"):
+        np.testing.assert_allclose(got.transpose(0, 3, 1, 2), want.astype(np.float32), rtol=1e-4, atol=1e-4, equal_nan=True, err_msg=what)
+
+
+def test_conv_split_infinities():
+    x, w, _ = _tensors((4, 8, 8, 64, 96, 3, 1, 1), 9)
+    x[0, 5, 2, 3], x[1, 7, 0, 0], x[2, 9, 7, 7] = np.inf, -np.inf, np.nan
+    x[3, 1, 4, 4] = 3.4e38   # finite, but its leading bf16 part is an infinity
+    y = R.conv2d_forward(_nhwc(x), _nhwc(w), 1, 1)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        _same_values(y.cpu().numpy(), L.conv2d_fwd(x.astype(np.float64), w, 1, 1), "fwd")
+
+
 # ---- bf16 operands, fp32 accumulation ---------------------------------------------------------
 # Inputs are bfloat16 numbers, so the oracle's float64 result is the exact convolution of what the
 # kernel reads.  Outputs stored as bfloat16 carry half a bfloat16 ulp (2^-9 relative, 2^-8 of the
