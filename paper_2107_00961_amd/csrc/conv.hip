@@ -11,6 +11,7 @@
 //   wgrad    dW[k][r][s][c]   = sum_{m=(n,p,q)} dY[m][k] * X[n, p*st+r-pad, q*st+s-pad, c]
 // Tiles are staged through LDS (double buffered, one barrier per K-chunk); every wave owns a
 // grid of 32x32 accumulator tiles held in registers.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -713,15 +714,6 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(WgradArgs a) {
     }
 }
 
-// LDS transpose read (ds_read_b64_tr_b16).  Within each block of 16 lanes, lane s supplies the
-// address of 4 consecutive 16-bit values; lane j receives, as element e, the value number j%4 of
-// the four that lane 4*e + j/4 pointed at.  When lane s points at row s/4, columns 4*(s%4)..+3 of a
-// row-major tile, lane j therefore ends up with rows 0..3 of column j: a 4x16 -> 16x4 transpose.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-__device__ inline s16x4 lds_read_tr(const __bf16 *p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p));
-}
-
 // Weight gradient with bf16 operands on v_mfma_f32_32x32x16_bf16.  The matrix instruction wants 8
 // consecutive values of the reduction index (output pixels m) per lane, while both operands arrive
 // from memory with the channel index contiguous ([m][channel]); the tiles are therefore stored in LDS
@@ -811,19 +803,13 @@ __global__ __launch_bounds__(kThreads) void wgrad_bf16_kernel(WgradArgs a) {
   auto load_frags = [&](int buf, int stage, int ks) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const s16x4 lo = lds_read_tr(&As[stage][ks * 16 + frow][wm * WTM + i * 32 + fcol]);
-      const s16x4 hi = lds_read_tr(&As[stage][ks * 16 + frow + 4][wm * WTM + i * 32 + fcol]);
-      typedef short s16x8 __attribute__((ext_vector_type(8)));
-      const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      fa[buf][i] = __builtin_bit_cast(bf16x8, v);
+      fa[buf][i] = lds_read_tr_pair(&As[stage][ks * 16 + frow][wm * WTM + i * 32 + fcol],
+                                    &As[stage][ks * 16 + frow + 4][wm * WTM + i * 32 + fcol]);
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const s16x4 lo = lds_read_tr(&Bs[stage][ks * 16 + frow][wn * WTN + j * 32 + fcol]);
-      const s16x4 hi = lds_read_tr(&Bs[stage][ks * 16 + frow + 4][wn * WTN + j * 32 + fcol]);
-      typedef short s16x8 __attribute__((ext_vector_type(8)));
-      const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      fb[buf][j] = __builtin_bit_cast(bf16x8, v);
+      fb[buf][j] = lds_read_tr_pair(&Bs[stage][ks * 16 + frow][wn * WTN + j * 32 + fcol],
+                                    &Bs[stage][ks * 16 + frow + 4][wn * WTN + j * 32 + fcol]);
     }
   };
   auto lds_barrier = [&]() {
@@ -904,7 +890,30 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
   if (g == 0 && i < n4) reinterpret_cast<f32x4 *>(out)[i] = acc;
 }
 
-struct WgradPlan { int bm, bn, splits, rows_per_split; };
+constexpr size_t kStaticScratchBytes = (size_t)32 << 20;   // library-owned partial sums (see conv_wgrad_static)
+
+struct WgradPlan { int bm, bn, splits, rows_per_split; bool taps9 = false; };
+
+// Nine-tap kernel (wgrad3.hip): 64 x 64 channels of all taps per workgroup, one workgroup per CU.  Its time is that of
+// the rounds of 256 workgroups, 0.05 us per row and 128 rows' worth for its start and end, 0.06 us per partial tile
+// written and read back, 4 us for the launch that adds them; the number of splits is the one with the least, among those whose partial sums stay below
+// max_floats.
+WgradPlan plan_wgrad3(const ConvGeom &g, long long max_floats) {
+  WgradPlan p;
+  p.bm = p.bn = 64;
+  p.taps9 = true;
+  const long long tiles = (long long)((g.K + 63) / 64) * ((g.C + 63) / 64), M = (long long)g.N * g.P * g.Q;
+  const long long slice = (long long)g.K * 9 * g.C;
+  long long best = -1;
+  for (long long s = 1; s <= 256 && (s == 1 || (s - 1) * 64 < M); ++s) {
+    if (s > 1 && s * slice > max_floats) break;
+    const long long rows = ((M + s - 1) / s + kWBK - 1) / kWBK * kWBK;
+    const long long used = (M + rows - 1) / rows;
+    const long long cost = (tiles * used + 255) / 256 * (rows + 128) * 5 + (used > 1 ? tiles * used * 6 + 400 : 0);
+    if (best < 0 || cost < best) { best = cost; p.splits = (int)used; p.rows_per_split = (int)rows; }
+  }
+  return p;
+}
 
 WgradPlan plan_wgrad(const ConvGeom &g) {
   WgradPlan p;
@@ -926,15 +935,20 @@ WgradPlan plan_wgrad(const ConvGeom &g) {
 
 }  // namespace
 
-int64_t wgrad_scratch_floats(const ConvGeom &g) {
-  const WgradPlan p = plan_wgrad(g);
-  return p.splits > 1 ? (int64_t)p.splits * g.K * g.R * g.S * g.C : 0;
-}
+namespace {
+int64_t plan_floats(const WgradPlan &p, const ConvGeom &g) { return p.splits > 1 ? (int64_t)p.splits * g.K * g.R * g.S * g.C : 0; }
 
-int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial, hipStream_t st) {
-  RESIST_TRY(check_geom(g, dt));
-  const WgradPlan p = plan_wgrad(g);
+int run_wgrad(const WgradPlan &p, const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial, hipStream_t st) {
   if (p.splits > 1 && !partial) return set_error(RESIST_EWORKSPACE, "wgrad needs split scratch");
+  if (p.taps9) {
+    {
+      const double M = (double)g.N * g.P * g.Q;
+      prof::Scope ps("wgrad3_f32", 2.0 * M * g.K * g.C * 9, 4.0 * (M * (g.K + g.C) + 9.0 * g.K * g.C), st);
+      RESIST_TRY(wgrad3_launch(g, static_cast<const float *>(dy), static_cast<const float *>(x), p.splits > 1 ? partial : dw, p.splits,
+                               p.rows_per_split, st));
+    }
+    return p.splits > 1 ? splitk_reduce(partial, dw, (long long)g.K * 9 * g.C / 4, p.splits, st) : RESIST_OK;
+  }
   WgradArgs a{};
   a.dy = dy; a.x = x; a.out = p.splits > 1 ? partial : dw;
   a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.R = g.R; a.S = g.S;
@@ -965,6 +979,23 @@ int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *
   return RESIST_OK;
 }
 
+}  // namespace
+
+// A layer whose one-tap plan fits the static scratch has a nine-tap plan that fits it too: conv_wgrad_static takes the
+// same layers, and gives the same bits as conv_wgrad, whichever kernel runs.
+static WgradPlan plan_for(const ConvGeom &g, int dt) {
+  const WgradPlan p = plan_wgrad(g);
+  if (dt != DT_F32 || !wgrad3_takes(g)) return p;
+  return plan_wgrad3(g, plan_floats(p, g) * 4 <= (int64_t)kStaticScratchBytes ? (long long)(kStaticScratchBytes / 4) : INT64_MAX);
+}
+
+int64_t wgrad_scratch_floats(const ConvGeom &g, int dt) { return plan_floats(plan_for(g, dt), g); }
+
+int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial, hipStream_t st) {
+  RESIST_TRY(check_geom(g, dt));
+  return run_wgrad(plan_for(g, dt), g, dt, dy, x, dw, partial, st);
+}
+
 int splitk_reduce(const float *partial, float *out, long long n4, int splits, hipStream_t st) {
   prof::Scope ps("splitk_reduce", 0, 16.0 * n4 * (splits + 1), st);
   // enough threads per output vector that the launch has at least ~64k loads in flight
@@ -980,7 +1011,6 @@ int splitk_reduce(const float *partial, float *out, long long n4, int splits, hi
 // For callers that cannot allocate (HIP graph capture, serving loops): the split-reduction scratch of
 // conv_wgrad lives in a file-scope device array instead of a caller-provided workspace.  Host code
 // never uses the array's name as an address: its device address is looked up once per device.
-constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -1009,7 +1039,7 @@ int64_t wgrad_static_scratch_bytes() { return (int64_t)kStaticScratchBytes; }
 
 int conv_wgrad_static(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, hipStream_t st) {
   RESIST_TRY(check_geom(g, dt));
-  const int64_t need = wgrad_scratch_floats(g) * 4;
+  const int64_t need = std::max(wgrad_scratch_floats(g, dt), plan_floats(plan_wgrad(g), g)) * 4;
   if (need > (int64_t)kStaticScratchBytes)
     return set_error(RESIST_EWORKSPACE, "split partial sums need %lld bytes, the static scratch holds %lld",
                      (long long)need, (long long)kStaticScratchBytes);

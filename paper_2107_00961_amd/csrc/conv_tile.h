@@ -95,6 +95,21 @@ __device__ inline u32x2 split_part(f32x4 &v) {
   return u32x2{a, b};
 }
 
+// LDS transpose read (ds_read_b64_tr_b16).  Within each block of 16 lanes, lane s supplies the
+// address of 4 consecutive 16-bit values; lane j receives, as element e, the value number j%4 of
+// the four that lane 4*e + j/4 pointed at.  When lane s points at row s/4, columns 4*(s%4)..+3 of a
+// row-major tile, lane j therefore ends up with rows 0..3 of column j: a 4x16 -> 16x4 transpose.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+__device__ inline s16x4 lds_read_tr(const void *p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p));
+}
+// two of them: eight consecutive values of the reduction index for the matrix instruction
+__device__ inline bf16x8 lds_read_tr_pair(const void *first, const void *second) {
+  const s16x4 lo = lds_read_tr(first), hi = lds_read_tr(second);
+  return __builtin_bit_cast(bf16x8, (s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}));
+}
+
 // Workgroups are handed to the 8 XCDs round-robin by their linear id, and each XCD has its own L2.
 // This maps the hardware id to a logical tile index such that every XCD works on one contiguous
 // range of logical tiles, so tiles that share operand rows meet in the same L2.
@@ -297,5 +312,8 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
 // 3x3 stride-1 convolutions in fp32 through operands split into three bf16 parts (conv3.hip)
 bool conv3_takes(const IgemmArgs &a);
 int conv3_launch(const IgemmArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);
+// the weight gradient of such a convolution (wgrad3.hip): out [splits][K][3][3][C], a multiple of 32 rows each
+bool wgrad3_takes(const ConvGeom &g);
+int wgrad3_launch(const ConvGeom &g, const float *dy, const float *x, float *out, int splits, int rows_per_split, hipStream_t st);
 
 }  // namespace resist

@@ -21,7 +21,7 @@ extern "C" int resist_conv2d_workspace_bytes(const resist_conv_shape *s, int64_t
   RESIST_TRY(to_geom(s, &g));
   if (!bytes) return set_error(RESIST_EINVAL, "bytes is NULL");
   const int64_t filt = align256((int64_t)g.K * g.R * g.S * g.C * esize(s->dtype));
-  const int64_t split = align256(wgrad_scratch_floats(g) * 4);
+  const int64_t split = align256(wgrad_scratch_floats(g, s->dtype) * 4);
   *bytes = std::max<int64_t>(std::max(filt, split), 256);
   return RESIST_OK;
 }
@@ -51,7 +51,7 @@ extern "C" int resist_conv2d_wgrad(const resist_conv_shape *s, const void *dy, c
   ConvGeom g;
   RESIST_TRY(to_geom(s, &g));
   if (!dy || !x || !dw) return set_error(RESIST_EINVAL, "NULL tensor");
-  const int64_t need = wgrad_scratch_floats(g) * 4;
+  const int64_t need = wgrad_scratch_floats(g, s->dtype) * 4;
   if (need > 0 && (!workspace || workspace_bytes < need)) return set_error(RESIST_EWORKSPACE, "workspace too small for split-K partial sums");
   return conv_wgrad(g, s->dtype, dy, x, dw, (float *)workspace, (hipStream_t)hip_stream);
 }

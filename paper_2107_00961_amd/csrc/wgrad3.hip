@@ -1,0 +1,288 @@
+// Weight gradient of a 3x3 stride-1 convolution of fp32 tensors on the bf16 matrix core (three bf16 parts per operand,
+// six products, small terms first; infinities through a second pass on the fp32 instruction: see conv3.hip).
+//
+//   dW[k][r][s][c] = sum over pixels m of dY[m][k] * X[m + (r-1)*W + (s-1)][c]     (X of a tap off the image is zero)
+//
+// A workgroup owns 64 x 64 channels of all nine taps and a range of pixels: every pixel of dY and X is taken apart and
+// staged once for nine taps (one tap at a time, as a plain split-K GEMM does it, staging costs more than the products).
+// X rows live in a ring of 256 pixels, of which the 32 of a chunk and the W + 1 before and behind them are in use.
+// Twelve waves: wave (r, kq, cq) accumulates the three taps of filter row r for one 32 x 32 quadrant of the channels.
+// Both operands arrive pixel by pixel with the channels contiguous and are read back through the LDS transpose read.
+//
+// Measured with the reduction of the partial sums, us, fp32 instruction a tap at a time -> this kernel, batch 128:
+//   64 ch 32x32  96 -> 59    128 ch 16x16  95 -> 59    256 ch 8x8  101 -> 61    512 ch 4x4  110 -> 59
+// The products are 23 us of it at nominal clock (35 at the clock they run at); the 38 MB of partial sums of 256
+// workgroups, written and read back, about 15.  Error against float64: 2e-8 to 1.3e-7, before 2e-8 to 4.9e-7.
+#include "conv_tile.h"
+
+namespace resist {
+namespace {
+
+constexpr int kNT = 768, kCh = 32, kRing = 256;
+constexpr int kMirror = 6;                 // ring rows repeated behind its end: a tap's rows are at fixed offsets from the first
+constexpr int kPart = 128;                 // bytes of one part (64 channels) of a staged row
+constexpr int kPitch = 3 * kPart + 64;     // four consecutive rows fall on disjoint banks of a transpose read
+constexpr int kStage = kCh * kPitch;
+
+struct Wgrad3Args {
+  const float *dy, *x;
+  float *out;               // [splits][K][9][C]
+  int M, W, H, C, K, rows_per_split, tiles_c, tiles;
+  FastDiv div_tiles, div_tc, div_plane, div_w;
+};
+
+__global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
+  // dY stages, X ring and the first rows of it again, zero rows, tap validity of the staged pixels
+  __shared__ __attribute__((aligned(16))) char lds[2 * kStage + (kRing + 2 * kMirror + 1) * kPitch];
+  __shared__ unsigned short taps_ok[2][kCh];
+  char *const Xs = lds + 2 * kStage;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = wave >> 2, kq = (wave >> 1) & 1, cq = wave & 1;   // filter row, channel quadrant
+  // tiles fastest: the workgroups that share a range of pixels share an L2
+  const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int split = fdiv(bid, a.div_tiles), tile = bid - split * a.tiles;
+  const int tk = fdiv(tile, a.div_tc), tc = tile - tk * a.tiles_c;
+  const int k0 = tk * 64, c0 = tc * 64, W = a.W;
+  const int mbeg = split * a.rows_per_split, mend = min(a.M, mbeg + a.rows_per_split);
+  const int chunks = (mend - mbeg + kCh - 1) / kCh;
+
+  const __amdgpu_buffer_rsrc_t rdy = make_rsrc(a.dy, (unsigned)a.M * a.K * 4u);
+  const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (unsigned)a.M * a.C * 4u);
+
+  // ---- staging: threads 0..511, 16 lanes (4 channels each) per row, one row of dY and one of X per chunk
+  const bool stager = wave < 8;
+  const int srow = (tid >> 4) & 31, sch = (tid & 15) * 4;
+  // byte offsets of this thread's piece of dY row mbeg and of ring row 0 (pixel mbeg - W - 1); a channel past the last
+  // one starts at kOOB and stays past the end whatever rows are added
+  const unsigned dyo = k0 + sch < a.K ? (unsigned)((mbeg + srow) * a.K + k0 + sch) * 4u : kOOB;
+  const unsigned xo = c0 + sch < a.C ? (unsigned)((mbeg - W - 1 + srow) * a.C + c0 + sch) * 4u : kOOB;
+  f32x4 rd = {0.f, 0.f, 0.f, 0.f}, rxv = {0.f, 0.f, 0.f, 0.f};
+  int xrow = 0, dyrow = 0;   // ring row and dY row (from mbeg) requested next
+  auto x_offset = [&]() {    // pixels off the tensor: an offset past its end
+    return (unsigned)(mbeg - W - 1 + xrow + srow) < (unsigned)a.M ? xo + (unsigned)(xrow * a.C) * 4u : kOOB;
+  };
+  auto load = [&](__amdgpu_buffer_rsrc_t r, unsigned o) {
+    asm("" : "+v"(o));   // a selected offset; left alone, the compiler makes two loads behind a branch
+    return buffer_load_16B(r, o);
+  };
+  auto request = [&]() {
+    rd = load(rdy, mbeg + dyrow + srow < mend ? dyo + (unsigned)(dyrow * a.K) * 4u : kOOB);
+    rxv = load(rx, x_offset());
+    dyrow += kCh;
+    xrow += kCh;
+  };
+  auto store_dy = [&](int stage) {
+    char *d = lds + stage * kStage + srow * kPitch + sch * 2;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(d + p * kPart) = split_part(rd);
+  };
+  auto store_x = [&](int row) {
+    const int slot = (row + srow) & (kRing - 1);
+    char *d = Xs + slot * kPitch + sch * 2;
+    u32x2 v[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(d + p * kPart) = v[p] = split_part(rxv);
+    if (slot < kMirror) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(d + kRing * kPitch + p * kPart) = v[p];
+    }
+  };
+  // which taps of pixel m read inside its image
+  auto taps_of = [&](int m) {
+    const int n = fdiv(m, a.div_plane), rem = m - n * (a.H * W);
+    const int h = fdiv(rem, a.div_w), w = rem - h * W;
+    const int rows = (h > 0 ? 1 : 0) | 2 | (h + 1 < a.H ? 4 : 0), cols = (w > 0 ? 1 : 0) | 2 | (w + 1 < W ? 4 : 0);
+    int v = 0;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) v |= (rows >> r) & 1 ? cols << (3 * r) : 0;
+    return v;
+  };
+
+  // ---- fragments.  Lane l supplies row 8*(l/32) + (l%16)/4 (and that + 4) of a 16-pixel k-step and columns
+  // 16*((l/16)%2) + 4*(l%4) .. +3 of a 32-channel tile, and receives column l%32 of rows 8*(l/32) .. +7
+  const int frow = (lane >> 5) * 8 + ((lane & 15) >> 2);
+  const int fcol = (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+  const int acol = frow * kPitch + kq * 64 + fcol, bcol = cq * 64 + fcol;
+  constexpr int kZero = (kRing + kMirror) * kPitch;
+  bf16x8 fa0[2], fa[3], fb[2][3];   // the filter-row tiles of a part in slots 0 and 1 in turn
+  int baddr[3][2];
+  auto fetch_a = [&](int set, int q, int at) {
+    const char *p = lds + at + acol + q * kPart;
+    const bf16x8 v = lds_read_tr_pair(p, p + 4 * kPitch);
+    if (q == 0) fa0[set] = v;
+    else fa[q] = v;
+  };
+  auto fetch_b = [&](int slot, int q) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      fb[slot][s] = lds_read_tr_pair(Xs + baddr[s][0] + s * kPitch + q * kPart, Xs + baddr[s][1] + (s + 4) * kPitch + q * kPart);
+  };
+  int ok0 = 0, ok1 = 0;    // validity bits of filter row fr for this lane's two rows of the k-step aimed at next
+  auto fetch_ok = [&](int stage, int ks) {
+    ok0 = taps_ok[stage][ks * 16 + frow] >> (3 * fr);
+    ok1 = taps_ok[stage][ks * 16 + frow + 4] >> (3 * fr);
+  };
+  auto aim = [&](int row) {   // row: ring row of this lane's first pixel at tap (fr, 0)
+    const int at = (row & (kRing - 1)) * kPitch;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const int v0 = (ok0 << (31 - s)) >> 31, v1 = (ok1 << (31 - s)) >> 31;
+      baddr[s][0] = ((at & v0) | (kZero & ~v0)) + bcol;
+      baddr[s][1] = ((at & v1) | (kZero & ~v1)) + bcol;
+    }
+  };
+
+  // Two accumulators a tap: the five products with a small factor add up apart from the leading one, so that a sum is
+  // rounded at its full size once per 16 pixels
+  f32x16 acc[3], small[3];
+#pragma unroll
+  for (int s = 0; s < 3; ++s)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[s][e] = small[s][e] = 0.f;
+  auto product = [&](f32x16 (&sum)[3], bf16x8 pa, int slot) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s) sum[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa, fb[slot][s], sum[s], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto lds_barrier = [&]() {
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+  };
+  auto taps_to_lds = [&](int stage, int m) {
+    if (tid < kCh) taps_ok[stage][tid] = (unsigned short)(m + tid < mend ? taps_of(m + tid) : 0);   // (no infinity past the end times 0)
+  };
+
+  // the ring up to the last row chunk 0 needs: rows 0 .. 2W + 33
+  for (int i = tid; i < (kMirror + 1) * kPitch / 4; i += kNT) *reinterpret_cast<unsigned *>(Xs + (kRing + kMirror) * kPitch + i * 4) = 0;
+  const int ahead = (2 * W + 2 + kCh - 1) / kCh * kCh;   // whole passes of X rows staged before chunk 0's own
+  if (stager) {
+    for (; xrow < ahead; xrow += kCh) {
+      rxv = load(rx, x_offset());
+      store_x(xrow);
+    }
+    request();             // dY of chunk 0, X rows ahead .. ahead + 31
+    store_dy(0);
+    store_x(ahead);
+    request();
+  }
+  taps_to_lds(0, mbeg);
+  lds_barrier();
+  fetch_ok(0, 0);
+  aim(frow + fr * W);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) fetch_a(0, q, 0);
+  fetch_b(0, 2);
+  fetch_ok(0, 1);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // Two k-steps of six product groups per chunk.  A part is fetched once its registers have served their last product:
+  // the parts of X one after the other into two slots, those of dY for the next k-step.  The next chunk goes to LDS
+  // during the first k-step; the barrier stands before the first fetch that reaches into it.
+  for (int it = 0; it < chunks; ++it) {
+    const int st = (it & 1) * kStage, nst = kStage - st;
+    const int row = it * kCh + frow + fr * W;
+    // ---- k-step 0: part 2 of X is in slot 0
+    fetch_b(1, 1);
+    product(small, fa0[0], 0);
+    fetch_b(0, 0);
+    if (stager) store_dy(nst ? 1 : 0);
+    product(small, fa0[0], 1);
+    product(small, fa[1], 1);
+    aim(row + 16);
+    fetch_b(1, 2);
+    if (stager) store_x(ahead + (it + 1) * kCh);
+    product(small, fa[2], 0);
+    fetch_a(1, 2, st + 16 * kPitch);
+    fetch_a(1, 0, st + 16 * kPitch);
+    taps_to_lds((it + 1) & 1, mbeg + (it + 1) * kCh);
+    product(small, fa[1], 0);
+    fetch_a(1, 1, st + 16 * kPitch);
+    product(acc, fa0[0], 0);
+    // ---- k-step 1: part 2 of X is in slot 1 (behind the last chunk, the fetches for the next bring rows nobody uses)
+    fetch_b(0, 1);
+    if (stager) request();
+    product(small, fa0[1], 1);
+    fetch_b(1, 0);
+    product(small, fa0[1], 0);
+    lds_barrier();
+    fetch_ok((it + 1) & 1, 0);
+    product(small, fa[1], 0);
+    aim(row + kCh);
+    fetch_b(0, 2);
+    fetch_ok((it + 1) & 1, 1);
+    product(small, fa[2], 1);
+    fetch_a(0, 2, nst);
+    fetch_a(0, 0, nst);
+    product(small, fa[1], 1);
+    fetch_a(0, 1, nst);
+    product(acc, fa0[1], 1);
+  }
+
+#pragma unroll
+  for (int s = 0; s < 3; ++s) acc[s] += small[s];
+  bool bad = false;
+#pragma unroll
+  for (int s = 0; s < 3; ++s)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) bad |= acc[s][e] != acc[s][e];
+  const int lr = lane & 31, lg = lane >> 5;
+  const int c = c0 + cq * 32 + lr;
+  if (__syncthreads_or(bad)) {
+    // a NaN somewhere in the tile: again in fp32, without staging
+    const int k = k0 + kq * 32 + lr;
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[s][e] = 0.f;
+    for (int m2 = mbeg; m2 < mend; m2 += 2) {
+      const int m = m2 + lg;
+      const int n = fdiv(m, a.div_plane), rem = m - n * (a.H * W);
+      const int h = fdiv(rem, a.div_w), w = rem - h * W;
+      const bool in = m < mend && (unsigned)(h + fr - 1) < (unsigned)a.H;
+      const float d = m < mend && k < a.K ? a.dy[(size_t)m * a.K + k] : 0.f;
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        const bool ok = in && (unsigned)(w + s - 1) < (unsigned)W && c < a.C;
+        const float x = ok ? a.x[(size_t)(m + (fr - 1) * W + s - 1) * a.C + c] : 0.f;
+        acc[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(d, x, acc[s], 0, 0, 0);
+      }
+    }
+  }
+  float *out = a.out + (size_t)split * a.K * 9 * a.C;
+#pragma unroll
+  for (int s = 0; s < 3; ++s)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int k = k0 + kq * 32 + (e >> 2) * 8 + lg * 4 + (e & 3);
+      if (k < a.K && c < a.C) out[((size_t)k * 9 + fr * 3 + s) * a.C + c] = acc[s][e];
+    }
+}
+
+}  // namespace
+
+constexpr int kWgrad3MaxW = 56;
+
+// Not the smallest layers, where the one-tap kernel has nine times the workgroups: 16 x 16 channels, 128 pixels 13 us
+// there, 16 here; 1024 pixels 16 either way; 16384 pixels (the first taken here) 22 there, 19 here.
+bool wgrad3_takes(const ConvGeom &g) {
+  return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 && g.W <= kWgrad3MaxW &&
+         (long long)g.N * g.H * g.W * g.K * g.C >= 1LL << 22;
+}
+
+int wgrad3_launch(const ConvGeom &g, const float *dy, const float *x, float *out, int splits, int rows_per_split, hipStream_t st) {
+  Wgrad3Args a{};
+  a.dy = dy; a.x = x; a.out = out;
+  a.M = g.N * g.H * g.W; a.W = g.W; a.H = g.H; a.C = g.C; a.K = g.K; a.rows_per_split = rows_per_split;
+  a.tiles_c = (g.C + 63) / 64;
+  a.tiles = a.tiles_c * ((g.K + 63) / 64);
+  a.div_tiles = make_fastdiv((unsigned)a.tiles); a.div_tc = make_fastdiv((unsigned)a.tiles_c);
+  a.div_plane = make_fastdiv((unsigned)(g.H * g.W)); a.div_w = make_fastdiv((unsigned)g.W);
+  if (rows_per_split < kCh || rows_per_split % kCh || (long long)splits * rows_per_split < a.M ||
+      (long long)(splits - 1) * rows_per_split >= a.M)
+    return set_error(RESIST_EINVAL, "wgrad3: %d splits of %d rows for %d rows", splits, rows_per_split, a.M);
+  hipLaunchKernelGGL(wgrad3_split_kernel, dim3((unsigned)(a.tiles * splits)), dim3(kNT), 0, st, a);
+  RESIST_CHECK_LAUNCH("wgrad3");
+  return RESIST_OK;
+}
+
+}  // namespace resist

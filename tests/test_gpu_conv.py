@@ -106,6 +106,24 @@ def test_conv_split_forward_and_dgrad(case):
     assert_close(dx.cpu().numpy().transpose(0, 3, 1, 2), want, f"conv dgrad {case}")
 
 
+# nine-tap weight gradient: ragged channel tiles and pixel chunks, one split and several, the ring of staged pixels run
+# through many times, images one pixel wide and the widest that is staged, and a layer just too small for it
+#              N   H   W   C    K   R st pad
+WGRAD3_CASES = [(3, 3, 1, 700, 680, 3, 1, 1), (1, 5, 5, 512, 344, 3, 1, 1), (2, 45, 56, 36, 40, 3, 1, 1), (7, 19, 33, 64, 64, 3, 1, 1),
+                (64, 16, 16, 16, 16, 3, 1, 1), (63, 16, 16, 16, 16, 3, 1, 1), (130, 4, 4, 80, 132, 3, 1, 1), (2, 31, 57, 64, 64, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("case", WGRAD3_CASES)
+def test_conv_nine_tap_wgrad(case):
+    print("case", case, flush=True)
+    x, w, dy = _tensors(case, 10)
+    N, H, W, C, K = case[:5]
+    dy = (dy / np.sqrt(N * H * W)).astype(np.float32)
+    dw = R.conv2d_wgrad(_nhwc(dy), _nhwc(x), (K, 3, 3, C), 1, 1)
+    torch.cuda.synchronize()
+    assert_close(dw.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_wgrad(dy, x, w.shape, 1, 1), f"conv wgrad {case}")
+
+
 def _same_values(got, want, what):
     # infinities and NaN where float64 has them, everything else close (values next to the largest float included)
     with np.errstate(over="ignore"):
@@ -120,6 +138,18 @@ def test_conv_split_infinities():
     torch.cuda.synchronize()
     with np.errstate(invalid="ignore"):
         _same_values(y.cpu().numpy(), L.conv2d_fwd(x.astype(np.float64), w, 1, 1), "fwd")
+
+
+def test_conv_nine_tap_wgrad_infinities():
+    case = (8, 16, 16, 72, 72, 3, 1, 1)
+    x, w, dy = _tensors(case, 11)
+    dy /= 64
+    x[0, 5, 2, 3], x[1, 66, 8, 0], x[2, 9, 7, 7], dy[3, 70, 9, 9] = np.inf, -np.inf, np.nan, np.inf
+    x[4, 2, 8, 8] = 3.4e38
+    dw = R.conv2d_wgrad(_nhwc(dy), _nhwc(x), (72, 3, 3, 72), 1, 1)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        _same_values(dw.cpu().numpy(), L.conv2d_wgrad(dy.astype(np.float64), x, w.shape, 1, 1), "wgrad")
 
 
 # ---- bf16 operands, fp32 accumulation ---------------------------------------------------------
