@@ -302,6 +302,8 @@ int launch_igemm(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
 
 template <typename T, int MODE>
 int dispatch_igemm(const IgemmArgs &a, hipStream_t st, StatParts *tiles_m_out = nullptr) {
+  constexpr int dt = sizeof(T) == 2 ? DT_BF16 : DT_F32;
+  if (conv_small_takes(a, dt)) return conv_small_launch(a, dt, MODE, st, tiles_m_out);
   if constexpr (sizeof(T) == 4) {
     if (conv3_takes(a)) return conv3_launch(a, MODE, st, tiles_m_out);
   }
@@ -358,8 +360,9 @@ int check_geom(const ConvGeom &g, int dt) {
 int conv_check(const ConvGeom &g, int dt) { return check_geom(g, dt); }
 
 int64_t conv_stats_floats(const ConvGeom &g) {
-  // the smallest row tile any forward kernel uses is 64
-  return (int64_t)3 * (((int64_t)g.N * g.P * g.Q + 63) / 64) * g.K;
+  // the smallest row tile a forward kernel uses is 64, of a small output 32
+  const int64_t M = (int64_t)g.N * g.P * g.Q, rows = conv_small_rows(M, g.K, 1) ? 32 : 64;
+  return 3 * ((M + rows - 1) / rows) * g.K;
 }
 
 int conv_fwd(const ConvGeom &g, int dt, const void *x, const void *w, void *y, const void *addend, float *stats, StatParts *stat_parts,
@@ -406,8 +409,9 @@ int conv_dgrad(const ConvGeom &g, int dt, const void *dy, const void *wT, void *
 }
 
 int64_t conv_dgrad_bn_sums_floats(const ConvGeom &g) {
-  // the smallest row tile any data-gradient kernel uses is 64
-  return (int64_t)2 * (((int64_t)g.N * g.H * g.W + 63) / 64) * g.C;
+  // the smallest row tile a data-gradient kernel uses is 64, of a small output 32
+  const int64_t M = (int64_t)g.N * g.H * g.W, rows = conv_small_rows(M, g.C, 1) ? 32 : 64;
+  return 2 * ((M + rows - 1) / rows) * g.C;
 }
 
 // ---- filter preparation: wT[c][r][s][k] = w[k][r][s][c] (and a low-precision copy of w) ------------

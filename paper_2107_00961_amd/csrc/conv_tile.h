@@ -141,7 +141,8 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
   T *out = static_cast<T *>(a.out);
   const T *addend = static_cast<const T *>(a.addend);
   constexpr int CV = BN / VEC;            // 16-byte pieces per tile row
-  constexpr int RPS = NT / CV;      // rows per pass
+  constexpr bool kSpare = NT / CV > BM;   // a tile with fewer pieces than there are threads
+  constexpr int RPS = kSpare ? BM : NT / CV;      // rows per pass
   constexpr int NP = BM / RPS;      // passes over the tile
   constexpr int PG = NP < 8 ? NP : 8;   // passes whose side inputs are in flight together
   static_assert(BM % RPS == 0 && CV <= 32 && NP % PG == 0, "output tile rows per pass");
@@ -161,7 +162,8 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
   auto request_side = [&](int p0) {
 #pragma unroll
     for (int g = 0; g < PG; ++g) {
-      const int ro = row_off[row0 + (p0 + g) * RPS];
+      int ro = -1;
+      if (!kSpare || row0 < BM) ro = row_off[row0 + (p0 + g) * RPS];
       live[g] = ro >= 0 && col_ok;
       offs[g] = live[g] ? (size_t)ro * a.OC + n0 + cv : 0;
       q_ad[g] = q_mk[g] = q_y[g] = typename Vec<T>::Raw{};
@@ -312,6 +314,10 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
 // 3x3 stride-1 convolutions in fp32 through operands split into three bf16 parts (conv3.hip)
 bool conv3_takes(const IgemmArgs &a);
 int conv3_launch(const IgemmArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);
+// convolutions with few output tiles: 32x32 tiles, the reduction split among the waves of a workgroup (conv_small.hip)
+bool conv_small_takes(const IgemmArgs &a, int dt);
+bool conv_small_rows(long long pixels, int OC, int cls);   // whether it may take an output of this size, in 32-row tiles
+int conv_small_launch(const IgemmArgs &a, int dt, int mode, hipStream_t st, StatParts *tiles_m_out);
 // the weight gradient of such a convolution (wgrad3.hip): out [splits][K][3][3][C], a multiple of 32 rows each
 bool wgrad3_takes(const ConvGeom &g);
 int wgrad3_launch(const ConvGeom &g, const float *dy, const float *x, float *out, int splits, int rows_per_split, hipStream_t st);

@@ -152,6 +152,40 @@ def test_conv_nine_tap_wgrad_infinities():
         _same_values(dw.cpu().numpy(), L.conv2d_wgrad(dy.astype(np.float64), x, w.shape, 1, 1), "wgrad")
 
 
+# ---- small outputs: 32x32 tiles, the reduction split among eight waves ------------------------------------------------
+# One tile and 256 (and just past them: the larger tiles), ragged pixel and channel tiles, channels that fill a part of a
+# 128-byte unit, fewer units than waves, an odd share, strides, 1x1 / 5x5 / 7x7 filters, parity classes without a tap
+#              N   H   W   C    K   R st pad
+SMALL_CASES = [(1, 1, 1, 144, 8, 1, 1, 0), (1, 4, 4, 512, 512, 3, 1, 1), (1, 7, 7, 520, 40, 3, 1, 1), (2, 5, 3, 16, 24, 3, 1, 1),
+               (4, 16, 16, 128, 256, 3, 1, 1), (33, 8, 8, 128, 128, 3, 1, 1), (3, 9, 11, 1032, 72, 1, 1, 0), (2, 14, 14, 256, 64, 3, 2, 1),
+               (1, 8, 8, 640, 96, 1, 2, 0), (5, 4, 6, 64, 136, 5, 1, 2), (2, 8, 10, 48, 32, 7, 2, 3), (1, 2, 2, 1024, 2048, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("case", SMALL_CASES)
+def test_conv_small_forward_and_dgrad(case, dt):
+    print("case", case, dt, flush=True)
+    N, H, W, C, K, R_, st, pad = case
+    x, w, _ = _tensors(case, 12)
+    bf = dt == "bf16"
+    wt = np.ascontiguousarray(w.transpose(1, 0, 2, 3))   # layer K -> C
+    rnd = (lambda t: torch.from_numpy(t).bfloat16().float().numpy()) if bf else (lambda t: t)
+    dev = (lambda t: _nhwc(t).bfloat16()) if bf else _nhwc
+    x, w, wt = rnd(x), rnd(w), rnd(wt)
+    y = R.conv2d_forward(dev(x), dev(w), st, pad)
+    P, Q = (H + 2 * pad - R_) // st + 1, (W + 2 * pad - R_) // st + 1
+    # data gradient of a layer K -> C, whose output gradient [N][P][Q][C] makes the reduction as long as the forward's
+    g = rnd(np.random.default_rng(13).standard_normal((N, C, P, Q)).astype(np.float32))
+    dx = R.conv2d_dgrad(dev(g), dev(wt), (N, H, W, K), st, pad)
+    torch.cuda.synchronize()
+    # results are of order 1.  bf16: the output's own rounding, 2^-9 of a value; fp32: each of up to 4680 additions rounds by at
+    # most 2^-24 of a partial sum of order 1, in random directions: sqrt(4680) * 2^-24 = 4e-6, and 5 times that for the largest
+    tol = dict(rtol=2.0 ** -8, atol=2e-3) if bf else dict(rtol=1e-5, atol=2e-5)
+    np.testing.assert_allclose(y.float().cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_fwd(x, w, st, pad), err_msg=f"fwd {case}", **tol)
+    np.testing.assert_allclose(dx.float().cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_dgrad(g, wt, (N, K, H, W), st, pad),
+                               err_msg=f"dgrad {case}", **tol)
+
+
 # ---- bf16 operands, fp32 accumulation ---------------------------------------------------------
 # Inputs are bfloat16 numbers, so the oracle's float64 result is the exact convolution of what the
 # kernel reads.  Outputs stored as bfloat16 carry half a bfloat16 ulp (2^-9 relative, 2^-8 of the
