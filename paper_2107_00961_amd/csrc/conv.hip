@@ -896,7 +896,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 
 constexpr size_t kStaticScratchBytes = (size_t)32 << 20;   // library-owned partial sums (see conv_wgrad_static)
 
-struct WgradPlan { int bm, bn, splits, rows_per_split; bool taps9 = false; };
+struct WgradPlan { int bm, bn, splits, rows_per_split; bool taps9 = false, taps3 = false; };
 
 // Nine-tap kernel (wgrad3.hip): 64 x 64 channels of all taps per workgroup, one workgroup per CU.  Its time is that of
 // the rounds of 256 workgroups, 0.05 us per row and 128 rows' worth for its start and end, 0.06 us per partial tile
@@ -916,6 +916,23 @@ WgradPlan plan_wgrad3(const ConvGeom &g, long long max_floats) {
     const long long cost = (tiles * used + 255) / 256 * (rows + 128) * 5 + (used > 1 ? tiles * used * 6 + 400 : 0);
     if (best < 0 || cost < best) { best = cost; p.splits = (int)used; p.rows_per_split = (int)rows; }
   }
+  return p;
+}
+
+// One filter row per workgroup (wgrad3_row_bf16_kernel): as many splits as give 384 workgroups, which leaves compute units
+// room for the data gradients that run beside them (CIFAR-shaped model, batch 128: 256 workgroups 5.70 ms, 384 5.65, 512
+// 5.72), but not two: a second split of 192 or more tiles costs as much in partial sums as it saves (512 -> 512 channels
+// at 7x7, batch 64: 36 us in one, 32 + 5 in two; batch 8: 12 and 17 + 6).
+WgradPlan plan_wgrad_rows(const ConvGeom &g) {
+  WgradPlan p;
+  p.bm = p.bn = 64;
+  p.taps3 = true;
+  const long long tiles = (long long)((g.K + 63) / 64) * ((g.C + 63) / 64) * 3, M = (long long)g.N * g.P * g.Q;
+  long long splits = std::min(384 / tiles, (M + 255) / 256);
+  if (splits <= 2) splits = 1;
+  const long long rows = ((M + splits - 1) / splits + 63) / 64 * 64;
+  p.rows_per_split = (int)rows;
+  p.splits = (int)((M + rows - 1) / rows);
   return p;
 }
 
@@ -950,6 +967,14 @@ int run_wgrad(const WgradPlan &p, const ConvGeom &g, int dt, const void *dy, con
       prof::Scope ps("wgrad3_f32", 2.0 * M * g.K * g.C * 9, 4.0 * (M * (g.K + g.C) + 9.0 * g.K * g.C), st);
       RESIST_TRY(wgrad3_launch(g, static_cast<const float *>(dy), static_cast<const float *>(x), p.splits > 1 ? partial : dw, p.splits,
                                p.rows_per_split, st));
+    }
+    return p.splits > 1 ? splitk_reduce(partial, dw, (long long)g.K * 9 * g.C / 4, p.splits, st) : RESIST_OK;
+  }
+  if (p.taps3) {
+    {
+      const double M = (double)g.N * g.P * g.Q;
+      prof::Scope ps("wgrad3_row_bf16", 2.0 * M * g.K * g.C * 9, 2.0 * M * (g.K + g.C) + 36.0 * g.K * g.C, st);
+      RESIST_TRY(wgrad3_row_launch(g, dy, x, p.splits > 1 ? partial : dw, p.splits, p.rows_per_split, st));
     }
     return p.splits > 1 ? splitk_reduce(partial, dw, (long long)g.K * 9 * g.C / 4, p.splits, st) : RESIST_OK;
   }
@@ -989,6 +1014,7 @@ int run_wgrad(const WgradPlan &p, const ConvGeom &g, int dt, const void *dy, con
 // same layers, and gives the same bits as conv_wgrad, whichever kernel runs.
 static WgradPlan plan_for(const ConvGeom &g, int dt) {
   const WgradPlan p = plan_wgrad(g);
+  if (dt == DT_BF16 && wgrad3_row_takes(g)) return plan_wgrad_rows(g);   // at most 19 MB of partial sums
   if (dt != DT_F32 || !wgrad3_takes(g)) return p;
   return plan_wgrad3(g, plan_floats(p, g) * 4 <= (int64_t)kStaticScratchBytes ? (long long)(kStaticScratchBytes / 4) : INT64_MAX);
 }

@@ -320,6 +320,9 @@ bool conv_small_rows(long long pixels, int OC, int cls);   // whether it may tak
 int conv_small_launch(const IgemmArgs &a, int dt, int mode, hipStream_t st, StatParts *tiles_m_out);
 // the weight gradient of such a convolution (wgrad3.hip): out [splits][K][3][3][C], a multiple of 32 rows each
 bool wgrad3_takes(const ConvGeom &g);
+// the same in bf16, one filter row per workgroup
+bool wgrad3_row_takes(const ConvGeom &g);
+int wgrad3_row_launch(const ConvGeom &g, const void *dy, const void *x, float *out, int splits, int rows_per_split, hipStream_t st);
 int wgrad3_launch(const ConvGeom &g, const float *dy, const float *x, float *out, int splits, int rows_per_split, hipStream_t st);
 
 }  // namespace resist

@@ -258,6 +258,185 @@ __global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
     }
 }
 
+// ---- bf16 tensors: one filter row per workgroup -----------------------------------------------------------------------
+//
+// With one part an operand costs no arithmetic to stage, and the partial sums of nine taps per workgroup would take longer
+// than the products; with one tap per workgroup (wgrad_bf16_kernel) every pixel comes from the L2 nine times.  Here a
+// workgroup owns 64 x 64 channels of the three taps of one filter row: tap s of pixel m is pixel m + (r-1)*W + s - 1, so the
+// 64 pixels of a chunk and one on either side serve three taps.  X rows live in a ring as above.  Eight waves: four
+// quadrants of the channels, two halves of a chunk's pixels, added through LDS at the end.
+//
+// Measured with the reduction of the partial sums, us, one tap -> one filter row per workgroup:
+//   batch 128: 256 ch 8x8 32.1 -> 32.3    128 ch 16x16 31.3 -> 31.6    64 ch 32x32 29.8 -> 28.8    512 ch 4x4 27.8 -> 26.7
+//   batch 64:  256 ch 14x14 40.3 -> 39.7  128 ch 28x28 38.5 -> 37.9    64 ch 56x56 37.8 -> 36.5
+// Alone it is little faster: it is bound by the LDS reads of the fragments, 1.3 per product.  Beside the data gradients of a
+// step, which are short of L2 bandwidth, it is: CIFAR-shaped model, batch 128, 5.89 -> 5.65 ms.
+constexpr int kRowNT = 512, kRowCh = 64, kRowRing = 256, kRowPitch = kPart + 64;
+
+struct WgradRowArgs {
+  const void *dy, *x;
+  float *out;               // [splits][K][9][C]
+  int M, W, H, C, K, rows_per_split, tiles_c, tiles;
+  FastDiv div_tiles, div_tc, div_plane, div_w;
+};
+
+__global__ __launch_bounds__(kRowNT) void wgrad3_row_bf16_kernel(WgradRowArgs a) {
+  constexpr int kDyStage = kRowCh * kRowPitch;
+  __shared__ __attribute__((aligned(16))) char lds[2 * kDyStage + (kRowRing + 2 * kMirror + 1) * kRowPitch];
+  __shared__ unsigned char taps_ok[2][kRowCh];
+  static_assert(2 * kDyStage + kRowRing * kRowPitch >= 4 * 3 * 4096, "half of the accumulators fits");
+  char *const Xs = lds + 2 * kDyStage;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = wave >> 2, kq = (wave >> 1) & 1, cq = wave & 1;
+  // tiles fastest, then filter rows: the workgroups that share a range of pixels share an L2
+  const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int sr = fdiv(bid, a.div_tiles), tile = bid - sr * a.tiles;
+  const int split = sr / 3, fr = sr - split * 3;
+  const int tk = fdiv(tile, a.div_tc), tc = tile - tk * a.tiles_c;
+  const int k0 = tk * 64, c0 = tc * 64, W = a.W;
+  const int mbeg = split * a.rows_per_split, mend = min(a.M, mbeg + a.rows_per_split);
+  const int chunks = (mend - mbeg + kRowCh - 1) / kRowCh;
+
+  const __amdgpu_buffer_rsrc_t rdy = make_rsrc(a.dy, (unsigned)a.M * a.K * 2u);
+  const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (unsigned)a.M * a.C * 2u);
+
+  // ---- staging: 8 lanes (8 channels each) per row, one row of dY and one of X per thread and chunk
+  const int srow = tid >> 3, sch = (tid & 7) * 8;
+  const bool k_ok = k0 + sch < a.K, c_ok = c0 + sch < a.C;
+  const int xpix = mbeg + (fr - 1) * W - 1 + srow;   // pixel of ring row srow
+  f32x4 rd[2], rxv[2];
+  int xrow = 0, dyrow = 0;
+  auto load = [&](__amdgpu_buffer_rsrc_t r, unsigned o) {
+    asm("" : "+v"(o));   // a selected offset; left alone, the compiler makes two loads behind a branch
+    return buffer_load_16B(r, o);
+  };
+  auto request_x = [&](int set) {
+    const int m = xpix + xrow;
+    rxv[set] = load(rx, c_ok && (unsigned)m < (unsigned)a.M ? (unsigned)(m * a.C + c0 + sch) * 2u : kOOB);
+    xrow += kRowCh;
+  };
+  auto request_dy = [&](int set) {
+    const int m = mbeg + dyrow + srow;
+    rd[set] = load(rdy, k_ok && m < mend ? (unsigned)(m * a.K + k0 + sch) * 2u : kOOB);
+    dyrow += kRowCh;
+  };
+  auto store_dy = [&](int stage, int set) { *reinterpret_cast<f32x4 *>(lds + stage * kDyStage + srow * kRowPitch + sch * 2) = rd[set]; };
+  auto store_x = [&](int row, int set) {
+    const int slot = (row + srow) & (kRowRing - 1);
+    char *d = Xs + slot * kRowPitch + sch * 2;
+    *reinterpret_cast<f32x4 *>(d) = rxv[set];
+    if (slot < kMirror) *reinterpret_cast<f32x4 *>(d + kRowRing * kRowPitch) = rxv[set];
+  };
+  // which taps of this filter row read inside the image of pixel m
+  auto taps_to_lds = [&](int stage, int m0) {
+    if (tid < kRowCh) {
+      const int m = m0 + tid;
+      const int n = fdiv(m, a.div_plane), rem = m - n * (a.H * W);
+      const int h = fdiv(rem, a.div_w), w = rem - h * W;
+      const bool in = m < mend && (unsigned)(h + fr - 1) < (unsigned)a.H;
+      taps_ok[stage][tid] = (unsigned char)(in ? (w > 0 ? 1 : 0) | 2 | (w + 1 < W ? 4 : 0) : 0);
+    }
+  };
+
+  // ---- fragments, as above; this wave's pixels of a chunk start at half * 32
+  const int frow = (lane >> 5) * 8 + ((lane & 15) >> 2);
+  const int fcol = (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+  const int acol = (half * 32 + frow) * kRowPitch + kq * 64 + fcol, bcol = cq * 64 + fcol;
+  constexpr int kZero = (kRowRing + kMirror) * kRowPitch;
+  bf16x8 fa[2], fb[2][3];
+  int ok[2][2];   // per k-step: tap bits of this lane's two pixels
+  auto fetch_ok = [&](int stage) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      ok[ks][0] = taps_ok[stage][half * 32 + ks * 16 + frow];
+      ok[ks][1] = taps_ok[stage][half * 32 + ks * 16 + frow + 4];
+    }
+  };
+  auto fetch = [&](int ks, int stage, int it) {
+    const char *p = lds + stage * kDyStage + acol + ks * 16 * kRowPitch;
+    fa[ks] = lds_read_tr_pair(p, p + 4 * kRowPitch);
+    const int at = ((it * kRowCh + half * 32 + ks * 16 + frow) & (kRowRing - 1)) * kRowPitch;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const int b0 = ((ok[ks][0] >> s) & 1 ? at : kZero) + bcol, b1 = ((ok[ks][1] >> s) & 1 ? at : kZero) + bcol;
+      fb[ks][s] = lds_read_tr_pair(Xs + b0 + s * kRowPitch, Xs + b1 + (s + 4) * kRowPitch);
+    }
+  };
+  f32x16 acc[3];
+#pragma unroll
+  for (int s = 0; s < 3; ++s)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[s][e] = 0.f;
+  auto product = [&](int ks) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s) acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks][s], acc[s], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto lds_barrier = [&]() {
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+  };
+
+  // Chunk t needs ring rows 64 t .. 64 t + 65, i.e. passes t and t + 1 of X.  Behind chunk t wait, in register set (t + 1) % 2,
+  // dY of chunk t + 1 and pass t + 2; those of chunk t + 2 are in flight.
+  request_x(0); request_x(1); request_dy(0);
+  for (int i = tid; i < (kMirror + 1) * kRowPitch / 4; i += kRowNT) *reinterpret_cast<unsigned *>(Xs + kZero + i * 4) = 0;
+  taps_to_lds(0, mbeg);
+  store_x(0, 0); store_x(kRowCh, 1); store_dy(0, 0);
+  request_dy(1); request_x(1);
+  request_dy(0); request_x(0);
+  lds_barrier();
+  fetch_ok(0);
+  fetch(0, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  auto chunk = [&](int set, int it) {
+    const int st = it & 1;
+    fetch(1, st, it);
+    store_dy(st ^ 1, set);
+    store_x((it + 2) * kRowCh, set);
+    taps_to_lds(st ^ 1, mbeg + (it + 1) * kRowCh);
+    request_dy(set);
+    request_x(set);
+    __builtin_amdgcn_sched_barrier(0);
+    product(0);
+    lds_barrier();
+    fetch_ok(st ^ 1);
+    fetch(0, st ^ 1, it + 1);   // behind the last chunk: zeros nobody uses
+    __builtin_amdgcn_sched_barrier(0);
+    product(1);
+  };
+  for (int it = 0; it < chunks; it += 2) {   // behind an odd number of them: one without a valid pixel
+    chunk(1, it);
+    chunk(0, it + 1);
+  }
+
+  // the second half's sums go to the first
+  __syncthreads();
+  f32x4 *const red = reinterpret_cast<f32x4 *>(lds);
+  if (half == 1) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        red[(((wave & 3) * 3 + s) * 4 + g) * 64 + lane] = f32x4{acc[s][4 * g], acc[s][4 * g + 1], acc[s][4 * g + 2], acc[s][4 * g + 3]};
+  }
+  __syncthreads();
+  if (half == 1) return;
+  const int lr = lane & 31, lg = lane >> 5, c = c0 + cq * 32 + lr;
+  float *out = a.out + (size_t)split * a.K * 9 * a.C;
+#pragma unroll
+  for (int s = 0; s < 3; ++s)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 o = red[((wave * 3 + s) * 4 + g) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = k0 + kq * 32 + g * 8 + lg * 4 + e;
+        if (k < a.K && c < a.C) out[((size_t)k * 9 + fr * 3 + s) * a.C + c] = acc[s][4 * g + e] + o[e];
+      }
+    }
+}
+
 }  // namespace
 
 constexpr int kWgrad3MaxW = 56;
@@ -282,6 +461,30 @@ int wgrad3_launch(const ConvGeom &g, const float *dy, const float *x, float *out
     return set_error(RESIST_EINVAL, "wgrad3: %d splits of %d rows for %d rows", splits, rows_per_split, a.M);
   hipLaunchKernelGGL(wgrad3_split_kernel, dim3((unsigned)(a.tiles * splits)), dim3(kNT), 0, st, a);
   RESIST_CHECK_LAUNCH("wgrad3");
+  return RESIST_OK;
+}
+
+// From 2^28 products a tap, or where the tiles of the three rows nearly fill the chip by themselves: one split, no partial
+// sums (512 -> 512 channels, batch 8 at 7x7: 22.5 -> 11.8 us, batch 16 at 4x4: 10.7 -> 9.1).  Below that the one-tap
+// kernel's nine times as many workgroups win: 256 ch 8x8, batch 16 15.2 there, 16.0 here; 128 ch 28x28, batch 8 17.2 and 20.
+bool wgrad3_row_takes(const ConvGeom &g) {
+  return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 &&
+         ((long long)g.N * g.H * g.W * g.K * g.C >= 1LL << 28 || (long long)g.K * g.C >= 1LL << 18);
+}
+
+int wgrad3_row_launch(const ConvGeom &g, const void *dy, const void *x, float *out, int splits, int rows_per_split, hipStream_t st) {
+  WgradRowArgs a{};
+  a.dy = dy; a.x = x; a.out = out;
+  a.M = g.N * g.H * g.W; a.W = g.W; a.H = g.H; a.C = g.C; a.K = g.K; a.rows_per_split = rows_per_split;
+  a.tiles_c = (g.C + 63) / 64;
+  a.tiles = a.tiles_c * ((g.K + 63) / 64);
+  a.div_tiles = make_fastdiv((unsigned)a.tiles); a.div_tc = make_fastdiv((unsigned)a.tiles_c);
+  a.div_plane = make_fastdiv((unsigned)(g.H * g.W)); a.div_w = make_fastdiv((unsigned)g.W);
+  const long long grid = (long long)a.tiles * 3 * splits;
+  if (rows_per_split < 1 || (long long)splits * rows_per_split < a.M || (long long)(splits - 1) * rows_per_split >= a.M || grid > 0x7fffffffLL)
+    return set_error(RESIST_EINVAL, "wgrad3 rows: %d splits of %d rows for %d rows", splits, rows_per_split, a.M);
+  hipLaunchKernelGGL(wgrad3_row_bf16_kernel, dim3((unsigned)grid), dim3(kRowNT), 0, st, a);
+  RESIST_CHECK_LAUNCH("wgrad3_row");
   return RESIST_OK;
 }
 

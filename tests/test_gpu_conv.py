@@ -233,7 +233,15 @@ def test_conv_dgrad_bf16(case):
                  rtol=2.0 ** -8, atol=1e-5)
 
 
-@pytest.mark.parametrize("case", BF16_CASES)
+# one filter row per workgroup (bf16 3x3 weight gradients from 2^28 products a tap, or 2^18 pairs of channels): ragged channel
+# tiles, one split and several, odd and even numbers of 64-pixel chunks, the ring of staged rows run through many times, images
+# one pixel wide and wide ones, and a layer just too small for it
+#                  N   H   W   C    K   R st pad
+WGRAD_ROW_CASES = [(1, 5, 5, 512, 512, 3, 1, 1), (3, 7, 1, 520, 512, 3, 1, 1), (2, 1, 90, 584, 456, 3, 1, 1), (7, 4, 4, 1032, 264, 3, 1, 1),
+                   (5, 64, 45, 136, 152, 3, 1, 1), (33, 45, 45, 64, 64, 3, 1, 1), (16, 64, 64, 64, 64, 3, 1, 1), (16, 64, 63, 64, 64, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("case", BF16_CASES + WGRAD_ROW_CASES)
 def test_conv_wgrad_bf16(case):
     print("case", case, flush=True)
     x, w, dy = _bf16_tensors(case, 5)
