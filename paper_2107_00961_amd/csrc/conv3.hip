@@ -7,7 +7,8 @@
 // v_mfma_f32_32x32x2_f32 per cycle, so six of them take 6/16 of the time one fp32 product takes.
 //
 // Infinities (and finite values that round to one) leave a NaN in the difference a - h and so in every output they
-// reach; a workgroup that finds a NaN in its tile computes the tile again on the fp32 matrix instruction.
+// reach, and h*h' may overflow where a*b, within 0.8 % of the largest float, does not; a workgroup that finds a result that is not finite computes its
+// tile again on the fp32 matrix instruction.
 //
 // What bounds this kernel is the staging: an operand element costs 5.5 vector instructions to take apart and 6 bytes of
 // LDS.  So the input pixels of a tile are staged once per 64 channels and serve all nine taps: the tile is a range of
@@ -288,12 +289,12 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
 #pragma unroll
       for (int k = 1; k < kWGK; ++k) v[g] += red[((wm * kWGK + k) * NSUB * 4 + wk * NSUB + g) * 64 + lane];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) bad |= v[g][e] != v[g][e];
+      for (int e = 0; e < 4; ++e) bad |= !__builtin_isfinite(v[g][e]);
     }
     // group g of this wave: rows 8*ge + 4*lg .. +3 of sub-tile u, column lr
     const int g0 = wk * NSUB;
     if (__syncthreads_or(bad)) {
-      // a NaN somewhere in the tile: again in fp32, without staging
+      // a result that is not finite somewhere in the tile: again in fp32, without staging
       const int u = g0 / 4, i = u / kTN, j = u % kTN;
       const float *in = static_cast<const float *>(a.in), *wt = static_cast<const float *>(a.wt);
       const int m = m0 + wm * WTM + i * 32 + lr, oc = n0 + j * 32 + lr;

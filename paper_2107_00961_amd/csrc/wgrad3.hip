@@ -1,5 +1,5 @@
 // Weight gradient of a 3x3 stride-1 convolution of fp32 tensors on the bf16 matrix core (three bf16 parts per operand,
-// six products, small terms first; infinities through a second pass on the fp32 instruction: see conv3.hip).
+// six products, small terms first; results that are not finite through a second pass on the fp32 instruction: see conv3.hip).
 //
 //   dW[k][r][s][c] = sum over pixels m of dY[m][k] * X[m + (r-1)*W + (s-1)][c]     (X of a tap off the image is zero)
 //
@@ -224,11 +224,11 @@ __global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
 #pragma unroll
   for (int s = 0; s < 3; ++s)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) bad |= acc[s][e] != acc[s][e];
+    for (int e = 0; e < 16; ++e) bad |= !__builtin_isfinite(acc[s][e]);
   const int lr = lane & 31, lg = lane >> 5;
   const int c = c0 + cq * 32 + lr;
   if (__syncthreads_or(bad)) {
-    // a NaN somewhere in the tile: again in fp32, without staging
+    // a result that is not finite somewhere in the tile: again in fp32, without staging
     const int k = k0 + kq * 32 + lr;
 #pragma unroll
     for (int s = 0; s < 3; ++s)

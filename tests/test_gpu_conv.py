@@ -152,6 +152,49 @@ def test_conv_nine_tap_wgrad_infinities():
         _same_values(dw.cpu().numpy(), L.conv2d_wgrad(dy.astype(np.float64), x, w.shape, 1, 1), "wgrad")
 
 
+def _launched(f):
+    """The result of f and the names of the kernels it launched."""
+    R.profile_enable(True)
+    try:
+        out = f()
+        return out, {k["name"] for k in R.profile_read()}
+    finally:
+        R.profile_enable(False)
+
+
+# forward (or data gradient) on 64- and on 128-pixel tiles, and the weight gradient of the same layers
+#                   N   H   W   C    K   R st pad
+SPLIT_EDGE_CASES = [((33, 8, 8, 96, 288, 3, 1, 1), "64x64"), ((65, 16, 16, 64, 128, 3, 1, 1), "128x64")]
+
+
+def _split_layer(case, x, w, dy):
+    """y and dx (of the layer with in- and output channels exchanged) and dw on the kernels that take operands apart."""
+    (N, H, W, C, K, *_), tile = case
+    wt = np.ascontiguousarray(w.transpose(1, 0, 2, 3))
+    xd, wd, wtd, dyd = _nhwc(x), _nhwc(w), _nhwc(wt), _nhwc(dy)
+    (y, dx, dw), ran = _launched(lambda: (R.conv2d_forward(xd, wd, 1, 1), R.conv2d_dgrad(xd, wtd, (N, H, W, K), 1, 1),
+                                          R.conv2d_wgrad(dyd, xd, (K, 3, 3, C), 1, 1)))
+    assert {"conv3_f32_fwd_" + tile, "conv3_f32_bwd_" + tile, "wgrad3_f32"} <= ran, ran
+    return [t.cpu().numpy() for t in (y, dx, dw)]
+
+
+@pytest.mark.parametrize("case", SPLIT_EDGE_CASES)
+def test_conv_split_products_near_the_largest_float(case):
+    """v * v is finite in fp32, the product of the bf16 numbers next to v is not."""
+    print("case", case, flush=True)
+    x, w, dy = _tensors(case[0], 14)
+    v = np.float32((2 - 2.0 ** -9.5) * 2.0 ** 63)
+    x[1, 5, 2, 3], x[2, 6, 7, 7] = v, -v
+    w[3, 5, 1, 1] = w[7, 6, 0, 2] = v
+    dy /= 64
+    dy[1, 9, 2, 3] = v
+    want = [L.conv2d_fwd(x, w, 1, 1), L.conv2d_dgrad(x, w.transpose(1, 0, 2, 3), (len(x), len(w)) + x.shape[2:], 1, 1),
+            L.conv2d_wgrad(dy, x, w.shape, 1, 1)]
+    for got, t, what in zip(_split_layer(case, x, w, dy), want, ("fwd", "dgrad", "wgrad")):
+        assert np.abs(t).max() > 3.39e38 and np.isfinite(t.astype(np.float32)).all()
+        _same_values(got, t, what)
+
+
 # ---- small outputs: 32x32 tiles, the reduction split among eight waves ------------------------------------------------
 # One tile and 256 (and just past them: the larger tiles), ragged pixel and channel tiles, channels that fill a part of a
 # 128-byte unit, fewer units than waves, an odd share, strides, 1x1 / 5x5 / 7x7 filters, parity classes without a tap
