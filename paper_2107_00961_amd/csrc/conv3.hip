@@ -6,9 +6,10 @@
 // accumulated in fp32, small terms first.  v_mfma_f32_32x32x16_bf16 does 16 times the work of
 // v_mfma_f32_32x32x2_f32 per cycle, so six of them take 6/16 of the time one fp32 product takes.
 //
-// Infinities (and finite values that round to one) leave a NaN in the difference a - h and so in every output they
-// reach, and h*h' may overflow where a*b, within 0.8 % of the largest float, does not; a workgroup that finds a result that is not finite computes its
-// tile again on the fp32 matrix instruction.
+// Where that is not so, a workgroup computes its tile again on the fp32 matrix instruction: where a result is not finite
+// (an infinity, or a finite value that rounds to one, leaves a NaN in the difference a - h and so in every output it
+// reaches, and h*h' may overflow where a*b, within 0.8 % of the largest float, does not), and where it has staged an
+// operand of so small a magnitude (below 2^-110; from 2^-103 up never) that its parts run out of bf16's bits.
 //
 // What bounds this kernel is the staging: an operand element costs 5.5 vector instructions to take apart and 6 bytes of
 // LDS.  So the input pixels of a tile are staged once per 64 channels and serve all nine taps: the tile is a range of
@@ -35,9 +36,12 @@ constexpr int kPitch = 3 * kPlane + 16;    // row pitch: rows 4 banks apart, con
 constexpr int kStageB = kBN * kPitch;
 
 // the three bf16 parts of four floats to their places in a staged row
-__device__ inline void store_split(char *row, f32x4 v) {
+__device__ inline void store_split(char *row, f32x4 v, unsigned long long &missed) {
 #pragma unroll
-  for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(row + p * kPlane) = split_part(v);
+  for (int p = 0; p < 3; ++p) {
+    if (p == 2) split_check(v, missed);
+    *reinterpret_cast<u32x2 *>(row + p * kPlane) = split_part(v);
+  }
 }
 
 // 8 waves: 2 along the pixels, 4 sharing the reduction (wave slice k takes 16 of every 64 channels), so that a wave's
@@ -97,6 +101,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
   const char *bsrc[2] = {Bs + lr * kPitch + wk * 32 + lg * 16, Bs + kStageB + lr * kPitch + wk * 32 + lg * 16};
   char *const pdst = Px + srow * kPitch + sch * 2;
   f32x4 rp[PA], rb[2][PB];
+  unsigned long long missed = 0;   // operands that three parts do not hold
   unsigned boff[PB];
 #pragma unroll
   for (int i = 0; i < PB; ++i) {
@@ -117,7 +122,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
     ++pc;
   };
   auto store_pixels = [&](int i) {
-    if (i * 32 < px) store_split(pdst + i * 32 * kPitch, rp[i]);   // uniform
+    if (i * 32 < px) store_split(pdst + i * 32 * kPitch, rp[i], missed);   // uniform
   };
   int bt = 0, bc = 0;         // tap and chunk of the filter rows requested next
   auto request_filter = [&](int set) {
@@ -130,7 +135,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
     bc = wrap ? bc + 1 : bc;
   };
   // the rows of step t wait in register set t % 2 and go to LDS stage t % 2
-  auto store_filter = [&](int set, int i) { store_split(bdst[set] + i * 32 * kPitch, rb[set][i]); };
+  auto store_filter = [&](int set, int i) { store_split(bdst[set] + i * 32 * kPitch, rb[set][i], missed); };
 
   // ---- fragments: three parts of TM pixel tiles and kTN filter tiles.  A part is fetched for the next step as soon as
   // its last product of this step is issued; only the leading parts (index 0), which the last product of a step and the
@@ -282,7 +287,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
       }
     __syncthreads();
     f32x4 v[NSUB];
-    bool bad = false;
+    bool bad = missed != 0;
 #pragma unroll
     for (int g = 0; g < NSUB; ++g) {
       v[g] = red[((wm * kWGK) * NSUB * 4 + wk * NSUB + g) * 64 + lane];
@@ -294,7 +299,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
     // group g of this wave: rows 8*ge + 4*lg .. +3 of sub-tile u, column lr
     const int g0 = wk * NSUB;
     if (__syncthreads_or(bad)) {
-      // a result that is not finite somewhere in the tile: again in fp32, without staging
+      // a result that is not finite, or an operand the parts do not hold, somewhere in the tile: again in fp32, without staging
       const int u = g0 / 4, i = u / kTN, j = u % kTN;
       const float *in = static_cast<const float *>(a.in), *wt = static_cast<const float *>(a.wt);
       const int m = m0 + wm * WTM + i * 32 + lr, oc = n0 + j * 32 + lr;

@@ -1,5 +1,6 @@
 // Weight gradient of a 3x3 stride-1 convolution of fp32 tensors on the bf16 matrix core (three bf16 parts per operand,
-// six products, small terms first; results that are not finite through a second pass on the fp32 instruction: see conv3.hip).
+// six products, small terms first; results that are not finite, and operands too small for the parts, through a second
+// pass on the fp32 instruction: see conv3.hip).
 //
 //   dW[k][r][s][c] = sum over pixels m of dY[m][k] * X[m + (r-1)*W + (s-1)][c]     (X of a tap off the image is zero)
 //
@@ -46,42 +47,45 @@ __global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
   const int mbeg = split * a.rows_per_split, mend = min(a.M, mbeg + a.rows_per_split);
   const int chunks = (mend - mbeg + kCh - 1) / kCh;
 
-  const __amdgpu_buffer_rsrc_t rdy = make_rsrc(a.dy, (unsigned)a.M * a.K * 4u);
+  const __amdgpu_buffer_rsrc_t rdy = make_rsrc(a.dy, (unsigned)mend * a.K * 4u);   // rows of other splits: zeros
   const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (unsigned)a.M * a.C * 4u);
 
   // ---- staging: threads 0..511, 16 lanes (4 channels each) per row, one row of dY and one of X per chunk
   const bool stager = wave < 8;
   const int srow = (tid >> 4) & 31, sch = (tid & 15) * 4;
-  // byte offsets of this thread's piece of dY row mbeg and of ring row 0 (pixel mbeg - W - 1); a channel past the last
-  // one starts at kOOB and stays past the end whatever rows are added
+  // byte offsets of this thread's piece of dY row mbeg and of ring row 0 (pixel mbeg - W - 1).  A channel past the last one
+  // starts at kOOB; pixels before the first and past the last of the tensor come back as zeros too (offsets wrap above its
+  // size).  Where a tensor is so large that such an offset comes round to it, the value read belongs to a channel or a tap
+  // that is not used.
   const unsigned dyo = k0 + sch < a.K ? (unsigned)((mbeg + srow) * a.K + k0 + sch) * 4u : kOOB;
   const unsigned xo = c0 + sch < a.C ? (unsigned)((mbeg - W - 1 + srow) * a.C + c0 + sch) * 4u : kOOB;
   f32x4 rd = {0.f, 0.f, 0.f, 0.f}, rxv = {0.f, 0.f, 0.f, 0.f};
+  unsigned long long missed = 0;   // operands that three parts do not hold
   int xrow = 0, dyrow = 0;   // ring row and dY row (from mbeg) requested next
-  auto x_offset = [&]() {    // pixels off the tensor: an offset past its end
-    return (unsigned)(mbeg - W - 1 + xrow + srow) < (unsigned)a.M ? xo + (unsigned)(xrow * a.C) * 4u : kOOB;
-  };
-  auto load = [&](__amdgpu_buffer_rsrc_t r, unsigned o) {
-    asm("" : "+v"(o));   // a selected offset; left alone, the compiler makes two loads behind a branch
-    return buffer_load_16B(r, o);
-  };
+  auto request_x = [&]() { rxv = buffer_load_16B(rx, xo + (unsigned)(xrow * a.C) * 4u); };
   auto request = [&]() {
-    rd = load(rdy, mbeg + dyrow + srow < mend ? dyo + (unsigned)(dyrow * a.K) * 4u : kOOB);
-    rxv = load(rx, x_offset());
+    rd = buffer_load_16B(rdy, dyo + (unsigned)(dyrow * a.K) * 4u);
+    request_x();
     dyrow += kCh;
     xrow += kCh;
   };
   auto store_dy = [&](int stage) {
     char *d = lds + stage * kStage + srow * kPitch + sch * 2;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(d + p * kPart) = split_part(rd);
+    for (int p = 0; p < 3; ++p) {
+      if (p == 2) split_check(rd, missed);
+      *reinterpret_cast<u32x2 *>(d + p * kPart) = split_part(rd);
+    }
   };
   auto store_x = [&](int row) {
     const int slot = (row + srow) & (kRing - 1);
     char *d = Xs + slot * kPitch + sch * 2;
     u32x2 v[3];
 #pragma unroll
-    for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(d + p * kPart) = v[p] = split_part(rxv);
+    for (int p = 0; p < 3; ++p) {
+      if (p == 2) split_check(rxv, missed);
+      *reinterpret_cast<u32x2 *>(d + p * kPart) = v[p] = split_part(rxv);
+    }
     if (slot < kMirror) {
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2 *>(d + kRing * kPitch + p * kPart) = v[p];
@@ -157,7 +161,7 @@ __global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
   const int ahead = (2 * W + 2 + kCh - 1) / kCh * kCh;   // whole passes of X rows staged before chunk 0's own
   if (stager) {
     for (; xrow < ahead; xrow += kCh) {
-      rxv = load(rx, x_offset());
+      request_x();
       store_x(xrow);
     }
     request();             // dY of chunk 0, X rows ahead .. ahead + 31
@@ -220,7 +224,7 @@ __global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
 
 #pragma unroll
   for (int s = 0; s < 3; ++s) acc[s] += small[s];
-  bool bad = false;
+  bool bad = missed != 0;
 #pragma unroll
   for (int s = 0; s < 3; ++s)
 #pragma unroll
@@ -228,7 +232,7 @@ __global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
   const int lr = lane & 31, lg = lane >> 5;
   const int c = c0 + cq * 32 + lr;
   if (__syncthreads_or(bad)) {
-    // a result that is not finite somewhere in the tile: again in fp32, without staging
+    // a result that is not finite, or an operand the parts do not hold, somewhere in the tile: again in fp32, without staging
     const int k = k0 + kq * 32 + lr;
 #pragma unroll
     for (int s = 0; s < 3; ++s)

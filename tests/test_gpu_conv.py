@@ -195,6 +195,27 @@ def test_conv_split_products_near_the_largest_float(case):
         _same_values(got, t, what)
 
 
+@pytest.mark.parametrize("e", [-100, -104, -110, -118, -126, -134])
+@pytest.mark.parametrize("case", SPLIT_EDGE_CASES)
+def test_conv_split_small_operands(case, e):
+    """Operands so small that bf16 has no numbers for their lower parts, against others large enough for normal results."""
+    print("case", case, e, flush=True)
+    x, w, dy = _tensors(case[0], 15)
+    dy = dy / np.float32(64)
+    s = np.float32(2.0 ** 60)
+    for small_x in (True, False):
+        t = np.ldexp(np.float32(1), e).astype(np.float32)
+        xs, ws, ds = (x * t, w * s, dy * s) if small_x else (x * s, w * t, dy * t)
+        y, dx, dw = _split_layer(case, xs, ws, ds)
+        r = 1 / (float(t) * float(s))
+        X, W, D = xs.astype(np.float64), ws.astype(np.float64) * r, ds.astype(np.float64) * r
+        shape = (len(x), len(w)) + x.shape[2:]
+        for got, want, what in ((y, L.conv2d_fwd(X, W, 1, 1), "fwd"), (dx, L.conv2d_dgrad(X, W.transpose(1, 0, 2, 3), shape, 1, 1), "dgrad"),
+                                (dw, L.conv2d_wgrad(D, X, w.shape, 1, 1), "wgrad")):
+            # up to 2592 fp32 additions, each rounding by at most 2^-24 of a partial sum, in random directions
+            assert np.linalg.norm(got.transpose(0, 3, 1, 2) * r - want) <= np.sqrt(2592) * 2.0 ** -24 * np.linalg.norm(want), what
+
+
 # ---- small outputs: 32x32 tiles, the reduction split among eight waves ------------------------------------------------
 # One tile and 256 (and just past them: the larger tiles), ragged pixel and channel tiles, channels that fill a part of a
 # 128-byte unit, fewer units than waves, an odd share, strides, 1x1 / 5x5 / 7x7 filters, parity classes without a tap
