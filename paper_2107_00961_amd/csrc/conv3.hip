@@ -9,7 +9,9 @@
 // Where that is not so, a workgroup computes its tile again on the fp32 matrix instruction: where a result is not finite
 // (an infinity, or a finite value that rounds to one, leaves a NaN in the difference a - h and so in every output it
 // reaches, and h*h' may overflow where a*b, within 0.8 % of the largest float, does not), and where it has staged an
-// operand of so small a magnitude (below 2^-110; from 2^-103 up never) that its parts run out of bf16's bits.
+// operand of so small a magnitude (below 2^-110; from 2^-103 up never) that its parts run out of bf16's bits.  A layer all of
+// whose tiles are computed twice takes twice the time that the fp32 instruction takes on staged tiles (batch 128, all NaN:
+// 64 ch 32x32 193 us, 128 ch 16x16 174, 256 ch 8x8 161, 512 ch 4x4 169; with one load in flight per wave 551, 524, 497, 925).
 //
 // What bounds this kernel is the staging: an operand element costs 5.5 vector instructions to take apart and 6 bytes of
 // LDS.  So the input pixels of a tile are staged once per 64 channels and serve all nine taps: the tile is a range of
@@ -299,31 +301,75 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
     // group g of this wave: rows 8*ge + 4*lg .. +3 of sub-tile u, column lr
     const int g0 = wk * NSUB;
     if (__syncthreads_or(bad)) {
-      // a result that is not finite, or an operand the parts do not hold, somewhere in the tile: again in fp32, without staging
+      // a result that is not finite, or an operand the parts do not hold, somewhere in the tile: again in fp32, from memory
+      // straight to the matrix instruction (lane l: row l%32, four of eight channels), 32 channels of a tap at a time and the
+      // next 32 in flight.  Where two waves share a sub-tile, they take every other 32.
+      constexpr int kShare = 4 / NSUB;
       const int u = g0 / 4, i = u / kTN, j = u % kTN;
-      const float *in = static_cast<const float *>(a.in), *wt = static_cast<const float *>(a.wt);
       const int m = m0 + wm * WTM + i * 32 + lr, oc = n0 + j * 32 + lr;
       int vm = valid[0];
       if constexpr (TM == 2) vm = i ? valid[1] : valid[0];
+      f32x4 x[2][4], y[2][4];
+      int t = 0, c0 = 0;       // tap and first channel requested next
+      auto request_fp32 = [&](int set) {
+        const int d = ((t / 3 - 1) * W + t % 3 - 1) * (MODE == kBwd ? -1 : 1);
+        const bool x_ok = t < 9 && ((vm >> t) & 1), y_ok = t < 9 && oc < a.OC;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int ch = c0 + k * 8 + lg * 4;   // IC is a multiple of four
+          unsigned xo = x_ok && ch < IC ? (unsigned)((m + d) * IC + ch) * 4u : kOOB;
+          unsigned yo = y_ok && ch < IC ? (unsigned)((oc * 9 + t) * IC + ch) * 4u : kOOB;
+          asm("" : "+v"(xo), "+v"(yo));
+          x[set][k] = buffer_load_16B(rin, xo);
+          y[set][k] = buffer_load_16B(rwt, yo);
+        }
+#pragma unroll
+        for (int k = 0; k < kShare; ++k) {
+          c0 += 32;
+          if (c0 >= IC) { c0 = 0; ++t; }
+        }
+      };
       f32x16 c;
 #pragma unroll
       for (int e = 0; e < 16; ++e) c[e] = 0.f;
-      for (int t = 0; t < 9; ++t) {
-        const int d = ((t / 3 - 1) * W + t % 3 - 1) * (MODE == kBwd ? -1 : 1);
-        const bool ok = (vm >> t) & 1;
-        for (int ch = lg; ch < IC; ch += 2) {   // IC is even
-          const float x = ok ? in[(size_t)(m + d) * IC + ch] : 0.f;
-          const float y = oc < a.OC ? wt[((size_t)oc * 9 + t) * IC + ch] : 0.f;
-          c = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, c, 0, 0, 0);
+      if (kShare == 2 && (wk & 1)) {
+        c0 = 32;
+        if (c0 >= IC) { c0 = 0; ++t; }
+      }
+      const int batches = 9 * ((IC + 31) / 32);
+      request_fp32(0);
+      for (int it = 0; it < batches; it += 2 * kShare) {   // behind the last one: zeros
+#pragma unroll
+        for (int set = 0; set < 2; ++set) {
+          request_fp32(set ^ 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) Elem<float>::mma(c, x[set][k], y[set][k]);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
+      if constexpr (NSUB == 4) {
 #pragma unroll
-      for (int g = 0; g < NSUB; ++g)
+        for (int g = 0; g < 4; ++g) v[g] = f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+      } else {   // to each of the two its rows of the other's sums, through LDS behind the output tile
+        static_assert(kTile + 8 * 2 * 64 * 16 <= kBytes, "exchanged sums fit");
+        f32x4 *const half = reinterpret_cast<f32x4 *>(lds + kTile);
+        const bool odd = wk & 1;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if constexpr (NSUB == 4) v[g][e] = c[4 * g + e];
-          else v[g][e] = (wk & 1) ? c[8 + 4 * g + e] : c[4 * g + e];
+        for (int g = 0; g < 2; ++g) {
+          f32x4 other;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float first = c[4 * g + e], second = c[8 + 4 * g + e];
+            v[g][e] = odd ? second : first;
+            other[e] = odd ? first : second;
+          }
+          half[(wave * 2 + g) * 64 + lane] = other;
         }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < 2; ++g) v[g] += half[((wave ^ 1) * 2 + g) * 64 + lane];
+      }
     }
 #pragma unroll
     for (int g = 0; g < NSUB; ++g) {

@@ -1,6 +1,6 @@
 // Weight gradient of a 3x3 stride-1 convolution of fp32 tensors on the bf16 matrix core (three bf16 parts per operand,
 // six products, small terms first; results that are not finite, and operands too small for the parts, through a second
-// pass on the fp32 instruction: see conv3.hip).
+// pass on the fp32 instruction: see conv3.hip; all tiles twice, batch 128: 161 to 188 us, with one load in flight 202 to 358).
 //
 //   dW[k][r][s][c] = sum over pixels m of dY[m][k] * X[m + (r-1)*W + (s-1)][c]     (X of a tap off the image is zero)
 //
@@ -232,23 +232,45 @@ __global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
   const int lr = lane & 31, lg = lane >> 5;
   const int c = c0 + cq * 32 + lr;
   if (__syncthreads_or(bad)) {
-    // a result that is not finite, or an operand the parts do not hold, somewhere in the tile: again in fp32, without staging
+    // a result that is not finite, or an operand the parts do not hold, somewhere in the tile: again in fp32, from memory
+    // straight to the matrix instruction, eight pixels at a time and the next eight in flight
     const int k = k0 + kq * 32 + lr;
+    float d[2][4], x[2][4][3];
+    int m2 = mbeg;           // pixel requested next
+    auto request_fp32 = [&](int set) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int m = m2 + 2 * i + lg;
+        const int n = fdiv(m, a.div_plane), rem = m - n * (a.H * W);
+        const int h = fdiv(rem, a.div_w), w = rem - h * W;
+        const bool in = m < mend && (unsigned)(h + fr - 1) < (unsigned)a.H;
+        unsigned o = m < mend && k < a.K ? (unsigned)(m * a.K + k) * 4u : kOOB;
+        asm("" : "+v"(o));
+        d[set][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rdy, (int)o, 0, 0));
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          o = in && (unsigned)(w + s - 1) < (unsigned)W && c < a.C ? (unsigned)((m + (fr - 1) * W + s - 1) * a.C + c) * 4u : kOOB;
+          asm("" : "+v"(o));
+          x[set][i][s] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, (int)o, 0, 0));
+        }
+      }
+      m2 += 8;
+    };
 #pragma unroll
     for (int s = 0; s < 3; ++s)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[s][e] = 0.f;
-    for (int m2 = mbeg; m2 < mend; m2 += 2) {
-      const int m = m2 + lg;
-      const int n = fdiv(m, a.div_plane), rem = m - n * (a.H * W);
-      const int h = fdiv(rem, a.div_w), w = rem - h * W;
-      const bool in = m < mend && (unsigned)(h + fr - 1) < (unsigned)a.H;
-      const float d = m < mend && k < a.K ? a.dy[(size_t)m * a.K + k] : 0.f;
+    request_fp32(0);
+    while (m2 - 8 < mend) {   // behind an odd number of eights: zeros
 #pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        const bool ok = in && (unsigned)(w + s - 1) < (unsigned)W && c < a.C;
-        const float x = ok ? a.x[(size_t)(m + (fr - 1) * W + s - 1) * a.C + c] : 0.f;
-        acc[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(d, x, acc[s], 0, 0, 0);
+      for (int set = 0; set < 2; ++set) {
+        request_fp32(set ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int s = 0; s < 3; ++s) acc[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(d[set][i], x[set][i][s], acc[s], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }

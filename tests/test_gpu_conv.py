@@ -162,9 +162,11 @@ def _launched(f):
         R.profile_enable(False)
 
 
-# forward (or data gradient) on 64- and on 128-pixel tiles, and the weight gradient of the same layers
+# forward (or data gradient) on 64- and on 128-pixel tiles, and the weight gradient of the same layers; the last one ragged
+# in every size
 #                   N   H   W   C    K   R st pad
-SPLIT_EDGE_CASES = [((33, 8, 8, 96, 288, 3, 1, 1), "64x64"), ((65, 16, 16, 64, 128, 3, 1, 1), "128x64")]
+SPLIT_EDGE_CASES = [((33, 8, 8, 96, 288, 3, 1, 1), "64x64"), ((65, 16, 16, 64, 128, 3, 1, 1), "128x64"),
+                    ((37, 9, 7, 52, 300, 3, 1, 1), "64x64")]
 
 
 def _split_layer(case, x, w, dy):
@@ -184,7 +186,7 @@ def test_conv_split_products_near_the_largest_float(case):
     print("case", case, flush=True)
     x, w, dy = _tensors(case[0], 14)
     v = np.float32((2 - 2.0 ** -9.5) * 2.0 ** 63)
-    x[1, 5, 2, 3], x[2, 6, 7, 7] = v, -v
+    x[1, 5, 2, 3], x[2, 6, 7, 5] = v, -v
     w[3, 5, 1, 1] = w[7, 6, 0, 2] = v
     dy /= 64
     dy[1, 9, 2, 3] = v
@@ -193,6 +195,23 @@ def test_conv_split_products_near_the_largest_float(case):
     for got, t, what in zip(_split_layer(case, x, w, dy), want, ("fwd", "dgrad", "wgrad")):
         assert np.abs(t).max() > 3.39e38 and np.isfinite(t.astype(np.float32)).all()
         _same_values(got, t, what)
+
+
+@pytest.mark.parametrize("case", SPLIT_EDGE_CASES)
+def test_conv_split_infinities_on_both_tiles(case):
+    """As the tests of infinities above, on layers too large for the 32x32 tiles; tiles with and without one."""
+    print("case", case, flush=True)
+    x, w, dy = _tensors(case[0], 16)
+    dy /= 64
+    x[0, 5, 2, 3], x[1, 37, 0, 0], x[2, 9, 7, 5], dy[3, 50, 4, 3] = np.inf, -np.inf, np.nan, np.inf
+    x[4, 1, 4, 4] = 3.4e38   # finite, but its leading bf16 part is an infinity
+    with np.errstate(invalid="ignore", over="ignore"):
+        X = x.astype(np.float64)
+        want = [L.conv2d_fwd(X, w, 1, 1), L.conv2d_dgrad(X, w.transpose(1, 0, 2, 3), (len(x), len(w)) + x.shape[2:], 1, 1),
+                L.conv2d_wgrad(dy.astype(np.float64), X, w.shape, 1, 1)]
+        for got, t, what in zip(_split_layer(case, x, w, dy), want, ("fwd", "dgrad", "wgrad")):
+            assert np.isfinite(t).any() and not np.isfinite(t).all()
+            _same_values(got, t, what)
 
 
 @pytest.mark.parametrize("e", [-100, -104, -110, -118, -126, -134])
