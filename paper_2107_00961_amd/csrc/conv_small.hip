@@ -123,7 +123,12 @@ __global__ __launch_bounds__(kNT) void conv_small_kernel(IgemmArgs a) {
     tr = swrap ? tr + tstep : tr;
   };
   // The staged rows belong to this wave alone and LDS accesses of a wave take place in their order: no barrier, and one
-  // buffer: the next unit is written behind the reads of this one.
+  // buffer: the next unit is written behind the reads of this one.  The lanes exchange them, so the order is one between
+  // lanes and has to be told to the compiler (which emits nothing for it).
+  auto wave_order = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
   char *const mine = lds + wave * kRows * kPitch;
   char *const dst = mine + srow * kPitch + (lane & 7) * 16;
   const char *const src = mine + lr * kPitch + lg * 16;
@@ -138,11 +143,13 @@ __global__ __launch_bounds__(kNT) void conv_small_kernel(IgemmArgs a) {
   int cu = c0;   // first channel of the unit multiplied next
   auto unit = [&](int set) {
     f32x4 fa[NS], fb[NS];
+    wave_order();
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
       fa[k] = *reinterpret_cast<const f32x4 *>(src + k * 32);
       fb[k] = *reinterpret_cast<const f32x4 *>(src + kBM * kPitch + k * 32);
     }
+    wave_order();
     store(set);
     request(set);
     __builtin_amdgcn_sched_barrier(0);
