@@ -39,7 +39,7 @@ constexpr int kStages = 2;     // LDS double buffering in the implicit-GEMM kern
 // and the tap counters are advanced with selects.  With no branch in the loop the scheduler is free
 // to place the address arithmetic, the LDS traffic and the global loads in the shadow of the MFMAs.
 template <typename T, int BM, int BN, int BK, int WGM, int WGN, int MODE>
-__global__ __launch_bounds__(WGM * WGN * 64) void igemm_kernel(IgemmArgs a) {
+__global__ __launch_bounds__(WGM * WGN * 64) void igemm_kernel(ArgsOf<MODE> a) {
   using E = Elem<T>;
   constexpr int NT = WGM * WGN * 64;             // threads: one wave per wave tile, 4 or 8 waves
   constexpr int VEC = E::VEC;
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void igemm_kernel(IgemmArgs a) {
 }
 
 template <typename T, int BM, int BN, int BK, int WGM, int WGN, int MODE>
-int launch_igemm(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
+int launch_igemm(EvalArgs a, hipStream_t st, StatParts *tiles_m_out) {
   a.tiles_m = (a.Mrows + BM - 1) / BM;
   if (tiles_m_out) { tiles_m_out->parts = a.tiles_m; tiles_m_out->rows = BM; }
   a.tiles_n = (a.OC + BN - 1) / BN;
@@ -294,14 +294,14 @@ int launch_igemm(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
                                        (MODE == kEval ? (a.out ? 1 : 0) + (a.act_res ? 1 : 0) : 0)) +
                                       (double)a.OC * a.R * a.S * a.IC);
     prof::Scope ps(label.c_str(), flops, bytes, st);
-    hipLaunchKernelGGL((igemm_kernel<T, BM, BN, BK, WGM, WGN, MODE>), dim3((unsigned)grid), dim3(WGM * WGN * 64), 0, st, a);
+    hipLaunchKernelGGL((igemm_kernel<T, BM, BN, BK, WGM, WGN, MODE>), dim3((unsigned)grid), dim3(WGM * WGN * 64), 0, st, static_cast<const ArgsOf<MODE> &>(a));
   }
   RESIST_CHECK_LAUNCH("igemm");
   return RESIST_OK;
 }
 
 template <typename T, int MODE>
-int dispatch_igemm(const IgemmArgs &a, hipStream_t st, StatParts *tiles_m_out = nullptr) {
+int dispatch_igemm(const EvalArgs &a, hipStream_t st, StatParts *tiles_m_out = nullptr) {
   constexpr int dt = sizeof(T) == 2 ? DT_BF16 : DT_F32;
   if (conv_small_takes(a, dt)) return conv_small_launch(a, dt, MODE, st, tiles_m_out);
   if constexpr (sizeof(T) == 4) {
@@ -369,7 +369,7 @@ int conv_fwd(const ConvGeom &g, int dt, const void *x, const void *w, void *y, c
              hipStream_t st, const EvalAct *act) {
   RESIST_TRY(check_geom(g, dt));
   if (stats && !stat_parts) return set_error(RESIST_EINVAL, "conv_fwd: stats without stat_parts");
-  IgemmArgs a{};
+  EvalArgs a{};
   a.in = x; a.wt = w; a.out = y; a.addend = addend; a.stats = stats;
   a.N = g.N; a.IH = g.H; a.IW = g.W; a.IC = g.C;
   a.OH = g.P; a.OW = g.Q; a.OC = g.K;
@@ -390,7 +390,7 @@ int conv_dgrad(const ConvGeom &g, int dt, const void *dy, const void *wT, void *
   RESIST_TRY(check_geom(g, dt));
   if (g.stride == 2 && ((g.H & 1) || (g.W & 1)))
     return set_error(RESIST_ESHAPE, "stride-2 dgrad needs even input size, got %dx%d", g.H, g.W);
-  IgemmArgs a{};
+  EvalArgs a{};
   a.in = dy; a.wt = wT; a.out = dx; a.addend = addend; a.relu_mask = relu_mask;
   a.N = g.N; a.IH = g.P; a.IW = g.Q; a.IC = g.K;
   a.OH = g.H; a.OW = g.W; a.OC = g.C;

@@ -49,7 +49,7 @@ __device__ inline void store_split(char *row, f32x4 v, unsigned long long &misse
 // 8 waves: 2 along the pixels, 4 sharing the reduction (wave slice k takes 16 of every 64 channels), so that a wave's
 // tile is as large as the registers allow (BM/2 x 64): an operand fragment read from LDS feeds 2*TM or 2*TN products.
 template <int BM, int MODE>
-__global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
+__global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
   constexpr int WTM = BM / kWGM, TM = WTM / 32, NSUB = TM * kTN;
   constexpr int PA = (BM + 2 * kMaxW + 2 + 31) / 32, PB = kBN / 32;   // staging passes of 32 rows x 16 lanes
   constexpr int PX = PA * 32;                     // staged pixels; the row after them is zero
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(IgemmArgs a) {
 }
 
 template <int BM, int MODE>
-int launch(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
+int launch(EvalArgs a, hipStream_t st, StatParts *tiles_m_out) {
   a.tiles_m = (a.Mrows + BM - 1) / BM;
   a.tiles_n = (a.OC + kBN - 1) / kBN;
   if (tiles_m_out) { tiles_m_out->parts = a.tiles_m; tiles_m_out->rows = BM; }
@@ -396,7 +396,7 @@ int launch(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
     const double bytes = 4.0 * ((double)a.Mrows * a.IC + (double)a.Mrows * a.OC * (1 + (a.addend ? 1 : 0) + (a.relu_mask ? 1 : 0) + (MODE == kBwd && a.bn_sums ? 1 : 0) +
                                 (MODE == kEval ? (a.out ? 1 : 0) + (a.act_res ? 1 : 0) : 0)) + (double)a.OC * 9 * a.IC);
     prof::Scope ps(label.c_str(), flops, bytes, st);
-    hipLaunchKernelGGL((conv3_split_kernel<BM, MODE>), dim3((unsigned)grid), dim3(kNT), 0, st, a);
+    hipLaunchKernelGGL((conv3_split_kernel<BM, MODE>), dim3((unsigned)grid), dim3(kNT), 0, st, static_cast<const ArgsOf<MODE> &>(a));
   }
   RESIST_CHECK_LAUNCH("conv3");
   return RESIST_OK;
@@ -404,7 +404,7 @@ int launch(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
 
 // 64-pixel tiles where 128-pixel ones would not give every CU a workgroup (512 ch 4x4, batch 128: 128 tiles)
 template <int MODE>
-int pick(const IgemmArgs &a, hipStream_t st, StatParts *p) {
+int pick(const EvalArgs &a, hipStream_t st, StatParts *p) {
   const long long t128 = (long long)((a.Mrows + 127) / 128) * ((a.OC + kBN - 1) / kBN);
   return t128 >= 256 ? launch<128, MODE>(a, st, p) : launch<64, MODE>(a, st, p);
 }
@@ -415,7 +415,7 @@ bool conv3_takes(const IgemmArgs &a) {
   return a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.IW <= kMaxW && a.IC >= 48;
 }
 
-int conv3_launch(const IgemmArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out) {
+int conv3_launch(const EvalArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out) {
   return mode == kFwd ? pick<kFwd>(a, st, tiles_m_out) : mode == kBwd ? pick<kBwd>(a, st, tiles_m_out) : pick<kEval>(a, st, tiles_m_out);
 }
 

@@ -25,7 +25,7 @@ constexpr int kLDC = kBN + 8;
 constexpr int kPitch = 128 + 16;   // consecutive rows 4 banks apart: conflict-free 16-byte reads
 
 template <typename T, int MODE>
-__global__ __launch_bounds__(kNT) void conv_small_kernel(IgemmArgs a) {
+__global__ __launch_bounds__(kNT) void conv_small_kernel(ArgsOf<MODE> a) {
   using E = Elem<T>;
   constexpr int VEC = E::VEC, ES = (int)sizeof(T), BK = 8 * VEC;   // channels a unit
   constexpr int NS = 4;                                            // matrix steps a unit
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kNT) void conv_small_kernel(IgemmArgs a) {
 }
 
 template <typename T, int MODE>
-int launch(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
+int launch(EvalArgs a, hipStream_t st, StatParts *tiles_m_out) {
   a.tiles_m = (a.Mrows + kBM - 1) / kBM;
   a.tiles_n = (a.OC + kBN - 1) / kBN;
   if (tiles_m_out) { tiles_m_out->parts = a.tiles_m; tiles_m_out->rows = kBM; }
@@ -199,7 +199,7 @@ int launch(IgemmArgs a, hipStream_t st, StatParts *tiles_m_out) {
                                        (MODE == kEval ? (a.out ? 1 : 0) + (a.act_res ? 1 : 0) : 0)) +
                                       (double)a.OC * a.R * a.S * a.IC);
     prof::Scope ps(label.c_str(), flops, bytes, st);
-    hipLaunchKernelGGL((conv_small_kernel<T, MODE>), dim3((unsigned)grid), dim3(kNT), 0, st, a);
+    hipLaunchKernelGGL((conv_small_kernel<T, MODE>), dim3((unsigned)grid), dim3(kNT), 0, st, static_cast<const ArgsOf<MODE> &>(a));
   }
   RESIST_CHECK_LAUNCH("conv_small");
   return RESIST_OK;
@@ -222,7 +222,7 @@ bool conv_small_rows(long long pixels, int OC, int cls) {
   return (m + kBM - 1) / kBM * ((OC + kBN - 1) / kBN) * cls * cls <= 256;
 }
 
-int conv_small_launch(const IgemmArgs &a, int dt, int mode, hipStream_t st, StatParts *p) {
+int conv_small_launch(const EvalArgs &a, int dt, int mode, hipStream_t st, StatParts *p) {
   if (dt == DT_BF16)
     return mode == kFwd ? launch<__bf16, kFwd>(a, st, p) : mode == kBwd ? launch<__bf16, kBwd>(a, st, p) : launch<__bf16, kEval>(a, st, p);
   return mode == kFwd ? launch<float, kFwd>(a, st, p) : mode == kBwd ? launch<float, kBwd>(a, st, p) : launch<float, kEval>(a, st, p);

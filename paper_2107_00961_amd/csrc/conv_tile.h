@@ -1,6 +1,8 @@
 // Device-side parts shared by the convolution kernels (conv.hip, conv3.hip): element traits, launch arguments,
 // tile order, bounds-checked loads and the epilogue that takes a tile from the accumulators to memory.
 #pragma once
+#include <type_traits>
+
 #include "elem.h"
 #include "internal.h"
 
@@ -36,12 +38,6 @@ struct IgemmArgs {
   const float *bn_mean, *bn_invstd, *bn_scale, *bn_shift;
   float *bn_sums;
   int bn_self;
-  // test-time forward (kEval): out (if not NULL) is stored as above, and v, the value as stored there, goes on to
-  //   act = max(act_scale*v + act_shift [+ res_scale*act_res + res_shift], 0)    (NULL res_scale: + act_res)
-  void *act;
-  const float *act_scale, *act_shift;
-  const void *act_res;
-  const float *res_scale, *res_shift;
   int N, IH, IW, IC;
   int OH, OW, OC;
   int R, S, stride, pad;
@@ -60,6 +56,17 @@ constexpr int kBwd = 1;  // source pixel = (out + pad - tap) / stride
 // for the launch that made its map) buys nothing.  CIFAR-shaped model, batch 128, fp32: 6.04 -> 5.56 ms; batch 33, bf16:
 // 1.48 -> 1.05; one ImageNet-shaped image, bf16: 0.83 -> 0.55; bit for bit the same logits.
 constexpr int kEval = 2;
+// Its arguments.  The other kernels are launched without them: a longer argument block puts what the launch appends to it
+// (grid size) in another cache line, 0.1 us of every launch.
+struct EvalArgs : IgemmArgs {
+  // out (if not NULL) is stored as above, and v, the value as stored there, goes on to
+  //   act = max(act_scale*v + act_shift [+ res_scale*act_res + res_shift], 0)    (NULL res_scale: + act_res)
+  void *act;
+  const float *act_scale, *act_shift;
+  const void *act_res;
+  const float *res_scale, *res_shift;
+};
+template <int MODE> using ArgsOf = std::conditional_t<MODE == kEval, EvalArgs, IgemmArgs>;
 
 namespace {
 
@@ -146,7 +153,7 @@ __device__ inline f32x4 buffer_load_16B(__amdgpu_buffer_rsrc_t r, unsigned voff)
 // be free); from there global memory sees 16-byte accesses along the channel axis.  row_off: per tile row the index
 // of its output pixel, -1 past the end.  The optional addend is added in fp32 before the one rounding to T.
 template <typename T, int BM, int BN, int NT, int MODE, typename PutTile>
-__device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], const int *row_off, int tm, int n0, PutTile put_tile) {
+__device__ inline void conv_epilogue(const ArgsOf<MODE> &a, float (*Cs)[BN + 8], const int *row_off, int tm, int n0, PutTile put_tile) {
   using E = Elem<T>;
   constexpr int VEC = E::VEC;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -183,7 +190,9 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
         if (addend) q_ad[g] = Vec<T>::load_raw(addend + offs[g]);
         if (has_mask) q_mk[g] = Vec<T>::load_raw(maskp + offs[g]);
         if (bn_bwd) q_y[g] = Vec<T>::load_raw(bnyp + offs[g]);
-        if (MODE == kEval && a.act_res) q_y[g] = Vec<T>::load_raw(static_cast<const T *>(a.act_res) + offs[g]);
+        if constexpr (MODE == kEval) {
+          if (a.act_res) q_y[g] = Vec<T>::load_raw(static_cast<const T *>(a.act_res) + offs[g]);
+        }
       }
     }
   };
@@ -207,13 +216,15 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
       bmu[e] = a.bn_mean[c]; bis[e] = a.bn_invstd[c]; bsc[e] = a.bn_scale[c]; bsh[e] = a.bn_shift[c];
     }
   }
-  if (MODE == kEval && col_ok) {
+  if constexpr (MODE == kEval) {
+    if (col_ok) {
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const int c = n0 + cv + e;
-      bsc[e] = a.act_scale[c]; bsh[e] = a.act_shift[c];
-      bmu[e] = a.res_scale ? a.res_scale[c] : 1.f;
-      bis[e] = a.res_scale ? a.res_shift[c] : 0.f;
+      for (int e = 0; e < VEC; ++e) {
+        const int c = n0 + cv + e;
+        bsc[e] = a.act_scale[c]; bsh[e] = a.act_shift[c];
+        bmu[e] = a.res_scale ? a.res_scale[c] : 1.f;
+        bis[e] = a.res_scale ? a.res_shift[c] : 0.f;
+      }
     }
   }
   if (MODE == kFwd && a.stats) {
@@ -250,7 +261,7 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
         for (int e = 0; e < VEC; ++e) v[e] = mk[e] > 0.f ? v[e] : 0.f;
       }
       if (MODE != kEval || out) Vec<T>::store(out + off, v);
-      if (MODE == kEval) {
+      if constexpr (MODE == kEval) {
         // the arithmetic of bn_apply_kernel on the value as stored
         float rv[VEC], o[VEC];
         if (a.act_res) Vec<T>::unpack(q_y[g], rv);
@@ -325,11 +336,11 @@ __device__ inline void conv_epilogue(const IgemmArgs &a, float (*Cs)[BN + 8], co
 
 // 3x3 stride-1 convolutions in fp32 through operands split into three bf16 parts (conv3.hip)
 bool conv3_takes(const IgemmArgs &a);
-int conv3_launch(const IgemmArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);
+int conv3_launch(const EvalArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);
 // convolutions with few output tiles: 32x32 tiles, the reduction split among the waves of a workgroup (conv_small.hip)
 bool conv_small_takes(const IgemmArgs &a, int dt);
 bool conv_small_rows(long long pixels, int OC, int cls);   // whether it may take an output of this size, in 32-row tiles
-int conv_small_launch(const IgemmArgs &a, int dt, int mode, hipStream_t st, StatParts *tiles_m_out);
+int conv_small_launch(const EvalArgs &a, int dt, int mode, hipStream_t st, StatParts *tiles_m_out);
 // the weight gradient of such a convolution (wgrad3.hip): out [splits][K][3][3][C], a multiple of 32 rows each
 bool wgrad3_takes(const ConvGeom &g);
 // the same in bf16, one filter row per workgroup
