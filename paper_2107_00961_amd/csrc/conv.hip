@@ -938,8 +938,7 @@ WgradPlan plan_wgrad_rows(const ConvGeom &g) {
 
 WgradPlan plan_wgrad(const ConvGeom &g) {
   WgradPlan p;
-  p.bm = (g.K >= 128 && g.C >= 128 && (long long)g.K * g.C * g.R * g.S >= 128LL * 128 * 9 * 16) ? 128 : 64;
-  p.bn = p.bm;
+  p.bm = p.bn = wgrad_tile(g);
   const long long tiles = (long long)((g.K + p.bm - 1) / p.bm) * ((g.C + p.bn - 1) / p.bn) * g.R * g.S;
   const long long M = (long long)g.N * g.P * g.Q;
   long long splits = 768 / tiles;   // at most three workgroups per CU: all resident at once (measured best)
@@ -1009,6 +1008,10 @@ int run_wgrad(const WgradPlan &p, const ConvGeom &g, int dt, const void *dy, con
 }
 
 }  // namespace
+
+int wgrad_tile(const ConvGeom &g) {
+  return g.K >= 128 && g.C >= 128 && (long long)g.K * g.C * g.R * g.S >= 128LL * 128 * 9 * 16 ? 128 : 64;
+}
 
 // A layer whose one-tap plan fits the static scratch has a nine-tap plan that fits it too: conv_wgrad_static takes the
 // same layers, and gives the same bits as conv_wgrad, whichever kernel runs.

@@ -341,6 +341,7 @@ int conv3_launch(const EvalArgs &a, int mode, hipStream_t st, StatParts *tiles_m
 bool conv_small_takes(const IgemmArgs &a, int dt);
 bool conv_small_rows(long long pixels, int OC, int cls);   // whether it may take an output of this size, in 32-row tiles
 int conv_small_launch(const EvalArgs &a, int dt, int mode, hipStream_t st, StatParts *tiles_m_out);
+int wgrad_tile(const ConvGeom &g);   // channels (square) a workgroup of the one-tap weight gradient takes
 // the weight gradient of such a convolution (wgrad3.hip): out [splits][K][3][3][C], a multiple of 32 rows each
 bool wgrad3_takes(const ConvGeom &g);
 // the same in bf16, one filter row per workgroup

@@ -467,11 +467,16 @@ __global__ __launch_bounds__(kRowNT) void wgrad3_row_bf16_kernel(WgradRowArgs a)
 
 constexpr int kWgrad3MaxW = 56;
 
-// Not the smallest layers, where the one-tap kernel has nine times the workgroups: 16 x 16 channels, 128 pixels 13 us
-// there, 16 here; 1024 pixels 16 either way; 16384 pixels (the first taken here) 22 there, 19 here.
+// From 2^14 pixels, counted once for every 64 x 64 channels: below that the one-tap kernel's nine times as many workgroups
+// win, most where the reduction of a layer is short.  us, one tap -> here: 64 ch 56x56, batch 1 12.6 -> 16.8, batch 4 21.5 -> 25.8,
+// 32x32, batch 14 21.4 -> 25.9, batch 16 (the first taken) 27.0 -> 27.3; 128 ch 4x4, batch 80 14.3 -> 19.2, 8x8, batch 64 (taken)
+// 26.4 -> 25.6; 256 ch 14x14, batch 1 9.3 -> 16.6; 16 ch 16x16, batch 64 (taken) 21.7 -> 17.9.  And from 640 pixels, unless the
+// one-tap kernel would take 128 x 128 channels: with 64 x 64 it needs no split of that few, 304 -> 496 ch 4x4, batch 26 23.4 ->
+// 25.1, 432 ch 16x16, batch 2 27.7 -> 32.2, but 448 ch 32x32, batch 1 45.3 -> 39.1, 512 ch 4x4, batch 16 28.2 -> 22.1.
 bool wgrad3_takes(const ConvGeom &g) {
-  return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 && g.W <= kWgrad3MaxW &&
-         (long long)g.N * g.H * g.W * g.K * g.C >= 1LL << 22;
+  const long long M = (long long)g.N * g.H * g.W, tiles = (long long)((g.K + 63) / 64) * ((g.C + 63) / 64);
+  return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 && g.W <= kWgrad3MaxW && M * tiles >= 1 << 14 &&
+         (M >= 640 || wgrad_tile(g) == 128);
 }
 
 int wgrad3_launch(const ConvGeom &g, const float *dy, const float *x, float *out, int splits, int rows_per_split, hipStream_t st) {

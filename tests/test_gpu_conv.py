@@ -166,7 +166,7 @@ def _launched(f):
 # in every size
 #                   N   H   W   C    K   R st pad
 SPLIT_EDGE_CASES = [((33, 8, 8, 96, 288, 3, 1, 1), "64x64"), ((65, 16, 16, 64, 128, 3, 1, 1), "128x64"),
-                    ((37, 9, 7, 52, 300, 3, 1, 1), "64x64")]
+                    ((53, 9, 7, 52, 300, 3, 1, 1), "64x64")]
 
 
 def _split_layer(case, x, w, dy):
@@ -178,6 +178,27 @@ def _split_layer(case, x, w, dy):
                                           R.conv2d_wgrad(dyd, xd, (K, 3, 3, C), 1, 1)))
     assert {"conv3_f32_fwd_" + tile, "conv3_f32_bwd_" + tile, "wgrad3_f32"} <= ran, ran
     return [t.cpu().numpy() for t in (y, dx, dw)]
+
+
+# which weight gradient a layer gets: around 2^14 pixels per 64 x 64 channels and around 640 pixels, ragged channel tiles and pixel
+# chunks, one split and several, images one pixel wide, the widest that the nine-tap kernel stages and a wider one
+#                     N   H   W   C    K   R st pad
+WGRAD3_EDGE_CASES = [((64, 16, 16, 16, 16, 3, 1, 1), True), ((63, 16, 16, 16, 16, 3, 1, 1), False), ((700, 3, 1, 140, 200, 3, 1, 1), True),
+                     ((3, 3, 1, 700, 680, 3, 1, 1), False), ((16, 4, 4, 512, 512, 3, 1, 1), True), ((2, 16, 16, 432, 432, 3, 1, 1), False),
+                     ((10, 8, 8, 324, 328, 3, 1, 1), True), ((9, 8, 8, 324, 328, 3, 1, 1), False), ((7, 45, 56, 36, 40, 3, 1, 1), True),
+                     ((5, 64, 57, 64, 64, 3, 1, 1), False), ((27, 19, 33, 64, 64, 3, 1, 1), True), ((200, 4, 4, 80, 132, 3, 1, 1), True)]
+
+
+@pytest.mark.parametrize("case", WGRAD3_EDGE_CASES)
+def test_conv_wgrad_route(case):
+    print("case", case, flush=True)
+    (N, H, W, C, K, *_), nine = case
+    x, w, dy = _tensors(case[0], 17)
+    dy = (dy / np.sqrt(N * H * W)).astype(np.float32)
+    xd, dyd = _nhwc(x), _nhwc(dy)
+    dw, ran = _launched(lambda: R.conv2d_wgrad(dyd, xd, (K, 3, 3, C), 1, 1))
+    assert ("wgrad3_f32" in ran) == nine, ran
+    assert_close(dw.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_wgrad(dy, x, w.shape, 1, 1), f"conv wgrad {case}")
 
 
 @pytest.mark.parametrize("case", SPLIT_EDGE_CASES)
