@@ -919,17 +919,21 @@ WgradPlan plan_wgrad3(const ConvGeom &g, long long max_floats) {
   return p;
 }
 
-// One filter row per workgroup (wgrad3_row_bf16_kernel): as many splits as give 384 workgroups, which leaves compute units
-// room for the data gradients that run beside them (CIFAR-shaped model, batch 128: 256 workgroups 5.70 ms, 384 5.65, 512
-// 5.72), but not two: a second split of 192 or more tiles costs as much in partial sums as it saves (512 -> 512 channels
-// at 7x7, batch 64: 36 us in one, 32 + 5 in two; batch 8: 12 and 17 + 6).
-WgradPlan plan_wgrad_rows(const ConvGeom &g) {
+// One filter row per workgroup (wgrad3_row_bf16_kernel).  Beside the data gradients of a step, as many splits as give 384
+// workgroups, which leaves compute units room for them (CIFAR-shaped model, batch 128: 256 workgroups 5.70 ms, 384 5.65, 512
+// 5.72).  Alone, one workgroup for every compute unit, or two where the reduction is long enough to pay for the partial sums,
+// from 3 * 2^28 padded products a tap: us, up to 256 | 384 | 512 workgroups (one tap a workgroup), 256 ch 8x8, batch 128 29.6 |
+// 30.9 | 31.0 (29.7), 16x16 128 ch, batch 77 23.7 | 27.2 | 26.7 (24.2), 14x14 256 ch, batch 64 36.3 | 39.0 | 33.7 (38.7), batch 256
+// 104 | 104 | 90 (134).  A second split of 192 or more tiles costs as much in partial sums as it saves (512 -> 512 channels at
+// 7x7, batch 64: 36 us in one, 32 + 5 in two; batch 8: 12 and 17 + 6).
+WgradPlan plan_wgrad_rows(const ConvGeom &g, bool beside) {
   WgradPlan p;
   p.bm = p.bn = 64;
   p.taps3 = true;
   const long long tiles = (long long)((g.K + 63) / 64) * ((g.C + 63) / 64) * 3, M = (long long)g.N * g.P * g.Q;
-  long long splits = std::min(384 / tiles, (M + 255) / 256);
-  if (splits <= 2) splits = 1;
+  const long long wgs = beside ? 384 : M * tiles >= 9LL << 16 ? 512 : 256;
+  long long splits = std::min(wgs / tiles, (M + 255) / 256);
+  if (tiles >= 192 || (beside && splits <= 2) || splits < 1) splits = 1;
   const long long rows = ((M + splits - 1) / splits + 63) / 64 * 64;
   p.rows_per_split = (int)rows;
   p.splits = (int)((M + rows - 1) / rows);
@@ -1015,18 +1019,18 @@ int wgrad_tile(const ConvGeom &g) {
 
 // A layer whose one-tap plan fits the static scratch has a nine-tap plan that fits it too: conv_wgrad_static takes the
 // same layers, and gives the same bits as conv_wgrad, whichever kernel runs.
-static WgradPlan plan_for(const ConvGeom &g, int dt) {
+static WgradPlan plan_for(const ConvGeom &g, int dt, bool beside = false) {
   const WgradPlan p = plan_wgrad(g);
-  if (dt == DT_BF16 && wgrad3_row_takes(g)) return plan_wgrad_rows(g);   // at most 19 MB of partial sums
+  if (dt == DT_BF16 && wgrad3_row_takes(g)) return plan_wgrad_rows(g, beside);   // at most 25 MB of partial sums
   if (dt != DT_F32 || !wgrad3_takes(g)) return p;
   return plan_wgrad3(g, plan_floats(p, g) * 4 <= (int64_t)kStaticScratchBytes ? (long long)(kStaticScratchBytes / 4) : INT64_MAX);
 }
 
-int64_t wgrad_scratch_floats(const ConvGeom &g, int dt) { return plan_floats(plan_for(g, dt), g); }
+int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool beside) { return plan_floats(plan_for(g, dt, beside), g); }
 
-int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial, hipStream_t st) {
+int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial, hipStream_t st, bool beside) {
   RESIST_TRY(check_geom(g, dt));
-  return run_wgrad(plan_for(g, dt), g, dt, dy, x, dw, partial, st);
+  return run_wgrad(plan_for(g, dt, beside), g, dt, dy, x, dw, partial, st);
 }
 
 int splitk_reduce(const float *partial, float *out, long long n4, int splits, hipStream_t st) {

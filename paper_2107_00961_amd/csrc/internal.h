@@ -153,10 +153,11 @@ int prepare_filter(const ConvGeom &g, int src_dt, int dt, const void *w, void *w
 // the same for many filters at once (fp32 masters -> copies and transposes in dt, times `scale`)
 struct FilterPrep { ConvGeom g; const float *w; void *w_lp; void *wT; float scale = 1.f; };
 int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st);
-// dw (fp32) = wgrad(dy, x); partial: split-reduction scratch of wgrad_scratch_floats(g, dt) floats
-int64_t wgrad_scratch_floats(const ConvGeom &g, int dt);
+// dw (fp32) = wgrad(dy, x); partial: split-reduction scratch of wgrad_scratch_floats(g, dt, beside) floats; beside: other
+// kernels run at the same time
+int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool beside = false);
 int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial,
-               hipStream_t st);
+               hipStream_t st, bool beside = false);
 // the same with the split partial sums in the library's static device array (no allocation anywhere);
 // RESIST_EWORKSPACE when the split partial sums exceed wgrad_static_scratch_bytes()
 int64_t wgrad_static_scratch_bytes();

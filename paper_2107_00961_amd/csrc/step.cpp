@@ -29,7 +29,7 @@ struct WgradSide {
   hipStream_t stream() const { return side.stream(); }
   int launch(const ConvGeom &g, const void *dyb, const void *xin, float *dw) {
     RESIST_TRY(side.fork());
-    RESIST_TRY(conv_wgrad(g, dt, dyb, xin, dw, splitk, side.stream()));
+    RESIST_TRY(conv_wgrad(g, dt, dyb, xin, dw, splitk, side.stream(), true));
     hipEvent_t e = nullptr;
     RESIST_TRY(side.mark(&e));
     for (auto &r : readers)
@@ -224,7 +224,7 @@ int build_plan(const resist_model_desc *desc, const int32_t *blocks, int32_t nbl
     max_act = std::max<int64_t>(max_act, c.M() * c.g.K);
     max_act = std::max<int64_t>(max_act, (int64_t)c.g.N * c.g.H * c.g.W * c.g.C);
     (void)needs_dgrad;
-    max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(c.g, net.d.compute_dtype));
+    max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(c.g, net.d.compute_dtype, true));
     max_c = std::max(max_c, c.g.K);
   };
 
@@ -514,7 +514,7 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
     if (shape_rc == RESIST_OK) shape_rc = conv_check(g, net.d.compute_dtype);
     max_act = std::max<int64_t>(max_act, (int64_t)g.N * g.P * g.Q * g.K);
     max_act = std::max<int64_t>(max_act, (int64_t)g.N * g.H * g.W * g.C);
-    max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(g, net.d.compute_dtype));
+    max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(g, net.d.compute_dtype, true));
     if (stats) max_stats = std::max<int64_t>(max_stats, conv_stats_floats(g));
     max_c = std::max(max_c, std::max(g.K, g.C));
   };

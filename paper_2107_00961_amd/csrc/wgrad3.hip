@@ -498,9 +498,13 @@ int wgrad3_launch(const ConvGeom &g, const float *dy, const float *x, float *out
 // From 2^28 products a tap, or where the tiles of the three rows nearly fill the chip by themselves: one split, no partial
 // sums (512 -> 512 channels, batch 8 at 7x7: 22.5 -> 11.8 us, batch 16 at 4x4: 10.7 -> 9.1).  Below that the one-tap
 // kernel's nine times as many workgroups win: 256 ch 8x8, batch 16 15.2 there, 16.0 here; 128 ch 28x28, batch 8 17.2 and 20.
+// Not between 192 and 512 workgroups of a reduction beyond 2^30 padded products: one split of them leaves compute units idle
+// for its whole length, and with more the partial sums take what they save (512 -> 512 channels at 14x14, us, one tap | one
+// split | four: batch 32 55 | 64 | 55, batch 64 89 | 121 | 92; at 7x7, batch 64, the largest taken, 39.5 | 38.7 | 39.9).
 bool wgrad3_row_takes(const ConvGeom &g) {
-  return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 &&
-         ((long long)g.N * g.H * g.W * g.K * g.C >= 1LL << 28 || (long long)g.K * g.C >= 1LL << 18);
+  const long long M = (long long)g.N * g.H * g.W, tiles = (long long)((g.K + 63) / 64) * ((g.C + 63) / 64);
+  if (tiles >= 64 && tiles < 171 && M * tiles > 1 << 18) return false;
+  return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 && (M * g.K * g.C >= 1LL << 28 || (long long)g.K * g.C >= 1LL << 18);
 }
 
 int wgrad3_row_launch(const ConvGeom &g, const void *dy, const void *x, float *out, int splits, int rows_per_split, hipStream_t st) {

@@ -358,6 +358,19 @@ def test_conv_wgrad_bf16(case):
     assert_close(dw.cpu().numpy().transpose(0, 3, 1, 2), want, f"bf16 conv wgrad {case}")
 
 
+# which bf16 weight gradient a layer gets: long reductions of few tiles (two workgroups a compute unit), 64 tiles up to 2^12
+# pixels and beyond
+#                        N   H   W   C    K   R st pad
+WGRAD_ROW_EDGE_CASES = [((201, 32, 32, 40, 40, 3, 1, 1), True), ((49, 16, 16, 256, 256, 3, 1, 1), True),
+                        ((64, 8, 8, 512, 456, 3, 1, 1), True), ((65, 8, 8, 512, 456, 3, 1, 1), False)]
+
+
+@pytest.mark.parametrize("case", WGRAD_ROW_EDGE_CASES)
+def test_conv_wgrad_bf16_route(case):
+    _, ran = _launched(lambda: test_conv_wgrad_bf16(case[0]))
+    assert ("wgrad3_row_bf16" in ran) == case[1], ran
+
+
 # ---- the stem convolution: implicit GEMM straight from the [N,C,H,W] fp32 image ----------------------------
 #              N  C   H   W   K  R st pad
 STEM_CASES = [(4, 3, 16, 16, 16, 3, 1, 1),       # the tiny configuration's stem
