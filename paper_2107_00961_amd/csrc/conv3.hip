@@ -176,12 +176,17 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
     for (int j = 0; j < kTN; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  auto product = [&](int set, int pa, int pb) {
+  auto product = [&](int set, int pa, int pb, bool first = false) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < kTN; ++j)
         Elem<__bf16>::mma(acc[i][j], pa == 0 ? fa0[set][i] : fa[pa][i], pb == 0 ? fb0[set][j] : fb[pb][j]);
+    if (first) {   // a product, half of the staging's arithmetic beside it, the other product
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 14, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
   auto lds_barrier = [&]() {
@@ -219,8 +224,10 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
     const bool turn = tap == 8 && it + 1 < steps;   // uniform
     const int nx = set ^ 1;
     constexpr int H = (PA + 2) / 3;
+    // turn, said by the tap that follows: the compiler joins branches on the same condition, and then copies the fragments that
+    // the other side of it has just requested, a wait in every step (2 % of the kernel's time)
     auto replace = [&](int q) {
-      if (turn) {
+      if (ft == 1 && it + 1 < steps) {
 #pragma unroll
         for (int i = q * H; i < (q + 1) * H && i < PA; ++i) store_pixels(i);
         __builtin_amdgcn_sched_barrier(0);
@@ -242,7 +249,8 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
     replace(1);
     if (!turn) fetch_a(nx, 1);
     store_filter(set, 0);        // of step it + 2
-    product(set, 0, 1);
+    // (64-pixel data gradients: left alone, their wait for the filter rows comes before both products, 4 % of the time)
+    product(set, 0, 1, MODE == kBwd && TM == 1);
     replace(2);
     fetch_b(nx, 1);
     if (turn) {

@@ -256,6 +256,40 @@ def test_conv_split_small_operands(case, e):
             assert np.linalg.norm(got.transpose(0, 3, 1, 2) * r - want) <= np.sqrt(2592) * 2.0 ** -24 * np.linalg.norm(want), what
 
 
+@pytest.mark.parametrize("case", SPLIT_EDGE_CASES)
+def test_conv_split_one_small_operand(case):
+    """A single small operand among zeros, wherever it is staged: every tap of the filter in a 64-channel tile of its own, one
+    pixel an image."""
+    print("case", case, flush=True)
+    x, w, dy = _tensors(case[0], 18)
+    (N, H, W, C, K, *_), tile = case
+    big, small = np.float32(2.0 ** 60), np.float32(1.2345678e-36)   # 2^-119.3
+    r = float(big) * float(small)
+    tiles = (K + 63) // 64
+    rng = np.random.default_rng(19)
+    for first in range(0, 9, tiles):
+        w1 = np.zeros_like(w)
+        for t in range(first, min(9, first + tiles)):
+            w1[64 * (t - first) + 7 + t, (t * 11 + 3) % C, t // 3, t % 3] = small
+        (y, dx, _) = _split_layer(case, x * big, w1, dy)
+        shape = (N, K, H, W)
+        for got, want, what in ((y, L.conv2d_fwd(x, w1 / float(small), 1, 1), "fwd"),
+                                (dx, L.conv2d_dgrad(x, w1.transpose(1, 0, 2, 3) / float(small), shape, 1, 1), "dgrad")):
+            # one product: its rounding, and that of x * big and of small against what the oracle takes
+            assert np.linalg.norm(got.transpose(0, 3, 1, 2) / r - want) <= 2.0 ** -23 * np.linalg.norm(want), (first, what)
+    x1, d1 = np.zeros_like(x), np.zeros_like(dy)
+    for n in range(N):
+        x1[n, rng.integers(C), rng.integers(H), rng.integers(W)] = small
+        d1[n, rng.integers(K), rng.integers(H), rng.integers(W)] = small
+    y, dx, dw = _split_layer(case, x1, w * big, dy * big)
+    _, _, dw2 = _split_layer(case, x * big, w, d1)
+    X, D = x1 / float(small), d1 / float(small)
+    for got, want, what in ((y, L.conv2d_fwd(X, w, 1, 1), "fwd"), (dx, L.conv2d_dgrad(X, w.transpose(1, 0, 2, 3), shape, 1, 1), "dgrad"),
+                            (dw, L.conv2d_wgrad(dy, X, w.shape, 1, 1), "wgrad, x"), (dw2, L.conv2d_wgrad(D, x, w.shape, 1, 1), "wgrad, dy")):
+        # a few products at most
+        assert np.linalg.norm(got.transpose(0, 3, 1, 2) / r - want) <= 2.0 ** -22 * np.linalg.norm(want), what
+
+
 # ---- small outputs: 32x32 tiles, the reduction split among eight waves ------------------------------------------------
 # One tile and 256 (and just past them: the larger tiles), ragged pixel and channel tiles, channels that fill a part of a
 # 128-byte unit, fewer units than waves, an odd share, strides, 1x1 / 5x5 / 7x7 filters, parity classes without a tap
