@@ -1028,6 +1028,8 @@ static WgradPlan plan_for(const ConvGeom &g, int dt, bool beside = false) {
 
 int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool beside) { return plan_floats(plan_for(g, dt, beside), g); }
 
+int64_t wgrad_reserve_floats(const ConvGeom &g, int dt) { return std::max(wgrad_scratch_floats(g, dt), plan_floats(plan_wgrad(g), g)); }
+
 int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial, hipStream_t st, bool beside) {
   RESIST_TRY(check_geom(g, dt));
   return run_wgrad(plan_for(g, dt, beside), g, dt, dy, x, dw, partial, st);
@@ -1076,9 +1078,9 @@ int64_t wgrad_static_scratch_bytes() { return (int64_t)kStaticScratchBytes; }
 
 int conv_wgrad_static(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, hipStream_t st) {
   RESIST_TRY(check_geom(g, dt));
-  const int64_t need = std::max(wgrad_scratch_floats(g, dt), plan_floats(plan_wgrad(g), g)) * 4;
+  const int64_t need = wgrad_reserve_floats(g, dt) * 4;
   if (need > (int64_t)kStaticScratchBytes)
-    return set_error(RESIST_EWORKSPACE, "split partial sums need %lld bytes, the static scratch holds %lld",
+    return set_error(RESIST_EWORKSPACE, "split partial sums: %lld bytes reserved for this shape, the static scratch holds %lld",
                      (long long)need, (long long)kStaticScratchBytes);
   void *ptr = nullptr;
   RESIST_TRY(static_scratch(&ptr));

@@ -156,10 +156,13 @@ int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st
 // dw (fp32) = wgrad(dy, x); partial: split-reduction scratch of wgrad_scratch_floats(g, dt, beside) floats; beside: other
 // kernels run at the same time
 int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool beside = false);
+// what a caller is told to reserve for it: no less than the one-tap kernel's partial sums, whichever kernel runs, so that which
+// shapes fit a given scratch does not change with the rules that choose between them
+int64_t wgrad_reserve_floats(const ConvGeom &g, int dt);
 int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial,
                hipStream_t st, bool beside = false);
 // the same with the split partial sums in the library's static device array (no allocation anywhere);
-// RESIST_EWORKSPACE when the split partial sums exceed wgrad_static_scratch_bytes()
+// RESIST_EWORKSPACE when wgrad_reserve_floats(g, dt) * 4 exceeds wgrad_static_scratch_bytes()
 int64_t wgrad_static_scratch_bytes();
 int conv_wgrad_static(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, hipStream_t st);
 

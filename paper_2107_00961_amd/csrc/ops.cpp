@@ -21,7 +21,7 @@ extern "C" int resist_conv2d_workspace_bytes(const resist_conv_shape *s, int64_t
   RESIST_TRY(to_geom(s, &g));
   if (!bytes) return set_error(RESIST_EINVAL, "bytes is NULL");
   const int64_t filt = align256((int64_t)g.K * g.R * g.S * g.C * esize(s->dtype));
-  const int64_t split = align256(wgrad_scratch_floats(g, s->dtype) * 4);
+  const int64_t split = align256(wgrad_reserve_floats(g, s->dtype) * 4);
   *bytes = std::max<int64_t>(std::max(filt, split), 256);
   return RESIST_OK;
 }

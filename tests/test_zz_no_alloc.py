@@ -70,3 +70,29 @@ def test_wgrad_static_rejects_oversized_partial_sums():
         R.conv2d_wgrad_static(dy, x, dw, st, pad)
     torch.cuda.synchronize()
     assert bool((dw == 7.0).all())
+
+
+@pytest.mark.parametrize("case,fits", [((128, 4, 4, 512, 512), False), ((32, 4, 4, 512, 512), True), ((16, 14, 14, 512, 512), False),
+                                       ((128, 16, 16, 128, 128), True)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_wgrad_static_takes_what_the_query_says(case, fits, bf16):
+    """The call refuses a shape exactly where resist_conv2d_workspace_bytes asks for more than the array, also where the kernel
+    that runs needs no partial sums (bf16, 512 channels, 4x4); what it takes has the bits of the call with a workspace."""
+    N, H, W, C, K = case
+    sh = R.binding._conv_shape(N, H, W, C, K, 3, 1, 1, 1 if bf16 else 0)
+    n = ctypes.c_int64()
+    assert R.lib().resist_conv2d_workspace_bytes(ctypes.byref(sh), ctypes.byref(n)) == 0
+    assert (n.value <= R.conv2d_wgrad_static_limit()) == fits
+    dt = torch.bfloat16 if bf16 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(N, H, W, C, generator=gen, device="cuda").to(dt)
+    dy = torch.randn(N, H, W, K, generator=gen, device="cuda").to(dt)
+    dw = torch.full((K, 3, 3, C), 7.0, dtype=torch.float32, device="cuda")
+    if not fits:
+        with pytest.raises(R.ResistError, match="static scratch"):
+            R.conv2d_wgrad_static(dy, x, dw, 1, 1)
+        torch.cuda.synchronize()
+        assert bool((dw == 7.0).all())
+        return
+    R.conv2d_wgrad_static(dy, x, dw, 1, 1)
+    assert torch.equal(dw, R.conv2d_wgrad(dy, x, (K, 3, 3, C), 1, 1))
