@@ -165,3 +165,40 @@ def test_forward_eval_epilogue_ragged(kind, dtype):
         assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 2e-2
     else:
         assert_close(got, want, f"kind {kind} logits")
+
+
+# The same in the large tiles that a batch of the CIFAR- or ImageNet-shaped models runs on: (block kind, dtype, batch, the kernels
+# that have to be among those that ran).  Row tiles end in mid-image and the last one is ragged in every layer.
+EVAL_TILE_CASES = [(0, 0, 77, ["conv3_f32_eval_128x64", "conv3_f32_eval_64x64"]),
+                   (2, 0, 77, ["conv3_f32_eval_128x64", "conv3_f32_eval_64x64"]),
+                   (1, 0, 41, ["conv3_f32_eval_128x64", "igemm_f32_eval_128x128x32"]),
+                   (0, 1, 101, ["igemm_bf16_eval_128x64x64_w8", "igemm_bf16_eval_128x128x64_w8", "igemm_bf16_eval_64x64x128"]),
+                   (2, 1, 101, ["igemm_bf16_eval_128x64x64_w8", "igemm_bf16_eval_128x128x64_w8"]),
+                   (0, 1, 77, ["igemm_bf16_eval_128x64x128_w8"]), (2, 1, 77, ["igemm_bf16_eval_128x64x128_w8"]),
+                   (1, 1, 41, ["igemm_bf16_eval_128x128x64"])]
+
+
+@pytest.mark.parametrize("case", EVAL_TILE_CASES)
+def test_forward_eval_epilogue_large_tiles(case):
+    from oracle import resnet as OR
+    kind, dtype, batch, kernels = case
+    print("case", case, flush=True)
+    model = dict(get_config("cfg1")["model"], block_kind=kind, widths=[64, 128, 256] if kind != 1 else [64, 128], in_h=28, in_w=36,
+                 blocks=[1, 2, 2] if kind != 1 else [2, 2], num_classes=9, compute_dtype=dtype)
+    nb = R.num_blocks(model)
+    params = make_params(model, 12, perturb_bn=True)
+    x, _ = make_batch(model, batch, 5)
+    scale = [1.0, 0.5, 0.25, 1.0, 0.5][:nb]
+    dev, xd = DeviceModel(model, list(range(nb)), params), to_device_batch(x, np.zeros(batch))[0]
+    R.profile_enable(True)
+    try:
+        got = dev.predict(xd, branch_scale=scale).cpu().numpy()
+        ran = {k["name"] for k in R.profile_read()}
+    finally:
+        R.profile_enable(False)
+    assert set(kernels) <= ran, ran
+    want = OR.forward_eval(model, list(range(nb)), params, x, branch_scale=scale)
+    if dtype == 1:
+        assert np.linalg.norm(got - want) / np.linalg.norm(want) <= 2e-2
+    else:
+        assert_close(got, want, f"kind {kind} logits")
