@@ -86,6 +86,7 @@ def test_conv_wgrad(case):
 # ---- fp32 3x3 stride-1 layers of at least 48 input channels: operands taken apart into three bf16 parts --------------
 # Edges of the 64- and 128-pixel tiles, of the 64-channel chunks (the last one ragged, an odd and an even number of them)
 # and of the 64-wide output tiles; images one pixel wide, smaller than a tile, and at and past the widest that is staged.
+# (All but two of these have so few output tiles that they run on the small-output kernel; see SPLIT_LARGE_CASES.)
 #              N   H   W   C    K   R st pad
 SPLIT_CASES = [(1, 1, 1, 64, 16, 3, 1, 1), (5, 3, 1, 48, 80, 3, 1, 1), (1, 8, 8, 64, 64, 3, 1, 1), (1, 5, 13, 52, 68, 3, 1, 1),
                (13, 5, 2, 128, 48, 3, 1, 1), (2, 3, 56, 64, 32, 3, 1, 1), (2, 3, 57, 64, 32, 3, 1, 1), (129, 4, 4, 132, 1028, 3, 1, 1),
@@ -108,6 +109,7 @@ def test_conv_split_forward_and_dgrad(case):
 
 # nine-tap weight gradient: ragged channel tiles and pixel chunks, one split and several, the ring of staged pixels run
 # through many times, images one pixel wide and the widest that is staged, and a layer just too small for it
+# (Most of these are too small for that kernel; see WGRAD3_EDGE_CASES.)
 #              N   H   W   C    K   R st pad
 WGRAD3_CASES = [(3, 3, 1, 700, 680, 3, 1, 1), (1, 5, 5, 512, 344, 3, 1, 1), (2, 45, 56, 36, 40, 3, 1, 1), (7, 19, 33, 64, 64, 3, 1, 1),
                 (64, 16, 16, 16, 16, 3, 1, 1), (63, 16, 16, 16, 16, 3, 1, 1), (130, 4, 4, 80, 132, 3, 1, 1), (2, 31, 57, 64, 64, 3, 1, 1)]
@@ -178,6 +180,20 @@ def _split_layer(case, x, w, dy):
                                           R.conv2d_wgrad(dyd, xd, (K, 3, 3, C), 1, 1)))
     assert {"conv3_f32_fwd_" + tile, "conv3_f32_bwd_" + tile, "wgrad3_f32"} <= ran, ran
     return [t.cpu().numpy() for t in (y, dx, dw)]
+
+
+# the edges of SPLIT_CASES on layers of more than 256 tiles of 32x32, by the tile they run on (None: not taken apart)
+#                      N   H   W   C    K   R st pad
+SPLIT_LARGE_CASES = [((700, 3, 1, 48, 300, 3, 1, 1), "64x64"), ((1, 5, 13, 52, 2756, 3, 1, 1), "64x64"), ((170, 5, 2, 128, 324, 3, 1, 1), "64x64"),
+                     ((3, 29, 56, 64, 200, 3, 1, 1), "64x64"), ((3, 29, 57, 64, 200, 3, 1, 1), None), ((3, 29, 56, 44, 200, 3, 1, 1), None),
+                     ((129, 16, 16, 132, 68, 3, 1, 1), "128x64"), ((11, 60, 56, 48, 68, 3, 1, 1), "128x64"), ((2, 127, 31, 64, 300, 3, 1, 1), "128x64")]
+
+
+@pytest.mark.parametrize("case", SPLIT_LARGE_CASES)
+def test_conv_split_large(case):
+    _, ran = _launched(lambda: test_conv_split_forward_and_dgrad(case[0]))
+    names = {n for n in ran if n.startswith("conv3_f32")}
+    assert names == ({"conv3_f32_fwd_" + case[1], "conv3_f32_bwd_" + case[1]} if case[1] else set()), ran
 
 
 # which weight gradient a layer gets: around 2^14 pixels per 64 x 64 channels and around 640 pixels, ragged channel tiles and pixel
