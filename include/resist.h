@@ -79,7 +79,12 @@ typedef struct {
   int32_t width[RESIST_MAX_STAGES];   /* channel width per stage (multiple of 16)                */
   int32_t blocks[RESIST_MAX_STAGES];  /* residual blocks per stage (>= 1)                        */
   int32_t num_classes;
-  int32_t compute_dtype; /* 0: fp32 MFMA.  1: bf16 MFMA operands, fp32 accumulate, fp32 masters  */
+  int32_t compute_dtype; /* 0: fp32 tensors, products and sums.  (3x3 stride-1 convolutions of 48 or
+                               more input channels are multiplied on the bf16 matrix cores, every
+                               operand in three bf16 parts, six products: all 24 bits of it, and an
+                               error against exact arithmetic no larger than the fp32 matrix
+                               instruction's, over all of fp32's range; infinities and NaN as there.)
+                            1: bf16 MFMA operands, fp32 accumulate, fp32 masters                  */
   float bn_eps;
   float bn_momentum;
 } resist_model_desc;

@@ -2,7 +2,7 @@
 //
 // Every fp32 operand a is taken apart into three bf16 numbers, a = h + m + l, each the nearest bf16 to what the ones
 // before it leave: 8 + 8 + 8 significant bits, so nothing of a's 24 is lost.  A product is then six bf16 products
-//   a*b = h*h' + (h*m' + m*h') + (m*m' + h*l' + l*h')      (what is left out is below 2^-26 of |a*b|)
+//   a*b = h*h' + (h*m' + m*h') + (m*m' + h*l' + l*h')      (what is left out is at most 2^-24 of |a*b|, 2^-27.5 in the mean)
 // accumulated in fp32, small terms first.  v_mfma_f32_32x32x16_bf16 does 16 times the work of
 // v_mfma_f32_32x32x2_f32 per cycle, so six of them take 6/16 of the time one fp32 product takes.
 //
@@ -19,11 +19,13 @@
 // BM + 2W + 2 pixels holds every tap, whatever H, W and the image boundaries are; a tap that falls off its image reads
 // a row of zeros instead.
 //
-// Measured, us, fp32 instruction -> this kernel (forward | data gradient with its filter transpose), batch 128:
-//   64 ch 32x32  87 -> 63 | 93 -> 67     128 ch 16x16  83 -> 54 | 88 -> 59
-//  256 ch  8x8   95 -> 54 | 98 -> 60     512 ch  4x4   89 -> 60 | 99 -> 68
-// The 256-channel forward kernel is busy with products 57 % of its cycles (43 us with nothing else left in the loop: the
-// matrix core does not hold its nominal clock); the filter rows staged per tap cost 8 us of the rest, the fragment reads 4.
+// Measured, us, fp32 instruction -> this kernel (forward | data gradient with its filter transpose):
+//   batch 128: 64 ch 32x32  88 -> 68 | 94 -> 72    128 ch 16x16  83 -> 57 | 89 -> 61
+//             256 ch  8x8   82 -> 50 | 89 -> 56    512 ch  4x4   90 -> 62 | 100 -> 72
+//   batch  77: 64 ch 32x32  68 -> 49 | 74 -> 54    128 ch 16x16  65 -> 52 | 70 -> 56
+//             256 ch  8x8   80 -> 59 | 87 -> 64    512 ch  4x4   89 -> 58 | 99 -> 65
+// The matrix cores of the 256-channel forward kernel, batch 128, are busy 53 % of its cycles, at the 1.9 GHz that the shader
+// holds under it (29 us; 23 at the nominal clock); the filter rows staged per tap cost 8 us of the rest, the fragment reads 4.
 // Error against float64 over 27 to 4608 products per output: 1.6e-7 to 4.6e-7 (2-norm), the fp32 instruction's 2.5e-7 to
 // 1.1e-6.
 #include "conv_tile.h"
@@ -419,6 +421,9 @@ int pick(const EvalArgs &a, hipStream_t st, StatParts *p) {
 
 }  // namespace
 
+// From 48 input channels: a chunk is 64 of them, however many there are.  us, fp32 instruction and here, 32x32, batch 128: 32 ->
+// 32 channels 49 and 62, 48 -> 48 87 and 65.  (40 and 44 channels, which no network of this library can have, 87 and 62.)  And
+// images no wider than the staged range allows.
 bool conv3_takes(const IgemmArgs &a) {
   return a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.IW <= kMaxW && a.IC >= 48;
 }

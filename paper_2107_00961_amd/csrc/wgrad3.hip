@@ -10,10 +10,11 @@
 // Twelve waves: wave (r, kq, cq) accumulates the three taps of filter row r for one 32 x 32 quadrant of the channels.
 // Both operands arrive pixel by pixel with the channels contiguous and are read back through the LDS transpose read.
 //
-// Measured with the reduction of the partial sums, us, fp32 instruction a tap at a time -> this kernel, batch 128:
-//   64 ch 32x32  96 -> 59    128 ch 16x16  95 -> 59    256 ch 8x8  101 -> 61    512 ch 4x4  110 -> 59
-// The products are 23 us of it at nominal clock (35 at the clock they run at); the 38 MB of partial sums of 256
-// workgroups, written and read back, about 15.  Error against float64: 2e-8 to 1.3e-7, before 2e-8 to 4.9e-7.
+// Measured with the reduction of the partial sums, us, fp32 instruction a tap at a time -> this kernel:
+//   batch 128: 64 ch 32x32  96 -> 56    128 ch 16x16  96 -> 55    256 ch 8x8  101 -> 56    512 ch 4x4  111 -> 56
+//   batch  77: 64 ch 32x32  62 -> 41    128 ch 16x16  63 -> 41    256 ch 8x8   65 -> 43    512 ch 4x4   78 -> 44
+// The products are 32 us of it at the 1.75 GHz that the shader holds under them (23 at the nominal clock); the 38 MB of partial
+// sums of 256 workgroups, written and read back, about 15.  Error against float64: 2e-8 to 1.3e-7, before 2e-8 to 4.9e-7.
 #include "conv_tile.h"
 
 namespace resist {
@@ -292,11 +293,11 @@ __global__ __launch_bounds__(kNT) void wgrad3_split_kernel(Wgrad3Args a) {
 // 64 pixels of a chunk and one on either side serve three taps.  X rows live in a ring as above.  Eight waves: four
 // quadrants of the channels, two halves of a chunk's pixels, added through LDS at the end.
 //
-// Measured with the reduction of the partial sums, us, one tap -> one filter row per workgroup:
-//   batch 128: 256 ch 8x8 32.1 -> 32.3    128 ch 16x16 31.3 -> 31.6    64 ch 32x32 29.8 -> 28.8    512 ch 4x4 27.8 -> 26.7
-//   batch 64:  256 ch 14x14 40.3 -> 39.7  128 ch 28x28 38.5 -> 37.9    64 ch 56x56 37.8 -> 36.5
-// Alone it is little faster: it is bound by the LDS reads of the fragments, 1.3 per product.  Beside the data gradients of a
-// step, which are short of L2 bandwidth, it is: CIFAR-shaped model, batch 128, 5.89 -> 5.65 ms.
+// Measured with the reduction of the partial sums, us, one tap -> one filter row per workgroup, alone:
+//   batch 128: 256 ch 8x8 29.1 -> 28.7    128 ch 16x16 28.7 -> 29.3    64 ch 32x32 27.9 -> 27.5    512 ch 4x4 32.9 -> 25.6
+//   batch 64:  256 ch 14x14 38.7 -> 33.7  128 ch 28x28 36.3 -> 32.5    64 ch 56x56 36.6 -> 32.8
+// It is bound by the LDS reads of the fragments, 1.3 per product.  Beside the data gradients of a step, which are short of L2
+// bandwidth, it gains more: CIFAR-shaped model, batch 128, 5.89 -> 5.65 ms.
 constexpr int kRowNT = 512, kRowCh = 64, kRowRing = 256, kRowPitch = kPart + 64;
 
 struct WgradRowArgs {
