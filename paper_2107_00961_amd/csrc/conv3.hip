@@ -39,13 +39,19 @@ constexpr int kPlane = kBK * 2;            // bytes of one part of a staged row
 constexpr int kPitch = 3 * kPlane + 16;    // row pitch: rows 4 banks apart, conflict-free 16-byte reads of consecutive rows
 constexpr int kStageB = kBN * kPitch;
 
-// the three bf16 parts of four floats to their places in a staged row
-__device__ inline void store_split(char *row, f32x4 v, unsigned long long &missed) {
+// the three bf16 parts of four floats to their places in a staged row; returns what the first two leave, checked if CHECK
+template <bool CHECK>
+__device__ inline f32x4 store_split(char *row, f32x4 v, unsigned long long &missed) {
+  f32x4 rest;
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
-    if (p == 2) split_check(v, missed);
+    if (p == 2) {
+      rest = v;
+      if (CHECK) split_check(v, missed);
+    }
     *reinterpret_cast<u32x2 *>(row + p * kPlane) = split_part(v);
   }
+  return rest;
 }
 
 // 8 waves: 2 along the pixels, 4 sharing the reduction (wave slice k takes 16 of every 64 channels), so that a wave's
@@ -126,7 +132,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
     ++pc;
   };
   auto store_pixels = [&](int i) {
-    if (i * 32 < px) store_split(pdst + i * 32 * kPitch, rp[i], missed);   // uniform
+    if (i * 32 < px) store_split<true>(pdst + i * 32 * kPitch, rp[i], missed);   // uniform
   };
   int bt = 0, bc = 0;         // tap and chunk of the filter rows requested next
   auto request_filter = [&](int set) {
@@ -139,7 +145,11 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
     bc = wrap ? bc + 1 : bc;
   };
   // the rows of step t wait in register set t % 2 and go to LDS stage t % 2
-  auto store_filter = [&](int set, int i) { store_split(bdst[set] + i * 32 * kPitch, rb[set][i], missed); };
+  // 128-pixel tiles check the filter rows a group of products later, where nobody waits for it (128 ch 16x16, batch 128: 60.3 ->
+  // 59.3 us; 64-pixel tiles, with half the products, 59.7 -> 61.5)
+  constexpr bool kLater = TM == 2;
+  f32x4 rest[PB];
+  auto store_filter = [&](int set, int i) { rest[i] = store_split<!kLater>(bdst[set] + i * 32 * kPitch, rb[set][i], missed); };
 
   // ---- fragments: three parts of TM pixel tiles and kTN filter tiles.  A part is fetched for the next step as soon as
   // its last product of this step is issued; only the leading parts (index 0), which the last product of a step and the
@@ -203,9 +213,13 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
 #pragma unroll
   for (int i = 0; i < PA; ++i) store_pixels(i);
 #pragma unroll
-  for (int i = 0; i < PB; ++i) store_filter(0, i);
+  for (int i = 0; i < PB; ++i) {
+    store_filter(0, i);
+    if (kLater) split_check(rest[i], missed);
+  }
   request_filter(0);
   store_filter(1, 0);
+  if (kLater) split_check(rest[0], missed);
   request_pixels();
   lds_barrier();
   aim();
@@ -244,6 +258,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
     lds_barrier();
     fetch_b(nx, 2);
     if (!turn) fetch_a(nx, 0);
+    if (kLater) split_check(rest[1], missed);
     product(set, 1, 1);
     replace(0);
     fetch_b(nx, 0);
@@ -261,6 +276,7 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
 #pragma unroll
       for (int q = 2; q >= 0; --q) fetch_a(nx, q);
     }
+    if (kLater) split_check(rest[0], missed);
     product(set, 0, 0);
     tap = tap == 8 ? 0 : tap + 1;
   };

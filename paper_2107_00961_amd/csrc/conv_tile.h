@@ -103,8 +103,9 @@ __device__ inline u32x2 split_part(f32x4 &v) {
 }
 // Between the second call and the third: adds to `missed` the lanes whose parts may not hold all of a value.  The last bit of
 // bf16's smallest numbers is 2^-133, so below 2^-110 the parts of a value run out of bits; what two parts leave of such a
-// value is a subnormal float (and of values from 2^-103 up it never is).  It costs the forward and data-gradient kernels 3 %
-// (256 ch 8x8, batch 128: 49.3 -> 50.9 us; the largest or the smallest magnitude of what is staged instead: the same or more).
+// value is a subnormal float (and of values from 2^-103 up it never is).  It costs the forward kernel 2 % and the data
+// gradient 1 (14x14, 256 ch, batch 64: 88.8 -> 90.9 us, 96.4 -> 97.9; the largest or the smallest magnitude of what is staged
+// instead: the same or more).
 __device__ inline void split_check(const f32x4 &v, unsigned long long &missed) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {   // one instruction into a scalar mask; the builtin of it goes through a vector register
