@@ -304,9 +304,6 @@ template <typename T, int MODE>
 int dispatch_igemm(const EvalArgs &a, hipStream_t st, StatParts *tiles_m_out = nullptr) {
   constexpr int dt = sizeof(T) == 2 ? DT_BF16 : DT_F32;
   if (conv_small_takes(a, dt)) return conv_small_launch(a, dt, MODE, st, tiles_m_out);
-  if constexpr (sizeof(T) == 4) {
-    if (conv3_takes(a)) return conv3_launch(a, MODE, st, tiles_m_out);
-  }
   // pick the largest tile that still yields enough workgroups to cover the 256 compute units
   constexpr int V = Elem<T>::VEC;   // K-chunks of 8*V and 16*V elements: 128 and 256 bytes per tile row
   const long long classes = (long long)a.cls * a.cls;
@@ -359,18 +356,34 @@ int check_geom(const ConvGeom &g, int dt) {
 
 int conv_check(const ConvGeom &g, int dt) { return check_geom(g, dt); }
 
+bool filter_in_fragments(const ConvGeom &g, int dt, bool dgrad) {
+  if (g.R != 3 || g.S != 3 || g.stride != 1 || g.pad != 1 || (int64_t)g.N * g.H * g.W > 0x7fffffff) return false;
+  IgemmArgs a{};
+  a.N = g.N; a.IH = a.OH = a.OHc = g.H; a.IW = a.OW = a.OWc = g.W;
+  a.IC = dgrad ? g.K : g.C; a.OC = dgrad ? g.C : g.K;
+  a.R = a.S = 3; a.stride = a.pad = a.cls = 1;
+  a.Mrows = g.N * g.H * g.W;
+  return conv3_takes(a, dt) && !conv_small_takes(a, dt);
+}
+
+int64_t filter_bytes(const ConvGeom &g, int dt, bool fragments, bool dgrad) {
+  if (!fragments) return (int64_t)g.K * g.R * g.S * g.C * esize(dt);
+  return conv3_filter_bytes(dgrad ? g.C : g.K, dgrad ? g.K : g.C, dt);
+}
+
 int64_t conv_stats_floats(const ConvGeom &g) {
   // the smallest row tile a forward kernel uses is 64, of a small output 32
   const int64_t M = (int64_t)g.N * g.P * g.Q, rows = conv_small_rows(M, g.K, 1) ? 32 : 64;
   return 3 * ((M + rows - 1) / rows) * g.K;
 }
 
-int conv_fwd(const ConvGeom &g, int dt, const void *x, const void *w, void *y, const void *addend, float *stats, StatParts *stat_parts,
+int conv_fwd(const ConvGeom &g, int dt, const void *x, const Filter &w, void *y, const void *addend, float *stats, StatParts *stat_parts,
              hipStream_t st, const EvalAct *act) {
   RESIST_TRY(check_geom(g, dt));
   if (stats && !stat_parts) return set_error(RESIST_EINVAL, "conv_fwd: stats without stat_parts");
   EvalArgs a{};
-  a.in = x; a.wt = w; a.out = y; a.addend = addend; a.stats = stats;
+  a.in = x; a.wt = w.fragments || !w.prep ? w.w : w.prep; a.out = y; a.addend = addend; a.stats = stats;
+  if (!a.wt && !w.fragments) return set_error(RESIST_EINVAL, "conv_fwd: no filter");
   a.N = g.N; a.IH = g.H; a.IW = g.W; a.IC = g.C;
   a.OH = g.P; a.OW = g.Q; a.OC = g.K;
   a.R = g.R; a.S = g.S; a.stride = g.stride; a.pad = g.pad;
@@ -380,18 +393,21 @@ int conv_fwd(const ConvGeom &g, int dt, const void *x, const void *w, void *y, c
     if (stats || !act->out || !act->scale || !act->shift) return set_error(RESIST_EINVAL, "conv_fwd: fused activation");
     a.act = act->out; a.act_scale = act->scale; a.act_shift = act->shift;
     a.act_res = act->res; a.res_scale = act->rscale; a.res_shift = act->rshift;
+    if (w.fragments) return conv3_launch(a, w, dt, kEval, st, nullptr);
     return dt == DT_BF16 ? dispatch_igemm<__bf16, kEval>(a, st) : dispatch_igemm<float, kEval>(a, st);
   }
+  if (w.fragments) return conv3_launch(a, w, dt, kFwd, st, stat_parts);
   return dt == DT_BF16 ? dispatch_igemm<__bf16, kFwd>(a, st, stat_parts) : dispatch_igemm<float, kFwd>(a, st, stat_parts);
 }
 
-int conv_dgrad(const ConvGeom &g, int dt, const void *dy, const void *wT, void *dx, const void *addend, const void *relu_mask,
+int conv_dgrad(const ConvGeom &g, int dt, const void *dy, const Filter &w, void *dx, const void *addend, const void *relu_mask,
                hipStream_t st, const BnBwdFuse *bn) {
   RESIST_TRY(check_geom(g, dt));
   if (g.stride == 2 && ((g.H & 1) || (g.W & 1)))
     return set_error(RESIST_ESHAPE, "stride-2 dgrad needs even input size, got %dx%d", g.H, g.W);
   EvalArgs a{};
-  a.in = dy; a.wt = wT; a.out = dx; a.addend = addend; a.relu_mask = relu_mask;
+  if (!w.prep) return set_error(RESIST_EINVAL, "conv_dgrad: no prepared filter");
+  a.in = dy; a.wt = w.fragments ? w.w : w.prep; a.out = dx; a.addend = addend; a.relu_mask = relu_mask;
   a.N = g.N; a.IH = g.P; a.IW = g.Q; a.IC = g.K;
   a.OH = g.H; a.OW = g.W; a.OC = g.C;
   a.R = g.R; a.S = g.S; a.stride = g.stride; a.pad = g.pad;
@@ -403,7 +419,8 @@ int conv_dgrad(const ConvGeom &g, int dt, const void *dy, const void *wT, void *
     a.bn_y = bn->y; a.bn_mean = bn->b.mean; a.bn_invstd = bn->b.invstd; a.bn_scale = bn->b.scale; a.bn_shift = bn->b.shift;
     a.bn_sums = bn->sums; a.bn_self = bn->relu_of_self ? 1 : 0;
   }
-  RESIST_TRY(dt == DT_BF16 ? (dispatch_igemm<__bf16, kBwd>(a, st, &parts)) : (dispatch_igemm<float, kBwd>(a, st, &parts)));
+  if (w.fragments) RESIST_TRY(conv3_launch(a, w, dt, kBwd, st, &parts));
+  else RESIST_TRY(dt == DT_BF16 ? (dispatch_igemm<__bf16, kBwd>(a, st, &parts)) : (dispatch_igemm<float, kBwd>(a, st, &parts)));
   if (bn) *bn->parts = parts;
   return RESIST_OK;
 }
@@ -414,57 +431,70 @@ int64_t conv_dgrad_bn_sums_floats(const ConvGeom &g) {
   return 2 * ((M + rows - 1) / rows) * g.C;
 }
 
-// ---- filter preparation: wT[c][r][s][k] = w[k][r][s][c] (and a low-precision copy of w) ------------
-namespace {
-template <typename S, typename T>
-__global__ __launch_bounds__(256) void prepare_filter_kernel(const S *__restrict__ w, T *__restrict__ wlp, T *__restrict__ wT,
-                                                             int K, int RS, int C) {
-  // 32x32 tiles of the [K][C] matrix at a fixed tap, through LDS so both sides stay coalesced
-  __shared__ float tile[32][33];
-  const int tap = blockIdx.z;
-  const int k0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  for (int i = ty; i < 32; i += 8) {
-    const int k = k0 + i, c = c0 + tx;
-    float v = 0.f;
-    if (k < K && c < C) {
-      v = Elem<S>::to_f32(w[((size_t)k * RS + tap) * C + c]);
-      if (wlp) wlp[((size_t)k * RS + tap) * C + c] = Elem<T>::from_f32(v);
-    }
-    tile[i][tx] = v;
-  }
-  __syncthreads();
-  if (wT)
-    for (int i = ty; i < 32; i += 8) {
-      const int c = c0 + i, k = k0 + tx;
-      if (k < K && c < C) wT[((size_t)c * RS + tap) * K + k] = Elem<T>::from_f32(tile[tx][i]);
-    }
-}
-}  // namespace
-
+// ---- filter preparation ------------------------------------------------------------------------------
 // All filters of a step in one launch (or a few: the table travels in the kernel arguments).
 namespace {
 constexpr int kPrepSegs = 48;
 struct PrepTable {
-  const float *w[kPrepSegs];
+  const void *w[kPrepSegs];
   void *wlp[kPrepSegs];
   void *wT[kPrepSegs];
   int K[kPrepSegs], RS[kPrepSegs], C[kPrepSegs];
   float scale[kPrepSegs];
   int first_wg[kPrepSegs + 1];
+  unsigned long long frag_copy, frag_transpose;   // bit per filter: in matrix fragments (conv3.hip) instead of rows
   int nseg;
 };
+// (a caller's filter or workspace need not be aligned to more than its elements)
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+typedef u32x2 __attribute__((aligned(2))) u32x2_any;
+__device__ inline f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4_any *>(p); }
+__device__ inline f32x4 load4(const __bf16 *p) {
+  const u32x2 t = *reinterpret_cast<const u32x2_any *>(p);
+  return f32x4{bf16_lo(t[0]), bf16_hi(t[0]), bf16_lo(t[1]), bf16_hi(t[1])};
+}
 // four consecutive elements of T from four floats
 __device__ inline void store4(float *p, float a, float b, float c, float d) {
-  *reinterpret_cast<f32x4 *>(p) = f32x4{a, b, c, d};
+  *reinterpret_cast<f32x4_any *>(p) = f32x4{a, b, c, d};
 }
 __device__ inline void store4(__bf16 *p, float a, float b, float c, float d) {
-  *reinterpret_cast<u32x2 *>(p) = u32x2{pack_bf16x2(a, b), pack_bf16x2(c, d)};
+  *reinterpret_cast<u32x2_any *>(p) = u32x2{pack_bf16x2(a, b), pack_bf16x2(c, d)};
+}
+
+// 64 output channels x 64 input channels of one tap, at(oc, ch), as the fragments that conv3.hip multiplies with: its layout is
+// [octile of 32][chunk of 64 channels][tap][slice of 16][part][lane][8 values], lane l holding output channel l % 32 and channels
+// 8 * (l / 32) .. +7 of its slice; fp32 in three bf16 parts.  Behind them one word per 64x64 tile and tap, [tile][chunk][tap]:
+// whether it holds a value that three parts do not.
+template <typename T, typename At>
+__device__ inline void store_fragments(void *out, int octiles, int chunks, int octile, int chunk, int tap, At at) {
+  constexpr int NP = sizeof(T) == 4 ? 3 : 1;
+  unsigned long long missed = 0;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int id = threadIdx.x + u * 256;          // (half, slice, lane)
+    const int lane = id & 63, slice = (id >> 6) & 3, half = id >> 8;
+    const int oc = half * 32 + (lane & 31), ch = slice * 16 + (lane >> 5) * 8;
+    f32x4 lo, hi;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { lo[e] = at(oc, ch + e); hi[e] = at(oc, ch + 4 + e); }
+    char *dst = static_cast<char *>(out) + ((((size_t)(octile * 2 + half) * chunks + chunk) * 9 + tap) * 4 + slice) * (NP * 1024) + lane * 16;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (NP == 3 && p == 2) { split_check(lo, missed); split_check(hi, missed); }
+      const u32x2 a = split_part(lo), b = split_part(hi);
+      *reinterpret_cast<u32x4 *>(dst + p * 1024) = u32x4{a[0], a[1], b[0], b[1]};
+    }
+  }
+  if constexpr (NP == 3) {
+    const int any = __syncthreads_or(missed != 0);
+    unsigned *flags = reinterpret_cast<unsigned *>(static_cast<char *>(out) + (size_t)octiles * 2 * chunks * 9 * 4 * (NP * 1024));
+    if (threadIdx.x == 0) flags[((size_t)octile * chunks + chunk) * 9 + tap] = any ? 1u : 0u;
+  }
 }
 
 // One 64x64 tile of the [K][C] matrix of one tap per workgroup, through LDS so that both sides move whole
 // vectors: 256-byte runs of the fp32 master in, 4-element vectors of the copy and of the transpose out.
-template <typename T>
+template <typename S, typename T>
 __global__ __launch_bounds__(256) void prepare_filters_kernel(PrepTable t) {
   constexpr int TS = 64;
   __shared__ float tile[TS][TS + 1];
@@ -476,8 +506,9 @@ __global__ __launch_bounds__(256) void prepare_filters_kernel(PrepTable t) {
   const int c0 = (id % ct) * TS;
   id /= ct;
   const int k0 = (id % kt) * TS, tap = id / kt;
-  const float *__restrict__ w = t.w[seg];
+  const S *__restrict__ w = static_cast<const S *>(t.w[seg]);
   const float sc = t.scale[seg];
+  const bool frag_copy = (t.frag_copy >> seg) & 1, frag_transpose = (t.frag_transpose >> seg) & 1;
   T *__restrict__ wlp = static_cast<T *>(t.wlp[seg]);
   T *__restrict__ wT = static_cast<T *>(t.wT[seg]);
   const int row = threadIdx.x >> 4, col = (threadIdx.x & 15) * 4;   // 16 rows x 16 vectors per pass
@@ -487,18 +518,20 @@ __global__ __launch_bounds__(256) void prepare_filters_kernel(PrepTable t) {
   for (int p = 0; p < TS / 16; ++p) {
     const int k = k0 + row + 16 * p, c = c0 + col;
     v[p] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (k < K && c < C) v[p] = *reinterpret_cast<const f32x4 *>(w + ((size_t)k * RS + tap) * C + c);
+    if (k < K && c < C) v[p] = load4(w + ((size_t)k * RS + tap) * C + c);
   }
 #pragma unroll
   for (int p = 0; p < TS / 16; ++p) {
     const int k = k0 + row + 16 * p, c = c0 + col;
     v[p] *= sc;
-    if (wlp && k < K && c < C) store4(wlp + ((size_t)k * RS + tap) * C + c, v[p][0], v[p][1], v[p][2], v[p][3]);
+    if (wlp && !frag_copy && k < K && c < C) store4(wlp + ((size_t)k * RS + tap) * C + c, v[p][0], v[p][1], v[p][2], v[p][3]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) tile[row + 16 * p][col + e] = v[p][e];
   }
   __syncthreads();
-  if (wT) {
+  if (wlp && frag_copy) store_fragments<T>(wlp, kt, ct, k0 / TS, c0 / TS, tap, [&](int oc, int ch) { return tile[oc][ch]; });
+  if (wT && frag_transpose) store_fragments<T>(wT, ct, kt, c0 / TS, k0 / TS, tap, [&](int oc, int ch) { return tile[ch][oc]; });
+  if (wT && !frag_transpose) {
 #pragma unroll
     for (int p = 0; p < TS / 16; ++p) {
       const int c = c0 + row + 16 * p, k = k0 + col;
@@ -510,7 +543,8 @@ __global__ __launch_bounds__(256) void prepare_filters_kernel(PrepTable t) {
 }
 }  // namespace
 
-int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st) {
+int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st, int src_dt) {
+  if (src_dt == DT_BF16 && dt != DT_BF16) return set_error(RESIST_EINVAL, "prepare_filters: bf16 source needs a bf16 target");
   size_t i = 0;
   while (i < items.size()) {
     PrepTable t{};
@@ -519,35 +553,25 @@ int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st
     while (i < items.size() && t.nseg < kPrepSegs) {
       const FilterPrep &f = items[i++];
       if ((f.g.K & 3) || (f.g.C & 3)) return set_error(RESIST_ESHAPE, "filter %dx%d: channel counts must be multiples of 4", f.g.K, f.g.C);
+      if (!f.w_lp && !f.wT) continue;
       const int n = t.nseg++;
       t.w[n] = f.w; t.wlp[n] = f.w_lp; t.wT[n] = f.wT;
       t.K[n] = f.g.K; t.RS[n] = f.g.R * f.g.S; t.C[n] = f.g.C;
       t.scale[n] = f.scale;
+      if (f.lp_fragments) t.frag_copy |= 1ull << n;
+      if (f.wT_fragments) t.frag_transpose |= 1ull << n;
       t.first_wg[n] = wg;
       wg += ((f.g.C + 63) / 64) * ((f.g.K + 63) / 64) * f.g.R * f.g.S;
-      bytes += (4.0 + (f.w_lp ? esize(dt) : 0) + (f.wT ? esize(dt) : 0)) * f.g.K * f.g.R * f.g.S * f.g.C;
+      bytes += (double)esize(src_dt) * f.g.K * f.g.R * f.g.S * f.g.C + (f.w_lp ? filter_bytes(f.g, dt, f.lp_fragments, false) : 0) + (f.wT ? filter_bytes(f.g, dt, f.wT_fragments, true) : 0);
     }
     t.first_wg[t.nseg] = wg;
     if (wg == 0) continue;
     prof::Scope ps("prepare_filters", 0, bytes, st);
-    if (dt == DT_BF16) hipLaunchKernelGGL(prepare_filters_kernel<__bf16>, dim3(wg), dim3(256), 0, st, t);
-    else hipLaunchKernelGGL(prepare_filters_kernel<float>, dim3(wg), dim3(256), 0, st, t);
+    if (src_dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<__bf16, __bf16>), dim3(wg), dim3(256), 0, st, t);
+    else if (dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<float, __bf16>), dim3(wg), dim3(256), 0, st, t);
+    else hipLaunchKernelGGL((prepare_filters_kernel<float, float>), dim3(wg), dim3(256), 0, st, t);
     RESIST_CHECK_LAUNCH("prepare_filters");
   }
-  return RESIST_OK;
-}
-
-int prepare_filter(const ConvGeom &g, int src_dt, int dt, const void *w, void *w_lp, void *wT, hipStream_t st) {
-  if (src_dt == DT_BF16 && dt != DT_BF16) return set_error(RESIST_EINVAL, "prepare_filter: bf16 source needs a bf16 target");
-  dim3 grid((g.C + 31) / 32, (g.K + 31) / 32, g.R * g.S);
-  prof::Scope ps("prepare_filter", 0, ((double)esize(src_dt) + (w_lp ? esize(dt) : 0) + (wT ? esize(dt) : 0)) * g.K * g.R * g.S * g.C, st);
-  if (src_dt == DT_BF16)
-    hipLaunchKernelGGL((prepare_filter_kernel<__bf16, __bf16>), grid, dim3(256), 0, st, (const __bf16 *)w, (__bf16 *)w_lp, (__bf16 *)wT, g.K, g.R * g.S, g.C);
-  else if (dt == DT_BF16)
-    hipLaunchKernelGGL((prepare_filter_kernel<float, __bf16>), grid, dim3(256), 0, st, (const float *)w, (__bf16 *)w_lp, (__bf16 *)wT, g.K, g.R * g.S, g.C);
-  else
-    hipLaunchKernelGGL((prepare_filter_kernel<float, float>), grid, dim3(256), 0, st, (const float *)w, (float *)w_lp, (float *)wT, g.K, g.R * g.S, g.C);
-  RESIST_CHECK_LAUNCH("prepare_filter");
   return RESIST_OK;
 }
 

@@ -1,4 +1,5 @@
-// 3x3 stride-1 convolution of fp32 tensors (forward and data gradient) on the bf16 matrix core.
+// 3x3 stride-1 convolution, forward and data gradient, on a filter laid out beforehand for the matrix instruction: fp32 tensors on
+// the bf16 matrix core, and bf16 tensors.
 //
 // Every fp32 operand a is taken apart into three bf16 numbers, a = h + m + l, each the nearest bf16 to what the ones
 // before it leave: 8 + 8 + 8 significant bits, so nothing of a's 24 is lost.  A product is then six bf16 products
@@ -8,86 +9,146 @@
 //
 // Where that is not so, a workgroup computes its tile again on the fp32 matrix instruction: where a result is not finite
 // (an infinity, or a finite value that rounds to one, leaves a NaN in the difference a - h and so in every output it
-// reaches, and h*h' may overflow where a*b, within 0.8 % of the largest float, does not), and where it has staged an
-// operand of so small a magnitude (below 2^-110; from 2^-103 up never) that its parts run out of bf16's bits.  A layer all of
-// whose tiles are computed twice takes twice the time that the fp32 instruction takes on staged tiles (batch 128, all NaN:
-// 64 ch 32x32 193 us, 128 ch 16x16 174, 256 ch 8x8 161, 512 ch 4x4 169; with one load in flight per wave 551, 524, 497, 925).
+// reaches, and h*h' may overflow where a*b, within 0.8 % of the largest float, does not), and where it has an
+// operand of so small a magnitude (below 2^-110; from 2^-103 up never) that its parts run out of bf16's bits: pixels are looked at
+// as they are staged, of a filter prepare_filters leaves one word per 64x64 channels and tap.
 //
-// What bounds this kernel is the staging: an operand element costs 5.5 vector instructions to take apart and 6 bytes of
-// LDS.  So the input pixels of a tile are staged once per 64 channels and serve all nine taps: the tile is a range of
-// BM consecutive pixels of the flattened [N*H*W], tap (r, s) of pixel m is pixel m + (r-1)*W + (s-1), so a range of
-// BM + 2W + 2 pixels holds every tap, whatever H, W and the image boundaries are; a tap that falls off its image reads
-// a row of zeros instead.
+// Pixels are staged once per 64 channels and serve all nine taps: the tile is a range of BM consecutive pixels of the flattened
+// [N*H*W], tap (r, s) of pixel m is pixel m + (r-1)*W + (s-1), so a range of BM + 2W + 2 pixels holds every tap, whatever H, W
+// and the image boundaries are; a tap that falls off its image reads a row of zeros instead.  The filter is not staged at all: a
+// wave's tile is all pixels by 32 channels, so that a fragment of the filter is used by one wave, which loads it from
+// where prepare_filters left it, 1 KB in lane order, three taps ahead.  Without filter rows to take apart and to
+// pass through LDS per tap there is no barrier but the one per 64 channels, and the LDS holds two sets of pixels: the next one is
+// staged between the products.
 //
-// Measured, us, fp32 instruction -> this kernel (forward | data gradient with its filter transpose):
-//   batch 128: 64 ch 32x32  88 -> 68 | 94 -> 72    128 ch 16x16  83 -> 57 | 89 -> 61
-//             256 ch  8x8   82 -> 50 | 89 -> 56    512 ch  4x4   90 -> 62 | 100 -> 72
-//   batch  77: 64 ch 32x32  68 -> 49 | 74 -> 54    128 ch 16x16  65 -> 52 | 70 -> 56
-//             256 ch  8x8   80 -> 59 | 87 -> 64    512 ch  4x4   89 -> 58 | 99 -> 65
-// The matrix cores of the 256-channel forward kernel, batch 128, are busy 53 % of its cycles, at the 1.9 GHz that the shader
-// holds under it (29 us; 23 at the nominal clock); the filter rows staged per tap cost 8 us of the rest, the fragment reads 4.
-// Error against float64 over 27 to 4608 products per output: 1.6e-7 to 4.6e-7 (2-norm), the fp32 instruction's 2.5e-7 to
+// What bounds it now, 256 channels 8x8, batch 128, fp32, 46 us (57 with the filter through LDS, 82 on the fp32 instruction): the
+// products, 36 us of it at the clock that the shader holds under them (without any operand fetched in the loop it takes 43), and 8 us
+// of a launch without products (first pixels, exchange of the four slices, epilogue).  bf16, the same layer: 14.5 us (18.7 with both
+// operands through LDS), 5.8 of them without products.
+//
+// Measured, us, filter through LDS (bf16: igemm_kernel) -> this kernel, forward | data gradient:
+//   fp32 batch 128: 64 ch 32x32  74 -> 64 | 74 -> 67    128 ch 16x16  64 -> 53 | 66 -> 56
+//                  256 ch  8x8   60 -> 47 | 58 -> 48    512 ch  4x4   67 -> 47 | 67 -> 48
+//   fp32 batch  77: 64 ch 32x32  54 -> 48 | 56 -> 48    128 ch 16x16  55 -> 37 | 55 -> 38
+//                  256 ch  8x8   63 -> 33 | 63 -> 33    512 ch  4x4   59 -> 39 | 58 -> 39
+//   bf16           256 ch 8x8, batch 128  18.7 -> 14.5 | 19.4 -> 14.5    512 ch 4x4, batch 128  22 -> 14.4 | 24.4 -> 14.1
+//                  256 ch 14x14, batch 64 26.1 -> 24.3 | 28.6 -> 24.6    512 ch 7x7, batch 64   31.8 -> 21.6 | 34.2 -> 21.9
+// Error against float64 over 27 to 4608 products per output: 1.3e-7 to 4.6e-7 (2-norm), the fp32 instruction's 2.5e-7 to
 // 1.1e-6.
+#include <algorithm>
+
 #include "conv_tile.h"
 
 namespace resist {
 namespace {
 
-constexpr int kMaxW = 56;
-constexpr int kBN = 64, kNT = 512, kBK = 64, kWGK = 4, kWGM = 2, kTN = 2;
-constexpr int kPlane = kBK * 2;            // bytes of one part of a staged row
-constexpr int kPitch = 3 * kPlane + 16;    // row pitch: rows 4 banks apart, conflict-free 16-byte reads of consecutive rows
-constexpr int kStageB = kBN * kPitch;
+constexpr int kWidest = 56;
+constexpr int kBN = 64, kNT = 512, kBK = 64, kWK = 4;
+constexpr int kRing = 3;      // taps of filter fragments in registers
+constexpr int kAhead = 4;     // filter pieces of 8 KB a workgroup asks for up front
 
-// the three bf16 parts of four floats to their places in a staged row; returns what the first two leave, checked if CHECK
-template <bool CHECK>
-__device__ inline f32x4 store_split(char *row, f32x4 v, unsigned long long &missed) {
-  f32x4 rest;
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    if (p == 2) {
-      rest = v;
-      if (CHECK) split_check(v, missed);
-    }
-    *reinterpret_cast<u32x2 *>(row + p * kPlane) = split_part(v);
-  }
-  return rest;
-}
-
-// 8 waves: 2 along the pixels, 4 sharing the reduction (wave slice k takes 16 of every 64 channels), so that a wave's
-// tile is as large as the registers allow (BM/2 x 64): an operand fragment read from LDS feeds 2*TM or 2*TN products.
-template <int BM, int MODE>
-__global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
-  constexpr int WTM = BM / kWGM, TM = WTM / 32, NSUB = TM * kTN;
-  constexpr int PA = (BM + 2 * kMaxW + 2 + 31) / 32, PB = kBN / 32;   // staging passes of 32 rows x 16 lanes
-  constexpr int PX = PA * 32;                     // staged pixels; the row after them is zero
+// 8 waves: 2 along the output channels, 4 sharing the reduction (wave slice k takes 16 of every 64 channels).  A wave's tile is
+// all BM pixels by 32 channels, so a filter fragment is used by one wave only and comes straight from memory.
+template <int NP, int BM, int NBUF, int kMaxW, int MODE>
+__global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<MODE> a) {
+  using T = std::conditional_t<NP == 3, float, __bf16>;
+  constexpr int ES = sizeof(T), VEC = 16 / ES;
+  constexpr int TM = BM / 32;
+  constexpr int kPlane = kBK * 2, kPitch = NP * kPlane + 16;
+  constexpr int LPR = kBK / VEC;                        // lanes per staged row
+  constexpr int RPP = kNT / LPR;                        // rows per staging pass
+  constexpr int PX = BM + 2 * kMaxW + 2;
+  constexpr int PA = (PX + RPP - 1) / RPP;
   constexpr int LDC = kBN + 8;
-  constexpr size_t kOperand = 2 * kStageB + (size_t)(PX + 1) * kPitch;
-  constexpr size_t kReduce = (size_t)kWGM * kWGK * NSUB * 4 * 64 * 16;
+  constexpr int kBuf = PX * kPitch;
+  constexpr size_t kOperand = (size_t)NBUF * kBuf + kPitch;   // staged pixels; the row behind them is zero
+  constexpr size_t kRound1 = (size_t)8 * 2 * TM * 1024, kRound2 = kRound1 / 2;
   constexpr size_t kTile = sizeof(float) * BM * LDC;
-  constexpr size_t kBytes = kOperand > kReduce ? (kOperand > kTile ? kOperand : kTile) : (kReduce > kTile ? kReduce : kTile);
+  constexpr size_t kEnd = kRound2 + kTile > kRound1 ? kRound2 + kTile : kRound1;
+  constexpr size_t kBytes = kOperand > kEnd ? kOperand : kEnd;
   __shared__ __attribute__((aligned(16))) char lds[kBytes];
   __shared__ int row_off[BM];
-  char *const Bs = lds, *const Px = lds + 2 * kStageB;
-  float (*Cs)[LDC] = reinterpret_cast<float (*)[LDC]>(lds);
+  char *const Px = lds;
+  float (*Cs)[LDC] = reinterpret_cast<float (*)[LDC]>(lds + kRound2);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wk = wave & 3, wm = wave >> 2;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave & 3, wn = wave >> 2;
   const int lr = lane & 31, lg = lane >> 5;
   const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int tm = fdiv(bid, a.div_tn), tn = bid - tm * a.tiles_n;
+  int tm, tn;
+  if (a.m_fast) { tn = fdiv(bid, a.div_tm); tm = bid - tn * a.tiles_m; }
+  else { tm = fdiv(bid, a.div_tn); tn = bid - tm * a.tiles_n; }
   const int m0 = tm * BM, n0 = tn * kBN;
   const int W = a.IW, IC = a.IC, px = BM + 2 * W + 2;   // staged pixels: m0 - W - 1 .. m0 + BM + W
-  const int cchunks = (IC + kBK - 1) / kBK;
-  const int steps = 9 * cchunks;
+  const int cchunks = a.cchunks;
 
   for (int r = tid; r < BM; r += kNT) row_off[r] = m0 + r < a.Mrows ? m0 + r : -1;
+
+  // ---- staging
+  const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, (unsigned)a.N * a.IH * W * IC * ES);
+  const int srow = tid / LPR, sch = (tid % LPR) * VEC;
+  char *const pdst = Px + srow * kPitch + sch * 2;
+  // pixels before the first and past the last of the tensor come back as zeros (offsets wrap above the size)
+  const unsigned poff = (unsigned)((m0 - W - 1 + srow) * IC + sch) * ES;
+  f32x4 rp[PA];
+  unsigned long long missed = 0;   // operands that three parts do not hold
+  auto request_pixels = [&](int pc) {
+    const bool ok = pc * kBK + sch < IC;
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+      unsigned o = ok && i * RPP + srow < px ? poff + (unsigned)(i * RPP * IC + pc * kBK) * ES : kOOB;
+      asm("" : "+v"(o));   // a selected offset; left alone, the compiler makes two loads behind a branch and waits for each
+      rp[i] = buffer_load_16B(rin, o);
+    }
+  };
+  auto store_pixels = [&](int i, int buf) {
+    if ((i + 1) * RPP <= PX || i * RPP + srow < PX) {
+      char *row = pdst + buf + i * RPP * kPitch;
+      if constexpr (NP == 3) {
+        f32x4 v = rp[i];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          if (p == 2) split_check(v, missed);
+          *reinterpret_cast<u32x2 *>(row + p * kPlane) = split_part(v);
+        }
+      } else {
+        *reinterpret_cast<f32x4 *>(row) = rp[i];
+      }
+    }
+  };
+  request_pixels(0);
+  unsigned flagged = 0;            // filter rows of this tile that three parts do not hold
+  if constexpr (NP == 3)
+    for (int i = tid; i < a.cchunks * 9; i += kNT) flagged |= a.flags[tn * a.cchunks * 9 + i];
+
+  // ---- filter fragments: [octile of 32][chunk][tap][wave slice][part][64 lanes][16 bytes]
+  const int chunk_bytes = 9 * kWK * NP * 1024;
+  const char *wbase = static_cast<const char *>(a.frag) + (size_t)(tn * 2 + wn) * a.cchunks * chunk_bytes;
+  const __amdgpu_buffer_rsrc_t rwt = make_rsrc(wbase, (unsigned)(a.cchunks * chunk_bytes));
+  const int woff = wk * NP * 1024 + lane * 16;
+  f32x4 fb[kRing][NP];
+  auto fetch_b = [&](int slot, int base) {   // base: uniform
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      fb[slot][p] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rwt, woff + p * 1024, base, 0));
+  };
+#pragma unroll
+  for (int t = 0; t < kRing; ++t) fetch_b(t, t * kWK * NP * 1024);
+  // Three taps of bf16 products are over before a line arrives from beyond the L2, and all workgroups of an XCD walk the filter
+  // in step.  So those that share it ask for a part each, up front.
+  f32x4 ahead[NP == 1 ? kAhead : 1];
+  if constexpr (NP == 1) {
+    const int first = (tm % a.share) * a.ahead * kNT * 16 + tid * 16;
+    const __amdgpu_buffer_rsrc_t rall = make_rsrc(static_cast<const char *>(a.frag) + (size_t)tn * 2 * a.cchunks * chunk_bytes, (unsigned)(2 * a.cchunks * chunk_bytes));
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) ahead[i] = buffer_load_16B(rall, i < a.ahead ? (unsigned)(first + i * kNT * 16) : kOOB);
+  }
 
   // which taps of this lane's pixels lie inside their image, and where in LDS its operands start
   int valid[TM], abase[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-    const int ml = wm * WTM + i * 32 + lr, m = m0 + ml;
+    const int ml = i * 32 + lr, m = m0 + ml;
     const int n = fdiv(m, a.div_plane), rem = m - n * (a.IH * W);
     const int h = fdiv(rem, a.div_w), w = rem - h * W;
     int v = 0;
@@ -99,269 +160,157 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
     valid[i] = m < a.Mrows ? v : 0;
     abase[i] = (ml + W + 1) * kPitch + wk * 32 + lg * 16;
   }
-  const int zbase = PX * kPitch + wk * 32 + lg * 16;
+  const int zbase = NBUF * kBuf + wk * 32 + lg * 16;
+  if (tid < kPitch / 4) *reinterpret_cast<unsigned *>(Px + NBUF * kBuf + tid * 4) = 0;
 
-  const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, (unsigned)a.N * a.IH * W * IC * 4u);
-  const __amdgpu_buffer_rsrc_t rwt = make_rsrc(a.wt, (unsigned)a.OC * 9u * IC * 4u);
-
-  // ---- staging: 16 lanes (4 channels each) per row
-  const int srow = tid >> 4, sch = (tid & 15) * 4;
-  // filter stage of a set: where a thread stores its rows, where a lane fetches its fragments
-  char *bdst[2] = {Bs + srow * kPitch + sch * 2, Bs + kStageB + srow * kPitch + sch * 2};
-  const char *bsrc[2] = {Bs + lr * kPitch + wk * 32 + lg * 16, Bs + kStageB + lr * kPitch + wk * 32 + lg * 16};
-  char *const pdst = Px + srow * kPitch + sch * 2;
-  f32x4 rp[PA], rb[2][PB];
-  unsigned long long missed = 0;   // operands that three parts do not hold
-  unsigned boff[PB];
-#pragma unroll
-  for (int i = 0; i < PB; ++i) {
-    const int oc = n0 + i * 32 + srow;
-    boff[i] = oc < a.OC ? (unsigned)(oc * 9 * IC + sch) * 4u : kOOB;
-  }
-  // pixels before the first and past the last of the tensor come back as zeros (offsets wrap above the size)
-  const unsigned poff = (unsigned)((m0 - W - 1 + srow) * IC + sch) * 4u;
-  int pc = 0;                 // chunk of the pixels requested next
-  auto request_pixels = [&]() {
-    const bool ok = pc < cchunks && pc * kBK + sch < IC;
-#pragma unroll
-    for (int i = 0; i < PA; ++i) {
-      unsigned o = ok && i * 32 + srow < px ? poff + (unsigned)(i * 32 * IC + pc * kBK) * 4u : kOOB;
-      asm("" : "+v"(o));   // a selected offset; left alone, the compiler makes two loads behind a branch and waits for each
-      rp[i] = buffer_load_16B(rin, o);
-    }
-    ++pc;
-  };
-  auto store_pixels = [&](int i) {
-    if (i * 32 < px) store_split<true>(pdst + i * 32 * kPitch, rp[i], missed);   // uniform
-  };
-  int bt = 0, bc = 0;         // tap and chunk of the filter rows requested next
-  auto request_filter = [&](int set) {
-    const bool ok = bc < cchunks && bc * kBK + sch < IC;
-    const unsigned d = (unsigned)(bt * IC + bc * kBK) * 4u;
-#pragma unroll
-    for (int i = 0; i < PB; ++i) rb[set][i] = buffer_load_16B(rwt, ok ? boff[i] + d : kOOB);
-    const bool wrap = bt == 8;
-    bt = wrap ? 0 : bt + 1;
-    bc = wrap ? bc + 1 : bc;
-  };
-  // the rows of step t wait in register set t % 2 and go to LDS stage t % 2
-  // 128-pixel tiles check the filter rows a group of products later, where nobody waits for it (128 ch 16x16, batch 128: 60.3 ->
-  // 59.3 us; 64-pixel tiles, with half the products, 59.7 -> 61.5)
-  constexpr bool kLater = TM == 2;
-  f32x4 rest[PB];
-  auto store_filter = [&](int set, int i) { rest[i] = store_split<!kLater>(bdst[set] + i * 32 * kPitch, rb[set][i], missed); };
-
-  // ---- fragments: three parts of TM pixel tiles and kTN filter tiles.  A part is fetched for the next step as soon as
-  // its last product of this step is issued; only the leading parts (index 0), which the last product of a step and the
-  // first two of the next both use, have two register sets.
-  f32x4 fa0[2][TM], fb0[2][kTN], fa[3][TM], fb[3][kTN];
-  int ft = 0;                 // tap of the fragments fetched next
-  int aat[TM];                // where that tap's pixel is
-  auto aim = [&]() {
-    const int r = ft / 3, s = ft - r * 3;
-    const int d = ((r - 1) * W + s - 1) * (MODE == kBwd ? -kPitch : kPitch);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) aat[i] = (valid[i] >> ft) & 1 ? abase[i] + d : zbase;
-    ft = ft == 8 ? 0 : ft + 1;
-  };
-  auto fetch_a = [&](int set, int q) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(Px + aat[i] + q * kPlane);
-      if (q == 0) fa0[set][i] = v;
-      else fa[q][i] = v;
-    }
-  };
-  auto fetch_b = [&](int set, int q) {
-#pragma unroll
-    for (int j = 0; j < kTN; ++j) {
-      const f32x4 v = *reinterpret_cast<const f32x4 *>(bsrc[set] + j * 32 * kPitch + q * kPlane);
-      if (q == 0) fb0[set][j] = v;
-      else fb[q][j] = v;
-    }
-  };
-
-  f32x16 acc[TM][kTN];
+  f32x16 acc[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < kTN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  auto product = [&](int set, int pa, int pb, bool first = false) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < kTN; ++j)
-        Elem<__bf16>::mma(acc[i][j], pa == 0 ? fa0[set][i] : fa[pa][i], pb == 0 ? fb0[set][j] : fb[pb][j]);
-    if (first) {   // a product, half of the staging's arithmetic beside it, the other product
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, 14, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
+    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+
   auto lds_barrier = [&]() {
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
   };
 
-  request_pixels();
-  request_filter(0);
-  request_filter(1);
-  if (tid < 100) *reinterpret_cast<unsigned *>(Px + PX * kPitch + tid * 4) = 0;
 #pragma unroll
-  for (int i = 0; i < PA; ++i) store_pixels(i);
-#pragma unroll
-  for (int i = 0; i < PB; ++i) {
-    store_filter(0, i);
-    if (kLater) split_check(rest[i], missed);
-  }
-  request_filter(0);
-  store_filter(1, 0);
-  if (kLater) split_check(rest[0], missed);
-  request_pixels();
+  for (int i = 0; i < PA; ++i) store_pixels(i, 0);
   lds_barrier();
-  aim();
-#pragma unroll
-  for (int q = 0; q < 3; ++q) { fetch_a(0, q); fetch_b(0, q); }
-  __builtin_amdgcn_sched_barrier(0);
 
-  // Step (chunk, tap), six groups of products, small terms first.  Beside them, spread so that neither the LDS nor the
-  // vector unit sees a burst: the second half of the next step's filter rows goes to LDS and the rows three steps ahead
-  // are requested (all workgroups walk the filter in step, so each row comes from beyond the L2 once per XCD and every
-  // one of them waits for it); the barrier, after which the filter fragments of the next step are fetched; the first
-  // half of the rows of the step after it.  The last step of a chunk also replaces the pixels: all fragments of this
-  // chunk are in registers once its barrier is passed.  (The products stand outside the branches: inside, the
-  // accumulators are copied.)
-  static_assert(PB == 2, "filter rows per step");
-  int tap = 0;
-  auto step = [&](int set, int it) {
-    const bool turn = tap == 8 && it + 1 < steps;   // uniform
-    const int nx = set ^ 1;
-    constexpr int H = (PA + 2) / 3;
-    // turn, said by the tap that follows: the compiler joins branches on the same condition, and then copies the fragments that
-    // the other side of it has just requested, a wait in every step (2 % of the kernel's time)
-    auto replace = [&](int q) {
-      if (ft == 1 && it + 1 < steps) {
+  // ---- one chunk of 64 channels, nine taps.  The pixel fragments of a tap are fetched during the products of the tap before it,
+  // each part as soon as its last product is issued; only the leading parts, which the last product of a tap and the second of the
+  // next both use, have two register sets.  MORE: the next chunk's pixels are staged beside the products.
+  f32x4 fa0[2][TM], fa[NP][TM];
+  int at[TM];
+  auto aim = [&](int t, int here) {
+    const int d = ((t / 3 - 1) * W + t % 3 - 1) * (MODE == kBwd ? -kPitch : kPitch) + here;
 #pragma unroll
-        for (int i = q * H; i < (q + 1) * H && i < PA; ++i) store_pixels(i);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    aim();
-    store_filter(nx, 1);
-    product(set, 2, 0);
-    if (!turn) fetch_a(nx, 2);
-    request_filter(nx);
-    product(set, 0, 2);
-    lds_barrier();
-    fetch_b(nx, 2);
-    if (!turn) fetch_a(nx, 0);
-    if (kLater) split_check(rest[1], missed);
-    product(set, 1, 1);
-    replace(0);
-    fetch_b(nx, 0);
-    product(set, 1, 0);
-    replace(1);
-    if (!turn) fetch_a(nx, 1);
-    store_filter(set, 0);        // of step it + 2
-    // (64-pixel data gradients: left alone, their wait for the filter rows comes before both products, 4 % of the time)
-    product(set, 0, 1, MODE == kBwd && TM == 1);
-    replace(2);
-    fetch_b(nx, 1);
-    if (turn) {
-      request_pixels();
-      lds_barrier();
-#pragma unroll
-      for (int q = 2; q >= 0; --q) fetch_a(nx, q);
-    }
-    if (kLater) split_check(rest[0], missed);
-    product(set, 0, 0);
-    tap = tap == 8 ? 0 : tap + 1;
+    for (int i = 0; i < TM; ++i) at[i] = (valid[i] >> t) & 1 ? abase[i] + d : zbase;
   };
-  // An odd number of steps starts with one on its own, after which the sets change places: a loop that could end between
-  // its two steps makes the compiler wait for every load at its top.  (Behind the last step: rows nobody uses.)
-  int it = 0;
-  if (steps & 1) {
-    step(0, 0);
-    it = 1;
+  auto fetch_a = [&](int set, int q) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) fa0[0][i] = fa0[1][i];
-#pragma unroll
-    for (int j = 0; j < kTN; ++j) fb0[0][j] = fb0[1][j];
-#pragma unroll
-    for (int i = 0; i < PB; ++i) { const f32x4 t = rb[0][i]; rb[0][i] = rb[1][i]; rb[1][i] = t; }
-    char *const d = bdst[0]; bdst[0] = bdst[1]; bdst[1] = d;
-    const char *const f = bsrc[0]; bsrc[0] = bsrc[1]; bsrc[1] = f;
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  do {
-    step(0, it);
-    step(1, it + 1);
-    it += 2;
-  } while (it < steps);
-
-  conv_epilogue<float, BM, kBN, kNT, MODE>(a, Cs, row_off, tm, n0, [&]() {
-    // the four slices of a wave tile are added in slice order; wave slice k finishes the k-th quarter of it
-    f32x4 *const red = reinterpret_cast<f32x4 *>(lds);
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < NSUB; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const f32x16 &c = acc[u / kTN][u % kTN];
-        red[(((wm * kWGK + wk) * NSUB + u) * 4 + e) * 64 + lane] = f32x4{c[4 * e], c[4 * e + 1], c[4 * e + 2], c[4 * e + 3]};
-      }
-    __syncthreads();
-    f32x4 v[NSUB];
-    bool bad = missed != 0;
-#pragma unroll
-    for (int g = 0; g < NSUB; ++g) {
-      v[g] = red[((wm * kWGK) * NSUB * 4 + wk * NSUB + g) * 64 + lane];
-#pragma unroll
-      for (int k = 1; k < kWGK; ++k) v[g] += red[((wm * kWGK + k) * NSUB * 4 + wk * NSUB + g) * 64 + lane];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) bad |= !__builtin_isfinite(v[g][e]);
+    for (int i = 0; i < TM; ++i) {
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(Px + at[i] + q * kPlane);
+      if (q == 0) fa0[set][i] = v;
+      else fa[q][i] = v;
     }
-    // group g of this wave: rows 8*ge + 4*lg .. +3 of sub-tile u, column lr
-    const int g0 = wk * NSUB;
-    if (__syncthreads_or(bad)) {
-      // a result that is not finite, or an operand the parts do not hold, somewhere in the tile: again in fp32, from memory
-      // straight to the matrix instruction (lane l: row l%32, four of eight channels), 32 channels of a tap at a time and the
-      // next 32 in flight.  Where two waves share a sub-tile, they take every other 32.
-      constexpr int kShare = 4 / NSUB;
-      const int u = g0 / 4, i = u / kTN, j = u % kTN;
-      const int m = m0 + wm * WTM + i * 32 + lr, oc = n0 + j * 32 + lr;
-      int vm = valid[0];
-      if constexpr (TM == 2) vm = i ? valid[1] : valid[0];
-      f32x4 x[2][4], y[2][4];
-      int t = 0, c0 = 0;       // tap and first channel requested next
-      auto request_fp32 = [&](int set) {
-        const int d = ((t / 3 - 1) * W + t % 3 - 1) * (MODE == kBwd ? -1 : 1);
-        const bool x_ok = t < 9 && ((vm >> t) & 1), y_ok = t < 9 && oc < a.OC;
+  };
+  auto product = [&](int set, int slot, int pa, int pb) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int ch = c0 + k * 8 + lg * 4;   // IC is a multiple of four
-          unsigned xo = x_ok && ch < IC ? (unsigned)((m + d) * IC + ch) * 4u : kOOB;
-          unsigned yo = y_ok && ch < IC ? (unsigned)((oc * 9 + t) * IC + ch) * 4u : kOOB;
-          asm("" : "+v"(xo), "+v"(yo));
-          x[set][k] = buffer_load_16B(rin, xo);
-          y[set][k] = buffer_load_16B(rwt, yo);
-        }
+    for (int i = 0; i < TM; ++i) Elem<__bf16>::mma(acc[i], pa == 0 ? fa0[set][i] : fa[pa][i], fb[slot][pb]);
 #pragma unroll
-        for (int k = 0; k < kShare; ++k) {
-          c0 += 32;
-          if (c0 >= IC) { c0 = 0; ++t; }
+    for (int i = 0; i < TM; ++i) {   // what else is to be done here goes between the products
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto chunk = [&](auto more_tag, int c) {
+    constexpr bool MORE = decltype(more_tag)::value;
+    // (left alone, the compiler keeps the addresses of all nine taps in registers)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) asm("" : "+v"(valid[i]));
+    const int here = NBUF == 2 && (c & 1) ? kBuf : 0, there = NBUF == 2 ? kBuf - here : 0;
+    const int base = c * chunk_bytes, next = MORE ? base + chunk_bytes : base;
+    aim(0, here);
+    if constexpr (NP == 3) fetch_a(0, 2);
+    fetch_a(0, 0);
+    if constexpr (NP == 3) fetch_a(0, 1);
+    if (MORE) request_pixels(c + 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int slot = t % kRing, set = t & 1, nx = set ^ 1;
+      auto stage = [&](int third) {   // passes are spread over taps 2 to 8
+        if constexpr (MORE && NBUF == 2) {
+#pragma unroll
+          for (int i = 0; i < PA; ++i)
+            if (t >= 2 && i * 7 / PA == t - 2 && i % 3 == third) store_pixels(i, there);
         }
       };
-      f32x16 c;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) c[e] = 0.f;
-      if (kShare == 2 && (wk & 1)) {
-        c0 = 32;
-        if (c0 >= IC) { c0 = 0; ++t; }
+      if (t < 8) aim(t + 1, here);
+      if constexpr (NP == 3) {
+        stage(0);
+        product(set, slot, 2, 0);
+        if (t < 8) fetch_a(nx, 2);
+        product(set, slot, 0, 2);
+        if (t < 8) fetch_a(nx, 0);
+        stage(1);
+        product(set, slot, 1, 1);
+        product(set, slot, 1, 0);
+        if (t < 8) fetch_a(nx, 1);
+        stage(2);
+        product(set, slot, 0, 1);
+        product(set, slot, 0, 0);
+      } else {
+        if (t < 8) fetch_a(nx, 0);
+        stage(0); stage(1); stage(2);
+        product(set, slot, 0, 0);
       }
+      fetch_b(slot, t + kRing < 9 ? base + (t + kRing) * kWK * NP * 1024 : next + (t + kRing - 9) * kWK * NP * 1024);
+    }
+    if (MORE) {
+      lds_barrier();
+      if constexpr (NBUF == 1) {
+#pragma unroll
+        for (int i = 0; i < PA; ++i) store_pixels(i, 0);
+        lds_barrier();
+      }
+    }
+  };
+  for (int c = 0; c + 1 < cchunks; ++c) chunk(std::true_type{}, c);
+  chunk(std::false_type{}, cchunks - 1);
+
+  // A result that is not finite, or an operand the parts do not hold, somewhere in the tile: again on the fp32 instruction, from
+  // memory straight to it (lane l: row l%32, four of eight channels), 32 channels of a tap at a time and the next 32 in flight.
+  // Wave slice i computes the tile's pixels 32*i .. +31; of 64-pixel tiles two slices each, every other 32 channels.
+  auto fp32_tile = [&]() {
+    constexpr int kShare = TM <= 2 ? 2 : 1;
+    static_assert(TM == 2 || TM == 3 || TM == 4, "slices of a tile");
+    const int i = kShare == 2 ? wk & 1 : wk, share = kShare == 2 ? wk >> 1 : 0;
+    const int m = m0 + i * 32 + lr, oc = n0 + wn * 32 + lr;
+    const bool mine = i < TM;
+    const __amdgpu_buffer_rsrc_t rw32 = make_rsrc(a.wt, (unsigned)a.OC * 9u * IC * 4u);
+    int vm = 0;
+#pragma unroll
+    for (int k = 0; k < TM; ++k) vm = i == k ? valid[k] : vm;
+    f32x4 x[2][4], y[2][4];
+    int t = 0, c0 = 0;       // tap and first channel requested next
+    auto next_channels = [&]() {
+      c0 += 32;
+      if (c0 >= IC) { c0 = 0; ++t; }
+    };
+    auto request_fp32 = [&](int set) {
+      const int d = ((t / 3 - 1) * W + t % 3 - 1) * (MODE == kBwd ? -1 : 1);
+      const bool x_ok = t < 9 && ((vm >> t) & 1), y_ok = t < 9 && oc < a.OC;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int ch = c0 + k * 8 + lg * 4;   // IC is a multiple of four
+        unsigned xo = x_ok && ch < IC ? (unsigned)((m + d) * IC + ch) * 4u : kOOB;
+        asm("" : "+v"(xo));
+        x[set][k] = buffer_load_16B(rin, xo);
+        if (MODE == kBwd) {   // the filter as it is stored, [IC][9][OC]
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            unsigned yo = y_ok && ch < IC ? (unsigned)(((ch + e) * 9 + t) * a.OC + oc) * 4u : kOOB;
+            asm("" : "+v"(yo));
+            y[set][k][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rw32, (int)yo, 0, 0));
+          }
+        } else {
+          unsigned yo = y_ok && ch < IC ? (unsigned)((oc * 9 + t) * IC + ch) * 4u : kOOB;
+          asm("" : "+v"(yo));
+          y[set][k] = buffer_load_16B(rw32, yo);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kShare; ++k) next_channels();
+    };
+    f32x16 c;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) c[e] = 0.f;
+    if (mine) {
+      if (share) next_channels();
       const int batches = 9 * ((IC + 31) / 32);
       request_fp32(0);
       for (int it = 0; it < batches; it += 2 * kShare) {   // behind the last one: zeros
@@ -370,82 +319,160 @@ __global__ __launch_bounds__(kNT) void conv3_split_kernel(ArgsOf<MODE> a) {
           request_fp32(set ^ 1);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int k = 0; k < 4; ++k) Elem<float>::mma(c, x[set][k], y[set][k]);
+          for (int k = 0; k < 4; ++k) Elem<float>::mma(c, x[set][k], y[set][k] * a.wscale);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      if constexpr (NSUB == 4) {
+    }
+    f32x4 *const other = reinterpret_cast<f32x4 *>(lds);   // the second share's sums, below the output tile
+    if constexpr (kShare == 2) {
+      static_assert((size_t)4 * 4 * 64 * 16 <= kRound2, "exchanged sums fit");
+      if (share) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) v[g] = f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
-      } else {   // to each of the two its rows of the other's sums, through LDS behind the output tile
-        static_assert(kTile + 8 * 2 * 64 * 16 <= kBytes, "exchanged sums fit");
-        f32x4 *const half = reinterpret_cast<f32x4 *>(lds + kTile);
-        const bool odd = wk & 1;
+        for (int g = 0; g < 4; ++g) other[((wn * 2 + i) * 4 + g) * 64 + lane] = f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+      }
+      __syncthreads();
+    }
+    if (mine && !share) {
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          f32x4 other;
+      for (int g = 0; g < 4; ++g) {
+        f32x4 s = f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+        if constexpr (kShare == 2) s += other[((wn * 2 + i) * 4 + g) * 64 + lane];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float first = c[4 * g + e], second = c[8 + 4 * g + e];
-            v[g][e] = odd ? second : first;
-            other[e] = odd ? first : second;
-          }
-          half[(wave * 2 + g) * 64 + lane] = other;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int g = 0; g < 2; ++g) v[g] += half[((wave ^ 1) * 2 + g) * 64 + lane];
+        for (int e = 0; e < 4; ++e) Cs[i * 32 + g * 8 + lg * 4 + e][wn * 32 + lr] = s[e];
       }
     }
+  };
+
+  conv_epilogue<T, BM, kBN, kNT, MODE>(a, Cs, row_off, tm, n0, [&]() {
+    // The four slices of a wave tile meet in two exchanges: with the neighbour slice, after which each holds half of the tile's
+    // groups of four rows, then with the one two away.  Sums are (0 + 1) + (2 + 3).
+    f32x4 *const red = reinterpret_cast<f32x4 *>(lds);
+    const bool odd = wk & 1, high = wk & 2;
+    auto group = [&](int g) {
+      const f32x16 &c = acc[g >> 2];
+      const int e = (g & 3) * 4;
+      return f32x4{c[e], c[e + 1], c[e + 2], c[e + 3]};
+    };
+    auto either = [](bool second, const f32x4 &x, const f32x4 &y) {
+      f32x4 r;
 #pragma unroll
-    for (int g = 0; g < NSUB; ++g) {
-      const int u = (g0 + g) / 4, ge = (g0 + g) % 4;
-      const int row = wm * WTM + (u / kTN) * 32 + ge * 8 + lg * 4, col = (u % kTN) * 32 + lr;
+      for (int e = 0; e < 4; ++e) r[e] = second ? y[e] : x[e];
+      return r;
+    };
+    if constexpr (NP == 1) {
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) asm volatile("" : : "v"(ahead[i]));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < 2 * TM; ++g) red[(wave * 2 * TM + g) * 64 + lane] = either(odd, group(g + 2 * TM), group(g));
+    __syncthreads();
+    f32x4 half[2 * TM], v[TM];
+#pragma unroll
+    for (int g = 0; g < 2 * TM; ++g) half[g] = either(odd, group(g), group(g + 2 * TM)) + red[((wave ^ 1) * 2 * TM + g) * 64 + lane];
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < TM; ++g) red[(wave * TM + g) * 64 + lane] = either(high, half[g + TM], half[g]);
+    __syncthreads();
+    bool bad = missed != 0 || flagged != 0;
+#pragma unroll
+    for (int g = 0; g < TM; ++g) {
+      v[g] = either(high, half[g], half[g + TM]) + red[((wave ^ 2) * TM + g) * 64 + lane];
+      if constexpr (NP == 3) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad |= !__builtin_isfinite(v[g][e]);
+      }
+    }
+    const int col = wn * 32 + lr;
+    if constexpr (NP == 3) {
+      if (__syncthreads_or(bad)) {
+        fp32_tile();
+        return;
+      }
+    }
+    const int g0 = (odd ? 2 * TM : 0) + (high ? TM : 0);
+#pragma unroll
+    for (int g = 0; g < TM; ++g) {
+      const int row = ((g0 + g) >> 2) * 32 + ((g0 + g) & 3) * 8 + lg * 4;
 #pragma unroll
       for (int e = 0; e < 4; ++e) Cs[row + e][col] = v[g][e];
     }
   });
 }
 
-template <int BM, int MODE>
-int launch(EvalArgs a, hipStream_t st, StatParts *tiles_m_out) {
+template <int NP, int BM, int NBUF, int MAXW, int MODE>
+int launch(Conv3Args<kEval> a, hipStream_t st, StatParts *tiles_m_out) {
   a.tiles_m = (a.Mrows + BM - 1) / BM;
   a.tiles_n = (a.OC + kBN - 1) / kBN;
   if (tiles_m_out) { tiles_m_out->parts = a.tiles_m; tiles_m_out->rows = BM; }
   a.div_plane = make_fastdiv((unsigned)(a.IH * a.IW)); a.div_w = make_fastdiv((unsigned)a.IW);
-  a.div_tn = make_fastdiv((unsigned)a.tiles_n);
+  a.div_tn = make_fastdiv((unsigned)a.tiles_n); a.div_tm = make_fastdiv((unsigned)a.tiles_m);
   const long long grid = (long long)a.tiles_m * a.tiles_n;
   if (grid <= 0 || grid > 0x7fffffffLL) return set_error(RESIST_ESHAPE, "conv3 grid %lld", grid);
+  Conv3Args<MODE> k;
+  static_cast<ArgsOf<MODE> &>(k) = a;
+  k.frag = a.frag; k.flags = a.flags; k.wscale = a.wscale; k.cchunks = a.cchunks;
+  k.m_fast = (long long)a.OC * 9 * a.IC * NP * 2 > (long long)a.Mrows * a.IC * (NP == 3 ? 4 : 2);
+  const long long per_xcd = (grid + 7) / 8, sharing = k.m_fast ? std::min<long long>(per_xcd, a.tiles_m) : per_xcd / a.tiles_n;
+  k.share = (int)std::max<long long>(1, sharing);
+  k.ahead = (int)std::min<long long>(kAhead, (9LL * 8 * 1024 * NP * a.cchunks + (long long)k.share * kNT * 16 - 1) / ((long long)k.share * kNT * 16));
   {
-    static const std::string label = std::string("conv3_f32_") + (MODE == kFwd ? "fwd_" : MODE == kEval ? "eval_" : "bwd_") + std::to_string(BM) + "x64";
+    static const std::string label = std::string("conv3_") + (NP == 3 ? "f32_" : "bf16_") + (MODE == kFwd ? "fwd_" : MODE == kEval ? "eval_" : "bwd_") + std::to_string(BM) + "x64";
     const double flops = 2.0 * a.Mrows * a.OC * a.IC * 9;
-    const double bytes = 4.0 * ((double)a.Mrows * a.IC + (double)a.Mrows * a.OC * (1 + (a.addend ? 1 : 0) + (a.relu_mask ? 1 : 0) + (MODE == kBwd && a.bn_sums ? 1 : 0) +
+    const double bytes = (NP == 3 ? 4.0 : 2.0) * ((double)a.Mrows * a.IC + (double)a.Mrows * a.OC * (1 + (a.addend ? 1 : 0) + (a.relu_mask ? 1 : 0) + (MODE == kBwd && a.bn_sums ? 1 : 0) +
                                 (MODE == kEval ? (a.out ? 1 : 0) + (a.act_res ? 1 : 0) : 0)) + (double)a.OC * 9 * a.IC);
     prof::Scope ps(label.c_str(), flops, bytes, st);
-    hipLaunchKernelGGL((conv3_split_kernel<BM, MODE>), dim3((unsigned)grid), dim3(kNT), 0, st, static_cast<const ArgsOf<MODE> &>(a));
+    hipLaunchKernelGGL((conv3_kernel<NP, BM, NBUF, MAXW, MODE>), dim3((unsigned)grid), dim3(kNT), 0, st, k);
   }
   RESIST_CHECK_LAUNCH("conv3");
   return RESIST_OK;
 }
 
-// 64-pixel tiles where 128-pixel ones would not give every CU a workgroup (512 ch 4x4, batch 128: 128 tiles)
+// fp32: one workgroup to a compute unit (LDS).  128-pixel tiles, or 64-pixel ones where those would not give every unit a
+// tile.  In training steps, on whole chunks of channels and at least two of them, whichever of 128, 96 and 64 pixels leaves the units
+// idle least, what a tile costs beside its products (8 of 46 us) being what 24 pixels cost: 256 ch 8x8, batch 77: 64 pixels 42, 96
+// 33 us; 128 ch 16x16: 128 pixels 49, 96 37; batch 128: 96 pixels 65 and 61, 128 47 and 53.
+// (Images wider than 32: the pixels of 128 are staged once at a time.)  bf16: 64-pixel tiles, two workgroups to a unit; 128-pixel
+// ones with one, 256 ch 8x8, batch 128: 16.5 us.
 template <int MODE>
-int pick(const EvalArgs &a, hipStream_t st, StatParts *p) {
-  const long long t128 = (long long)((a.Mrows + 127) / 128) * ((a.OC + kBN - 1) / kBN);
-  return t128 >= 256 ? launch<128, MODE>(a, st, p) : launch<64, MODE>(a, st, p);
+int pick(const Conv3Args<kEval> &a, int dt, hipStream_t st, StatParts *p) {
+  if (dt == DT_BF16) return launch<1, 64, 2, 56, MODE>(a, st, p);
+  auto tiles = [&](int bm) { return (long long)((a.Mrows + bm - 1) / bm) * ((a.OC + kBN - 1) / kBN); };
+  int bm = tiles(128) >= 256 ? 128 : 64;
+  if (a.IW > 32) return bm == 128 ? launch<3, 128, 1, 56, MODE>(a, st, p) : launch<3, 64, 2, 56, MODE>(a, st, p);
+  if constexpr (MODE != kEval) {
+    if (a.IC >= 2 * kBK && a.IC % kBK == 0) {
+      auto cost = [&](int bm) { return (tiles(bm) + 255) / 256 * (bm + 24); };
+      bm = cost(128) <= cost(96) && cost(128) <= cost(64) ? 128 : cost(96) <= cost(64) ? 96 : 64;
+      if (bm == 96) return launch<3, 96, 2, 32, MODE>(a, st, p);
+    }
+  }
+  return bm == 128 ? launch<3, 128, 2, 32, MODE>(a, st, p) : launch<3, 64, 2, 32, MODE>(a, st, p);
 }
 
 }  // namespace
 
-// From 48 input channels: a chunk is 64 of them, however many there are.  us, fp32 instruction and here, 32x32, batch 128: 32 ->
-// 32 channels 49 and 62, 48 -> 48 87 and 65.  (40 and 44 channels, which no network of this library can have, 87 and 62.)  And
-// images no wider than the staged range allows.
-bool conv3_takes(const IgemmArgs &a) {
-  return a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.IW <= kMaxW && a.IC >= 48;
+// fp32 from 48 input channels: a chunk is 64 of them, however many there are (32 -> 32 channels, 32x32, batch 128: 49 us on the fp32
+// instruction).  bf16 from 256: 128 ch 16x16 18 us here and 17 in igemm_kernel's tiles, 64 ch 32x32 24.5 and 22.  Images no wider
+// than the staged range allows, and filters whose 64 rows an offset reaches.
+bool conv3_takes(const IgemmArgs &a, int dt) {
+  return a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.IW <= kWidest && a.IC >= (dt == DT_BF16 ? 256 : 48) && a.IC <= 8192;
 }
 
-int conv3_launch(const EvalArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out) {
-  return mode == kFwd ? pick<kFwd>(a, st, tiles_m_out) : mode == kBwd ? pick<kBwd>(a, st, tiles_m_out) : pick<kEval>(a, st, tiles_m_out);
+int64_t conv3_filter_bytes(int OC, int IC, int dt) {
+  const int64_t tiles = (int64_t)((OC + kBN - 1) / kBN) * ((IC + kBK - 1) / kBK) * 9;
+  return tiles * 2 * kWK * 1024 * (dt == DT_BF16 ? 1 : 3) + (dt == DT_BF16 ? 0 : tiles * 4);
+}
+
+int conv3_launch(const EvalArgs &e, const Filter &w, int dt, int mode, hipStream_t st, StatParts *p) {
+  Conv3Args<kEval> a;
+  static_cast<EvalArgs &>(a) = e;
+  a.cchunks = (e.IC + kBK - 1) / kBK;
+  a.frag = w.prep;
+  a.flags = reinterpret_cast<const unsigned *>(static_cast<const char *>(w.prep) + (int64_t)((e.OC + kBN - 1) / kBN) * a.cchunks * 9 * 2 * kWK * 3 * 1024);
+  a.wscale = w.scale;
+  return mode == kFwd ? pick<kFwd>(a, dt, st, p) : mode == kBwd ? pick<kBwd>(a, dt, st, p) : pick<kEval>(a, dt, st, p);
 }
 
 }  // namespace resist

@@ -67,6 +67,13 @@ struct EvalArgs : IgemmArgs {
   const float *res_scale, *res_shift;
 };
 template <int MODE> using ArgsOf = std::conditional_t<MODE == kEval, EvalArgs, IgemmArgs>;
+// of a convolution on a prepared filter
+template <int MODE> struct Conv3Args : ArgsOf<MODE> {
+  const void *frag;
+  const unsigned *flags;   // behind the fragments: which hold operands that three parts do not
+  float wscale;
+  int cchunks, m_fast, share, ahead;
+};
 
 namespace {
 
@@ -335,9 +342,10 @@ __device__ inline void conv_epilogue(const ArgsOf<MODE> &a, float (*Cs)[BN + 8],
 
 }  // namespace
 
-// 3x3 stride-1 convolutions in fp32 through operands split into three bf16 parts (conv3.hip)
-bool conv3_takes(const IgemmArgs &a);
-int conv3_launch(const EvalArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);
+// 3x3 stride-1 convolutions on filters in matrix fragments, in fp32 through operands split into three bf16 parts (conv3.hip)
+bool conv3_takes(const IgemmArgs &a, int dt);
+int64_t conv3_filter_bytes(int OC, int IC, int dt);
+int conv3_launch(const EvalArgs &a, const Filter &w, int dt, int mode, hipStream_t st, StatParts *tiles_m_out);
 // convolutions with few output tiles: 32x32 tiles, the reduction split among the waves of a workgroup (conv_small.hip)
 bool conv_small_takes(const IgemmArgs &a, int dt);
 bool conv_small_rows(long long pixels, int OC, int cls);   // whether it may take an output of this size, in 32-row tiles

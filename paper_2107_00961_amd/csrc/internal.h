@@ -135,9 +135,16 @@ int64_t conv_stats_floats(const ConvGeom &g);
 // act->out = max(scale*v + shift [+ BN(res)], 0), the arithmetic of bn_apply, with the shortcut's own affine map
 // rscale, rshift (NULL: res is added as it is).  No statistics are taken then.
 struct EvalAct { void *out; const float *scale, *shift; const void *res = nullptr; const float *rscale = nullptr, *rshift = nullptr; };
-int conv_fwd(const ConvGeom &g, int dt, const void *x, const void *w, void *y, const void *addend, float *stats,
+// A filter as a convolution reads it.  w: [K][R][S][C] in dt (fp32: the master).  prep (optional): what prepare_filters made of it,
+// in matrix fragments if `fragments` says so (as planned: filter_in_fragments), else rows: [K][R][S][C] for the forward pass,
+// [C][R][S][K] for the data gradient.  w may be NULL where prep is there, but for fp32 fragments, which hold only what
+// three bf16 numbers do; scale: what the prepared values are times w.
+struct Filter { const void *w; const void *prep; bool fragments; float scale = 1.f; };
+bool filter_in_fragments(const ConvGeom &g, int dt, bool dgrad);
+int64_t filter_bytes(const ConvGeom &g, int dt, bool fragments, bool dgrad);   // of a prepared filter
+int conv_fwd(const ConvGeom &g, int dt, const void *x, const Filter &w, void *y, const void *addend, float *stats,
              StatParts *stat_parts, hipStream_t st, const EvalAct *act = nullptr);
-// dx = dgrad(dy, wT) [+ addend]; wT is the [C][R][S][K] transpose made by prepare_filter.  relu_mask
+// dx = dgrad(dy, w) [+ addend]; w.prep is needed.  relu_mask
 // (optional, indexed like dx): the output of the ReLU that produced the convolution's input; dx is set
 // to zero where it is not positive, i.e. the gradient leaves this kernel already taken through that ReLU
 // bn (optional, stride 1 only): the convolution's input was the output of a BN (+ReLU); the kernel also
@@ -145,14 +152,12 @@ int conv_fwd(const ConvGeom &g, int dt, const void *x, const void *w, void *y, c
 // against the BN's input y, in bn->sums [2][parts][C] (gm = dx, or dx where the BN's own ReLU passed),
 // and says in bn->parts how many row tiles of how many rows it used.  bn_backward takes them as pre_sums.
 struct BnBwdFuse;
-int conv_dgrad(const ConvGeom &g, int dt, const void *dy, const void *wT, void *dx, const void *addend,
+int conv_dgrad(const ConvGeom &g, int dt, const void *dy, const Filter &w, void *dx, const void *addend,
                const void *relu_mask, hipStream_t st, const BnBwdFuse *bn = nullptr);
 int64_t conv_dgrad_bn_sums_floats(const ConvGeom &g);
-// from a filter stored in src_dt: optional copy in dt (w_lp) and optional transpose in dt (wT)
-int prepare_filter(const ConvGeom &g, int src_dt, int dt, const void *w, void *w_lp, void *wT, hipStream_t st);
-// the same for many filters at once (fp32 masters -> copies and transposes in dt, times `scale`)
-struct FilterPrep { ConvGeom g; const float *w; void *w_lp; void *wT; float scale = 1.f; };
-int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st);
+// filters [K][R][S][C] in src_dt, times `scale`, prepared in dt for the forward pass (w_lp) and for the data gradient (wT), each optional
+struct FilterPrep { ConvGeom g; const void *w; void *w_lp; bool lp_fragments; void *wT; bool wT_fragments; float scale = 1.f; };
+int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st, int src_dt = DT_F32);
 // dw (fp32) = wgrad(dy, x); partial: split-reduction scratch of wgrad_scratch_floats(g, dt, beside) floats; beside: other
 // kernels run at the same time
 int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool beside = false);

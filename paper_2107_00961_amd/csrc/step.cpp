@@ -54,13 +54,17 @@ struct WgradSide {
       if (r.first == buf && r.second) { RESIST_TRY(side.main_wait(r.second)); r.second = nullptr; }
     return RESIST_OK;
   }
-  // Filter copies and transposes.  In fp32 mode the forward pass multiplies the master filters, so the
-  // transposes are first needed by the backward pass: made on the side stream while the forward runs.
+  // Filters as the convolutions read them.  What the forward pass multiplies is made first, on the caller's stream; in fp32 mode
+  // what only the data gradients read, on the side stream while the forward runs.
   hipEvent_t prepared = nullptr;
   int prepare(const std::vector<FilterPrep> &prep) {
     if (dt != DT_F32 || !side.on()) return prepare_filters(prep, dt, side.main());
+    std::vector<FilterPrep> fwd = prep, bwd = prep;
+    for (FilterPrep &f : fwd) f.wT = nullptr;
+    for (FilterPrep &f : bwd) f.w_lp = nullptr;
+    RESIST_TRY(prepare_filters(fwd, dt, side.main()));
     RESIST_TRY(side.fork());
-    RESIST_TRY(prepare_filters(prep, dt, side.stream()));
+    RESIST_TRY(prepare_filters(bwd, dt, side.stream()));
     return side.mark(&prepared);
   }
   int filters_ready() {   // before the first data gradient
@@ -100,6 +104,25 @@ struct Arena {
   void *take_act(int64_t count, int es) { return take<char>(count * es); }
 };
 
+// What is made of a filter before it is multiplied: for the forward pass (wlp) its matrix fragments or, in bf16, its rows (in
+// fp32 the rows are the master's own), and for the data gradient (wT) fragments or the [C][R][S][K] transpose.
+struct Prepared {
+  void *wlp = nullptr, *wT = nullptr;
+  bool lp_frag = false, wT_frag = false;
+  // scaled: the values are not the master's, so that a copy is needed in any case
+  void take_forward(Arena &A, const ConvGeom &g, int dt, bool scaled = false) {
+    lp_frag = filter_in_fragments(g, dt, false);
+    if (lp_frag || dt == DT_BF16 || scaled) wlp = A.take_act(filter_bytes(g, dt, lp_frag, false), 1);
+  }
+  void take_dgrad(Arena &A, const ConvGeom &g, int dt) {
+    wT_frag = filter_in_fragments(g, dt, true);
+    wT = A.take_act(filter_bytes(g, dt, wT_frag, true), 1);
+  }
+  FilterPrep prep(const ConvGeom &g, const float *w, float scale = 1.f) const { return FilterPrep{g, w, wlp, lp_frag, wT, wT_frag, scale}; }
+  Filter forward(const float *w, float scale = 1.f) const { return Filter{w, wlp, lp_frag, scale}; }
+  Filter dgrad(const float *w) const { return Filter{w, wT, wT_frag}; }
+};
+
 struct ConvLayer {
   ConvGeom g;
   int64_t w_off, gamma_off, beta_off, rmean_off, rvar_off;  // offsets inside the block buffer
@@ -107,8 +130,7 @@ struct ConvLayer {
   void *y = nullptr;         // pre-BN output
   void *a = nullptr;         // post-BN(+ReLU) output; NULL for the layer that ends a block
   float *mean = nullptr, *invstd = nullptr, *scale = nullptr, *shift = nullptr;   // [K] each
-  void *wlp = nullptr;       // the filter in the compute type (bf16 mode; fp32 mode multiplies the master)
-  void *wT = nullptr;        // [C][R][S][K] transpose in the compute type, for the data gradient
+  Prepared f;
   int64_t M() const { return (int64_t)g.N * g.P * g.Q; }
 };
 
@@ -208,9 +230,8 @@ int build_plan(const resist_model_desc *desc, const int32_t *blocks, int32_t nbl
 
   int64_t max_act = 0, max_splitk = 0, max_stats = 0, max_stats_ds = 0;
   auto take_filters = [&](ConvLayer &c) {
-    const int64_t n = (int64_t)c.g.K * c.g.R * c.g.S * c.g.C;
-    c.wT = A.take_act(n, es);
-    if (net.d.compute_dtype == DT_BF16) c.wlp = A.take_act(n, es);
+    c.f.take_dgrad(A, c.g, net.d.compute_dtype);
+    c.f.take_forward(A, c.g, net.d.compute_dtype);
   };
   auto take_bn = [&](ConvLayer &c) {
     float *p = A.take<float>((int64_t)4 * c.g.K);
@@ -418,14 +439,14 @@ int build_forward_plan(const resist_model_desc *desc, const int32_t *blocks, int
       ConvLayer &c = bp.convs[j];
       c.in = x;
       take_affine(c);
-      if (net.d.compute_dtype == DT_BF16) c.wlp = A.take_act((int64_t)c.g.K * c.g.R * c.g.S * c.g.C, es);
+      c.f.take_forward(A, c.g, net.d.compute_dtype);
       if (j + 1 < bp.convs.size()) { c.a = abuf[j & 1]; x = c.a; }
     }
     if (bp.has_ds) {
       bp.ds.in = bp.in;
       bp.ds.y = ydsbuf;
       take_affine(bp.ds);
-      if (net.d.compute_dtype == DT_BF16) bp.ds.wlp = A.take_act((int64_t)bp.ds.g.K * bp.ds.g.C, es);
+      bp.ds.f.take_forward(A, bp.ds.g, net.d.compute_dtype);
     }
     bp.out = obuf[oi];
     cur = bp.out;
@@ -458,7 +479,7 @@ struct PreUnit {
   void *a = nullptr;         // ReLU(BN(u)): the convolution's input, kept for the backward pass
   void *h = nullptr;         // convolution output (the block output for the last unit)
   float *mean = nullptr, *invstd = nullptr, *scale = nullptr, *shift = nullptr;   // [g.C] each
-  void *wlp = nullptr, *wT = nullptr;
+  Prepared f;
   int64_t rows() const { return (int64_t)g.N * g.H * g.W; }   // rows of the BN input
 };
 
@@ -469,7 +490,7 @@ struct PreBlock {
   bool has_ds = false;
   ConvGeom dsg;
   int64_t ds_w_off = 0;
-  void *ds_wlp = nullptr, *ds_wT = nullptr;
+  Prepared ds_f;
   void *out = nullptr;
 };
 
@@ -501,7 +522,6 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
   RESIST_TRY(check_block_list(net, blocks, nblocks, batch));
   const int B = (int)net.blocks.size();
   const int N = batch, es = esize(net.d.compute_dtype);
-  const bool lp = net.d.compute_dtype == DT_BF16;
   Arena A(ws);
   P->layouts.resize(nblocks + 2);
   RESIST_TRY(block_layout(net, -1, &P->layouts[0]));
@@ -563,9 +583,8 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
       un.h = A.take_act((int64_t)N * un.g.P * un.g.Q * un.g.K, es);
       float *p = A.take<float>((int64_t)4 * un.g.C);
       un.mean = p; un.invstd = p + un.g.C; un.scale = p + 2 * un.g.C; un.shift = p + 3 * un.g.C;
-      const int64_t nf = (int64_t)un.g.K * un.g.R * un.g.S * un.g.C;
-      un.wT = A.take_act(nf, es);
-      if (lp) un.wlp = A.take_act(nf, es);
+      un.f.take_dgrad(A, un.g, net.d.compute_dtype);
+      un.f.take_forward(A, un.g, net.d.compute_dtype);
       track(un.g, true);
       u = un.h;
       pb.units.push_back(un);
@@ -574,9 +593,8 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
     if (bs.has_ds) {
       pb.dsg = make_geom(N, bs.h_in, bs.w_in, bs.c_in, bs.c_out, 1, bs.stride, 0);
       pb.ds_w_off = L.off(T_CONVW, 3);
-      const int64_t nf = (int64_t)bs.c_out * bs.c_in;
-      pb.ds_wT = A.take_act(nf, es);
-      if (lp) pb.ds_wlp = A.take_act(nf, es);
+      pb.ds_f.take_dgrad(A, pb.dsg, net.d.compute_dtype);
+      pb.ds_f.take_forward(A, pb.dsg, net.d.compute_dtype);
       track(pb.dsg, false);
     }
     pb.out = pb.units.back().h;
@@ -648,13 +666,11 @@ int local_step_preact(const resist_model_desc *desc, const int32_t *blocks, int3
     std::vector<FilterPrep> prep;
     for (PreBlock &pb : P.blocks) {
       float *pp = params(pb.slot);
-      for (PreUnit &un : pb.units) prep.push_back(FilterPrep{un.g, pp + un.w_off, un.wlp, un.wT});
-      if (pb.has_ds) prep.push_back(FilterPrep{pb.dsg, pp + pb.ds_w_off, pb.ds_wlp, pb.ds_wT});
+      for (PreUnit &un : pb.units) prep.push_back(un.f.prep(un.g, pp + un.w_off));
+      if (pb.has_ds) prep.push_back(pb.ds_f.prep(pb.dsg, pp + pb.ds_w_off));
     }
     RESIST_TRY(wg.prepare(prep));
   }
-  auto fwd_filter = [&](const float *w, const void *wlp) -> const void * { return dt == DT_F32 ? (const void *)w : wlp; };
-
   // ================= forward =================
   const int K0 = net.d.width[0];
   const int taps = net.stem_rs * net.stem_rs * net.d.in_c;
@@ -670,9 +686,9 @@ int local_step_preact(const resist_model_desc *desc, const int32_t *blocks, int3
       RESIST_TRY(bn_finalize(P.stats, parts, un.rows(), un.g.C, b, eps, bnm, P.bn_scratch, st));
       RESIST_TRY(bn_apply(dt, un.u, un.rows(), un.g.C, b, nullptr, nullptr, true, un.a, st));
       if (j == 0 && pb.has_ds)
-        RESIST_TRY(conv_fwd(pb.dsg, dt, un.a, fwd_filter(pp + pb.ds_w_off, pb.ds_wlp), P.sc, nullptr, nullptr, nullptr, st));
+        RESIST_TRY(conv_fwd(pb.dsg, dt, un.a, pb.ds_f.forward(pp + pb.ds_w_off), P.sc, nullptr, nullptr, nullptr, st));
       const void *addend = j + 1 == n ? (pb.has_ds ? (const void *)P.sc : pb.x) : nullptr;
-      RESIST_TRY(conv_fwd(un.g, dt, un.a, fwd_filter(pp + un.w_off, un.wlp), un.h, addend, P.stats, &parts, st));
+      RESIST_TRY(conv_fwd(un.g, dt, un.a, un.f.forward(pp + un.w_off), un.h, addend, P.stats, &parts, st));
     }
   }
   const int J = net.d.num_classes, CH = net.head_c;
@@ -714,10 +730,10 @@ int local_step_preact(const resist_model_desc *desc, const int32_t *blocks, int3
       if (j == 0 && pb.has_ds) {
         // the shortcut convolution reads the same a_1: its data gradient joins the branch's
         RESIST_TRY(wg.launch(pb.dsg, G, un.a, gg + pb.ds_w_off));
-        RESIST_TRY(conv_dgrad(pb.dsg, dt, G, pb.ds_wT, P.dsgrad, nullptr, nullptr, st));
+        RESIST_TRY(conv_dgrad(pb.dsg, dt, G, pb.ds_f.dgrad(pp + pb.ds_w_off), P.dsgrad, nullptr, nullptr, st));
         addend = P.dsgrad;
       }
-      RESIST_TRY(conv_dgrad(un.g, dt, gcur, un.wT, P.da, addend, nullptr, st));
+      RESIST_TRY(conv_dgrad(un.g, dt, gcur, un.f.dgrad(pp + un.w_off), P.da, addend, nullptr, st));
       BnBufs b = pre_bn_bufs(un, pp, gg);
       if (j > 0) {
         RESIST_TRY(wg.before_write(dy));
@@ -827,13 +843,11 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
     std::vector<FilterPrep> prep;
     for (BlockPlan &bp : P.blocks) {
       float *pp = params(bp.slot);
-      for (ConvLayer &c : bp.convs) prep.push_back(FilterPrep{c.g, pp + c.w_off, c.wlp, c.wT});
-      if (bp.has_ds) prep.push_back(FilterPrep{bp.ds.g, pp + bp.ds.w_off, bp.ds.wlp, bp.ds.wT});
+      for (ConvLayer &c : bp.convs) prep.push_back(c.f.prep(c.g, pp + c.w_off));
+      if (bp.has_ds) prep.push_back(bp.ds.f.prep(bp.ds.g, pp + bp.ds.w_off));
     }
     RESIST_TRY(wg.prepare(prep));
   }
-  auto fwd_filter = [&](const ConvLayer &c, const float *w) -> const void * { return dt == DT_F32 ? (const void *)w : c.wlp; };
-
   // ================= forward =================
   {
     ConvLayer &s = P.stem;
@@ -859,7 +873,7 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
       ConvLayer &d = bp.ds;
       RESIST_TRY(wg.off_chain([&](hipStream_t s) {
         StatParts parts;
-        RESIST_TRY(conv_fwd(d.g, dt, d.in, fwd_filter(d, pp + d.w_off), d.y, nullptr, P.stats_ds, &parts, s));
+        RESIST_TRY(conv_fwd(d.g, dt, d.in, d.f.forward(pp + d.w_off), d.y, nullptr, P.stats_ds, &parts, s));
         return bn_finalize(P.stats_ds, parts, d.M(), d.g.K, bn_bufs(d, pp, gg), eps, bnm, P.bn_scratch_ds, s);
       }));
       RESIST_TRY(wg.side.mark(&ds_done));
@@ -867,7 +881,7 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
     for (size_t j = 0; j < bp.convs.size(); ++j) {
       ConvLayer &c = bp.convs[j];
       StatParts parts;
-      RESIST_TRY(conv_fwd(c.g, dt, c.in, fwd_filter(c, pp + c.w_off), c.y, nullptr, P.stats, &parts, st));
+      RESIST_TRY(conv_fwd(c.g, dt, c.in, c.f.forward(pp + c.w_off), c.y, nullptr, P.stats, &parts, st));
       BnBufs b = bn_bufs(c, pp, gg);
       RESIST_TRY(bn_finalize(P.stats, parts, c.M(), c.g.K, b, eps, bnm, P.bn_scratch, st));
       if (c.a) RESIST_TRY(bn_apply(dt, c.y, c.M(), c.g.K, b, nullptr, nullptr, true, c.a, st));
@@ -881,7 +895,7 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
         RESIST_TRY(wg.side.main_wait(ds_done));
       } else {
         StatParts parts;
-        RESIST_TRY(conv_fwd(d.g, dt, d.in, fwd_filter(d, pp + d.w_off), d.y, nullptr, P.stats, &parts, st));
+        RESIST_TRY(conv_fwd(d.g, dt, d.in, d.f.forward(pp + d.w_off), d.y, nullptr, P.stats, &parts, st));
         RESIST_TRY(bn_finalize(P.stats, parts, d.M(), d.g.K, bd, eps, bnm, P.bn_scratch, st));
       }
       RESIST_TRY(bn_apply(dt, last.y, last.M(), last.g.K, bl, d.y, &bd, true, bp.out, st));
@@ -936,7 +950,7 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
       RESIST_TRY(wg.before_write(P.gm));
       RESIST_TRY(bn_backward(dt, G, false, d.y, d.M(), d.g.K, bd, P.gm, nullptr, P.bn_scratch, st));
       RESIST_TRY(wg.launch(d.g, P.gm, d.in, gg + d.w_off));
-      RESIST_TRY(conv_dgrad(d.g, dt, P.gm, d.wT, Gn, nullptr, nullptr, st));
+      RESIST_TRY(conv_dgrad(d.g, dt, P.gm, d.f.dgrad(pp + d.w_off), Gn, nullptr, nullptr, st));
     }
     void *dy = P.dy0, *dy_other = P.dy1;
     for (int j = nc - 1; j >= 0; --j) {
@@ -948,7 +962,7 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
         StatParts sp{};
         const BnBwdFuse f{prev.y, bp_, true, P.stats, &sp};
         const bool fz = fuse_bn && c.g.stride == 1;
-        RESIST_TRY(conv_dgrad(c.g, dt, dy, c.wT, P.da, nullptr, nullptr, st, fz ? &f : nullptr));
+        RESIST_TRY(conv_dgrad(c.g, dt, dy, c.f.dgrad(pp + c.w_off), P.da, nullptr, nullptr, st, fz ? &f : nullptr));
         RESIST_TRY(wg.before_write(dy_other));
         RESIST_TRY(bn_backward(dt, P.da, true, prev.y, prev.M(), prev.g.K, bp_, dy_other, nullptr, P.bn_scratch, st,
                                fz ? P.stats : nullptr, sp));
@@ -962,9 +976,9 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
           BlockPlan &below = P.blocks[bi - 1];
           ConvLayer &bl_last = below.convs.back();
           const BnBwdFuse f{bl_last.y, bn_bufs(bl_last, params(below.slot), grads(below.slot)), false, P.stats, &pre};
-          RESIST_TRY(conv_dgrad(c.g, dt, dy, c.wT, Gn, bp.has_ds ? Gn : G, bp.in, st, &f));
+          RESIST_TRY(conv_dgrad(c.g, dt, dy, c.f.dgrad(pp + c.w_off), Gn, bp.has_ds ? Gn : G, bp.in, st, &f));
         } else {
-          RESIST_TRY(conv_dgrad(c.g, dt, dy, c.wT, Gn, bp.has_ds ? Gn : G, bi > 0 ? bp.in : nullptr, st));
+          RESIST_TRY(conv_dgrad(c.g, dt, dy, c.f.dgrad(pp + c.w_off), Gn, bp.has_ds ? Gn : G, bi > 0 ? bp.in : nullptr, st));
         }
         have_pre = fz;
       }
@@ -1059,8 +1073,7 @@ int build_preact_forward_plan(const resist_model_desc *desc, const int32_t *bloc
       un.rmean_off = L.off(T_RMEAN, (int)j);
       un.rvar_off = L.off(T_RVAR, (int)j);
       // a copy of the filter in the compute type; the last unit's always (it carries the branch scale)
-      if (net.d.compute_dtype == DT_BF16 || j + 1 == gs.size())
-        un.wlp = A.take_act((int64_t)un.g.K * un.g.R * un.g.S * un.g.C, es);
+      un.f.take_forward(A, un.g, net.d.compute_dtype, j + 1 == gs.size());
       un.scale = A.take<float>((int64_t)2 * un.g.C);
       un.shift = un.scale + un.g.C;
       RESIST_TRY(conv_check(un.g, net.d.compute_dtype));
@@ -1072,7 +1085,7 @@ int build_preact_forward_plan(const resist_model_desc *desc, const int32_t *bloc
     if (bs.has_ds) {
       pb.dsg = make_geom(N, bs.h_in, bs.w_in, bs.c_in, bs.c_out, 1, bs.stride, 0);
       pb.ds_w_off = L.off(T_CONVW, 3);
-      if (net.d.compute_dtype == DT_BF16) pb.ds_wlp = A.take_act((int64_t)bs.c_out * bs.c_in, es);
+      pb.ds_f.take_forward(A, pb.dsg, net.d.compute_dtype);
     }
   }
   P->wpad = A.take_act((int64_t)K0 * P->kpad, es);
@@ -1123,12 +1136,9 @@ int forward_preact(const resist_model_desc *desc, const int32_t *blocks, int32_t
       float *pp = params(pb.slot);
       for (size_t j = 0; j < pb.units.size(); ++j) {
         PreUnit &un = pb.units[j];
-        if (!un.wlp) continue;
-        FilterPrep f{un.g, pp + un.w_off, un.wlp, nullptr};
-        if (j + 1 == pb.units.size() && branch_scale) f.scale = branch_scale[bi];
-        prep.push_back(f);
+        prep.push_back(un.f.prep(un.g, pp + un.w_off, j + 1 == pb.units.size() && branch_scale ? branch_scale[bi] : 1.f));
       }
-      if (pb.ds_wlp) prep.push_back(FilterPrep{pb.dsg, pp + pb.ds_w_off, pb.ds_wlp, nullptr});
+      if (pb.has_ds) prep.push_back(pb.ds_f.prep(pb.dsg, pp + pb.ds_w_off));
     }
     RESIST_TRY(prepare_filters(prep, dt, st));
   }
@@ -1159,10 +1169,9 @@ int forward_preact(const resist_model_desc *desc, const int32_t *blocks, int32_t
     for (size_t j = 0; j < n; ++j) {
       PreUnit &un = pb.units[j];
       if (j == 0 && pb.has_ds) {
-        const void *wd = dt == DT_F32 ? (const void *)(pp + pb.ds_w_off) : pb.ds_wlp;
-        RESIST_TRY(conv_fwd(pb.dsg, dt, un.a, wd, P.sc, nullptr, nullptr, nullptr, st));
+        RESIST_TRY(conv_fwd(pb.dsg, dt, un.a, pb.ds_f.forward(pp + pb.ds_w_off), P.sc, nullptr, nullptr, nullptr, st));
       }
-      const void *wf = un.wlp ? un.wlp : (const void *)(pp + un.w_off);
+      const Filter wf = un.f.forward(pp + un.w_off, j + 1 == n && branch_scale ? branch_scale[bi] : 1.f);
       const void *addend = j + 1 == n ? (pb.has_ds ? (const void *)P.sc : pb.x) : nullptr;
       // the BN-ReLU of whoever reads this output: the next unit, the next block's first, or the head
       const PreUnit *next = j + 1 < n ? &pb.units[j + 1] : bi + 1 < P.blocks.size() ? &P.blocks[bi + 1].units[0] : nullptr;
@@ -1223,16 +1232,15 @@ extern "C" int resist_forward(const resist_model_desc *desc, const int32_t *bloc
   const int N = batch, dt = net.d.compute_dtype;
   const float eps = net.d.bn_eps;
   auto params = [&](int slot) { return (float *)block_params[slot]; };
-  if (dt == DT_BF16) {
+  {
     std::vector<FilterPrep> prep;
     for (BlockPlan &bp : P.blocks) {
       float *pp = params(bp.slot);
-      for (ConvLayer &c : bp.convs) prep.push_back(FilterPrep{c.g, pp + c.w_off, c.wlp, nullptr});
-      if (bp.has_ds) prep.push_back(FilterPrep{bp.ds.g, pp + bp.ds.w_off, bp.ds.wlp, nullptr});
+      for (ConvLayer &c : bp.convs) prep.push_back(c.f.prep(c.g, pp + c.w_off));
+      if (bp.has_ds) prep.push_back(bp.ds.f.prep(bp.ds.g, pp + bp.ds.w_off));
     }
     RESIST_TRY(prepare_filters(prep, dt, st));
   }
-  auto filter = [&](const ConvLayer &c, const float *w) -> const void * { return dt == DT_F32 ? (const void *)w : c.wlp; };
   {
     std::vector<BnEval> affine{bn_eval_item(P.stem, params(0), 1.f)};
     for (size_t bi = 0; bi < P.blocks.size(); ++bi) {
@@ -1256,7 +1264,7 @@ extern "C" int resist_forward(const resist_model_desc *desc, const int32_t *bloc
   for (BlockPlan &bp : P.blocks) {
     float *pp = params(bp.slot);
     const ConvLayer &d = bp.ds;
-    if (bp.has_ds) RESIST_TRY(conv_fwd(d.g, dt, d.in, filter(d, pp + d.w_off), d.y, nullptr, nullptr, nullptr, st));
+    if (bp.has_ds) RESIST_TRY(conv_fwd(d.g, dt, d.in, d.f.forward(pp + d.w_off), d.y, nullptr, nullptr, nullptr, st));
     for (ConvLayer &c : bp.convs) {
       EvalAct act{c.a, c.scale, c.shift};
       if (!c.a) {   // the last one: the shortcut joins, and the block's output is written
@@ -1264,7 +1272,7 @@ extern "C" int resist_forward(const resist_model_desc *desc, const int32_t *bloc
         act.res = bp.has_ds ? d.y : bp.in;
         if (bp.has_ds) { act.rscale = d.scale; act.rshift = d.shift; }
       }
-      RESIST_TRY(conv_fwd(c.g, dt, c.in, filter(c, pp + c.w_off), nullptr, nullptr, nullptr, nullptr, st, &act));
+      RESIST_TRY(conv_fwd(c.g, dt, c.in, c.f.forward(pp + c.w_off), nullptr, nullptr, nullptr, nullptr, st, &act));
     }
   }
   const int J = net.d.num_classes, CH = net.head_c;

@@ -495,3 +495,81 @@ def test_conv_rejects_bad_shapes():
     w = torch.zeros((8, 3, 3, 8), device="cuda")
     with pytest.raises(R.ResistError):
         R.conv2d_dgrad(torch.zeros((1, 3, 3, 8), device="cuda"), w, (1, 5, 5, 8), 2, 1)   # odd size, stride 2
+
+
+# 3x3 layers on filters in matrix fragments, by the tile they run on, the data gradient on the layer with in- and output channels
+# exchanged: 96 pixels (two to four chunks, the last tile ragged, 65 and 130 output channels' worth of column tiles), filters larger than
+# the pixels (tiles ordered along the pixels), bf16 from 256 channels (one that ends in mid-chunk, images one pixel wide and
+# the widest)
+#                       dt  N   H   W   C    K   R st pad
+FRAGMENT_CASES = [(("f32", 77, 8, 8, 256, 256, 3, 1, 1), "96x64"), (("f32", 160, 11, 11, 128, 68, 3, 1, 1), "96x64"), (("f32", 171, 5, 5, 192, 260, 3, 1, 1), "96x64"),
+                  (("f32", 40, 4, 4, 512, 512, 3, 1, 1), "64x64"), (("bf16", 33, 8, 8, 256, 256, 3, 1, 1), "64x64"), (("bf16", 13, 9, 7, 264, 336, 3, 1, 1), "64x64"),
+                  (("bf16", 300, 3, 1, 320, 320, 3, 1, 1), "64x64"), (("bf16", 1, 19, 56, 256, 264, 3, 1, 1), "64x64"), (("bf16", 40, 4, 4, 512, 520, 3, 1, 1), "64x64")]
+
+
+def _bf16_exact(a):
+    return torch.from_numpy(a).to(torch.bfloat16).float().numpy()
+
+
+@pytest.mark.parametrize("case", FRAGMENT_CASES)
+def test_conv_filter_fragments(case):
+    (dt, *shape), tile = case
+    print("case", case, flush=True)
+    N, H, W, C, K = shape[:5]
+    x, w, _ = _tensors(tuple(shape), 21)
+    bf16 = dt == "bf16"
+    if bf16:
+        x, w = _bf16_exact(x), _bf16_exact(w)
+    dev = lambda a: _nhwc(a).to(torch.bfloat16 if bf16 else torch.float32)
+    xd, wd, wtd = dev(x), dev(w), dev(np.ascontiguousarray(w.transpose(1, 0, 2, 3)))
+    (y, dx), ran = _launched(lambda: (R.conv2d_forward(xd, wd, 1, 1), R.conv2d_dgrad(xd, wtd, (N, H, W, K), 1, 1)))
+    names = {f"conv3_{dt}_fwd_{tile}", f"conv3_{dt}_bwd_{tile}"}
+    if bf16 and C < 512:   # the forward call on its own reads the filter's rows
+        names.discard(f"conv3_{dt}_fwd_{tile}")
+    assert {n for n in ran if n.startswith("conv3_")} == names, ran
+    for got, want, what in ((y, L.conv2d_fwd(x, w, 1, 1), "fwd"), (dx, L.conv2d_dgrad(x, w.transpose(1, 0, 2, 3), (N, K, H, W), 1, 1), "dgrad")):
+        got = got.float().cpu().numpy().transpose(0, 3, 1, 2)
+        if bf16:   # half an ulp of the stored result beside the fp32 sums
+            np.testing.assert_allclose(got, want, rtol=2.0 ** -8, atol=1e-5, err_msg=what)
+        else:
+            assert_close(got, want, f"{what} {case}")
+
+
+def test_conv_forward_and_dgrad_with_little_workspace():
+    # what the calls take without room for the fragments: the same results from the kernels that read the filter's rows
+    import ctypes
+    from paper_2107_00961_amd import binding as B
+    case = (40, 8, 8, 64, 320, 3, 1, 1)
+    N, H, W, C, K = case[:5]
+    x, w, dy = _tensors(case, 22)
+    xd, wd, dyd = _nhwc(x), _nhwc(w), _nhwc(dy)
+    y, dx = torch.empty((N, H, W, K), device="cuda"), torch.empty((N, H, W, C), device="cuda")
+    ws = torch.empty(K * 9 * C, device="cuda")
+    sh, st = B._conv_shape(N, H, W, C, K, 3, 1, 1, 0), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    lib = B.lib()
+    _, ran = _launched(lambda: (B._check(lib.resist_conv2d_forward(ctypes.byref(sh), xd.data_ptr(), wd.data_ptr(), y.data_ptr(), None, 0, st)),
+                                B._check(lib.resist_conv2d_dgrad(ctypes.byref(sh), dyd.data_ptr(), wd.data_ptr(), dx.data_ptr(), ws.data_ptr(), ws.numel() * 4, st))))
+    assert not any(n.startswith("conv3_") for n in ran), ran
+    assert_close(y.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_fwd(x, w, 1, 1), "fwd")
+    assert_close(dx.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_dgrad(dy, w, x.shape, 1, 1), "dgrad")
+    assert lib.resist_conv2d_dgrad(ctypes.byref(sh), dyd.data_ptr(), wd.data_ptr(), dx.data_ptr(), ws.data_ptr(), ws.numel() * 4 - 4, st) != 0
+
+
+def test_conv_fragments_second_pass_on_96_pixel_tiles():
+    """Infinities in the pixels, one value of the filter too small for three parts: tiles with and without them."""
+    shape = (171, 5, 5, 192, 260, 3, 1, 1)
+    N, H, W, C, K = shape[:5]
+    x, w, _ = _tensors(shape, 23)
+    x[0, 5, 2, 3], x[40, 150, 0, 0], x[99, 9, 4, 4] = np.inf, np.nan, 3.4e38
+    small = np.float32(1.2345678e-36)
+    w[200, 70, 1, 2] = small
+    x[3, 70, 2, 2] = np.float32(2.0 ** 120)   # times the small value: 1.6
+    wt = np.ascontiguousarray(w.transpose(1, 0, 2, 3))
+    xd, wd, wtd = _nhwc(x), _nhwc(w), _nhwc(wt)
+    (y, dx), ran = _launched(lambda: (R.conv2d_forward(xd, wd, 1, 1), R.conv2d_dgrad(xd, wtd, (N, H, W, K), 1, 1)))
+    assert {"conv3_f32_fwd_96x64", "conv3_f32_bwd_96x64"} <= ran, ran
+    with np.errstate(invalid="ignore", over="ignore"):
+        X = x.astype(np.float64)
+        for got, want in ((y, L.conv2d_fwd(X, w, 1, 1)), (dx, L.conv2d_dgrad(X, wt, (N, K, H, W), 1, 1))):
+            assert np.isfinite(want).any() and not np.isfinite(want).all()
+            _same_values(got.cpu().numpy(), want, "fwd or dgrad")
