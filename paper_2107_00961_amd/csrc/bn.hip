@@ -10,6 +10,8 @@
 // from run to run.
 // Activations are stored as fp32 or bf16; a thread owns V = 4 (fp32) or 8 (bf16) consecutive channels
 // (one 16-byte access) and all arithmetic is fp32 / fp64.
+#include <algorithm>
+
 #include "elem.h"
 #include "internal.h"
 
@@ -65,44 +67,54 @@ __device__ inline void load_params(const float *__restrict__ p, float (&v)[V]) {
 // so mean = k + S1/M and var = S2/M - (S1/M)^2 with S1/M of the order of the standard deviation
 // whatever the mean is: no cancellation between large numbers.  All merging is float64.
 //
-// Reduction over `parts` triples per channel, layout [3][parts][C]: a workgroup owns 16 channels;
-// R thread rows (R = 16 in a workgroup of 256 threads, 64 in one of 1024) each merge every R-th part
-// in index order, then thread row 0 adds the R partial sums in order.  Part p holds
-// min(rows, M - p*rows) rows.
-template <typename S, int R>
-__device__ inline void merge_parts(const S *__restrict__ st, int p0, int p1, int parts, int C, int c, int pl, long long M,
-                                   long long rows, double (*red)[R][16], double *k_out, double *s1_out, double *s2_out) {
-  const double k = (double)st[(size_t)p0 * C + c];
-  double s = 0, q = 0;
-  int p = p0 + pl;
-  auto merge = [&](int pp, S kp, S a1, S a2) {
-    long long n = M - (long long)pp * rows;
-    n = n < rows ? n : rows;
-    const double d = (double)kp - k, n_d = (double)n * d;
-    s += (double)a1 + n_d;
-    q += (double)a2 + d * (2.0 * (double)a1 + n_d);
-  };
-  // four loads of each array in flight per thread; the additions keep their order
-  for (; p + 3 * R < p1; p += 4 * R) {
-    S vk[4], v1[4], v2[4];
+// Reduction over `parts` triples per channel, layout [3][parts][C]: a workgroup owns 16 channels; R thread rows (R = 16 in a
+// workgroup of 256 threads, 64 in one of 1024) each merge every R-th part in index order; then the rows of a wave meet in
+// shuffles and the waves, in order, through LDS.  Part p holds `rows` rows, the last one `last`.
+// A launch is one memory round trip and a chain of float64 operations, so a thread has U parts' triples in flight, enough for the
+// usual lists in one go, and what thread row 0 needs behind the sums is requested before them (us in a bf16 step of the CIFAR-shaped
+// model: totals of 64 tiles 4.7 -> 4.1, of 256 to 1024 tiles' statistics 6.7 -> 5.4).
+template <int R>
+__device__ inline void add_rows(double &s, double &q, double (*red)[R / 4][16]) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      vk[u] = st[(size_t)(p + R * u) * C + c];
-      v1[u] = st[(size_t)(parts + p + R * u) * C + c];
-      v2[u] = st[(size_t)(2 * parts + p + R * u) * C + c];
+  for (int o = 16; o < 64; o <<= 1) { s += __shfl_xor(s, o, 64); q += __shfl_xor(q, o, 64); }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane < 16) { red[0][wave][lane] = s; red[1][wave][lane] = q; }
+  __syncthreads();
+  if (threadIdx.x < 16) {
+    double v[2][R / 4];
+#pragma unroll
+    for (int j = 0; j < R / 4; ++j) { v[0][j] = red[0][j][lane]; v[1][j] = red[1][j][lane]; }
+    s = v[0][0]; q = v[1][0];
+#pragma unroll
+    for (int j = 1; j < R / 4; ++j) { s += v[0][j]; q += v[1][j]; }
+  }
+}
+
+template <typename S, int R, int U>
+__device__ inline void merge_parts(const S *__restrict__ st, int p0, int p1, int parts, int C, int c, int pl, double rows, double last,
+                                   double (*red)[R / 4][16], double *k_out, double *s1_out, double *s2_out) {
+  const S first = st[(size_t)p0 * C + c];
+  double s = 0, q = 0;
+  for (int p = p0 + pl; p < p1; p += U * R) {
+    S vk[U], v1[U], v2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t at = (size_t)min(p + R * u, p1 - 1) * C + c, next = (size_t)parts * C;
+      vk[u] = st[at];
+      v1[u] = st[at + next];
+      v2[u] = st[at + 2 * next];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) merge(p + R * u, vk[u], v1[u], v2[u]);
+    for (int u = 0; u < U; ++u) {
+      const int pp = p + R * u;
+      const double n = pp == parts - 1 ? last : rows, a1 = (double)v1[u];
+      const double d = (double)vk[u] - (double)first, n_d = n * d;
+      s += pp < p1 ? a1 + n_d : 0.0;
+      q += pp < p1 ? (double)v2[u] + d * (2.0 * a1 + n_d) : 0.0;
+    }
   }
-  for (; p < p1; p += R) merge(p, st[(size_t)p * C + c], st[(size_t)(parts + p) * C + c], st[(size_t)(2 * parts + p) * C + c]);
-  const int cl = c & 15;
-  red[0][pl][cl] = s;
-  red[1][pl][cl] = q;
-  __syncthreads();
-  if (pl == 0) {
-    for (int j = 1; j < R; ++j) { s += red[0][j][cl]; q += red[1][j][cl]; }
-  }
-  *k_out = k;
+  add_rows<R>(s, q, red);
+  *k_out = (double)first;
   *s1_out = s;
   *s2_out = q;
 }
@@ -111,45 +123,50 @@ __device__ inline void merge_parts(const S *__restrict__ st, int p0, int p1, int
 // channels; output [3][Z][C] float64 triples (slice z then holds kSlice*rows rows, the last one fewer)
 constexpr int kSlice = 64;
 __global__ __launch_bounds__(kThreads) void bn_stats_reduce_kernel(const float *__restrict__ stats, int parts, int C,
-                                                                   long long M, long long rows, double *__restrict__ out) {
-  __shared__ double red[2][16][16];
+                                                                   double rows, double last, double *__restrict__ out) {
+  __shared__ double red[2][4][16];
   const int c = blockIdx.x * 16 + (threadIdx.x & 15), pl = threadIdx.x >> 4;
   const int z = blockIdx.y, Z = gridDim.y;
   const int p0 = z * kSlice, p1 = min(parts, p0 + kSlice);
   double k, s, q;
-  merge_parts<float, 16>(stats, p0, p1, parts, C, c, pl, M, rows, red, &k, &s, &q);
+  merge_parts<float, 16, 4>(stats, p0, p1, parts, C, c, pl, rows, last, red, &k, &s, &q);
   if (pl != 0) return;
   out[(size_t)z * C + c] = k;
   out[(size_t)(Z + z) * C + c] = s;
   out[(size_t)(2 * Z + z) * C + c] = q;
 }
 
-template <typename S, int R>
-__global__ __launch_bounds__(16 * R) void bn_finalize_kernel(const S *__restrict__ stats, int parts, long long rows, int C,
-                                                               long long M, float eps, float momentum,
+// M = rows normalised over; inv_M = 1/M, unbias = M/(M-1)
+template <typename S, int R, int U>
+__global__ __launch_bounds__(16 * R) void bn_finalize_kernel(const S *__restrict__ stats, int parts, double rows, double last, int C,
+                                                               double inv_M, double unbias, float eps, float momentum,
                                                                const float *__restrict__ gamma, const float *__restrict__ beta,
                                                                float *__restrict__ mean, float *__restrict__ invstd,
                                                                float *__restrict__ scale, float *__restrict__ shift,
                                                                float *__restrict__ rmean, float *__restrict__ rvar) {
-  __shared__ double red[2][R][16];
+  __shared__ double red[2][R / 4][16];
   const int c = blockIdx.x * 16 + (threadIdx.x & 15), pl = threadIdx.x >> 4;
+  float ga = 0, be = 0, rm = 0, rv = 0;
+  if (pl == 0) {
+    ga = gamma[c]; be = beta[c];
+    if (rmean) { rm = rmean[c]; rv = rvar[c]; }
+  }
   double k, s, q;
-  merge_parts<S, R>(stats, 0, parts, parts, C, c, pl, M, rows, red, &k, &s, &q);
+  merge_parts<S, R, U>(stats, 0, parts, parts, C, c, pl, rows, last, red, &k, &s, &q);
   if (pl != 0) return;
-  const double off = s / (double)M;       // mean - k
+  const double off = s * inv_M;           // mean - k
   const double m = k + off;
-  double var = q / (double)M - off * off;
+  double var = q * inv_M - off * off;
   if (var < 0) var = 0;
   const float mf = (float)m, isf = (float)(1.0 / sqrt(var + (double)eps));
   mean[c] = mf;
   invstd[c] = isf;
-  const float sc = gamma[c] * isf;
+  const float sc = ga * isf;
   scale[c] = sc;
-  shift[c] = beta[c] - mf * sc;
+  shift[c] = be - mf * sc;
   if (rmean) {
-    const double unb = M > 1 ? var * ((double)M / (double)(M - 1)) : var;
-    rmean[c] = (float)((1.0 - momentum) * (double)rmean[c] + (double)momentum * m);
-    rvar[c] = (float)((1.0 - momentum) * (double)rvar[c] + (double)momentum * unb);
+    rmean[c] = (float)((1.0 - momentum) * (double)rm + (double)momentum * m);
+    rvar[c] = (float)((1.0 - momentum) * (double)rv + (double)momentum * (var * unbias));
   }
 }
 
@@ -306,46 +323,29 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_partial_kernel(const T *__res
   }
 }
 
-// plain fixed-order reduction of two sums per channel, layout [2][parts][C] (the backward pass)
-template <int R, typename S>
-__device__ inline void reduce_parts(const S *__restrict__ scratch, int parts, int C, int c, int pl,
-                                    double (*red)[R][16], double *out0, double *out1) {
-  double s = 0, q = 0;
-  int p = pl;
-  // eight loads of each sum in flight per thread; the additions keep their order
-  for (; p + 7 * R < parts; p += 8 * R) {
-    S vs[8], vq[8];
+// Totals of two sums per channel, layout [2][parts][C] (the backward pass), as merge_parts adds them.
+// S = double: partial sums of bn_bwd_partial_kernel; S = float: per-row-tile sums left by a data gradient
+template <typename S, int R, int U>
+__global__ __launch_bounds__(16 * R) void bn_bwd_final_kernel(const S *__restrict__ scratch, int parts, int C,
+                                                              float *__restrict__ dgamma, float *__restrict__ dbeta) {
+  __shared__ double red[2][R / 4][16];
+  const int c = blockIdx.x * 16 + (threadIdx.x & 15), pl = threadIdx.x >> 4;
+  double b = 0, g = 0;
+  for (int p = pl; p < parts; p += U * R) {
+    S vb[U], vg[U];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      vs[u] = scratch[(size_t)(p + R * u) * C + c];
-      vq[u] = scratch[(size_t)(parts + p + R * u) * C + c];
+    for (int u = 0; u < U; ++u) {
+      const size_t at = (size_t)min(p + R * u, parts - 1) * C + c;
+      vb[u] = scratch[at];
+      vg[u] = scratch[at + (size_t)parts * C];
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) { s += vs[u]; q += vq[u]; }
+    for (int u = 0; u < U; ++u) {
+      b += p + R * u < parts ? (double)vb[u] : 0.0;
+      g += p + R * u < parts ? (double)vg[u] : 0.0;
+    }
   }
-  for (; p < parts; p += R) {
-    s += scratch[(size_t)p * C + c];
-    q += scratch[(size_t)(parts + p) * C + c];
-  }
-  const int cl = c & 15;
-  red[0][pl][cl] = s;
-  red[1][pl][cl] = q;
-  __syncthreads();
-  if (pl == 0) {
-    for (int j = 1; j < R; ++j) { s += red[0][j][cl]; q += red[1][j][cl]; }
-  }
-  *out0 = s;
-  *out1 = q;
-}
-
-// S = double: partial sums of bn_bwd_partial_kernel; S = float: per-row-tile sums left by a data gradient
-template <typename S>
-__global__ __launch_bounds__(kThreads) void bn_bwd_final_kernel(const S *__restrict__ scratch, int parts, int C,
-                                                                float *__restrict__ dgamma, float *__restrict__ dbeta) {
-  __shared__ double red[2][16][16];
-  const int c = blockIdx.x * 16 + (threadIdx.x & 15), pl = threadIdx.x >> 4;
-  double b, g;
-  reduce_parts<16, S>(scratch, parts, C, c, pl, red, &b, &g);
+  add_rows<R>(b, g, red);
   if (pl != 0) return;
   dbeta[c] = (float)b;
   dgamma[c] = (float)g;
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(BwdApplyArgs p) 
   for (int e = 0; e < V; ++e) { k1[e] *= invM; k2[e] *= invM; }   // means of gm and of gm*xhat
   const long long stride = (long long)gridDim.x * p.rpp;
   for (long long r0 = (long long)blockIdx.x * p.rpp + tr; r0 < p.M; r0 += stride * 2) {
-    float gv[2][V], yv[2][V], mv[2][V];
+    float gv[2][V], yv[2][V];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const long long r = r0 + u * stride;
@@ -435,17 +435,25 @@ unsigned apply_grid_x(int64_t M, const ColMap &m, int rows_per_thread) {
 
 inline int vec_of(int dt) { return dt == DT_BF16 ? 8 : 4; }
 
+// thread rows and parts in flight by the length of the list: every part of a list of up to 1024 in flight at once
+template <typename S>
+void launch_final(const S *sums, int parts, int C, const BnBufs &b, hipStream_t st) {
+  if (parts <= 32) hipLaunchKernelGGL((bn_bwd_final_kernel<S, 16, 2>), dim3(C / 16), dim3(256), 0, st, sums, parts, C, b.dgamma, b.dbeta);
+  else if (parts <= 128) hipLaunchKernelGGL((bn_bwd_final_kernel<S, 16, 8>), dim3(C / 16), dim3(256), 0, st, sums, parts, C, b.dgamma, b.dbeta);
+  else hipLaunchKernelGGL((bn_bwd_final_kernel<S, 64, 8>), dim3(C / 16), dim3(1024), 0, st, sums, parts, C, b.dgamma, b.dbeta);
+}
+
 template <typename T>
 void launch_bwd(int mode, dim3 gp, dim3 ga, hipStream_t st, const void *g, const void *y, int64_t M, int C,
                 const ColMap &m, const BnBufs &b, double *scratch, const BwdApplyArgs &p, int parts, const float *pre_sums) {
   const T *gg = (const T *)g, *yy = (const T *)y;
 #define RESIST_BN_BWD(MODE)                                                                                              \
   if (pre_sums) {                                                                                                        \
-    hipLaunchKernelGGL(bn_bwd_final_kernel<float>, dim3(C / 16), dim3(kThreads), 0, st, pre_sums, parts, C, b.dgamma, b.dbeta); \
+    launch_final<float>(pre_sums, parts, C, b, st);                                                                      \
   } else {                                                                                                               \
     hipLaunchKernelGGL((bn_bwd_partial_kernel<T, MODE>), gp, dim3(kThreads), 0, st, gg, yy, (long long)M, C, m.tpr, m.rpp, \
                        b.mean, b.invstd, b.scale, b.shift, scratch);                                                    \
-    hipLaunchKernelGGL(bn_bwd_final_kernel<double>, dim3(C / 16), dim3(kThreads), 0, st, (const double *)scratch, parts, C, b.dgamma, b.dbeta); \
+    launch_final<double>(scratch, parts, C, b, st);                                                                      \
   }                                                                                                                      \
   hipLaunchKernelGGL((bn_bwd_apply_kernel<T, MODE>), ga, dim3(kThreads), 0, st, p);
   if (mode == kMaskSelf) { RESIST_BN_BWD(kMaskSelf) }
@@ -465,22 +473,26 @@ int bn_finalize(const float *stats, StatParts sp, int64_t M, int C, const BnBufs
   if (parts < 1 || rows < 1 || !stats || (long long)parts * rows < M || (long long)(parts - 1) * rows >= M)
     return set_error(RESIST_EINVAL, "bn_finalize: %d partial sums of %lld rows for %lld rows", parts, rows, (long long)M);
   prof::Scope ps("bn_finalize", 0, 12.0 * parts * C, st);
+  const double last = (double)(M - (long long)(parts - 1) * rows), inv_M = 1.0 / (double)M, unbias = M > 1 ? (double)M / (double)(M - 1) : 1.0;
+  auto launch = [&](auto kernel, int threads, auto sums, int n, double per, double in_last) {
+    hipLaunchKernelGGL(kernel, dim3(C / 16), dim3(threads), 0, st, sums, n, per, in_last, C, inv_M, unbias, eps, momentum, b.gamma,
+                       b.beta, b.mean, b.invstd, b.scale, b.shift, b.rmean, b.rvar);
+  };
   if (parts > 4096) {
     // very long lists of row tiles: a first level over slices of kSlice parts, in its own launch
     const int Z = (parts + kSlice - 1) / kSlice;
     if (Z > kMaxParts || !scratch) return set_error(RESIST_ESHAPE, "bn_finalize: %d partial sums", parts);
-    hipLaunchKernelGGL(bn_stats_reduce_kernel, dim3(C / 16, Z), dim3(kThreads), 0, st, stats, parts, C, (long long)M, rows, scratch);
+    hipLaunchKernelGGL(bn_stats_reduce_kernel, dim3(C / 16, Z), dim3(kThreads), 0, st, stats, parts, C, (double)rows, last, scratch);
     RESIST_CHECK_LAUNCH("bn_stats_reduce");
-    hipLaunchKernelGGL((bn_finalize_kernel<double, 16>), dim3(C / 16), dim3(kThreads), 0, st, (const double *)scratch, Z,
-                       rows * kSlice, C, (long long)M, eps, momentum, b.gamma, b.beta, b.mean, b.invstd, b.scale, b.shift, b.rmean,
-                       b.rvar);
-  } else if (parts > 2 * kSlice) {
-    // one launch: 1024 threads per 16 channels, 64 thread rows share the parts
-    hipLaunchKernelGGL((bn_finalize_kernel<float, 64>), dim3(C / 16), dim3(1024), 0, st, stats, parts, rows, C, (long long)M, eps,
-                       momentum, b.gamma, b.beta, b.mean, b.invstd, b.scale, b.shift, b.rmean, b.rvar);
+    const long long slice = rows * kSlice;
+    launch(bn_finalize_kernel<double, 16, 8>, 256, (const double *)scratch, Z, (double)slice, (double)(M - (Z - 1) * slice));
+  } else if (parts > 128) {
+    // 1024 threads per 16 channels, 64 thread rows share the parts
+    launch(bn_finalize_kernel<float, 64, 8>, 1024, stats, parts, (double)rows, last);
+  } else if (parts > 32) {
+    launch(bn_finalize_kernel<float, 16, 8>, 256, stats, parts, (double)rows, last);
   } else {
-    hipLaunchKernelGGL((bn_finalize_kernel<float, 16>), dim3(C / 16), dim3(kThreads), 0, st, stats, parts, rows, C, (long long)M,
-                       eps, momentum, b.gamma, b.beta, b.mean, b.invstd, b.scale, b.shift, b.rmean, b.rvar);
+    launch(bn_finalize_kernel<float, 16, 2>, 256, stats, parts, (double)rows, last);
   }
   RESIST_CHECK_LAUNCH("bn_finalize");
   return RESIST_OK;
@@ -516,7 +528,10 @@ int bn_apply(int dt, const void *y, int64_t M, int C, const BnBufs &b, const voi
   if (res_bn) { p.rscale = res_bn->scale; p.rshift = res_bn->shift; }
   p.a = a; p.M = M; p.C = C; p.tpr = m.tpr; p.rpp = m.rpp; p.relu = relu ? 1 : 0;
   prof::Scope ps("bn_apply", 0, (double)esize(dt) * M * C * (res ? 3 : 2), st);
-  const dim3 grid(apply_grid_x(M, m, 2 * kUnroll), m.ctiles);
+  // eight rows a thread, fewer where that would be less than two workgroups to a compute unit (256 ch 8x8, batch 128, bf16:
+  // 128 workgroups 5.9 us, 512 5.0; 64 ch 32x32, with 2048 of them, 11 us either way)
+  const int rows = (int)std::min<int64_t>(2 * kUnroll, std::max<int64_t>(1, M * m.ctiles / ((int64_t)m.rpp * 512)));
+  const dim3 grid(apply_grid_x(M, m, rows), m.ctiles);
   if (dt == DT_BF16) hipLaunchKernelGGL(bn_apply_kernel<__bf16>, grid, dim3(kThreads), 0, st, p);
   else hipLaunchKernelGGL(bn_apply_kernel<float>, grid, dim3(kThreads), 0, st, p);
   RESIST_CHECK_LAUNCH("bn_apply");

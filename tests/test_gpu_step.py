@@ -96,6 +96,36 @@ def test_local_step_small_bn_first_pass_from_the_data_gradient(name):
         R.set_bn_fusion(1)
 
 
+# Lists of per-tile sums around the lengths at which the kernels that add them change their shape (32 and 128 tiles of 32 rows,
+# the last one ragged or not), forward and, taken by the data gradient, backward.  Forward quantities to the element; the last
+# block's BN gradients, behind one ReLU, as tensors (7e4 decisions, each within 1e-6 of a tie: at most one falls the other way,
+# a few 1e-3 of the norm).
+@pytest.mark.parametrize("hw,batch", [((16, 16), 4), ((12, 12), 8), ((12, 20), 17), ((16, 16), 16), ((12, 20), 18), ((16, 16), 17)])
+@pytest.mark.parametrize("fusion", [1, 2])
+def test_bn_sums_of_many_tiles(hw, batch, fusion):
+    model = dict(get_config("cfg1")["model"], in_h=hw[0], in_w=hw[1], blocks=[1])
+    params = make_params(model, 31, perturb_bn=True)
+    x, y = make_batch(model, batch, 32)
+    sub = SubResNet(model, [0], params, batch)
+    xd, yd = to_device_batch(x, y)
+    R.set_bn_fusion(fusion)
+    try:
+        sub.step(xd, yd, 0.1, 0.9, 5e-4)
+        torch.cuda.synchronize()
+    finally:
+        R.set_bn_fusion(1)
+    loss, grads, want, _ = OR.local_step(model, [0], params, zeros_like_params(params), x, y, 0.1, 0.9, 5e-4)
+    assert_close(sub.loss.cpu().numpy()[0], loss, "loss")
+    got, got_g = sub.download(), sub.download_grads()
+    for k in sub.keys:
+        for name, w in want[k].items():
+            if not OR.is_trainable(name):
+                assert_close(got[k][name], w, f"{k} {name}")
+    for name, g in grads[0].items():
+        if name.startswith("bn"):
+            assert np.linalg.norm(got_g[0][name] - g) <= 1e-2 * np.linalg.norm(g), name
+
+
 @pytest.mark.parametrize("beta", [6.0, 50.0])
 def test_bn_input_with_mean_far_from_zero(beta):
     """Every BN offset set to `beta`: every activation is beta + O(1), so the convolution outputs the
