@@ -475,3 +475,34 @@ def test_aggregate_full_size_cfg3():
                 assert_close(got[k][n], acc / len(holders), f"cfg3 reassembly {k} {n}", rtol=3e-7, atol=1e-7)
             checked += 1
     assert checked > 50 and any(owner[b] == 1 for b in sample if 0 <= b < nb)
+
+
+# The classifier and the poolings at sizes where their work is shared unevenly: two classes and one sample, classes and samples around the
+# groups of 4 and 8, more classes than dz is staged for at a time (512), pixels around eight a thread row, channel vectors that fill no
+# workgroup, odd images under the max-pool.  Forward quantities and the classifier's gradients have no ReLU decision behind them.
+@pytest.mark.parametrize("batch,classes,hw,widths", [(1, 2, 4, [16]), (9, 5, 10, [16, 48]), (17, 515, 12, [80]), (65, 13, 8, [16, 16, 272])])
+@pytest.mark.parametrize("stem", [0, 1])
+def test_head_at_odd_sizes(batch, classes, hw, widths, stem):
+    if stem:   # (whose kernel takes up to 64 channels at 7x7)
+        widths = [min(w, 64) for w in widths[:1]] + widths[1:]
+        hw = 4 * (hw // 2) + 5 if len(widths) == 1 else 4 * hw    # (strided stages need even sizes behind the pool)
+    model = dict(get_config("cfg1")["model"], stem_kind=stem, in_h=hw, in_w=hw + (0 if len(widths) > 1 else 2), widths=widths, blocks=[1] * len(widths),
+                 num_classes=classes)
+    blocks = list(range(len(widths)))
+    params = make_params(model, 41, perturb_bn=True)
+    x, y = make_batch(model, batch, 42)
+    sub = SubResNet(model, blocks, params, batch)
+    xd, yd = to_device_batch(x, y)
+    sub.step(xd, yd, 0.1, 0.9, 5e-4)
+    torch.cuda.synchronize()
+    loss, grads, _, _ = OR.local_step(model, blocks, params, zeros_like_params(params), x, y, 0.1, 0.9, 5e-4)
+    assert_close(sub.loss.cpu().numpy()[0], loss, "loss")
+    got = sub.download_grads()
+    head = len(widths)
+    for name, g in grads[head].items():
+        assert_close(got[head][name], g, name)
+    # behind dx, the poolings' gradients and a few ReLU decisions: as tensors
+    for k in [-1] + blocks:
+        for name, g in grads[k].items():
+            if np.linalg.norm(g) > 1e-4:
+                assert np.linalg.norm(got[k][name] - g) <= 1e-2 * np.linalg.norm(g), (k, name)
