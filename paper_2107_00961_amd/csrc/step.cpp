@@ -20,16 +20,17 @@ inline double geom_flops(const ConvGeom &g) { return 2.0 * g.N * g.P * g.Q * g.K
 struct WgradSide {
   SideStream side;
   int dt;
+  bool beside;   // by the work of the step alone: with the second stream switched off the sums have the same order
   float *splitk;
   std::vector<std::pair<const void *, hipEvent_t>> readers;   // buffer -> its last reader on the side stream
   // `flops`: convolution work of the step.  Below ~20 GFLOP a step is bound by launch latency and the
   // event calls of the second stream cost more than the overlap returns: everything stays on `main`.
   WgradSide(hipStream_t main, int dt_, float *splitk_, double flops)
-      : side(main, overlap_mode() == 2 || (overlap_mode() == 1 && flops >= 2e10)), dt(dt_), splitk(splitk_) {}
+      : side(main, overlap_mode() == 2 || (overlap_mode() == 1 && flops >= 2e10)), dt(dt_), beside(flops >= 2e10), splitk(splitk_) {}
   hipStream_t stream() const { return side.stream(); }
   int launch(const ConvGeom &g, const void *dyb, const void *xin, float *dw) {
     RESIST_TRY(side.fork());
-    RESIST_TRY(conv_wgrad(g, dt, dyb, xin, dw, splitk, side.stream(), true));
+    RESIST_TRY(conv_wgrad(g, dt, dyb, xin, dw, splitk, side.stream(), beside));
     hipEvent_t e = nullptr;
     RESIST_TRY(side.mark(&e));
     for (auto &r : readers)
@@ -245,7 +246,7 @@ int build_plan(const resist_model_desc *desc, const int32_t *blocks, int32_t nbl
     max_act = std::max<int64_t>(max_act, c.M() * c.g.K);
     max_act = std::max<int64_t>(max_act, (int64_t)c.g.N * c.g.H * c.g.W * c.g.C);
     (void)needs_dgrad;
-    max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(c.g, net.d.compute_dtype, true));
+    for (const bool beside : {false, true}) max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(c.g, net.d.compute_dtype, beside));
     max_c = std::max(max_c, c.g.K);
   };
 
@@ -534,7 +535,7 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
     if (shape_rc == RESIST_OK) shape_rc = conv_check(g, net.d.compute_dtype);
     max_act = std::max<int64_t>(max_act, (int64_t)g.N * g.P * g.Q * g.K);
     max_act = std::max<int64_t>(max_act, (int64_t)g.N * g.H * g.W * g.C);
-    max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(g, net.d.compute_dtype, true));
+    for (const bool beside : {false, true}) max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(g, net.d.compute_dtype, beside));
     if (stats) max_stats = std::max<int64_t>(max_stats, conv_stats_floats(g));
     max_c = std::max(max_c, std::max(g.K, g.C));
   };
