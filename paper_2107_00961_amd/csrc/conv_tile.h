@@ -48,6 +48,9 @@ struct IgemmArgs {
   FastDiv div_plane, div_w, div_tn, div_tm;   // by OHc*OWc, OWc, tiles_n, tiles_m: a tile's prologue is a chain of divisions
 };
 
+// of a streamed 1x1 convolution: pixels per workgroup and how many such ranges there are
+struct Conv1Args : IgemmArgs { int rows, parts; };
+
 // A-gather modes
 constexpr int kFwd = 0;  // source pixel = out*stride + tap - pad
 constexpr int kBwd = 1;  // source pixel = (out + pad - tap) / stride
@@ -346,6 +349,9 @@ __device__ inline void conv_epilogue(const ArgsOf<MODE> &a, float (*Cs)[BN + 8],
 bool conv3_takes(const IgemmArgs &a, int dt);
 int64_t conv3_filter_bytes(int OC, int IC, int dt);
 int conv3_launch(const EvalArgs &a, const Filter &w, int dt, int mode, hipStream_t st, StatParts *tiles_m_out);
+// widening 1x1 convolutions in bf16, streamed (conv1.hip)
+bool conv1_takes(const IgemmArgs &a, int dt, int mode);
+int conv1_launch(const IgemmArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);
 // convolutions with few output tiles: 32x32 tiles, the reduction split among the waves of a workgroup (conv_small.hip)
 bool conv_small_takes(const IgemmArgs &a, int dt);
 bool conv_small_rows(long long pixels, int OC, int cls);   // whether it may take an output of this size, in 32-row tiles

@@ -573,3 +573,27 @@ def test_conv_fragments_second_pass_on_96_pixel_tiles():
         for got, want in ((y, L.conv2d_fwd(X, w, 1, 1)), (dx, L.conv2d_dgrad(X, wt, (N, K, H, W), 1, 1))):
             assert np.isfinite(want).any() and not np.isfinite(want).all()
             _same_values(got.cpu().numpy(), want, "fwd or dgrad")
+
+
+# streamed 1x1 layers, forward and the data gradient of the layer with in- and output channels exchanged: the fewest pixels, a last
+# range and a last 32 pixels that are ragged, input channels that fill no 16, 64, 128 or 256, output channels that fill no 32 or 128,
+# and on either side of each limit
+#                     N   H   W   C    K   taken
+CONV1_CASES = [((64, 8, 8, 64, 128), True), ((65, 9, 7, 64, 128), False), ((66, 9, 7, 64, 128), True), ((1, 67, 71, 8, 136), True), ((5, 29, 31, 72, 200), True),
+               ((5, 29, 31, 104, 208), True), ((5, 29, 31, 104, 200), False), ((9, 23, 23, 136, 1000), True), ((9, 23, 23, 256, 512), True),
+               ((9, 23, 23, 264, 528), False), ((4097, 1, 1, 16, 152), True), ((70, 9, 7, 56, 120), False)]
+
+
+@pytest.mark.parametrize("case", CONV1_CASES)
+def test_conv_streamed_1x1(case):
+    print("case", case, flush=True)
+    (N, H, W, C, K), taken = case
+    x, w, _ = _tensors((N, H, W, C, K, 1, 1, 0), 24)
+    x, w = _bf16_exact(x), _bf16_exact(w)
+    dev = lambda a: _nhwc(a).to(torch.bfloat16)
+    xd, wd, wtd = dev(x), dev(w), dev(np.ascontiguousarray(w.transpose(1, 0, 2, 3)))
+    (y, dx), ran = _launched(lambda: (R.conv2d_forward(xd, wd, 1, 0), R.conv2d_dgrad(xd, wtd, (N, H, W, K), 1, 0)))
+    assert len([n for n in ran if n.startswith("conv1_")]) == (2 if taken else 0), ran
+    want = L.conv2d_fwd(x, w, 1, 0)
+    for got in (y, dx):   # the data gradient of the exchanged layer is the same product
+        np.testing.assert_allclose(got.float().cpu().numpy().transpose(0, 3, 1, 2), want, rtol=2.0 ** -8, atol=1e-5)
