@@ -12,6 +12,8 @@
 // (one 16-byte access) and all arithmetic is fp32 / fp64.
 #include <algorithm>
 
+#include <hip/hip_ext.h>
+
 #include "elem.h"
 #include "internal.h"
 
@@ -445,7 +447,7 @@ void launch_final(const S *sums, int parts, int C, const BnBufs &b, hipStream_t 
 
 template <typename T>
 void launch_bwd(int mode, dim3 gp, dim3 ga, hipStream_t st, const void *g, const void *y, int64_t M, int C,
-                const ColMap &m, const BnBufs &b, double *scratch, const BwdApplyArgs &p, int parts, const float *pre_sums) {
+                const ColMap &m, const BnBufs &b, double *scratch, const BwdApplyArgs &p, int parts, const float *pre_sums, hipEvent_t done) {
   const T *gg = (const T *)g, *yy = (const T *)y;
 #define RESIST_BN_BWD(MODE)                                                                                              \
   if (pre_sums) {                                                                                                        \
@@ -455,7 +457,8 @@ void launch_bwd(int mode, dim3 gp, dim3 ga, hipStream_t st, const void *g, const
                        b.mean, b.invstd, b.scale, b.shift, scratch);                                                    \
     launch_final<double>(scratch, parts, C, b, st);                                                                      \
   }                                                                                                                      \
-  hipLaunchKernelGGL((bn_bwd_apply_kernel<T, MODE>), ga, dim3(kThreads), 0, st, p);
+  if (done) hipExtLaunchKernelGGL((bn_bwd_apply_kernel<T, MODE>), ga, dim3(kThreads), 0, st, nullptr, done, 0, p);                       \
+  else hipLaunchKernelGGL((bn_bwd_apply_kernel<T, MODE>), ga, dim3(kThreads), 0, st, p);
   if (mode == kMaskSelf) { RESIST_BN_BWD(kMaskSelf) }
   else { RESIST_BN_BWD(kMaskNone) }
 #undef RESIST_BN_BWD
@@ -539,7 +542,7 @@ int bn_apply(int dt, const void *y, int64_t M, int C, const BnBufs &b, const voi
 }
 
 int bn_backward(int dt, const void *g, bool relu_of_self, const void *y, int64_t M, int C, const BnBufs &b, void *dy,
-                const void *addend, double *scratch, hipStream_t st, const float *pre_sums, StatParts pre) {
+                const void *addend, double *scratch, hipStream_t st, const float *pre_sums, StatParts pre, hipEvent_t done) {
   RESIST_TRY(check_bn(dt, M, C));
   const ColMap m = col_map(C, vec_of(dt));
   if (pre_sums && (pre.parts < 1 || pre.rows < 1 || (long long)pre.parts * pre.rows < M ||
@@ -554,8 +557,8 @@ int bn_backward(int dt, const void *g, bool relu_of_self, const void *y, int64_t
   p.dgamma = b.dgamma; p.dbeta = b.dbeta; p.dy = dy;
   p.M = M; p.C = C; p.tpr = m.tpr; p.rpp = m.rpp;
   const dim3 gp(parts, m.ctiles), ga(apply_grid_x(M, m, 4), m.ctiles);
-  if (dt == DT_BF16) launch_bwd<__bf16>(mode, gp, ga, st, g, y, M, C, m, b, scratch, p, parts, pre_sums);
-  else launch_bwd<float>(mode, gp, ga, st, g, y, M, C, m, b, scratch, p, parts, pre_sums);
+  if (dt == DT_BF16) launch_bwd<__bf16>(mode, gp, ga, st, g, y, M, C, m, b, scratch, p, parts, pre_sums, done);
+  else launch_bwd<float>(mode, gp, ga, st, g, y, M, C, m, b, scratch, p, parts, pre_sums, done);
   RESIST_CHECK_LAUNCH("bn_backward");
   return RESIST_OK;
 }

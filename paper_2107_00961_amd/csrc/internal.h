@@ -51,6 +51,8 @@ class SideStream {
   hipStream_t stream() const { return side_ ? side_ : main_; }   // where the off-path work goes
   hipStream_t main() const { return main_; }
   int fork();                     // the side stream waits for everything enqueued on the main stream so far
+  hipEvent_t kernel_event();      // an event for a kernel of the main stream to carry (NULL: launch it as ever, and fork)
+  int fork_from(hipEvent_t ev);   // the side stream waits for that kernel (and all before it)
   int mark(hipEvent_t *ev);       // *ev: completes when everything enqueued on the side stream so far has
   int main_wait(hipEvent_t ev);   // the main stream waits for ev (NULL: nothing to wait for)
   int join();                     // the main stream waits for everything enqueued on the side stream
@@ -216,7 +218,7 @@ int bn_apply(int dt, const void *y, int64_t M, int C, const BnBufs &b, const voi
 // ([2][pre.parts][C] floats, see conv_dgrad); then only the per-channel totals and the second pass run.
 int bn_backward(int dt, const void *g, bool relu_of_self, const void *y, int64_t M, int C, const BnBufs &b, void *dy,
                 const void *addend, double *scratch, hipStream_t st, const float *pre_sums = nullptr,
-                StatParts pre = StatParts{});
+                StatParts pre = StatParts{}, hipEvent_t done = nullptr);   // done: completes with its last kernel
 struct BnBwdFuse {
   const void *y;        // the BN's input, [M][C] in the compute type
   BnBufs b;             // mean, invstd, scale, shift are read

@@ -76,6 +76,20 @@ int SideStream::fork() {
   return RESIST_OK;
 }
 
+hipEvent_t SideStream::kernel_event() {
+  // (a stream that is being captured takes no kernel of this kind)
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (!side_ || hipStreamIsCapturing(main_, &c) != hipSuccess || c != hipStreamCaptureStatusNone) return nullptr;
+  return take();
+}
+
+int SideStream::fork_from(hipEvent_t ev) {
+  if (!side_) return RESIST_OK;
+  if (!ev) return fork();
+  RESIST_CHECK_HIP(hipStreamWaitEvent(side_, ev, 0));
+  return RESIST_OK;
+}
+
 int SideStream::mark(hipEvent_t *ev) {
   *ev = nullptr;
   if (!side_) return RESIST_OK;

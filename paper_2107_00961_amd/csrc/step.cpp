@@ -17,43 +17,74 @@ inline double geom_flops(const ConvGeom &g) { return 2.0 * g.N * g.P * g.Q * g.K
 // chain data gradient -> BN backward -> next layer, whose short kernels then overlap with them.  A
 // weight gradient starts once its output gradient is complete (fork), and a buffer it reads is not
 // overwritten before it has finished (before_write).
+constexpr int kDyRing = 6;
 struct WgradSide {
   SideStream side;
   int dt;
   bool beside;   // by the work of the step alone: with the second stream switched off the sums have the same order
   float *splitk;
-  std::vector<std::pair<const void *, hipEvent_t>> readers;   // buffer -> its last reader on the side stream
+  // The side stream runs in order, so its weight gradients are numbered and a wait for one covers all
+  // before it.  An event costs a packet in its stream and 5 us of the host, a wait 6 us of the chain:
+  // every second weight gradient leaves an event, and a buffer's writer waits, if no earlier wait covers
+  // the buffer's last reader, for the fourth last weight gradient of all.  (us, CIFAR-shaped
+  // pre-activation sub-ResNet, batch 77: fourth last 3163, third 3211, second 3232; an event behind every
+  // weight gradient, two buffers and waits for the last reader 3187, and 33 blocks in bf16 4922 for 4856.)
+  int launched = 0, waited = 0;
+  std::vector<std::pair<const void *, int>> readers;   // buffer -> its last reader
+  std::vector<std::pair<int, hipEvent_t>> marks;       // events behind weight gradients, ascending
   // `flops`: convolution work of the step.  Below ~20 GFLOP a step is bound by launch latency and the
   // event calls of the second stream cost more than the overlap returns: everything stays on `main`.
   WgradSide(hipStream_t main, int dt_, float *splitk_, double flops)
       : side(main, overlap_mode() == 2 || (overlap_mode() == 1 && flops >= 2e10)), dt(dt_), beside(flops >= 2e10), splitk(splitk_) {}
   hipStream_t stream() const { return side.stream(); }
-  int launch(const ConvGeom &g, const void *dyb, const void *xin, float *dw) {
-    RESIST_TRY(side.fork());
-    RESIST_TRY(conv_wgrad(g, dt, dyb, xin, dw, splitk, side.stream(), beside));
+  int mark() {
     hipEvent_t e = nullptr;
     RESIST_TRY(side.mark(&e));
-    for (auto &r : readers)
-      if (r.first == dyb) { r.second = e; return RESIST_OK; }
-    readers.emplace_back(dyb, e);
+    marks.emplace_back(launched, e);
     return RESIST_OK;
+  }
+  int read_by_last(const void *buf) {
+    ++launched;
+    bool known = false;
+    for (auto &r : readers)
+      if (r.first == buf) { r.second = launched; known = true; }
+    if (!known) readers.emplace_back(buf, launched);
+    return launched % 2 ? RESIST_OK : mark();
+  }
+  // ready: the event its output gradient's last kernel carries
+  int launch(const ConvGeom &g, const void *dyb, const void *xin, float *dw, hipEvent_t ready = nullptr) {
+    RESIST_TRY(side.fork_from(ready));
+    RESIST_TRY(conv_wgrad(g, dt, dyb, xin, dw, splitk, side.stream(), beside));
+    return read_by_last(dyb);
   }
   // the stem's weight gradient (implicit GEMM on the input image), same ordering rules
-  int launch_stem(const Net &net, int N, int kpad, const void *dyb, const float *x, float *dwpad) {
-    RESIST_TRY(side.fork());
+  int launch_stem(const Net &net, int N, int kpad, const void *dyb, const float *x, float *dwpad, hipEvent_t ready = nullptr) {
+    RESIST_TRY(side.fork_from(ready));
     RESIST_TRY(stem_conv_wgrad(dt, dyb, x, dwpad, splitk, N, net.d.in_c, net.d.in_h, net.d.in_w, net.d.width[0], net.stem_rs,
                                net.stem_stride, net.stem_pad, net.stem_h, net.stem_w, kpad, side.stream()));
-    hipEvent_t e = nullptr;
-    RESIST_TRY(side.mark(&e));
-    for (auto &r : readers)
-      if (r.first == dyb) { r.second = e; return RESIST_OK; }
-    readers.emplace_back(dyb, e);
-    return RESIST_OK;
+    return read_by_last(dyb);
   }
   int before_write(const void *buf) {
+    int reader = 0;
     for (auto &r : readers)
-      if (r.first == buf && r.second) { RESIST_TRY(side.main_wait(r.second)); r.second = nullptr; }
+      if (r.first == buf) reader = r.second;
+    if (!side.on() || reader <= waited) return RESIST_OK;
+    const int want = std::max(reader, launched - 3);
+    if (marks.empty() || marks.back().first < want) RESIST_TRY(mark());   // behind all so far
+    for (auto &m : marks)
+      if (m.first >= want) {
+        waited = m.first;
+        return side.main_wait(m.second);
+      }
     return RESIST_OK;
+  }
+  // output gradients take turns in a ring of buffers
+  void *const *dys = nullptr;
+  int next_dy = 0;
+  int take_dy(void **buf) {
+    *buf = dys[next_dy];
+    next_dy = (next_dy + 1) % kDyRing;
+    return before_write(*buf);
   }
   // Filters as the convolutions read them.  What the forward pass multiplies is made first, on the caller's stream; in fp32 mode
   // what only the data gradients read, on the side stream while the forward runs.
@@ -162,7 +193,7 @@ struct StepPlan {
   const void *feat = nullptr;
   int feat_hw = 0;
   // shared scratch
-  void *gbuf[2] = {nullptr, nullptr}, *gm = nullptr, *dy0 = nullptr, *dy1 = nullptr, *da = nullptr;
+  void *gbuf[2] = {nullptr, nullptr}, *gm = nullptr, *dys[kDyRing] = {}, *da = nullptr;
   float *splitk = nullptr;
   float *stats = nullptr;             // per-tile column sums left by a forward convolution
   double *bn_scratch = nullptr;
@@ -338,8 +369,7 @@ int build_plan(const resist_model_desc *desc, const int32_t *blocks, int32_t nbl
   P->gbuf[0] = A.take_act(max_act, es);
   P->gbuf[1] = A.take_act(max_act, es);
   P->gm = A.take_act(max_act, es);
-  P->dy0 = A.take_act(max_act, es);
-  P->dy1 = A.take_act(max_act, es);
+  for (void *&p : P->dys) p = A.take_act(max_act, es);
   P->da = A.take_act(max_act, es);
   P->splitk = A.take<float>(max_splitk);
   P->stats = A.take<float>(max_stats);
@@ -510,7 +540,7 @@ struct PrePlan {
   float *pooled = nullptr, *z = nullptr, *dz = nullptr, *row_loss = nullptr, *dpooled = nullptr;
   const void *feat_in = nullptr;
   int feat_hw = 0;
-  void *gbuf[2] = {nullptr, nullptr}, *sc = nullptr, *dsgrad = nullptr, *dy0 = nullptr, *dy1 = nullptr, *da = nullptr;
+  void *gbuf[2] = {nullptr, nullptr}, *sc = nullptr, *dsgrad = nullptr, *dys[kDyRing] = {}, *da = nullptr;
   float *splitk = nullptr, *stats = nullptr;
   double *bn_scratch = nullptr;
   std::vector<float *> own_grads;
@@ -621,8 +651,7 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
   P->gbuf[1] = A.take_act(max_act, es);
   P->sc = A.take_act(max_act, es);
   P->dsgrad = A.take_act(max_act, es);
-  P->dy0 = A.take_act(max_act, es);
-  P->dy1 = A.take_act(max_act, es);
+  for (void *&p : P->dys) p = A.take_act(max_act, es);
   P->da = A.take_act(max_act, es);
   P->splitk = A.take<float>(max_splitk);
   P->stats = A.take<float>(max_stats);
@@ -717,39 +746,43 @@ int local_step_preact(const resist_model_desc *desc, const int32_t *blocks, int3
   RESIST_TRY(avgpool_bwd(dt, P.dpooled, nullptr, P.da, N, P.feat_hw, CH, st));
   int gi = 0;
   RESIST_TRY(wg.filters_ready());
-  RESIST_TRY(bn_backward(dt, P.da, true, P.feat_in, P.head_rows, CH, hb, P.gbuf[gi], nullptr, P.bn_scratch, st));
+  wg.dys = P.dys;
+  hipEvent_t ready = wg.side.kernel_event();   // carried by the last kernel that writes what the next weight gradient reads
+  RESIST_TRY(bn_backward(dt, P.da, true, P.feat_in, P.head_rows, CH, hb, P.gbuf[gi], nullptr, P.bn_scratch, st, nullptr, StatParts{}, ready));
   for (int bi = (int)P.blocks.size() - 1; bi >= 0; --bi) {
     PreBlock &pb = P.blocks[bi];
     float *pp = params(pb.slot), *gg = grads(pb.slot);
     void *G = P.gbuf[gi], *Gn = P.gbuf[gi ^ 1];
     const void *gcur = G;
-    void *dy = P.dy0, *dy_other = P.dy1;
     for (int j = (int)pb.units.size() - 1; j >= 0; --j) {
       PreUnit &un = pb.units[j];
-      RESIST_TRY(wg.launch(un.g, gcur, un.a, gg + un.w_off));
+      RESIST_TRY(wg.launch(un.g, gcur, un.a, gg + un.w_off, ready));
       const void *addend = nullptr;
       if (j == 0 && pb.has_ds) {
         // the shortcut convolution reads the same a_1: its data gradient joins the branch's
-        RESIST_TRY(wg.launch(pb.dsg, G, un.a, gg + pb.ds_w_off));
+        RESIST_TRY(wg.launch(pb.dsg, G, un.a, gg + pb.ds_w_off, ready));   // (G is older than what `ready` says)
         RESIST_TRY(conv_dgrad(pb.dsg, dt, G, pb.ds_f.dgrad(pp + pb.ds_w_off), P.dsgrad, nullptr, nullptr, st));
         addend = P.dsgrad;
       }
       RESIST_TRY(conv_dgrad(un.g, dt, gcur, un.f.dgrad(pp + un.w_off), P.da, addend, nullptr, st));
       BnBufs b = pre_bn_bufs(un, pp, gg);
       if (j > 0) {
-        RESIST_TRY(wg.before_write(dy));
-        RESIST_TRY(bn_backward(dt, P.da, true, un.u, un.rows(), un.g.C, b, dy, nullptr, P.bn_scratch, st));
+        void *dy = nullptr;
+        RESIST_TRY(wg.take_dy(&dy));
+        ready = wg.side.kernel_event();
+        RESIST_TRY(bn_backward(dt, P.da, true, un.u, un.rows(), un.g.C, b, dy, nullptr, P.bn_scratch, st, nullptr, StatParts{}, ready));
         gcur = dy;
-        std::swap(dy, dy_other);
       } else {
         // gradient w.r.t. the block input: through BN_1, plus the identity shortcut's share
         RESIST_TRY(wg.before_write(Gn));
-        RESIST_TRY(bn_backward(dt, P.da, true, un.u, un.rows(), un.g.C, b, Gn, pb.has_ds ? nullptr : G, P.bn_scratch, st));
+        ready = wg.side.kernel_event();
+        RESIST_TRY(bn_backward(dt, P.da, true, un.u, un.rows(), un.g.C, b, Gn, pb.has_ds ? nullptr : G, P.bn_scratch, st, nullptr,
+                               StatParts{}, ready));
       }
     }
     gi ^= 1;
   }
-  RESIST_TRY(wg.launch_stem(net, N, P.kpad, P.gbuf[gi], x, P.dwpad));
+  RESIST_TRY(wg.launch_stem(net, N, P.kpad, P.gbuf[gi], x, P.dwpad, ready));
   RESIST_TRY(unpad_rows_f32(P.dwpad, grads(0) + P.stem_w_off, K0, taps, P.kpad, wg.stream()));
   RESIST_TRY(wg.join());
 
@@ -929,6 +962,7 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
   const bool fuse_bn = bn_fusion_mode() == 2 || (bn_fusion_mode() == 1 && dt == DT_BF16);
   StatParts pre{};        // P.stats holds the first pass for the BN that ends the block below
   bool have_pre = false;
+  wg.dys = P.dys;
   int gi = 0;
   void *G = P.gbuf[gi];
   RESIST_TRY(avgpool_bwd(dt, P.dpooled, P.feat, G, N, P.feat_hw, CH, st));
@@ -940,23 +974,25 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
     ConvLayer &last = bp.convs[nc - 1];
     BnBufs bl = bn_bufs(last, pp, gg);
     // the last BN of the residual branch
-    RESIST_TRY(wg.before_write(P.dy0));
-    RESIST_TRY(bn_backward(dt, G, false, last.y, last.M(), last.g.K, bl, P.dy0, nullptr, P.bn_scratch, st,
-                           have_pre ? P.stats : nullptr, pre));
+    void *dy = nullptr;
+    RESIST_TRY(wg.take_dy(&dy));
+    hipEvent_t ready = wg.side.kernel_event();   // carried by the last kernel that writes what the next weight gradient reads
+    RESIST_TRY(bn_backward(dt, G, false, last.y, last.M(), last.g.K, bl, dy, nullptr, P.bn_scratch, st,
+                           have_pre ? P.stats : nullptr, pre, ready));
     have_pre = false;
     if (bp.has_ds) {
       // shortcut branch: BN and 1x1 convolution; its data gradient initialises Gn
       ConvLayer &d = bp.ds;
       BnBufs bd = bn_bufs(d, pp, gg);
       RESIST_TRY(wg.before_write(P.gm));
-      RESIST_TRY(bn_backward(dt, G, false, d.y, d.M(), d.g.K, bd, P.gm, nullptr, P.bn_scratch, st));
-      RESIST_TRY(wg.launch(d.g, P.gm, d.in, gg + d.w_off));
+      const hipEvent_t ds_ready = wg.side.kernel_event();
+      RESIST_TRY(bn_backward(dt, G, false, d.y, d.M(), d.g.K, bd, P.gm, nullptr, P.bn_scratch, st, nullptr, StatParts{}, ds_ready));
+      RESIST_TRY(wg.launch(d.g, P.gm, d.in, gg + d.w_off, ds_ready));
       RESIST_TRY(conv_dgrad(d.g, dt, P.gm, d.f.dgrad(pp + d.w_off), Gn, nullptr, nullptr, st));
     }
-    void *dy = P.dy0, *dy_other = P.dy1;
     for (int j = nc - 1; j >= 0; --j) {
       ConvLayer &c = bp.convs[j];
-      RESIST_TRY(wg.launch(c.g, dy, c.in, gg + c.w_off));
+      RESIST_TRY(wg.launch(c.g, dy, c.in, gg + c.w_off, ready));
       if (j > 0) {
         ConvLayer &prev = bp.convs[j - 1];
         BnBufs bp_ = bn_bufs(prev, pp, gg);
@@ -964,10 +1000,10 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
         const BnBwdFuse f{prev.y, bp_, true, P.stats, &sp};
         const bool fz = fuse_bn && c.g.stride == 1;
         RESIST_TRY(conv_dgrad(c.g, dt, dy, c.f.dgrad(pp + c.w_off), P.da, nullptr, nullptr, st, fz ? &f : nullptr));
-        RESIST_TRY(wg.before_write(dy_other));
-        RESIST_TRY(bn_backward(dt, P.da, true, prev.y, prev.M(), prev.g.K, bp_, dy_other, nullptr, P.bn_scratch, st,
-                               fz ? P.stats : nullptr, sp));
-        std::swap(dy, dy_other);
+        RESIST_TRY(wg.take_dy(&dy));
+        ready = wg.side.kernel_event();
+        RESIST_TRY(bn_backward(dt, P.da, true, prev.y, prev.M(), prev.g.K, bp_, dy, nullptr, P.bn_scratch, st,
+                               fz ? P.stats : nullptr, sp, ready));
       } else {
         // gradient w.r.t. the block input = branch + shortcut (the identity shortcut passes G itself),
         // taken through the ReLU that ends the block before (the stem's ReLU is handled by its own BN backward)
@@ -997,9 +1033,11 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
       Gs = P.da;
     }
     BnBufs b = bn_bufs(s, params(0), grads(0));
-    RESIST_TRY(wg.before_write(P.dy0));
-    RESIST_TRY(bn_backward(dt, Gs, true, s.y, s.M(), K0, b, P.dy0, nullptr, P.bn_scratch, st));
-    RESIST_TRY(wg.launch_stem(net, N, P.kpad, P.dy0, x, P.dwpad));
+    void *dy = nullptr;
+    RESIST_TRY(wg.take_dy(&dy));
+    const hipEvent_t ready = wg.side.kernel_event();
+    RESIST_TRY(bn_backward(dt, Gs, true, s.y, s.M(), K0, b, dy, nullptr, P.bn_scratch, st, nullptr, StatParts{}, ready));
+    RESIST_TRY(wg.launch_stem(net, N, P.kpad, dy, x, P.dwpad, ready));
     RESIST_TRY(unpad_rows_f32(P.dwpad, grads(0) + s.w_off, K0, taps, P.kpad, wg.stream()));
   }
   RESIST_TRY(wg.join());
