@@ -436,13 +436,14 @@ int64_t conv_dgrad_bn_sums_floats(const ConvGeom &g) {
 // All filters of a step in one launch (or a few: the table travels in the kernel arguments).
 namespace {
 constexpr int kPrepSegs = 48;
-struct PrepTable {
-  const void *w[kPrepSegs];
-  void *wlp[kPrepSegs];
-  void *wT[kPrepSegs];
-  int K[kPrepSegs], RS[kPrepSegs], C[kPrepSegs];
-  float scale[kPrepSegs];
-  int first_wg[kPrepSegs + 1];
+// (a table of one for a single filter: shorter arguments and no search, 3.5 instead of 4.1 us for 256x80x3x3 in bf16)
+template <int N> struct PrepTable {
+  const void *w[N];
+  void *wlp[N];
+  void *wT[N];
+  int K[N], RS[N], C[N];
+  float scale[N];
+  int first_wg[N + 1];
   unsigned long long frag_copy, frag_transpose;   // bit per filter: in matrix fragments (conv3.hip) instead of rows
   int nseg;
 };
@@ -495,12 +496,12 @@ __device__ inline void store_fragments(void *out, int octiles, int chunks, int o
 
 // One 64x64 tile of the [K][C] matrix of one tap per workgroup, through LDS so that both sides move whole
 // vectors: 256-byte runs of the fp32 master in, 4-element vectors of the copy and of the transpose out.
-template <typename S, typename T>
-__global__ __launch_bounds__(256) void prepare_filters_kernel(PrepTable t) {
+template <typename S, typename T, int N>
+__global__ __launch_bounds__(256) void prepare_filters_kernel(PrepTable<N> t) {
   constexpr int TS = 64;
   __shared__ float tile[TS][TS + 1];
   int seg = 0;
-  while (seg + 1 < t.nseg && (int)blockIdx.x >= t.first_wg[seg + 1]) ++seg;
+  while (N > 1 && seg + 1 < t.nseg && (int)blockIdx.x >= t.first_wg[seg + 1]) ++seg;
   const int K = t.K[seg], RS = t.RS[seg], C = t.C[seg];
   const int ct = (C + TS - 1) / TS, kt = (K + TS - 1) / TS;
   int id = blockIdx.x - t.first_wg[seg];
@@ -542,16 +543,15 @@ __global__ __launch_bounds__(256) void prepare_filters_kernel(PrepTable t) {
     }
   }
 }
-}  // namespace
 
-int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st, int src_dt) {
-  if (src_dt == DT_BF16 && dt != DT_BF16) return set_error(RESIST_EINVAL, "prepare_filters: bf16 source needs a bf16 target");
+template <int N>
+int prepare_launch(const std::vector<FilterPrep> &items, int dt, hipStream_t st, int src_dt) {
   size_t i = 0;
   while (i < items.size()) {
-    PrepTable t{};
+    PrepTable<N> t{};
     int wg = 0;
     double bytes = 0;
-    while (i < items.size() && t.nseg < kPrepSegs) {
+    while (i < items.size() && t.nseg < N) {
       const FilterPrep &f = items[i++];
       if ((f.g.K & 3) || (f.g.C & 3)) return set_error(RESIST_ESHAPE, "filter %dx%d: channel counts must be multiples of 4", f.g.K, f.g.C);
       if (!f.w_lp && !f.wT) continue;
@@ -568,12 +568,18 @@ int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st
     t.first_wg[t.nseg] = wg;
     if (wg == 0) continue;
     prof::Scope ps("prepare_filters", 0, bytes, st);
-    if (src_dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<__bf16, __bf16>), dim3(wg), dim3(256), 0, st, t);
-    else if (dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<float, __bf16>), dim3(wg), dim3(256), 0, st, t);
-    else hipLaunchKernelGGL((prepare_filters_kernel<float, float>), dim3(wg), dim3(256), 0, st, t);
+    if (src_dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<__bf16, __bf16, N>), dim3(wg), dim3(256), 0, st, t);
+    else if (dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<float, __bf16, N>), dim3(wg), dim3(256), 0, st, t);
+    else hipLaunchKernelGGL((prepare_filters_kernel<float, float, N>), dim3(wg), dim3(256), 0, st, t);
     RESIST_CHECK_LAUNCH("prepare_filters");
   }
   return RESIST_OK;
+}
+}  // namespace
+
+int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st, int src_dt) {
+  if (src_dt == DT_BF16 && dt != DT_BF16) return set_error(RESIST_EINVAL, "prepare_filters: bf16 source needs a bf16 target");
+  return items.size() == 1 ? prepare_launch<1>(items, dt, st, src_dt) : prepare_launch<kPrepSegs>(items, dt, st, src_dt);
 }
 
 // ---- wgrad --------------------------------------------------------------------------------------
