@@ -7,6 +7,8 @@
 // float of the block buffer (a byte each for b > 4, a nibble each for b <= 4).  All kernels stream
 // through HBM once; the reassembly kernel reads b-bit codes instead of fp32 copies and decodes them
 // on the fly, so its traffic per parameter drops from 4*(count+1) to count*(1 or 1/2) + 4 bytes.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace resist {
@@ -17,29 +19,30 @@ namespace {
 
 constexpr int kChunk = 4096;  // floats per workgroup (256 threads x 4 vectors of 4)
 constexpr int kMaxT = 24;     // most tensors in one block buffer (bottleneck block with shortcut: 20)
-constexpr int kQSegs = 16;    // blocks per launch of the compression kernels
-constexpr int kSub = 8;       // chunks one workgroup of the min/max kernel walks
+constexpr int kQSegs = 36;    // blocks per launch of the compression kernels
+constexpr int kLayouts = 12;  // different block layouts per launch (four stages, with and without a shortcut, stem and head: at most 10)
 
 struct QRange { float lo, delta; int begin, end; };
 static_assert(sizeof(QRange) == sizeof(resist_qrange), "header record layout");
 
-// order-preserving map float -> int, so that integer atomic min / max order floats
+// order-preserving map float -> int, so that integer min / max order floats
 __device__ inline int f2ord(float f) {
   const int b = __float_as_int(f);
   return b >= 0 ? b : b ^ 0x7fffffff;
 }
 __device__ inline float ord2f(int o) { return __int_as_float(o >= 0 ? o : o ^ 0x7fffffff); }
 
+// Blocks of one shape share a layout, so that the blocks of a whole model fit one set of launches.
 struct QuantTable {
   const float *src[kQSegs];
   unsigned char *codes[kQSegs];
   QRange *ranges[kQSegs];
   int n[kQSegs];
-  int nt[kQSegs];
-  int begin[kQSegs][kMaxT];
-  int end[kQSegs][kMaxT];
-  int first_wg[kQSegs + 1];      // encode kernel: one workgroup per chunk
-  int first_wg_mm[kQSegs + 1];   // min/max kernel: one workgroup per kSub chunks
+  int layout[kQSegs];
+  int begin[kLayouts][kMaxT];
+  int end[kLayouts][kMaxT];
+  int nt[kLayouts];
+  int first_wg[kQSegs + 1];   // one workgroup per kChunk floats
   int nseg;
   int levels;   // 2^b - 1
   int nibble;   // two codes per byte
@@ -55,36 +58,47 @@ __device__ inline int find_seg(const int *first_wg, int nseg) {
   return __popcll(__ballot(past));
 }
 
-// header records with the running minimum / maximum in their order-preserving integer form
-__global__ __launch_bounds__(64) void quant_init_kernel(QuantTable t) {
-  const int seg = blockIdx.x, j = threadIdx.x;
-  if (j >= t.nt[seg]) return;
-  int *rec = reinterpret_cast<int *>(t.ranges[seg] + j);
-  rec[0] = f2ord(__int_as_float(0x7f800000));   // +inf
-  rec[1] = f2ord(__int_as_float(0xff800000));   // -inf
-  rec[2] = t.begin[seg][j];
-  rec[3] = t.end[seg][j];
+__device__ inline QRange final_record(int mn, int mx, int begin, int end, int levels) {
+  const float lo = ord2f(mn), hi = ord2f(mx);
+  return QRange{lo, (hi - lo) / (float)levels, begin, end};
 }
 
-// Minimum and maximum of every tensor.  A workgroup walks kSub consecutive chunks and keeps
-// per-thread running values as long as the chunks lie inside one tensor, so that a large tensor
-// receives one pair of atomics per kSub chunks: device-wide atomics on one address execute one after
-// the other at the memory side, and a pair per chunk made them the bottleneck of this kernel.
-
+// Minimum and maximum of every tensor, without atomics: a tensor inside one workgroup's chunk gets its record at once; of a
+// tensor that reaches over chunks every workgroup leaves its part, in order-preserving integers, in the code buffer, which is
+// written only afterwards.  At most two such tensors meet a chunk, the one that comes in from the left (part 0) and the one that
+// leaves on the right (part 1): 16 bytes per workgroup from the buffer's start, and a buffer of several chunks has over 2 KiB.
+// Bound by HBM: reading 63 MB that no cache holds makes room in the memory-side cache, which writes as much back.  us for 63 MB
+// (one worker) and 177 MB (the whole 33-block model): chunks of 2 Ki floats 19 and 34, 4 Ki 20 and 34, 8 Ki 27 and 43, contiguous
+// chunks per XCD no better; 32 Ki floats walked with a pair of atomics each, in launches of 16 blocks: 20 and 3 x 19, and two
+// header launches where the merge below is one (63 MB: 6.3 -> 4.3 us).
 __global__ __launch_bounds__(256) void quant_minmax_kernel(QuantTable t) {
   __shared__ float red[2][4];
-  const int seg = find_seg(t.first_wg_mm, t.nseg);
-  const int wg_base = (blockIdx.x - t.first_wg_mm[seg]) * (kChunk * kSub);
+  const int seg = __builtin_amdgcn_readfirstlane(find_seg(t.first_wg, t.nseg));
+  const int wg = blockIdx.x - t.first_wg[seg], base = wg * kChunk;
   const float *src = t.src[seg];
-  const int n = t.n[seg];
+  const int n = t.n[seg], lay = t.layout[seg], nt = t.nt[lay];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nt = t.nt[seg];
+  float v[4][4];
+  if (base + kChunk <= n) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const f32x4 x = *reinterpret_cast<const f32x4 *>(src + base + (u * 256 + threadIdx.x) * 4);
+      v[u][0] = x[0]; v[u][1] = x[1]; v[u][2] = x[2]; v[u][3] = x[3];
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = base + (u * 256 + threadIdx.x) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[u][e] = i + e < n ? src[i + e] : 0.f;   // (what is past n lies in no tensor)
+    }
+  }
   int my_b = 0, my_e = 0;   // lane j holds the bounds of tensor j
-  if (lane < nt) { my_b = t.begin[seg][lane]; my_e = t.end[seg][lane]; }
+  if (lane < nt) { my_b = t.begin[lay][lane]; my_e = t.end[lay][lane]; }
   const float inf = __int_as_float(0x7f800000);
 
-  // workgroup reduction of (mn, mx) and one pair of atomics on the record of tensor tt
-  auto publish = [&](int tt, float mn, float mx) {
+  // workgroup reduction of (mn, mx) of tensor tt, [b, en)
+  auto publish = [&](int tt, int b, int en, float mn, float mx) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       mn = fminf(mn, __shfl_xor(mn, o));
@@ -95,126 +109,128 @@ __global__ __launch_bounds__(256) void quant_minmax_kernel(QuantTable t) {
     if (threadIdx.x == 0) {
       mn = fminf(fminf(red[0][0], red[0][1]), fminf(red[0][2], red[0][3]));
       mx = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
-      int *rec = reinterpret_cast<int *>(t.ranges[seg] + tt);
-      atomicMin(rec + 0, f2ord(mn));
-      atomicMax(rec + 1, f2ord(mx));
+      if (b >= base && en <= base + kChunk) {
+        t.ranges[seg][tt] = final_record(f2ord(mn), f2ord(mx), b, en, t.levels);
+      } else {
+        int *part = reinterpret_cast<int *>(t.codes[seg]) + 4 * wg + (b < base ? 0 : 2);
+        part[0] = f2ord(mn);
+        part[1] = f2ord(mx);
+      }
     }
     __syncthreads();
   };
-  auto load_chunk = [&](int base, float (&v)[4][4]) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = base + (u * 256 + threadIdx.x) * 4;
-      if (i + 3 < n) {
-        const f32x4 x = *reinterpret_cast<const f32x4 *>(src + i);
-        v[u][0] = x[0]; v[u][1] = x[1]; v[u][2] = x[2]; v[u][3] = x[3];
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[u][e] = (i + e < n) ? src[i + e] : 0.f;
-      }
-    }
-  };
-
-  int cur = -1;              // tensor the running values belong to (the same in every thread)
-  float run_mn = inf, run_mx = -inf;
-  float v[4][4], vn[4][4];
-  load_chunk(wg_base, v);
-  for (int c = 0; c < kSub; ++c) {
-    const int base = wg_base + c * kChunk;
-    if (base >= n) break;
-    if (c + 1 < kSub && base + kChunk < n) load_chunk(base + kChunk, vn);   // next chunk in flight meanwhile
-    unsigned long long todo = __ballot(lane < nt && my_e > base && my_b < base + kChunk);
-    const int first = __ffsll((long long)todo) - 1;
-    const bool whole = first >= 0 && (todo & (todo - 1)) == 0 && __shfl(my_b, first) <= base &&
-                       __shfl(my_e, first) >= base + kChunk;
-    if (whole) {               // the usual case: the chunk lies inside one tensor
-      if (first != cur) {
-        if (cur >= 0) publish(cur, run_mn, run_mx);
-        cur = first; run_mn = inf; run_mx = -inf;
-      }
+  unsigned long long todo = __ballot(lane < nt && my_e > my_b && my_e > base && my_b < base + kChunk);
+  while (todo) {
+    const int tt = __ffsll((long long)todo) - 1;
+    todo &= todo - 1;
+    const int b = __shfl(my_b, tt), en = __shfl(my_e, tt);
+    float mn = inf, mx = -inf;
+    if (b <= base && en >= base + kChunk) {   // the usual case: the range lies inside one tensor
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { run_mn = fminf(run_mn, v[u][e]); run_mx = fmaxf(run_mx, v[u][e]); }
+        for (int e = 0; e < 4; ++e) { mn = fminf(mn, v[u][e]); mx = fmaxf(mx, v[u][e]); }
     } else {
-      if (cur >= 0) { publish(cur, run_mn, run_mx); cur = -1; }
-      while (todo) {
-        const int tt = __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        const int b = __shfl(my_b, tt), en = __shfl(my_e, tt);
-        float mn = inf, mx = -inf;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = base + (u * 256 + threadIdx.x) * 4;
+      for (int u = 0; u < 4; ++u) {
+        const int i = base + (u * 256 + threadIdx.x) * 4;
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (i + e >= b && i + e < en) { mn = fminf(mn, v[u][e]); mx = fmaxf(mx, v[u][e]); }
-        }
-        publish(tt, mn, mx);
+        for (int e = 0; e < 4; ++e)
+          if (i + e >= b && i + e < en) { mn = fminf(mn, v[u][e]); mx = fmaxf(mx, v[u][e]); }
       }
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[u][e] = vn[u][e];
+    publish(tt, b, en, mn, mx);
   }
-  if (cur >= 0) publish(cur, run_mn, run_mx);
 }
 
-__global__ __launch_bounds__(256) void quant_encode_kernel(QuantTable t) {
-  __shared__ float s_lo[kMaxT], s_delta[kMaxT];
-  __shared__ int s_begin[kMaxT], s_end[kMaxT];
-  const int seg = find_seg(t.first_wg, t.nseg);
-  const int base = (blockIdx.x - t.first_wg[seg]) * kChunk;
+// Records of the tensors that reach over ranges (and of tensors without elements): a wave per tensor.
+__global__ __launch_bounds__(256) void quant_merge_kernel(QuantTable t) {
+  const int seg = blockIdx.x, lane = threadIdx.x & 63;
+  const int tt = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6));
+  const int lay = t.layout[seg];
+  if (tt >= t.nt[lay]) return;
+  const int b = t.begin[lay][tt], en = t.end[lay][tt];
+  const int first = b / kChunk, last = en > b ? (en - 1) / kChunk : first - 1;
+  if (first == last) return;
+  const int *parts = reinterpret_cast<const int *>(t.codes[seg]);
+  int mn = f2ord(__int_as_float(0x7f800000)), mx = f2ord(__int_as_float(0xff800000));
+#pragma unroll 4
+  for (int w = first + lane; w <= last; w += 64) {
+    const int *part = parts + 4 * w + (w == first ? 2 : 0);
+    mn = min(mn, part[0]);
+    mx = max(mx, part[1]);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    mn = min(mn, __shfl_xor(mn, o));
+    mx = max(mx, __shfl_xor(mx, o));
+  }
+  if (lane == 0) t.ranges[seg][tt] = final_record(mn, mx, b, en, t.levels);
+}
+
+// One chunk of kChunk floats; FULL: the chunk ends at or before n.  Floats and records are requested together.  The code is
+// rint of the rounded quotient (x - lo) / delta, but a division costs ten instructions: a product with 1 / delta is off by less
+// than 2^-22 of the quotient, 6.1e-5 at 255 levels, so that away from the middle between two codes both round alike, and only
+// there (one value in 5000) is divided.  Where 1 / delta is no normal number, or a value is not finite, the product is made NaN,
+// and everything is divided.  (63 MB of floats: 16.2 us, with every value divided 18.0; 177 MB: 31 us, in three launches 3 x 16.)
+template <bool FULL>
+__device__ __forceinline__ void encode_chunk(const QuantTable &t, int seg, int base, int n, float4 *s_par, int *s_end) {
   const float *src = t.src[seg];
   unsigned char *codes = t.codes[seg];
-  const int n = t.n[seg], nt = t.nt[seg];
+  const int nt = t.nt[t.layout[seg]];
   const float levels = (float)t.levels;
+  float x[4][4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int i = base + (u * 256 + threadIdx.x) * 4;
+    if (FULL) {
+      const f32x4 xv = *reinterpret_cast<const f32x4 *>(src + i);
+      x[u][0] = xv[0]; x[u][1] = xv[1]; x[u][2] = xv[2]; x[u][3] = xv[3];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[u][e] = i + e < n ? src[i + e] : 0.f;
+    }
+  }
   if ((int)threadIdx.x < nt) {
-    const int *rec = reinterpret_cast<const int *>(t.ranges[seg] + threadIdx.x);
-    const float lo = ord2f(rec[0]), hi = ord2f(rec[1]);
-    s_lo[threadIdx.x] = lo;
-    s_delta[threadIdx.x] = (hi - lo) / levels;
-    s_begin[threadIdx.x] = rec[2];
-    s_end[threadIdx.x] = rec[3];
+    const QRange r = t.ranges[seg][threadIdx.x];
+    const bool usual = r.delta >= 0x1p-100f && r.delta <= 0x1p100f;
+    s_par[threadIdx.x] = make_float4(r.lo, r.delta, usual ? 1.f / r.delta : __int_as_float(0x7fc00000), __int_as_float(r.begin));
+    s_end[threadIdx.x] = r.end;
   }
   __syncthreads();
   int tt = 0;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int i = base + (u * 256 + threadIdx.x) * 4;
-    if (i >= n) break;
-    float x[4];
-    if (i + 3 < n) {
-      const f32x4 xv = *reinterpret_cast<const f32x4 *>(src + i);
-      x[0] = xv[0]; x[1] = xv[1]; x[2] = xv[2]; x[3] = xv[3];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = (i + e < n) ? src[i + e] : 0.f;
-    }
+    if (!FULL && i >= n) break;
     // tensors start at multiples of 4 floats: the vector lies in one tensor or in the padding behind it
-    while (tt + 1 < nt && i >= s_begin[tt + 1]) ++tt;
+    while (tt + 1 < nt && i >= __float_as_int(s_par[tt + 1].w)) ++tt;
     const int live = min(s_end[tt], n) - i;
-    const float lo = s_lo[tt], d = s_delta[tt];
-    unsigned c[4];
+    const float lo = s_par[tt].x, d = s_par[tt].y, inv = s_par[tt].z;
+    float q[4];
+    bool close = false;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      c[e] = 0;
-      if (e < live && d != 0.f) {
-        float q = rintf((x[e] - lo) / d);
-        q = fminf(fmaxf(q, 0.f), levels);
-        c[e] = (unsigned)q;
-      }
+      const float p = (x[u][e] - lo) * inv;
+      q[e] = rintf(p);
+      close = close || !(fabsf(p - q[e]) < 0.4999f);
     }
+    if (close) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[e] = rintf((x[u][e] - lo) / d);
+    }
+    unsigned c[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c[e] = e < live && d != 0.f ? (unsigned)fminf(fmaxf(q[e], 0.f), levels) : 0u;
     if (t.nibble) {
-      if (i + 3 < n) {
+      if (FULL || i + 3 < n) {
         *reinterpret_cast<unsigned short *>(codes + (i >> 1)) = (unsigned short)(c[0] | (c[1] << 4) | (c[2] << 8) | (c[3] << 12));
       } else {
         codes[i >> 1] = (unsigned char)(c[0] | (c[1] << 4));   // elements past n were given code 0
         if (i + 2 < n) codes[(i >> 1) + 1] = (unsigned char)(c[2] | (c[3] << 4));
       }
     } else {
-      if (i + 3 < n) {
+      if (FULL || i + 3 < n) {
         *reinterpret_cast<unsigned *>(codes + i) = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
       } else {
 #pragma unroll
@@ -225,14 +241,14 @@ __global__ __launch_bounds__(256) void quant_encode_kernel(QuantTable t) {
   }
 }
 
-// header records into their final form {lo, delta, begin, end}
-__global__ __launch_bounds__(64) void quant_finish_kernel(QuantTable t) {
-  const int seg = blockIdx.x, j = threadIdx.x;
-  if (j >= t.nt[seg]) return;
-  int *rec = reinterpret_cast<int *>(t.ranges[seg] + j);
-  const float lo = ord2f(rec[0]), hi = ord2f(rec[1]);
-  reinterpret_cast<float *>(rec)[0] = lo;
-  reinterpret_cast<float *>(rec)[1] = (hi - lo) / (float)t.levels;
+__global__ __launch_bounds__(256) void quant_encode_kernel(QuantTable t) {
+  __shared__ float4 s_par[kMaxT];   // (lo, delta, 1 / delta, begin)
+  __shared__ int s_end[kMaxT];
+  const int seg = __builtin_amdgcn_readfirstlane(find_seg(t.first_wg, t.nseg));
+  const int base = (blockIdx.x - t.first_wg[seg]) * kChunk;
+  const int n = t.n[seg];
+  if (base + kChunk <= n) encode_chunk<true>(t, seg, base, n, s_par, s_end);
+  else encode_chunk<false>(t, seg, base, n, s_par, s_end);
 }
 
 // ---- reassembly from compressed copies ------------------------------------------------------
@@ -445,47 +461,49 @@ extern "C" int resist_compress_blocks(const resist_model_desc *desc, int32_t nke
     QuantTable t{};
     t.levels = (1 << bits) - 1;
     t.nibble = bits <= 4;
-    int wg = 0, wg_mm = 0;
+    int wg = 0, layouts = 0;
     double nb = 0;
     for (; i < nkeys && t.nseg < kQSegs; ++i) {
       std::vector<int> b, e;
       int64_t n = 0;
       RESIST_TRY(tensor_ranges(net, keys[i], &b, &e, &n));
+      int lay = 0;
+      while (lay < layouts && !(t.nt[lay] == (int)b.size() && std::equal(b.begin(), b.end(), t.begin[lay]) &&
+                                std::equal(e.begin(), e.end(), t.end[lay])))
+        ++lay;
+      if (lay == kLayouts) break;   // the next set of launches
+      if (lay == layouts) {
+        t.nt[lay] = (int)b.size();
+        std::copy(b.begin(), b.end(), t.begin[lay]);
+        std::copy(e.begin(), e.end(), t.end[lay]);
+        ++layouts;
+      }
       const int k = t.nseg++;
       t.src[k] = (const float *)params[i];
       t.codes[k] = (unsigned char *)codes[i];
       t.ranges[k] = (QRange *)ranges[i];
       t.n[k] = (int)n;
-      t.nt[k] = (int)b.size();
-      for (size_t j = 0; j < b.size(); ++j) { t.begin[k][j] = b[j]; t.end[k][j] = e[j]; }
+      t.layout[k] = lay;
       t.first_wg[k] = wg;
       wg += (int)((n + kChunk - 1) / kChunk);
-      t.first_wg_mm[k] = wg_mm;
-      wg_mm += (int)((n + kChunk * kSub - 1) / (kChunk * kSub));
       nb += (double)n;
     }
     t.first_wg[t.nseg] = wg;
-    t.first_wg_mm[t.nseg] = wg_mm;
     if (wg == 0) continue;
     {
-      prof::Scope ps("compress_header", 0, 32.0 * kMaxT * t.nseg, st);
-      hipLaunchKernelGGL(quant_init_kernel, dim3(t.nseg), dim3(64), 0, st, t);
-      RESIST_CHECK_LAUNCH("quant_init");
+      prof::Scope ps("compress_minmax", 0, 4.0 * nb, st);
+      hipLaunchKernelGGL(quant_minmax_kernel, dim3(wg), dim3(256), 0, st, t);
+      RESIST_CHECK_LAUNCH("quant_minmax");
     }
     {
-      prof::Scope ps("compress_minmax", 0, 4.0 * nb, st);
-      hipLaunchKernelGGL(quant_minmax_kernel, dim3(wg_mm), dim3(256), 0, st, t);
-      RESIST_CHECK_LAUNCH("quant_minmax");
+      prof::Scope ps("compress_header", 0, 16.0 * wg + 16.0 * kMaxT * t.nseg, st);
+      hipLaunchKernelGGL(quant_merge_kernel, dim3(t.nseg, kMaxT / 4), dim3(256), 0, st, t);
+      RESIST_CHECK_LAUNCH("quant_merge");
     }
     {
       prof::Scope ps("compress_encode", 0, (4.0 + (t.nibble ? 0.5 : 1.0)) * nb, st);
       hipLaunchKernelGGL(quant_encode_kernel, dim3(wg), dim3(256), 0, st, t);
       RESIST_CHECK_LAUNCH("quant_encode");
-    }
-    {
-      prof::Scope ps("compress_header", 0, 32.0 * kMaxT * t.nseg, st);
-      hipLaunchKernelGGL(quant_finish_kernel, dim3(t.nseg), dim3(64), 0, st, t);
-      RESIST_CHECK_LAUNCH("quant_finish");
     }
   }
   return RESIST_OK;
@@ -513,7 +531,7 @@ extern "C" int resist_decompress_blocks(const resist_model_desc *desc, int32_t n
     g.nt = (int)b.size();
     g.n = n;
   }
-  return aggregate_compressed_launch<4>(segs, bits <= 4, (hipStream_t)hip_stream);   // one source per block: a plain decode
+  return aggregate_compressed_launch<1>(segs, bits <= 4, (hipStream_t)hip_stream);   // one source per block: a plain decode (4 sources' registers: 14.9 us for 63 MB, one's 14.2)
 }
 
 extern "C" int resist_aggregate_compressed(const resist_model_desc *desc, int32_t S, const int32_t *sub_offsets,

@@ -106,6 +106,38 @@ def test_decompress_blocks_is_the_oracle_decode_bit_for_bit(bits):
         assert not p.cpu().numpy()[~covered].any()
 
 
+@pytest.mark.parametrize("bits", [8, 5, 4, 2])
+def test_codes_of_large_and_awkward_tensors(bits):
+    """Tensors over up to ten chunks of 4096 floats, more blocks than one set of launches takes (36), and
+    values for which a product with 1 / delta would not do: exactly between two codes, with a delta
+    that is subnormal or so large that 1 / delta is, one value apart from all others.  Bit-exact."""
+    model = dict(get_config("cfg1")["model"], widths=[16, 64], blocks=[30, 8], in_h=8, in_w=8)
+    g = make_params(model, 5, perturb_bn=True)
+    rng = np.random.default_rng(bits)
+    L = (1 << bits) - 1
+    for i, (k, t) in enumerate(sorted(g.items())):
+        for j, (n, v) in enumerate(sorted(t.items())):
+            mode = (i + j) % 6
+            if mode == 0:                                     # delta 2: odd values lie between two codes
+                v = rng.integers(0, 2 * L + 1, v.shape).astype(np.float32)
+                v.flat[0], v.flat[-1] = 0, 2 * L
+            elif mode == 1:
+                v = (rng.standard_normal(v.shape) * 1e-39).astype(np.float32)
+            elif mode == 2:
+                v = (rng.uniform(-1, 1, v.shape) * 1.6e38).astype(np.float32)
+            elif mode == 3:
+                v = (rng.standard_normal(v.shape) * 2.0 ** -94).astype(np.float32)
+            elif mode == 4:
+                v = np.full_like(v, -0.25)
+                v.flat[v.size // 2] = 3.0
+            t[n] = v
+    dev = DeviceModel(model, list(range(R.num_blocks(model))), g)
+    codes, ranges = dev.compress(bits)
+    torch.cuda.synchronize()
+    with np.errstate(over="ignore"):
+        _check_compressed(model, dev, g, bits, codes, ranges)
+
+
 def test_constant_and_fresh_bn_tensors():
     """gamma = 1, beta = 0, running mean 0, running var 1 at initialisation: delta = 0, all codes 0,
     and the decoded block equals the original bit for bit on those tensors."""
