@@ -597,3 +597,49 @@ def test_conv_streamed_1x1(case):
     want = L.conv2d_fwd(x, w, 1, 0)
     for got in (y, dx):   # the data gradient of the exchanged layer is the same product
         np.testing.assert_allclose(got.float().cpu().numpy().transpose(0, 3, 1, 2), want, rtol=2.0 ** -8, atol=1e-5)
+
+
+# bf16 tiles chosen by how their last round fills the compute units: just past one round of 128x64, just past one of 128x128, a second
+# round of 64x64 and a reduction long enough for chunks of 128 channels; ragged rows and columns, forward and, with in- and output channels
+# exchanged, the data gradient
+TILE_CASES = [((35, 16, 16, 512, 256, 1), "128x128x64_w8"), ((45, 16, 16, 192, 320, 1), "128x64x64_w8"), ((135, 16, 16, 256, 136, 1), "64x64x64"),
+              ((9, 16, 15, 256, 264, 1), "64x64x128"), ((47, 13, 13, 1024, 256, 1), "128x64x128_w8"), ((349, 7, 7, 128, 184, 3), "128x64x64_w8"),
+              ((200, 16, 16, 256, 200, 1), "128x128x64")]
+
+
+@pytest.mark.parametrize("case", TILE_CASES)
+def test_conv_bf16_tiles(case):
+    print("case", case, flush=True)
+    (N, H, W, C, K, r), tile = case
+    x, w, _ = _tensors((N, H, W, C, K, r, 1, r // 2), 26)
+    x, w = _bf16_exact(x), _bf16_exact(w)
+    dev = lambda a: _nhwc(a).to(torch.bfloat16)
+    # the data gradient turns the filter's taps round
+    xd, wd, wtd = dev(x), dev(w), dev(np.ascontiguousarray(w.transpose(1, 0, 2, 3)[:, :, ::-1, ::-1]))
+    (y, dx), ran = _launched(lambda: (R.conv2d_forward(xd, wd, 1, r // 2), R.conv2d_dgrad(xd, wtd, (N, H, W, K), 1, r // 2)))
+    assert {n for n in ran if n != "prepare_filters"} == {f"igemm_bf16_fwd_{tile}", f"igemm_bf16_bwd_{tile}"}, ran
+    want = L.conv2d_fwd(x, w, 1, r // 2)
+    for got in (y, dx):
+        np.testing.assert_allclose(got.float().cpu().numpy().transpose(0, 3, 1, 2), want, rtol=2.0 ** -8, atol=1e-5)
+
+
+# fp32: 64x64 tiles in chunks of 64 channels up to two to a compute unit, in chunks of 32 from there up, forward and strided data gradient (whose four
+# parity classes count), ragged rows and columns
+F32_TILE_CASES = [((63, 16, 16, 128, 72, 1, 1), "64x64x64", None), ((65, 16, 17, 64, 68, 1, 1), "64x64x32", None), ((9, 56, 56, 64, 72, 3, 2), "64x64x64", "64x64x32"),
+                  ((130, 14, 14, 64, 128, 3, 2), "64x64x64", "64x64x64")]
+
+
+@pytest.mark.parametrize("case", F32_TILE_CASES)
+def test_conv_f32_tiles(case):
+    print("case", case, flush=True)
+    (N, H, W, C, K, r, st), tile, back = case
+    x, w, dy = _tensors((N, H, W, C, K, r, st, r // 2), 27)
+    xd, wd, dyd = _nhwc(x), _nhwc(w), _nhwc(dy)
+    y, ran = _launched(lambda: R.conv2d_forward(xd, wd, st, r // 2))
+    assert {n for n in ran if n.startswith("igemm")} == {f"igemm_f32_fwd_{tile}"}, ran
+    assert_close(y.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_fwd(x, w, st, r // 2), f"fwd {case}")
+    if back:
+        dx, ran = _launched(lambda: R.conv2d_dgrad(dyd, wd, (N, H, W, C), st, r // 2))
+        if K % 64 == 0 or back == "64x64x32":
+            assert {n for n in ran if n.startswith("igemm")} == {f"igemm_f32_bwd_{back}"}, ran
+        assert_close(dx.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_dgrad(dy, w, x.shape, st, r // 2), f"dgrad {case}")
