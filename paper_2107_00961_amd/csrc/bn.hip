@@ -4,9 +4,10 @@
 //   backward  gm = g, or g where this BN's own ReLU passed; dbeta = sum gm; dgamma = sum gm*xhat;
 //             dy = gamma*invstd*(gm - dbeta/M - xhat*dgamma/M)
 // These kernels are bound by HBM bandwidth.  The forward statistics arrive as per-row-tile fp32
-// shifted column sums written by the convolution that produced y (at most 128 rows each) and are
-// merged in float64; the backward sums are accumulated in float64 throughout (the vector fp64 rate is far
-// above what the memory stream needs).  Every reduction has a fixed order, so results are bit-stable
+// shifted column sums written by the convolution that produced y (taken in fp32 over at most 128 rows; where a
+// tile has more, in float64 from there) and are merged in float64; the backward sums are accumulated in float64
+// throughout (the vector fp64 rate is far above what the memory stream needs), those that a data gradient
+// leaves as the forward's.  Every reduction has a fixed order, so results are bit-stable
 // from run to run.
 // Activations are stored as fp32 or bf16; a thread owns V = 4 (fp32) or 8 (bf16) consecutive channels
 // (one 16-byte access) and all arithmetic is fp32 / fp64.

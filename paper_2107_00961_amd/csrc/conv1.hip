@@ -7,8 +7,10 @@
 // left operand, so that a lane holds one pixel and, after the halves of the wave have traded fours of channels
 // (v_permlane32_swap), 16-byte runs of channels: the output goes from the accumulators to memory, and the side inputs of the next 32
 // pixels are requested before the products of these, so that no wait for them stands behind a store.  The per-channel sums
-// of a BN (forward statistics, or the first pass of a backward) stay in registers for the whole range: one part per
-// workgroup, a third to a tenth of the tiles' number.
+// of a BN (forward statistics, or the first pass of a backward) stay in registers for the whole range, in fp32 for 128 pixels at a
+// time and from there in float64: one part per workgroup, for 56x56 and batch 64 349 forward and 242 backward where 128x128 tiles
+// have 1568, for 28x28 157 and 392, for 14x14 79 and 98.  (In fp32 throughout, which loses bits with every doubling of the range:
+// 64 -> 256 ch 56x56, batch 64, with its statistics 26.2 us, 27.4 this way; 128 -> 512 28x28 21.2 and 21.3.)
 //
 // Measured, us, 128x128 tiles -> this kernel:
 //   forward        64 -> 256 ch 56x56, batch 64 44.7 -> 24.3 (5.3 TB/s)   128 -> 512 28x28 29.7 -> 19.5   256 -> 1024 14x14 22.0 -> 18.2
@@ -20,6 +22,8 @@
 
 namespace resist {
 namespace {
+
+constexpr int kSumRows = 128;   // pixels whose BN sums are taken in fp32: no more than in a tile of the other kernels
 
 // PX pixels a step; NW waves of 32 output channels each, KC * 16 input channels.  Registers allow three waves to a SIMD forward,
 // two with the side inputs.
@@ -101,6 +105,33 @@ __global__ __launch_bounds__(NW * 64, MODE == kBwd ? 2 : 3) void conv1_stream_ke
       centre[e] = c < OC ? a.bn_mean[c] : 0.f;
     }
   }
+  // Over the 32 pixels of a lane half: each step a lane hands half of its sums to a partner, whose number differs in the bit that is
+  // looked at (and perhaps in lower ones), and takes the other half of the partner's: lane l ends with sum number l % 32 of its half.
+  double total = 0;   // of the range so far
+  auto add_up = [&]() {
+    float v[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, s1[e]), __builtin_bit_cast(unsigned, s2[e]), false, false);
+      const unsigned x = r[0], y = r[1];
+      v[e] = __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
+      s1[e] = s2[e] = 0.f;
+    }
+    auto hand_over = [&](auto half_tag, auto partner_tag) {
+      constexpr int half = decltype(half_tag)::value, partner = decltype(partner_tag)::value;
+      const bool up = lane & half;
+#pragma unroll
+      for (int i = 0; i < half; ++i) {
+        const float keep = up ? v[i + half] : v[i], give = up ? v[i] : v[i + half];
+        v[i] = keep + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give), partner, 0xf, 0xf, true));
+      }
+    };
+    hand_over(std::integral_constant<int, 8>{}, std::integral_constant<int, 0x140>{});   // row_mirror: lane ^ 15
+    hand_over(std::integral_constant<int, 4>{}, std::integral_constant<int, 0x141>{});   // row_half_mirror: lane ^ 7
+    hand_over(std::integral_constant<int, 2>{}, std::integral_constant<int, 0x1b>{});    // quad_perm 3 2 1 0
+    hand_over(std::integral_constant<int, 1>{}, std::integral_constant<int, 0xb1>{});    // quad_perm 1 0 3 2
+    total += (double)v[0];
+  };
   request_side(0, 0);
   store(0);
   request(m0 + PX);
@@ -180,29 +211,16 @@ __global__ __launch_bounds__(NW * 64, MODE == kBwd ? 2 : 3) void conv1_stream_ke
     }
     store(buf ^ 1);
     request(m + 2 * PX);
+    if (sums && ((m + PX - m0) % kSumRows == 0 || m + PX >= m1)) add_up();
     __syncthreads();
   }
   if (!sums) return;
-  // over the 32 pixels of a lane half: each step a lane hands half of its sums to its partner and takes the other half of the
-  // partner's; lane l ends with sum number l%32 of its half
-  float v[32];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) { v[e] = s1[e]; v[16 + e] = s2[e]; }
-#pragma unroll
-  for (int half = 16; half >= 1; half >>= 1) {
-    const bool up = lane & half;
-#pragma unroll
-    for (int i = 0; i < half; ++i) {
-      const float keep = up ? v[i + half] : v[i], give = up ? v[i] : v[i + half];
-      v[i] = keep + __shfl_xor(give, half, 64);
-    }
-  }
   const int e = lr & 15, c = c0 + (e & 7) + (e >> 3) * 16, second = lr >> 4;
   if (c < OC) {
     if (MODE == kFwd) {
-      a.stats[((size_t)(1 + second) * a.parts + part) * OC + c] = v[0];
+      a.stats[((size_t)(1 + second) * a.parts + part) * OC + c] = (float)total;
     } else {
-      a.bn_sums[((size_t)second * a.parts + part) * OC + c] = second ? v[0] * a.bn_invstd[c] : v[0];
+      a.bn_sums[((size_t)second * a.parts + part) * OC + c] = (float)(second ? total * (double)a.bn_invstd[c] : total);
     }
   }
   if (MODE == kFwd) {   // the shifts, from whichever lane: the first of each half writes its sixteen

@@ -643,3 +643,53 @@ def test_conv_f32_tiles(case):
         if K % 64 == 0 or back == "64x64x32":
             assert {n for n in ran if n.startswith("igemm")} == {f"igemm_f32_bwd_{back}"}, ran
         assert_close(dx.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_dgrad(dy, w, x.shape, st, r // 2), f"dgrad {case}")
+
+
+# Ranges of pixels of a streamed 1x1 layer that run to thousands: every pixel but the first of each 64 holds one value, so that each of a lane's
+# additions is rounded the same way and the error of a long fp32 sum grows with its length.  A sum of 128 pixels is nine roundings deep (four
+# pixels a lane, five exchanges), and there is one to a difference and one to the stored value: 12 * 2^-24 of it at most.
+def _same_values_but_first(M, channels, seed):
+    rng = np.random.default_rng(seed)
+    first, rest = rng.uniform(2.0 ** -9, 2.0 ** -8, channels), rng.uniform(1.0, 2.0, channels)
+    v = torch.from_numpy(rest.astype(np.float32)).cuda().to(torch.bfloat16).repeat(M, 1)
+    v[::64] = torch.from_numpy(first.astype(np.float32)).cuda().to(torch.bfloat16)
+    return v
+
+
+def test_conv_streamed_1x1_long_sums():
+    from tests import internals as I
+    N, H, W, C, K = 1, 2048, 2048, 16, 128
+    M = N * H * W
+    g = I.geom(N, H, W, C, K, 1, 1, 0)
+    x = torch.zeros(M, C, device="cuda", dtype=torch.bfloat16)
+    x[:, 0] = 1.0
+    x[:, 1] = 1.0
+    x[::64, 1] = 0.0     # output channel k: w[k][0], and w[k][0] + w[k][1] in all but the first pixel of each 64
+    v = _same_values_but_first(64, K, 51)
+    w = torch.zeros(K, C, device="cuda", dtype=torch.bfloat16)
+    w[:, 0], w[:, 1] = v[0], v[1] - v[0]
+    y = torch.empty(M, K, device="cuda", dtype=torch.bfloat16)
+    stats = torch.zeros(3 * ((M + 63) // 64) * K, device="cuda")
+    (parts, rows), ran = _launched(lambda: I.conv_fwd(g, 1, x, w, y, stats))
+    assert any(n.startswith("conv1_") for n in ran) and rows % 64 == 0 and rows > 2048 and (parts - 1) * rows < M <= parts * rows
+    bound = 12 * 2.0 ** -24
+    k, s1, s2 = (t.double() for t in stats[:3 * parts * K].view(3, parts, K))
+    for p in range(0, parts, 29):
+        d = y[p * rows:(p + 1) * rows].double() - k[p]
+        for got, want in ((s1[p], d.sum(0)), (s2[p], d.square().sum(0))):
+            assert float(((got - want).abs() / want.abs()).max()) <= bound, p
+
+    # backward: the output gradient's sum, and that of its product with the normalised input
+    gd = I.geom(N, H, W, K, C, 1, 1, 0)   # data gradient of a narrowing layer: K channels come out
+    dx = torch.empty(M, K, device="cuda", dtype=torch.bfloat16)
+    inp = _same_values_but_first(M, K, 52)
+    bn = dict(y=inp, mean=torch.full((K,), 0.3, device="cuda"), invstd=torch.full((K,), 1.7, device="cuda"), scale=torch.ones(K, device="cuda"),
+              shift=torch.zeros(K, device="cuda"), self=False, sums=torch.zeros(2 * ((M + 63) // 64) * K, device="cuda"))
+    (parts, rows), ran = _launched(lambda: I.conv_dgrad(gd, 1, x, w, dx, bn=bn))
+    assert any(n.startswith("conv1_bf16_bwd") for n in ran) and rows % 64 == 0 and rows > 2048 and (parts - 1) * rows < M <= parts * rows
+    s1, s2 = (t.double() for t in bn["sums"][:2 * parts * K].view(2, parts, K))
+    for p in range(0, parts, 29):
+        gm, yy = dx[p * rows:(p + 1) * rows].double(), inp[p * rows:(p + 1) * rows].double()
+        mean, invstd = bn["mean"].double(), bn["invstd"].double()
+        for got, want in ((s1[p], gm.sum(0)), (s2[p], (gm * (yy - mean)).sum(0) * invstd)):
+            assert float(((got - want).abs() / want.abs()).max()) <= bound, p
