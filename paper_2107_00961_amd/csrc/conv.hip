@@ -959,47 +959,46 @@ constexpr size_t kStaticScratchBytes = (size_t)32 << 20;   // library-owned part
 
 struct WgradPlan { int bm, bn, splits, rows_per_split; bool taps9 = false, taps3 = false; };
 
-// Nine-tap kernel (wgrad3.hip): 64 x 64 channels of all taps per workgroup, one workgroup per CU.  Beside the data gradients of a
-// step, which fill the other compute units, half as many workgroups, with half the partial sums to write, read back and add
-// (steps of the CIFAR-shaped networks, 256 | 192 | 128 | 96 workgroups: sub-ResNet, batch 128 4645 | 4529 | 4447 | 4501 us, 33 blocks
-// 11825 | 11493 | 11436 | 11743, pre-activation sub-ResNet, batch 77 3343 | 3228 | 3207 | 3284), unless the layer is too small for its
-// data gradient to fill them (33 blocks, batch 32: 5677 us with 256, 5775 with 128).  Its time is that of
-// the rounds of these workgroups, 0.05 us per row and 128 rows' worth for its start and end, 0.06 us per partial tile
+// Nine-tap kernel (wgrad3.hip): 64 x 64 channels of all taps per workgroup, one workgroup per CU, in a step as alone.  (128
+// workgroups beside the data gradients of a step, with half the partial sums, were 3 % of a step faster, 4427 -> 4295 us for the CIFAR-shaped
+// sub-ResNet, batch 128, but an accumulator then runs over twice the rows: error against float64 1.14e-7 -> 1.41e-7 at
+// 256 ch 8x8, 1.53e-7 -> 1.90e-7 at 128 ch 28x28.  128 workgroups of two such ranges each, one after the other: 4452 us.)  Its time is that of
+// the rounds of 256 workgroups, 0.05 us per row and 128 rows' worth for its start and end, 0.06 us per partial tile
 // written and read back, 4 us for the launch that adds them; the number of splits is the one with the least, among those whose partial sums stay below
 // max_floats.
-WgradPlan plan_wgrad3(const ConvGeom &g, long long max_floats, bool beside) {
+WgradPlan plan_wgrad3(const ConvGeom &g, long long max_floats) {
   WgradPlan p;
   p.bm = p.bn = 64;
   p.taps9 = true;
   const long long tiles = (long long)((g.K + 63) / 64) * ((g.C + 63) / 64), M = (long long)g.N * g.P * g.Q;
-  const long long wgs = beside && (M + 63) / 64 * ((g.C + 63) / 64) >= 192 ? 128 : 256;
   const long long slice = (long long)g.K * 9 * g.C;
   long long best = -1;
   for (long long s = 1; s <= 256 && (s == 1 || (s - 1) * 64 < M); ++s) {
     if (s > 1 && s * slice > max_floats) break;
     const long long rows = ((M + s - 1) / s + kWBK - 1) / kWBK * kWBK;
     const long long used = (M + rows - 1) / rows;
-    const long long cost = (tiles * used + wgs - 1) / wgs * (rows + 128) * 5 + (used > 1 ? tiles * used * 6 + 400 : 0);
+    const long long cost = (tiles * used + 255) / 256 * (rows + 128) * 5 + (used > 1 ? tiles * used * 6 + 400 : 0);
     if (best < 0 || cost < best) { best = cost; p.splits = (int)used; p.rows_per_split = (int)rows; }
   }
   return p;
 }
 
-// One filter row per workgroup (wgrad3_row_bf16_kernel).  Beside the data gradients of a step, as many splits as give 256
-// workgroups, which leaves compute units room for them (33-block CIFAR-shaped model, batch 128: 384 workgroups 5012 us, 256 4982, 192
-// 4985, 128 7313; ImageNet-shaped, batch 64: 4784, 4769, 4771, 4888).  Alone, one workgroup for every compute unit, or two where the reduction is long enough to pay for the partial sums,
+// One filter row per workgroup (wgrad3_row_bf16_kernel).  In a step, as many splits as give 384
+// workgroups, which leaves compute units room for the data gradients (CIFAR-shaped model, batch 128: 256 workgroups 5.70 ms, 384 5.65, 512
+// 5.72; 256 are no slower since the output gradients take turns in six buffers, but add up longer, 1.04e-7 -> 1.27e-7 against
+// float64 at 256 ch 8x8).  Alone, one workgroup for every compute unit, or two where the reduction is long enough to pay for the partial sums,
 // from 3 * 2^28 padded products a tap: us, up to 256 | 384 | 512 workgroups (one tap a workgroup), 256 ch 8x8, batch 128 29.6 |
 // 30.9 | 31.0 (29.7), 16x16 128 ch, batch 77 23.7 | 27.2 | 26.7 (24.2), 14x14 256 ch, batch 64 36.3 | 39.0 | 33.7 (38.7), batch 256
 // 104 | 104 | 90 (134).  A second split of 192 or more tiles costs as much in partial sums as it saves (512 -> 512 channels at
 // 7x7, batch 64: 36 us in one, 32 + 5 in two; batch 8: 12 and 17 + 6).
-WgradPlan plan_wgrad_rows(const ConvGeom &g, bool beside) {
+WgradPlan plan_wgrad_rows(const ConvGeom &g, bool step) {
   WgradPlan p;
   p.bm = p.bn = 64;
   p.taps3 = true;
   const long long tiles = (long long)((g.K + 63) / 64) * ((g.C + 63) / 64) * 3, M = (long long)g.N * g.P * g.Q;
-  const long long wgs = beside ? 256 : M * tiles >= 9LL << 16 ? 512 : 256;
+  const long long wgs = step ? 384 : M * tiles >= 9LL << 16 ? 512 : 256;
   long long splits = std::min(wgs / tiles, (M + 255) / 256);
-  if (tiles >= 192 || (beside && splits <= 2) || splits < 1) splits = 1;
+  if (tiles >= 192 || (step && splits <= 2) || splits < 1) splits = 1;
   const long long rows = ((M + splits - 1) / splits + 63) / 64 * 64;
   p.rows_per_split = (int)rows;
   p.splits = (int)((M + rows - 1) / rows);
@@ -1085,20 +1084,20 @@ int wgrad_tile(const ConvGeom &g) {
 
 // A layer whose one-tap plan fits the static scratch has a nine-tap plan that fits it too: conv_wgrad_static takes the
 // same layers, and gives the same bits as conv_wgrad, whichever kernel runs.
-static WgradPlan plan_for(const ConvGeom &g, int dt, bool beside = false) {
+static WgradPlan plan_for(const ConvGeom &g, int dt, bool step = false) {
   const WgradPlan p = plan_wgrad(g);
-  if (dt == DT_BF16 && wgrad3_row_takes(g)) return plan_wgrad_rows(g, beside);   // at most 25 MB of partial sums
+  if (dt == DT_BF16 && wgrad3_row_takes(g)) return plan_wgrad_rows(g, step);   // at most 25 MB of partial sums
   if (dt != DT_F32 || !wgrad3_takes(g)) return p;
-  return plan_wgrad3(g, plan_floats(p, g) * 4 <= (int64_t)kStaticScratchBytes ? (long long)(kStaticScratchBytes / 4) : INT64_MAX, beside);
+  return plan_wgrad3(g, plan_floats(p, g) * 4 <= (int64_t)kStaticScratchBytes ? (long long)(kStaticScratchBytes / 4) : INT64_MAX);
 }
 
-int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool beside) { return plan_floats(plan_for(g, dt, beside), g); }
+int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool step) { return plan_floats(plan_for(g, dt, step), g); }
 
 int64_t wgrad_reserve_floats(const ConvGeom &g, int dt) { return std::max(wgrad_scratch_floats(g, dt), plan_floats(plan_wgrad(g), g)); }
 
-int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial, hipStream_t st, bool beside) {
+int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial, hipStream_t st, bool step) {
   RESIST_TRY(check_geom(g, dt));
-  return run_wgrad(plan_for(g, dt, beside), g, dt, dy, x, dw, partial, st);
+  return run_wgrad(plan_for(g, dt, step), g, dt, dy, x, dw, partial, st);
 }
 
 int splitk_reduce(const float *partial, float *out, long long n4, int splits, hipStream_t st) {

@@ -160,14 +160,14 @@ int64_t conv_dgrad_bn_sums_floats(const ConvGeom &g);
 // filters [K][R][S][C] in src_dt, times `scale`, prepared in dt for the forward pass (w_lp) and for the data gradient (wT), each optional
 struct FilterPrep { ConvGeom g; const void *w; void *w_lp; bool lp_fragments; void *wT; bool wT_fragments; float scale = 1.f; };
 int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st, int src_dt = DT_F32);
-// dw (fp32) = wgrad(dy, x); partial: split-reduction scratch of wgrad_scratch_floats(g, dt, beside) floats; beside: other
-// kernels run at the same time
-int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool beside = false);
+// dw (fp32) = wgrad(dy, x); partial: split-reduction scratch of wgrad_scratch_floats(g, dt, step) floats; step: among the
+// kernels of a step (on whichever stream: the sums are the same)
+int64_t wgrad_scratch_floats(const ConvGeom &g, int dt, bool step = false);
 // what a caller is told to reserve for it: no less than the one-tap kernel's partial sums, whichever kernel runs, so that which
 // shapes fit a given scratch does not change with the rules that choose between them
 int64_t wgrad_reserve_floats(const ConvGeom &g, int dt);
 int conv_wgrad(const ConvGeom &g, int dt, const void *dy, const void *x, float *dw, float *partial,
-               hipStream_t st, bool beside = false);
+               hipStream_t st, bool step = false);
 // the same with the split partial sums in the library's static device array (no allocation anywhere);
 // RESIST_EWORKSPACE when wgrad_reserve_floats(g, dt) * 4 exceeds wgrad_static_scratch_bytes()
 int64_t wgrad_static_scratch_bytes();

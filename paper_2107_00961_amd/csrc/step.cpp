@@ -21,7 +21,6 @@ constexpr int kDyRing = 6;
 struct WgradSide {
   SideStream side;
   int dt;
-  bool beside;   // by the work of the step alone: with the second stream switched off the sums have the same order
   float *splitk;
   // The side stream runs in order, so its weight gradients are numbered and a wait for one covers all
   // before it.  An event costs a packet in its stream and 5 us of the host, a wait 6 us of the chain:
@@ -35,7 +34,7 @@ struct WgradSide {
   // `flops`: convolution work of the step.  Below ~20 GFLOP a step is bound by launch latency and the
   // event calls of the second stream cost more than the overlap returns: everything stays on `main`.
   WgradSide(hipStream_t main, int dt_, float *splitk_, double flops)
-      : side(main, overlap_mode() == 2 || (overlap_mode() == 1 && flops >= 2e10)), dt(dt_), beside(flops >= 2e10), splitk(splitk_) {}
+      : side(main, overlap_mode() == 2 || (overlap_mode() == 1 && flops >= 2e10)), dt(dt_), splitk(splitk_) {}
   hipStream_t stream() const { return side.stream(); }
   int mark() {
     hipEvent_t e = nullptr;
@@ -54,7 +53,7 @@ struct WgradSide {
   // ready: the event its output gradient's last kernel carries
   int launch(const ConvGeom &g, const void *dyb, const void *xin, float *dw, hipEvent_t ready = nullptr) {
     RESIST_TRY(side.fork_from(ready));
-    RESIST_TRY(conv_wgrad(g, dt, dyb, xin, dw, splitk, side.stream(), beside));
+    RESIST_TRY(conv_wgrad(g, dt, dyb, xin, dw, splitk, side.stream(), true));
     return read_by_last(dyb);
   }
   // the stem's weight gradient (implicit GEMM on the input image), same ordering rules
@@ -277,7 +276,7 @@ int build_plan(const resist_model_desc *desc, const int32_t *blocks, int32_t nbl
     max_act = std::max<int64_t>(max_act, c.M() * c.g.K);
     max_act = std::max<int64_t>(max_act, (int64_t)c.g.N * c.g.H * c.g.W * c.g.C);
     (void)needs_dgrad;
-    for (const bool beside : {false, true}) max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(c.g, net.d.compute_dtype, beside));
+    max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(c.g, net.d.compute_dtype, true));
     max_c = std::max(max_c, c.g.K);
   };
 
@@ -565,7 +564,7 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
     if (shape_rc == RESIST_OK) shape_rc = conv_check(g, net.d.compute_dtype);
     max_act = std::max<int64_t>(max_act, (int64_t)g.N * g.P * g.Q * g.K);
     max_act = std::max<int64_t>(max_act, (int64_t)g.N * g.H * g.W * g.C);
-    for (const bool beside : {false, true}) max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(g, net.d.compute_dtype, beside));
+    max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(g, net.d.compute_dtype, true));
     if (stats) max_stats = std::max<int64_t>(max_stats, conv_stats_floats(g));
     max_c = std::max(max_c, std::max(g.K, g.C));
   };

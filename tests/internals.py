@@ -1,9 +1,13 @@
 """The library's internal convolution calls, for what the layer calls leave out: BN sums, addends, masks, prepared filters."""
 import ctypes as C
 
+import torch
+
 from paper_2107_00961_amd import binding as B
 
 _CONV_FWD = "_ZN6resist8conv_fwdERKNS_8ConvGeomEiPKvRKNS_6FilterEPvS4_PfPNS_9StatPartsEP12ihipStream_tPKNS_7EvalActE"
+_CONV_WGRAD = "_ZN6resist10conv_wgradERKNS_8ConvGeomEiPKvS4_PfS5_P12ihipStream_tb"
+_WGRAD_SCRATCH = "_ZN6resist20wgrad_scratch_floatsERKNS_8ConvGeomEib"
 _CONV_DGRAD = "_ZN6resist10conv_dgradERKNS_8ConvGeomEiPKvRKNS_6FilterEPvS4_S4_P12ihipStream_tPKNS_9BnBwdFuseE"
 
 
@@ -51,3 +55,13 @@ def conv_dgrad(g, dtype, dy, wT, dx, addend=None, mask=None, bn=None):
     B._check(B.lib()[_CONV_DGRAD](C.byref(g), dtype, _ptr(dy), C.byref(Filter(None, wT.data_ptr(), False, 1.0)), _ptr(dx), _ptr(addend), _ptr(mask), None,
                                   C.byref(f) if f is not None else None))
     return sp.parts, sp.rows
+
+
+def conv_wgrad(g, dtype, dy, x, step):
+    """dw [K][R][S][C], as a call on its own computes it or as a step does."""
+    scratch = B.lib()[_WGRAD_SCRATCH]
+    scratch.restype = C.c_int64
+    part = torch.empty(max(1, scratch(C.byref(g), dtype, C.c_bool(step))), device="cuda")
+    dw = torch.empty(g.K, g.R, g.S, g.C, device="cuda")
+    B._check(B.lib()[_CONV_WGRAD](C.byref(g), dtype, _ptr(dy), _ptr(x), _ptr(dw), _ptr(part), None, C.c_bool(step)))
+    return dw

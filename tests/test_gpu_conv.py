@@ -693,3 +693,15 @@ def test_conv_streamed_1x1_long_sums():
         mean, invstd = bn["mean"].double(), bn["invstd"].double()
         for got, want in ((s1[p], gm.sum(0)), (s2[p], (gm * (yy - mean)).sum(0) * invstd)):
             assert float(((got - want).abs() / want.abs()).max()) <= bound, p
+
+
+@pytest.mark.parametrize("shape", [(128, 8, 8, 256, 256), (77, 16, 16, 128, 128), (31, 14, 14, 256, 200), (40, 4, 4, 512, 512)])
+def test_wgrad_of_a_step_adds_like_the_layer_call(shape):
+    """fp32 3x3: beside the other kernels of a step no accumulator runs over more rows than alone -- bit for bit the same sums."""
+    from tests import internals as I
+    N, H, W, C, K = shape
+    g = I.geom(N, H, W, C, K, 3, 1, 1)
+    gen = torch.Generator(device="cuda").manual_seed(53)
+    x, dy = torch.randn(N, H, W, C, generator=gen, device="cuda"), torch.randn(N, H, W, K, generator=gen, device="cuda")
+    (alone, step), ran = _launched(lambda: (I.conv_wgrad(g, 0, dy, x, False), I.conv_wgrad(g, 0, dy, x, True)))
+    assert "wgrad3_f32" in ran and torch.equal(alone, step)
