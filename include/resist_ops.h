@@ -29,8 +29,9 @@ typedef struct {
 } resist_conv_shape;
 
 /* Workspace (bytes) the three calls below use at most for this shape: a filter copy, or the split partial sums of the
- * weight gradient (of the kernel that needs most of those the shape could be given).  The forward call takes none or less as
- * well, the data gradient K*R*S*C elements at least; 3x3 layers then run on kernels that read the filter's rows.  host. */
+ * weight gradient (of the kernel that needs most of those the shape could be given).  The forward call takes any, NULL
+ * too, and leaves it as it is; the data gradient takes K*R*S*C elements at least, with the same results.  The two
+ * gradients write it: calls that overlap in time need one each.  host. */
 int resist_conv2d_workspace_bytes(const resist_conv_shape *s, int64_t *bytes);
 
 /* y[n,p,q,k] = sum_{r,s,c} x[n, p*stride+r-pad, q*stride+s-pad, c] * w[k,r,s,c]  (zero padding) */

@@ -304,6 +304,9 @@ template <typename T, int MODE>
 int dispatch_igemm(const EvalArgs &a, hipStream_t st, StatParts *tiles_m_out = nullptr) {
   constexpr int dt = sizeof(T) == 2 ? DT_BF16 : DT_F32;
   if (conv_small_takes(a, dt)) return conv_small_launch(a, dt, MODE, st, tiles_m_out);
+  if constexpr (sizeof(T) == 4 && MODE != kEval) {   // (the test-time forward prepares its filters)
+    if (conv3_takes(a, dt)) return conv3_launch_rows(a, MODE, st, tiles_m_out);
+  }
   if (conv1_takes(a, dt, MODE)) return conv1_launch(a, MODE, st, tiles_m_out);
   // pick the largest tile that still yields enough workgroups to cover the 256 compute units
   constexpr int V = Elem<T>::VEC;   // K-chunks of 8*V and 16*V elements: 128 and 256 bytes per tile row

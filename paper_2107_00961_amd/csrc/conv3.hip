@@ -49,7 +49,12 @@ constexpr int kAhead = 4;     // filter pieces of 8 KB a workgroup asks for up f
 
 // 8 waves: 2 along the output channels, 4 sharing the reduction (wave slice k takes 16 of every 64 channels).  A wave's tile is
 // all BM pixels by 32 channels, so a filter fragment is used by one wave only and comes straight from memory.
-template <int NP, int BM, int NBUF, int kMaxW, int MODE>
+// ROWS (fp32): on the filter as it is stored, or for a data gradient its transpose, rows [output channel][tap][IC], which a wave takes
+// apart as it goes: the same products in the same order, for calls with no room for the fragments.  us, with the filter through LDS -> this,
+// forward | data gradient with the transposition: batch 128, 64 ch 32x32 65.5 -> 63.0 | 68.6 -> 68.4, 128 ch 16x16 55.5 -> 52.5 |
+// 59.3 -> 57.9, 256 ch 8x8 51.1 -> 48.2 | 56.3 -> 54.7, 512 ch 4x4 61.2 -> 51.9 | 68.5 -> 57.4, batch 64, 64 ch 56x56 109.8 -> 105.8 |
+// 113.1 -> 113.0, 128 ch 28x28 105.4 -> 95.4 | 108.8 -> 101.1.
+template <int NP, int BM, int NBUF, int kMaxW, int MODE, bool ROWS>
 __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<MODE> a) {
   using T = std::conditional_t<NP == 3, float, __bf16>;
   constexpr int ES = sizeof(T), VEC = 16 / ES;
@@ -118,22 +123,49 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
   };
   request_pixels(0);
   unsigned flagged = 0;            // filter rows of this tile that three parts do not hold
-  if constexpr (NP == 3)
+  if constexpr (NP == 3 && !ROWS)
     for (int i = tid; i < a.cchunks * 9; i += kNT) flagged |= a.flags[tn * a.cchunks * 9 + i];
 
   // ---- filter fragments: [octile of 32][chunk][tap][wave slice][part][64 lanes][16 bytes]
   const int chunk_bytes = 9 * kWK * NP * 1024;
   const char *wbase = static_cast<const char *>(a.frag) + (size_t)(tn * 2 + wn) * a.cchunks * chunk_bytes;
-  const __amdgpu_buffer_rsrc_t rwt = make_rsrc(wbase, (unsigned)(a.cchunks * chunk_bytes));
+  const __amdgpu_buffer_rsrc_t rwt = ROWS ? make_rsrc(a.wt, (unsigned)a.OC * 9u * IC * 4u) : make_rsrc(wbase, (unsigned)(a.cchunks * chunk_bytes));
   const int woff = wk * NP * 1024 + lane * 16;
-  f32x4 fb[kRing][NP];
-  auto fetch_b = [&](int slot, int base) {   // base: uniform
+  // rows: lane l reads output channel l % 32, channels 8 * (l / 32) .. +7 of the wave's slice.  The values wait in `raw` and become
+  // the parts of the next tap during the products of this one.
+  static_assert(!ROWS || NP == 3, "filters in fp32");
+  const int wch = wk * 16 + lg * 8, woc = n0 + wn * 32 + lr;
+  const unsigned wrow = woc < a.OC ? (unsigned)(woc * 9 * IC + wch) * 4u : kOOB;
+  f32x4 fb[ROWS ? 2 : kRing][NP], raw[ROWS ? kRing : 1][2];
+  auto fetch_b = [&](int slot, int t, int c) {   // tap t of chunk c, both uniform
+    if constexpr (ROWS) {
+      const int left = IC - c * kBK - wch;   // a multiple of four
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
-      fb[slot][p] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rwt, woff + p * 1024, base, 0));
+      for (int h = 0; h < 2; ++h) {
+        unsigned o = left > h * 4 ? wrow + (unsigned)(c * kBK + h * 4) * 4u : kOOB;
+        asm("" : "+v"(o));
+        raw[slot][h] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rwt, (int)o, t * IC * 4, 0));
+      }
+    } else {
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        fb[slot][p] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rwt, woff + p * 1024, c * chunk_bytes + t * kWK * NP * 1024, 0));
+    }
+  };
+  unsigned long long wmissed = 0;
+  auto take_part = [&](int set, int slot, int p) {   // in order
+    if constexpr (ROWS) {
+      if (p == 2) {
+        split_check(raw[slot][0], wmissed);
+        split_check(raw[slot][1], wmissed);
+        asm("" : "+s"(wmissed));   // left alone, the compiler keeps every mask to the end, in lanes of vector registers
+      }
+      const u32x2 x = split_part(raw[slot][0]), y = split_part(raw[slot][1]);
+      fb[set][p] = __builtin_bit_cast(f32x4, u32x4{x[0], x[1], y[0], y[1]});
+    }
   };
 #pragma unroll
-  for (int t = 0; t < kRing; ++t) fetch_b(t, t * kWK * NP * 1024);
+  for (int t = 0; t < kRing; ++t) fetch_b(t, t, 0);
   // Three taps of bf16 products are over before a line arrives from beyond the L2, and all workgroups of an XCD walk the filter
   // in step.  So those that share it ask for a part each, up front.
   f32x4 ahead[NP == 1 ? kAhead : 1];
@@ -176,6 +208,11 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
 
 #pragma unroll
   for (int i = 0; i < PA; ++i) store_pixels(i, 0);
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) take_part(0, 0, p);
+    fetch_b(0, kRing, 0);
+  }
   lds_barrier();
 
   // ---- one chunk of 64 channels, nine taps.  The pixel fragments of a tap are fetched during the products of the tap before it,
@@ -210,9 +247,8 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
     constexpr bool MORE = decltype(more_tag)::value;
     // (left alone, the compiler keeps the addresses of all nine taps in registers)
 #pragma unroll
-    for (int i = 0; i < TM; ++i) asm("" : "+v"(valid[i]));
+    for (int i = 0; i < TM; ++i) asm("" : "+v"(valid[i]), "+v"(abase[i]));
     const int here = NBUF == 2 && (c & 1) ? kBuf : 0, there = NBUF == 2 ? kBuf - here : 0;
-    const int base = c * chunk_bytes, next = MORE ? base + chunk_bytes : base;
     aim(0, here);
     if constexpr (NP == 3) fetch_a(0, 2);
     fetch_a(0, 0);
@@ -221,7 +257,10 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
-      const int slot = t % kRing, set = t & 1, nx = set ^ 1;
+      const int set = t & 1, nx = set ^ 1, slot = ROWS ? set : t % kRing, later = (t + 1) % kRing;
+      auto next_part = [&](int p) {
+        if (t < 8 || MORE) take_part(nx, later, p);
+      };
       auto stage = [&](int third) {   // passes are spread over taps 2 to 8
         if constexpr (MORE && NBUF == 2) {
 #pragma unroll
@@ -234,21 +273,29 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
         stage(0);
         product(set, slot, 2, 0);
         if (t < 8) fetch_a(nx, 2);
+        next_part(0);
         product(set, slot, 0, 2);
         if (t < 8) fetch_a(nx, 0);
         stage(1);
         product(set, slot, 1, 1);
+        next_part(1);
         product(set, slot, 1, 0);
         if (t < 8) fetch_a(nx, 1);
         stage(2);
         product(set, slot, 0, 1);
+        next_part(2);
         product(set, slot, 0, 0);
       } else {
         if (t < 8) fetch_a(nx, 0);
         stage(0); stage(1); stage(2);
         product(set, slot, 0, 0);
       }
-      fetch_b(slot, t + kRing < 9 ? base + (t + kRing) * kWK * NP * 1024 : next + (t + kRing - 9) * kWK * NP * 1024);
+      const int next = t + (ROWS ? kRing + 1 : kRing);
+      if (next < 9 || MORE) fetch_b(ROWS ? later : slot, next % 9, c + next / 9);
+    }
+    if constexpr (ROWS && MORE) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) fb[0][p] = fb[1][p];
     }
     if (MORE) {
       lds_barrier();
@@ -290,7 +337,7 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
         unsigned xo = x_ok && ch < IC ? (unsigned)((m + d) * IC + ch) * 4u : kOOB;
         asm("" : "+v"(xo));
         x[set][k] = buffer_load_16B(rin, xo);
-        if (MODE == kBwd) {   // the filter as it is stored, [IC][9][OC]
+        if (MODE == kBwd && !ROWS) {   // the filter as it is stored, [IC][9][OC]
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             unsigned yo = y_ok && ch < IC ? (unsigned)(((ch + e) * 9 + t) * a.OC + oc) * 4u : kOOB;
@@ -375,7 +422,7 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
 #pragma unroll
     for (int g = 0; g < TM; ++g) red[(wave * TM + g) * 64 + lane] = either(high, half[g + TM], half[g]);
     __syncthreads();
-    bool bad = missed != 0 || flagged != 0;
+    bool bad = (missed | wmissed) != 0 || flagged != 0;
 #pragma unroll
     for (int g = 0; g < TM; ++g) {
       v[g] = either(high, half[g], half[g + TM]) + red[((wave ^ 2) * TM + g) * 64 + lane];
@@ -401,7 +448,7 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
   });
 }
 
-template <int NP, int BM, int NBUF, int MAXW, int MODE>
+template <int NP, int BM, int NBUF, int MAXW, int MODE, bool ROWS>
 int launch(Conv3Args<kEval> a, hipStream_t st, StatParts *tiles_m_out) {
   a.tiles_m = (a.Mrows + BM - 1) / BM;
   a.tiles_n = (a.OC + kBN - 1) / kBN;
@@ -423,7 +470,7 @@ int launch(Conv3Args<kEval> a, hipStream_t st, StatParts *tiles_m_out) {
     const double bytes = (NP == 3 ? 4.0 : 2.0) * ((double)a.Mrows * a.IC + (double)a.Mrows * a.OC * (1 + (a.addend ? 1 : 0) + (a.relu_mask ? 1 : 0) + (MODE == kBwd && a.bn_sums ? 1 : 0) +
                                 (MODE == kEval ? (a.out ? 1 : 0) + (a.act_res ? 1 : 0) : 0)) + (double)a.OC * 9 * a.IC);
     prof::Scope ps(label.c_str(), flops, bytes, st);
-    hipLaunchKernelGGL((conv3_kernel<NP, BM, NBUF, MAXW, MODE>), dim3((unsigned)grid), dim3(kNT), 0, st, k);
+    hipLaunchKernelGGL((conv3_kernel<NP, BM, NBUF, MAXW, MODE, ROWS>), dim3((unsigned)grid), dim3(kNT), 0, st, k);
   }
   RESIST_CHECK_LAUNCH("conv3");
   return RESIST_OK;
@@ -433,22 +480,26 @@ int launch(Conv3Args<kEval> a, hipStream_t st, StatParts *tiles_m_out) {
 // tile.  In training steps, on whole chunks of channels and at least two of them, whichever of 128, 96 and 64 pixels leaves the units
 // idle least, what a tile costs beside its products (8 of 46 us) being what 24 pixels cost: 256 ch 8x8, batch 77: 64 pixels 42, 96
 // 33 us; 128 ch 16x16: 128 pixels 49, 96 37; batch 128: 96 pixels 65 and 61, 128 47 and 53.
-// (Images wider than 32: the pixels of 128 are staged once at a time.)  bf16: 64-pixel tiles, two workgroups to a unit; 128-pixel
+// (Images wider than 32: the pixels of 128 are staged once at a time.  us, kernel with the filter through LDS -> this one, data gradient with
+// its filter's preparation: batch 64, 64 ch 56x56 113.2 -> 106.2, batch 16, 128 ch 56x56 110.3 -> 101.6, 48x48 82.8 -> 76.2, 40x40
+// 54.7 -> 51.2; 96 pixels at 40x40 60.4, 64 pixels 57.3.)  bf16: 64-pixel tiles, two workgroups to a unit; 128-pixel
 // ones with one, 256 ch 8x8, batch 128: 16.5 us.
-template <int MODE>
+template <int MODE, bool ROWS>
 int pick(const Conv3Args<kEval> &a, int dt, hipStream_t st, StatParts *p) {
-  if (dt == DT_BF16) return launch<1, 64, 2, 56, MODE>(a, st, p);
+  if constexpr (!ROWS) {
+    if (dt == DT_BF16) return launch<1, 64, 2, 56, MODE, false>(a, st, p);
+  }
   auto tiles = [&](int bm) { return (long long)((a.Mrows + bm - 1) / bm) * ((a.OC + kBN - 1) / kBN); };
   int bm = tiles(128) >= 256 ? 128 : 64;
-  if (a.IW > 32) return bm == 128 ? launch<3, 128, 1, 56, MODE>(a, st, p) : launch<3, 64, 2, 56, MODE>(a, st, p);
+  if (a.IW > 32) return bm == 128 ? launch<3, 128, 1, 56, MODE, ROWS>(a, st, p) : launch<3, 64, 2, 56, MODE, ROWS>(a, st, p);
   if constexpr (MODE != kEval) {
     if (a.IC >= 2 * kBK && a.IC % kBK == 0) {
       auto cost = [&](int bm) { return (tiles(bm) + 255) / 256 * (bm + 24); };
       bm = cost(128) <= cost(96) && cost(128) <= cost(64) ? 128 : cost(96) <= cost(64) ? 96 : 64;
-      if (bm == 96) return launch<3, 96, 2, 32, MODE>(a, st, p);
+      if (bm == 96) return launch<3, 96, 2, 32, MODE, ROWS>(a, st, p);
     }
   }
-  return bm == 128 ? launch<3, 128, 2, 32, MODE>(a, st, p) : launch<3, 64, 2, 32, MODE>(a, st, p);
+  return bm == 128 ? launch<3, 128, 2, 32, MODE, ROWS>(a, st, p) : launch<3, 64, 2, 32, MODE, ROWS>(a, st, p);
 }
 
 }  // namespace
@@ -472,7 +523,17 @@ int conv3_launch(const EvalArgs &e, const Filter &w, int dt, int mode, hipStream
   a.frag = w.prep;
   a.flags = reinterpret_cast<const unsigned *>(static_cast<const char *>(w.prep) + (int64_t)((e.OC + kBN - 1) / kBN) * a.cchunks * 9 * 2 * kWK * 3 * 1024);
   a.wscale = w.scale;
-  return mode == kFwd ? pick<kFwd>(a, dt, st, p) : mode == kBwd ? pick<kBwd>(a, dt, st, p) : pick<kEval>(a, dt, st, p);
+  return mode == kFwd ? pick<kFwd, false>(a, dt, st, p) : mode == kBwd ? pick<kBwd, false>(a, dt, st, p) : pick<kEval, false>(a, dt, st, p);
+}
+
+int conv3_launch_rows(const EvalArgs &e, int mode, hipStream_t st, StatParts *p) {
+  Conv3Args<kEval> a;
+  static_cast<EvalArgs &>(a) = e;
+  a.cchunks = (e.IC + kBK - 1) / kBK;
+  a.frag = nullptr;
+  a.flags = nullptr;
+  a.wscale = 1.f;
+  return mode == kFwd ? pick<kFwd, true>(a, DT_F32, st, p) : pick<kBwd, true>(a, DT_F32, st, p);
 }
 
 }  // namespace resist

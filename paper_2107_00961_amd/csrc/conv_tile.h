@@ -349,6 +349,7 @@ __device__ inline void conv_epilogue(const ArgsOf<MODE> &a, float (*Cs)[BN + 8],
 bool conv3_takes(const IgemmArgs &a, int dt);
 int64_t conv3_filter_bytes(int OC, int IC, int dt);
 int conv3_launch(const EvalArgs &a, const Filter &w, int dt, int mode, hipStream_t st, StatParts *tiles_m_out);
+int conv3_launch_rows(const EvalArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);   // fp32, on the filter's rows a.wt
 // widening 1x1 convolutions in bf16, streamed (conv1.hip)
 bool conv1_takes(const IgemmArgs &a, int dt, int mode);
 int conv1_launch(const IgemmArgs &a, int mode, hipStream_t st, StatParts *tiles_m_out);

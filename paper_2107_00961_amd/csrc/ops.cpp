@@ -14,9 +14,8 @@ int to_geom(const resist_conv_shape *s, ConvGeom *g) {
   return RESIST_OK;
 }
 int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
-bool takes_fragments(const ConvGeom &g, int dt, bool dgrad, const void *ws, int64_t bytes) {
-  return conv_check(g, dt) == RESIST_OK && filter_in_fragments(g, dt, dgrad) && ws && !((uintptr_t)ws & 15) &&
-         bytes >= filter_bytes(g, dt, true, dgrad);
+bool dgrad_on_fragments(const ConvGeom &g, int dt, const void *ws, int64_t bytes) {
+  return conv_check(g, dt) == RESIST_OK && filter_in_fragments(g, dt, true) && !((uintptr_t)ws & 15) && bytes >= filter_bytes(g, dt, true, true);
 }
 }  // namespace
 
@@ -25,8 +24,7 @@ extern "C" int resist_conv2d_workspace_bytes(const resist_conv_shape *s, int64_t
   RESIST_TRY(to_geom(s, &g));
   if (!bytes) return set_error(RESIST_EINVAL, "bytes is NULL");
   int64_t filt = filter_bytes(g, s->dtype, false, false);
-  for (const bool dgrad : {false, true})
-    if (filter_in_fragments(g, s->dtype, dgrad)) filt = std::max(filt, filter_bytes(g, s->dtype, true, dgrad));
+  if (filter_in_fragments(g, s->dtype, true)) filt = std::max(filt, filter_bytes(g, s->dtype, true, true));
   filt = align256(filt);
   const int64_t split = align256(wgrad_reserve_floats(g, s->dtype) * 4);
   *bytes = std::max<int64_t>(std::max(filt, split), 256);
@@ -38,17 +36,11 @@ extern "C" int resist_conv2d_forward(const resist_conv_shape *s, const void *x, 
   ConvGeom g;
   RESIST_TRY(to_geom(s, &g));
   if (!x || !w || !y) return set_error(RESIST_EINVAL, "NULL tensor");
-  hipStream_t st = (hipStream_t)hip_stream;
-  Filter f{w, nullptr, false};
-  // The workspace is for the fragments of the filter; without it, the kernels that read its rows.  So they do in bf16 up to 256
-  // channels, where the launch that makes the fragments costs what they save (us: 256 ch 8x8, batch 128 19.7 over 15.6 + 4.7;
-  // 512 ch 4x4 23.8 over 14.8 + 5.4).
-  if ((s->dtype == DT_F32 || g.C >= 512) && takes_fragments(g, s->dtype, false, workspace, workspace_bytes)) {
-    f.prep = workspace;
-    f.fragments = true;
-    RESIST_TRY(prepare_filters({FilterPrep{g, w, workspace, true, nullptr, false}}, s->dtype, st, s->dtype));
-  }
-  return conv_fwd(g, s->dtype, x, f, y, nullptr, nullptr, nullptr, st);
+  // The workspace stays as it is: calls on several streams may share it.  (The launch that makes a filter's fragments for one call takes
+  // about what they save, us: fp32 256 ch 8x8, batch 128 48.2 on the rows, 47.3 + 4.9 on fragments; 128 ch 28x28, batch 64 95.4,
+  // 88 + 3; bf16 256 ch 8x8 16.4, 14.5 + 4.7.)
+  (void)workspace; (void)workspace_bytes;
+  return conv_fwd(g, s->dtype, x, Filter{w, nullptr, false}, y, nullptr, nullptr, nullptr, (hipStream_t)hip_stream);
 }
 
 extern "C" int resist_conv2d_dgrad(const resist_conv_shape *s, const void *dy, const void *w, void *dx, void *workspace,
@@ -58,7 +50,7 @@ extern "C" int resist_conv2d_dgrad(const resist_conv_shape *s, const void *dy, c
   if (!dy || !w || !dx || !workspace) return set_error(RESIST_EINVAL, "NULL tensor");
   if (workspace_bytes < (int64_t)g.K * g.R * g.S * g.C * esize(s->dtype)) return set_error(RESIST_EWORKSPACE, "workspace too small for the transposed filter");
   hipStream_t st = (hipStream_t)hip_stream;
-  const bool frag = takes_fragments(g, s->dtype, true, workspace, workspace_bytes);
+  const bool frag = dgrad_on_fragments(g, s->dtype, workspace, workspace_bytes);
   RESIST_TRY(prepare_filters({FilterPrep{g, w, nullptr, false, workspace, frag}}, s->dtype, st, s->dtype));
   return conv_dgrad(g, s->dtype, dy, Filter{w, workspace, frag}, dx, nullptr, nullptr, st);
 }

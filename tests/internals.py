@@ -39,10 +39,11 @@ def _ptr(t):
     return C.c_void_p(t.data_ptr() if t is not None else None)
 
 
-def conv_fwd(g, dtype, x, w, y, stats=None):
-    """-> (parts, rows): `stats` [3][parts][K] holds that many ranges of that many output pixels."""
+def conv_fwd(g, dtype, x, w, y, stats=None, prep=None):
+    """-> (parts, rows): `stats` [3][parts][K] holds that many ranges of that many output pixels.  prep: w in matrix fragments."""
     sp = StatParts()
-    B._check(B.lib()[_CONV_FWD](C.byref(g), dtype, _ptr(x), C.byref(Filter(w.data_ptr(), None, False, 1.0)), _ptr(y), None, _ptr(stats), C.byref(sp), None, None))
+    f = Filter(w.data_ptr(), prep.data_ptr() if prep is not None else None, prep is not None, 1.0)
+    B._check(B.lib()[_CONV_FWD](C.byref(g), dtype, _ptr(x), C.byref(f), _ptr(y), None, _ptr(stats), C.byref(sp), None, None))
     return sp.parts, sp.rows
 
 
@@ -65,3 +66,27 @@ def conv_wgrad(g, dtype, dy, x, step):
     dw = torch.empty(g.K, g.R, g.S, g.C, device="cuda")
     B._check(B.lib()[_CONV_WGRAD](C.byref(g), dtype, _ptr(dy), _ptr(x), _ptr(dw), _ptr(part), None, C.c_bool(step)))
     return dw
+
+
+def workspace(shape, bf16):
+    """What the layer calls are told to bring for (N, H, W, C, K, R, stride, pad)."""
+    return B._conv_ws(B._conv_shape(*shape, int(bf16)))
+
+
+def _bytes(ws):
+    return (_ptr(ws), ws.numel() * ws.element_size()) if ws is not None else (None, 0)
+
+
+def forward_call(shape, x, w, ws):
+    N, H, W, _, K, _, stride, pad = shape
+    y = torch.empty((N, (H + 2 * pad - shape[5]) // stride + 1, (W + 2 * pad - shape[5]) // stride + 1, K), device="cuda", dtype=x.dtype)
+    sh = B._conv_shape(*shape, int(x.dtype == torch.bfloat16))
+    B._check(B.lib().resist_conv2d_forward(C.byref(sh), _ptr(x), _ptr(w), _ptr(y), *_bytes(ws), None))
+    return y
+
+
+def dgrad_call(shape, dy, w, ws):
+    dx = torch.empty(shape[:4], device="cuda", dtype=dy.dtype)
+    sh = B._conv_shape(*shape, int(dy.dtype == torch.bfloat16))
+    B._check(B.lib().resist_conv2d_dgrad(C.byref(sh), _ptr(dy), _ptr(w), _ptr(dx), *_bytes(ws), None))
+    return dx

@@ -522,11 +522,14 @@ def test_conv_filter_fragments(case):
         x, w = _bf16_exact(x), _bf16_exact(w)
     dev = lambda a: _nhwc(a).to(torch.bfloat16 if bf16 else torch.float32)
     xd, wd, wtd = dev(x), dev(w), dev(np.ascontiguousarray(w.transpose(1, 0, 2, 3)))
-    (y, dx), ran = _launched(lambda: (R.conv2d_forward(xd, wd, 1, 1), R.conv2d_dgrad(xd, wtd, (N, H, W, K), 1, 1)))
-    names = {f"conv3_{dt}_fwd_{tile}", f"conv3_{dt}_bwd_{tile}"}
-    if bf16 and C < 512:   # the forward call on its own reads the filter's rows
-        names.discard(f"conv3_{dt}_fwd_{tile}")
-    assert {n for n in ran if n.startswith("conv3_")} == names, ran
+    from tests import internals as I
+    # the data gradient leaves the fragments of the transposed filter in its workspace, which are those of w for a forward pass
+    ws = I.workspace((N, H, W, K, C, 3, 1, 1), bf16)
+    y = torch.empty((N, H, W, K), device="cuda", dtype=xd.dtype)
+    dx, ran = _launched(lambda: I.dgrad_call((N, H, W, K, C, 3, 1, 1), xd, wtd, ws))
+    assert {n for n in ran if n.startswith("conv3_")} == {f"conv3_{dt}_bwd_{tile}"}, ran
+    _, ran = _launched(lambda: I.conv_fwd(I.geom(N, H, W, C, K, 3, 1, 1), int(bf16), xd, wd, y, prep=ws))
+    assert {n for n in ran if n.startswith("conv3_")} == {f"conv3_{dt}_fwd_{tile}"}, ran
     for got, want, what in ((y, L.conv2d_fwd(x, w, 1, 1), "fwd"), (dx, L.conv2d_dgrad(x, w.transpose(1, 0, 2, 3), (N, K, H, W), 1, 1), "dgrad")):
         got = got.float().cpu().numpy().transpose(0, 3, 1, 2)
         if bf16:   # half an ulp of the stored result beside the fp32 sums
@@ -535,24 +538,48 @@ def test_conv_filter_fragments(case):
             assert_close(got, want, f"{what} {case}")
 
 
-def test_conv_forward_and_dgrad_with_little_workspace():
-    # what the calls take without room for the fragments: the same results from the kernels that read the filter's rows
-    import ctypes
-    from paper_2107_00961_amd import binding as B
-    case = (40, 8, 8, 64, 320, 3, 1, 1)
-    N, H, W, C, K = case[:5]
-    x, w, dy = _tensors(case, 22)
-    xd, wd, dyd = _nhwc(x), _nhwc(w), _nhwc(dy)
-    y, dx = torch.empty((N, H, W, K), device="cuda"), torch.empty((N, H, W, C), device="cuda")
-    ws = torch.empty(K * 9 * C, device="cuda")
-    sh, st = B._conv_shape(N, H, W, C, K, 3, 1, 1, 0), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    lib = B.lib()
-    _, ran = _launched(lambda: (B._check(lib.resist_conv2d_forward(ctypes.byref(sh), xd.data_ptr(), wd.data_ptr(), y.data_ptr(), None, 0, st)),
-                                B._check(lib.resist_conv2d_dgrad(ctypes.byref(sh), dyd.data_ptr(), wd.data_ptr(), dx.data_ptr(), ws.data_ptr(), ws.numel() * 4, st))))
-    assert not any(n.startswith("conv3_") for n in ran), ran
-    assert_close(y.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_fwd(x, w, 1, 1), "fwd")
-    assert_close(dx.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_dgrad(dy, w, x.shape, 1, 1), "dgrad")
-    assert lib.resist_conv2d_dgrad(ctypes.byref(sh), dyd.data_ptr(), wd.data_ptr(), dx.data_ptr(), ws.data_ptr(), ws.numel() * 4 - 4, st) != 0
+# fp32 3x3 layers without room for the filter's fragments run on its rows, in the same tiles: 64, 96 and 128 pixels, images up to 32
+# and up to 56 wide, one chunk of channels and several, input channels that end in mid-chunk at a multiple of eight and of four,
+# ragged pixels and output channels
+#                     N   H   W   C    K
+LITTLE_WS_CASES = [((40, 8, 8, 64, 320), "64x64"), ((77, 8, 8, 256, 256), "96x64"), ((160, 11, 11, 128, 68), "96x64"), ((65, 16, 16, 52, 132), "128x64"),
+                   ((65, 16, 17, 200, 128), "128x64"), ((3, 40, 37, 76, 72), "64x64"), ((17, 56, 56, 64, 48), "128x64"), ((11, 44, 56, 136, 96), "128x64")]
+
+
+@pytest.mark.parametrize("case", LITTLE_WS_CASES)
+@pytest.mark.parametrize("odd_values", [False, True])
+def test_conv_forward_and_dgrad_with_little_workspace(case, odd_values):
+    """Bit for bit the results of the calls with all the workspace they are told to bring; the forward call leaves its as it is."""
+    from tests import internals as I
+    print("case", case, odd_values, flush=True)
+    (N, H, W, C, K), tile = case
+    x, w, _ = _tensors((N, H, W, C, K, 3, 1, 1), 22)
+    if odd_values:   # tiles that are computed again in fp32
+        x[0, 5, 2, 3], x[N // 2, C - 1, 0, 0] = np.inf, np.nan
+        w[K // 2, 7, 1, 2] = np.float32(1.2345678e-36)
+    xd, wd, wtd = _nhwc(x), _nhwc(w), _nhwc(np.ascontiguousarray(w.transpose(1, 0, 2, 3)))
+    back = (N, H, W, K, C, 3, 1, 1)   # the data gradient of the layer with in- and output channels exchanged
+    ws, least = I.workspace(back, False), torch.empty(K * 9 * C, device="cuda")
+    dx, ran = _launched(lambda: I.dgrad_call(back, xd, wtd, ws))
+    assert f"conv3_f32_bwd_{tile}" in ran, ran
+    dx0, ran = _launched(lambda: I.dgrad_call(back, xd, wtd, least))
+    assert f"conv3_f32_bwd_{tile}" in ran, ran
+    y = torch.empty((N, H, W, K), device="cuda")
+    I.conv_fwd(I.geom(N, H, W, C, K, 3, 1, 1), 0, xd, wd, y, prep=ws)
+    full = torch.full_like(I.workspace((N, H, W, C, K, 3, 1, 1), False), 0x5a)
+    y0, ran = _launched(lambda: I.forward_call((N, H, W, C, K, 3, 1, 1), xd, wd, None))
+    assert f"conv3_f32_fwd_{tile}" in ran, ran
+    y1 = I.forward_call((N, H, W, C, K, 3, 1, 1), xd, wd, full)
+    torch.cuda.synchronize()
+    bits = lambda t: t.view(torch.int32)
+    assert torch.equal(bits(dx), bits(dx0)) and torch.equal(bits(y), bits(y0)) and torch.equal(bits(y), bits(y1))
+    assert bool((full == 0x5a).all())
+    assert bool(torch.isfinite(y).all()) != odd_values
+    if not odd_values:
+        assert_close(y.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_fwd(x, w, 1, 1), "fwd")
+        assert_close(dx.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_dgrad(x, w.transpose(1, 0, 2, 3), (N, K, H, W), 1, 1), "dgrad")
+    with pytest.raises(R.ResistError):
+        I.dgrad_call(back, xd, wtd, least[:-1])
 
 
 def test_conv_fragments_second_pass_on_96_pixel_tiles():
