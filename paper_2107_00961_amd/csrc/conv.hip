@@ -528,56 +528,64 @@ __device__ inline void store_fragments(void *out, int octiles, int chunks, int o
 }
 
 // One 64x64 tile of the [K][C] matrix of one tap per workgroup, through LDS so that both sides move whole
-// vectors: 256-byte runs of the fp32 master in, 4-element vectors of the copy and of the transpose out.
-template <typename S, typename T, int N>
+// vectors: 256-byte runs of the fp32 master in, 4-element vectors of the copy and of the transpose out.  A single filter that is
+// not wanted in fragments is a matter of latency, and taken in 32x32 tiles (data gradients of small 1x1 layers, with the preparation, us,
+// 64x64 -> 32x32: bf16 256 from 512 ch 14x14, batch 8 9.2 -> 8.3, fp32 128 from 64 ch 16x16, batch 64 11.8 -> 10.8).
+template <typename S, typename T, int N, int TS>
 __global__ __launch_bounds__(256) void prepare_filters_kernel(PrepTable<N> t) {
-  constexpr int TS = 64;
+  constexpr int kVecs = TS / 4, kRows = 256 / kVecs, kPasses = TS / kRows;
   __shared__ float tile[TS][TS + 1];
   int seg = 0;
   while (N > 1 && seg + 1 < t.nseg && (int)blockIdx.x >= t.first_wg[seg + 1]) ++seg;
   const int K = t.K[seg], RS = t.RS[seg], C = t.C[seg];
-  const int ct = (C + TS - 1) / TS, kt = (K + TS - 1) / TS;
-  int id = blockIdx.x - t.first_wg[seg];
-  const int c0 = (id % ct) * TS;
-  id /= ct;
-  const int k0 = (id % kt) * TS, tap = id / kt;
+  int ct, kt, c0, k0, tap;
+  if constexpr (N == 1) {
+    ct = gridDim.x; kt = gridDim.y;
+    c0 = blockIdx.x * TS; k0 = blockIdx.y * TS; tap = blockIdx.z;
+  } else {
+    ct = (C + TS - 1) / TS; kt = (K + TS - 1) / TS;
+    int id = blockIdx.x - t.first_wg[seg];
+    c0 = (id % ct) * TS;
+    id /= ct;
+    k0 = (id % kt) * TS; tap = id / kt;
+  }
   const S *__restrict__ w = static_cast<const S *>(t.w[seg]);
   const float sc = t.scale[seg];
   const bool frag_copy = (t.frag_copy >> seg) & 1, frag_transpose = (t.frag_transpose >> seg) & 1;
   T *__restrict__ wlp = static_cast<T *>(t.wlp[seg]);
   T *__restrict__ wT = static_cast<T *>(t.wT[seg]);
-  const int row = threadIdx.x >> 4, col = (threadIdx.x & 15) * 4;   // 16 rows x 16 vectors per pass
+  const int row = threadIdx.x / kVecs, col = (threadIdx.x % kVecs) * 4;   // kRows rows x kVecs vectors per pass
   // K and C are multiples of four (checked on the host)
-  f32x4 v[TS / 16];
+  f32x4 v[kPasses];
 #pragma unroll
-  for (int p = 0; p < TS / 16; ++p) {
-    const int k = k0 + row + 16 * p, c = c0 + col;
+  for (int p = 0; p < kPasses; ++p) {
+    const int k = k0 + row + kRows * p, c = c0 + col;
     v[p] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (k < K && c < C) v[p] = load4(w + ((size_t)k * RS + tap) * C + c);
   }
 #pragma unroll
-  for (int p = 0; p < TS / 16; ++p) {
-    const int k = k0 + row + 16 * p, c = c0 + col;
+  for (int p = 0; p < kPasses; ++p) {
+    const int k = k0 + row + kRows * p, c = c0 + col;
     v[p] *= sc;
     if (wlp && !frag_copy && k < K && c < C) store4(wlp + ((size_t)k * RS + tap) * C + c, v[p][0], v[p][1], v[p][2], v[p][3]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) tile[row + 16 * p][col + e] = v[p][e];
+    for (int e = 0; e < 4; ++e) tile[row + kRows * p][col + e] = v[p][e];
   }
   __syncthreads();
-  if (wlp && frag_copy) store_fragments<T>(wlp, kt, ct, k0 / TS, c0 / TS, tap, [&](int oc, int ch) { return tile[oc][ch]; });
-  if (wT && frag_transpose) store_fragments<T>(wT, ct, kt, c0 / TS, k0 / TS, tap, [&](int oc, int ch) { return tile[ch][oc]; });
+  if constexpr (TS == 64) {
+    if (wlp && frag_copy) store_fragments<T>(wlp, kt, ct, k0 / TS, c0 / TS, tap, [&](int oc, int ch) { return tile[oc][ch]; });
+    if (wT && frag_transpose) store_fragments<T>(wT, ct, kt, c0 / TS, k0 / TS, tap, [&](int oc, int ch) { return tile[ch][oc]; });
+  }
   if (wT && !frag_transpose) {
 #pragma unroll
-    for (int p = 0; p < TS / 16; ++p) {
-      const int c = c0 + row + 16 * p, k = k0 + col;
-      if (c < C && k < K)
-        store4(wT + ((size_t)c * RS + tap) * K + k, tile[col][row + 16 * p], tile[col + 1][row + 16 * p],
-               tile[col + 2][row + 16 * p], tile[col + 3][row + 16 * p]);
+    for (int p = 0; p < kPasses; ++p) {
+      const int c = c0 + row + kRows * p, k = k0 + col, at = row + kRows * p;
+      if (c < C && k < K) store4(wT + ((size_t)c * RS + tap) * K + k, tile[col][at], tile[col + 1][at], tile[col + 2][at], tile[col + 3][at]);
     }
   }
 }
 
-template <int N>
+template <int N, int TS = 64>
 int prepare_launch(const std::vector<FilterPrep> &items, int dt, hipStream_t st, int src_dt) {
   size_t i = 0;
   while (i < items.size()) {
@@ -601,9 +609,10 @@ int prepare_launch(const std::vector<FilterPrep> &items, int dt, hipStream_t st,
     t.first_wg[t.nseg] = wg;
     if (wg == 0) continue;
     prof::Scope ps("prepare_filters", 0, bytes, st);
-    if (src_dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<__bf16, __bf16, N>), dim3(wg), dim3(256), 0, st, t);
-    else if (dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<float, __bf16, N>), dim3(wg), dim3(256), 0, st, t);
-    else hipLaunchKernelGGL((prepare_filters_kernel<float, float, N>), dim3(wg), dim3(256), 0, st, t);
+    const dim3 grid = N == 1 ? dim3((t.C[0] + TS - 1) / TS, (t.K[0] + TS - 1) / TS, t.RS[0]) : dim3(wg);
+    if (src_dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<__bf16, __bf16, N, TS>), grid, dim3(256), 0, st, t);
+    else if (dt == DT_BF16) hipLaunchKernelGGL((prepare_filters_kernel<float, __bf16, N, TS>), grid, dim3(256), 0, st, t);
+    else hipLaunchKernelGGL((prepare_filters_kernel<float, float, N, TS>), grid, dim3(256), 0, st, t);
     RESIST_CHECK_LAUNCH("prepare_filters");
   }
   return RESIST_OK;
@@ -612,7 +621,9 @@ int prepare_launch(const std::vector<FilterPrep> &items, int dt, hipStream_t st,
 
 int prepare_filters(const std::vector<FilterPrep> &items, int dt, hipStream_t st, int src_dt) {
   if (src_dt == DT_BF16 && dt != DT_BF16) return set_error(RESIST_EINVAL, "prepare_filters: bf16 source needs a bf16 target");
-  return items.size() == 1 ? prepare_launch<1>(items, dt, st, src_dt) : prepare_launch<kPrepSegs>(items, dt, st, src_dt);
+  if (items.size() > 1) return prepare_launch<kPrepSegs>(items, dt, st, src_dt);
+  const bool fragments = !items.empty() && ((items[0].w_lp && items[0].lp_fragments) || (items[0].wT && items[0].wT_fragments));
+  return fragments ? prepare_launch<1>(items, dt, st, src_dt) : prepare_launch<1, 32>(items, dt, st, src_dt);
 }
 
 // ---- wgrad --------------------------------------------------------------------------------------
