@@ -264,8 +264,14 @@ int pick(const IgemmArgs &a, hipStream_t st, StatParts *p) {
 }  // namespace
 
 // Up to 256 input channels (their filter rows fill 64 registers); forward without an addend, data gradients without a
-// BN whose own ReLU has to be decided again (both would take registers that the kernel does not have).
+// BN whose own ReLU has to be decided again (both would take registers that the kernel does not have).  Few pixels, over which the load of a
+// filter of more than 128 channels does not pay, nor of more than 64 before side inputs.  us, igemm_kernel | here, by 2^20 output elements:
+//   256 channels, statistics  3.0: 8.1 | 10.0   6.1: 12.6 | 14.6   8.0: 13.6 | 15.1   9.2: 19.3 | 16.6   12.3: 22.4 | 19.4    192 channels  5.7: 11.7 | 12.5   11.5: 18.0 | 16.4
+//   128 channels, data gradient with all side inputs  3.1: 9.0 | 9.8   4.0: 9.5 | 10.4   6.1: 16.3 | 15.7    forward, statistics  4.0: 7.5 | 7.7   4.6: 10.9 | 9.7
 bool conv1_takes(const IgemmArgs &a, int dt, int mode) {
+  const long long out = (long long)a.Mrows * a.OC;
+  const bool side = a.addend || a.relu_mask || a.bn_sums;
+  if (out < (a.IC > 128 ? 9LL << 20 : a.IC > 64 && mode == kBwd && side ? 6LL << 20 : 0)) return false;
   return dt == DT_BF16 && mode != kEval && a.R == 1 && a.S == 1 && a.stride == 1 && a.pad == 0 && a.IC <= 256 && a.OC >= 128 && a.OC >= 2 * a.IC &&
          !(mode == kBwd ? a.bn_sums && a.bn_self : a.addend != nullptr) && a.Mrows >= 4096;
 }

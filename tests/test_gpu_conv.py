@@ -607,8 +607,8 @@ def test_conv_fragments_second_pass_on_96_pixel_tiles():
 # and on either side of each limit
 #                     N   H   W   C    K   taken
 CONV1_CASES = [((64, 8, 8, 64, 128), True), ((65, 9, 7, 64, 128), False), ((66, 9, 7, 64, 128), True), ((1, 67, 71, 8, 136), True), ((5, 29, 31, 72, 200), True),
-               ((5, 29, 31, 104, 208), True), ((5, 29, 31, 104, 200), False), ((9, 23, 23, 136, 1000), True), ((9, 23, 23, 256, 512), True),
-               ((9, 23, 23, 264, 528), False), ((4097, 1, 1, 16, 152), True), ((70, 9, 7, 56, 120), False)]
+               ((5, 29, 31, 104, 208), True), ((5, 29, 31, 104, 200), False), ((18, 23, 23, 136, 1000), True), ((9, 23, 23, 136, 1000), False),
+               ((35, 23, 23, 256, 512), True), ((34, 23, 23, 256, 512), False), ((19, 23, 23, 264, 1056), False), ((4097, 1, 1, 16, 152), True), ((70, 9, 7, 56, 120), False)]
 
 
 @pytest.mark.parametrize("case", CONV1_CASES)
