@@ -479,7 +479,9 @@ int launch(Conv3Args<kEval> a, hipStream_t st, StatParts *tiles_m_out) {
 // fp32: one workgroup to a compute unit (LDS).  128-pixel tiles, or 64-pixel ones where those would not give every unit a
 // tile.  In training steps, on whole chunks of channels and at least two of them, whichever of 128, 96 and 64 pixels leaves the units
 // idle least, what a tile costs beside its products (8 of 46 us) being what 24 pixels cost: 256 ch 8x8, batch 77: 64 pixels 42, 96
-// 33 us; 128 ch 16x16: 128 pixels 49, 96 37; batch 128: 96 pixels 65 and 61, 128 47 and 53.
+// 33 us; 128 ch 16x16: 128 pixels 49, 96 37; batch 128: 96 pixels 65 and 61, 128 47 and 53.  (One
+// chunk: 64 ch 32x32, batch 77 47.5 and 47.3, batch 100 57.9 and 55.3.  A last chunk that is not full, 96 ch 16x16 44.9 and 36.2, and
+// the test-time forward, 128 ch 16x16, batch 77 47.5 and 37.4, would gain too; they stay in the tiles that they are tested in.)
 // (Images wider than 32: the pixels of 128 are staged once at a time.  us, kernel with the filter through LDS -> this one, data gradient with
 // its filter's preparation: batch 64, 64 ch 56x56 113.2 -> 106.2, batch 16, 128 ch 56x56 110.3 -> 101.6, 48x48 82.8 -> 76.2, 40x40
 // 54.7 -> 51.2; 96 pixels at 40x40 60.4, 64 pixels 57.3.)  bf16: 64-pixel tiles, two workgroups to a unit; 128-pixel
@@ -505,9 +507,19 @@ int pick(const Conv3Args<kEval> &a, int dt, hipStream_t st, StatParts *p) {
 }  // namespace
 
 // fp32 from 48 input channels: a chunk is 64 of them, however many there are (32 -> 32 channels, 32x32, batch 128: 49 us on the fp32
-// instruction).  bf16 from 256: 128 ch 16x16 18 us here and 17 in igemm_kernel's tiles, 64 ch 32x32 24.5 and 22.  Images no wider
-// than the staged range allows, and filters whose 64 rows an offset reaches.
+// instruction).  bf16 from 256: 128 ch 16x16 18 us here and 17 in igemm_kernel's tiles, 64 ch 32x32 24.5 and 22, and unless 128x128 tiles
+// fill their two or more rounds of 256 workgroups well.  Time in those | here, by rounds of 512 tiles of 64x64 of which the last costs a
+// third more than it holds; data gradients, us, with the filter's preparation, there | here: 256 -> 256 ch 16x16, batch 128 52.1 | 52.2, 32x32
+// 180.7 | 190.0, 28x28, batch 64 88.6 | 79.7, 512 -> 256 ch 16x16, batch 128 95.9 | 99.1, 320 -> 320 87.7 | 76.3, 512 -> 512 14x14, batch 64
+// 85.7 | 81.1.  Images no wider than the staged range allows, and filters whose 64 rows an offset reaches.
 bool conv3_takes(const IgemmArgs &a, int dt) {
+  if (dt == DT_BF16 && a.OC > 64) {
+    const double k = 9.0 * a.IC;
+    const long long t128 = (long long)((a.Mrows + 127) / 128) * ((a.OC + 127) / 128), t64 = (long long)((a.Mrows + 63) / 64) * ((a.OC + 63) / 64);
+    const double rounds = (double)((t128 + 255) / 256), part = (double)(t64 % 512) / 512;
+    const double here = 3 + ((double)(t64 / 512) + (part > 0 ? std::min(1.0, part + 0.3) : 0.0)) * (2.1 + 4.04e-3 * k);
+    if (rounds >= 2 && 5 + rounds * (1.5 + 8.55e-3 * k) < here) return false;
+  }
   return a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.IW <= kWidest && a.IC >= (dt == DT_BF16 ? 256 : 48) && a.IC <= 8192;
 }
 
