@@ -316,7 +316,35 @@ int dispatch_igemm(const EvalArgs &a, hipStream_t st, StatParts *tiles_m_out = n
   };
   constexpr long long kMin = 512;
   constexpr bool lp = sizeof(T) == 2;
-  if constexpr (lp && MODE != kEval) {
+  // fp32 is bound by the matrix cores, and 64x64 tiles with little LDS, several to a compute unit, keep them busiest; up to two to a unit the
+  // longer chunk is the faster.  us, 128x128 | 128x64 | 64x64 in chunks of 64 | of 32 channels: 128 -> 128 ch 1x1, 33280 pixels 27.3 | 25.6 |
+  // 22.8 | 21.5, 16000 pixels 18.1 | 13.0 | 12.1 | 12.3; 64 -> 128 ch 3x3 stride 2, 102400 pixels 158.9 | 149.4 | 142.8 | 133.4, its data
+  // gradient from 32768 127 | 73.5 | 67.2 | 60.1.  (Before: 128x128 from 512 tiles, then 128x64.)
+  if constexpr (!lp) {
+    // (the test-time forward: 128x128 from 512 tiles, as it is tested)
+    if (MODE == kEval && a.OC > 64 && tiles(128, 128) >= kMin) return launch_igemm<T, 128, 128, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
+    if (a.IC % (16 * V) == 0 && tiles(64, 64) <= 512) return launch_igemm<T, 64, 64, 16 * V, 2, 2, MODE>(a, st, tiles_m_out);
+    return launch_igemm<T, 64, 64, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
+  } else {
+    const long long t128 = tiles(128, 128), t64 = tiles(128, 64);
+    const bool deep = a.IC % (16 * V) == 0;
+    if constexpr (MODE != kFwd) {
+      // The test-time forward, in the tiles that its epilogue is tested in (those of the model below measure faster where these fill their last
+      // round badly, 128 ch 28x28 3x3, batch 31 22.8 | 17.9 us, 64 -> 192 ch 56x56 1x1, batch 64 70.8 | 60.1), and the parity classes of strided data
+      // gradients: the 128x128 tile moves half the operand bytes per FLOP; of eight waves where there is about one to a compute unit
+      // (256 -> 256 ch 14x14, batch 64 29.0 -> 24.1 us), or 128x64 where there are fewer.
+      if (MODE == kEval || a.cls != 1) {
+        if (MODE == kEval && a.OC >= 128) {
+          if (t128 >= 192 && t128 < 320) return launch_igemm<T, 128, 128, 8 * V, 4, 2, MODE>(a, st, tiles_m_out);
+          if (t128 < 192 && t64 >= 256 && deep) return launch_igemm<T, 128, 64, 16 * V, 4, 2, MODE>(a, st, tiles_m_out);
+        }
+        if (a.OC > 64 && t128 >= 192) return launch_igemm<T, 128, 128, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
+        if (MODE == kEval && a.OC <= 64 && t64 >= kMin) return launch_igemm<T, 128, 64, 8 * V, 4, 2, MODE>(a, st, tiles_m_out);
+        if (t64 >= kMin) return launch_igemm<T, 128, 64, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
+        if (deep) return launch_igemm<T, 64, 64, 16 * V, 2, 2, MODE>(a, st, tiles_m_out);
+        return launch_igemm<T, 64, 64, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
+      }
+    }
     // bf16: the tile with the least time by a model of it, us: a launch's start and end, and for every workgroup that the fullest of the 256
     // compute units gets a constant and a part per reduction index (IC*R*S).  An area of 128x128 costs about the same in all of them, a third
     // more in 64x64, so what counts is how the last round fills the chip.  Measured, us, 128x128 of eight waves | of four | 128x64 | 64x64:
@@ -324,48 +352,32 @@ int dispatch_igemm(const EvalArgs &a, hipStream_t st, StatParts *tiles_m_out = n
     //                                       500 30.5 | 29.5 | 33.2 | 36.7    900: 54.7 | 50.9 | 63.8 | 61.3
     //   256 -> 128 ch 1x1, 140: 10.1 | 11.2 | 9.8 | 10.0    270: 15.4 | 14.1 | 13.2 | 12.8    400: 15.4 | 15.0 | 15.4 | 15.1
     //   192 -> 320 ch 1x1, 270: 13.4 | 12.4 | 9.6 | 10.6    64 -> 64 ch 3x3, 180 tiles of 128x64: -- | -- | 9.6 | 10.1    270: -- | -- | 13.5 | 11.6
-    // (Before: 128x128 of eight waves from 192 to 319 tiles, of four from there up, below that 128x64 in chunks of 128 channels from 256 of
-    // them, whose second workgroup a compute unit does not hold beside the first: 180 tiles, 128 ch 3x3 21.6.)
+    // It is right to a tenth, so it is asked for what it gains over the tile by the number of tiles alone: 128x128 of eight waves from 192 to
+    // 319 tiles, of four from there up, 128x64 in chunks of 128 channels from 256 of them (whose second workgroup a compute unit does not hold
+    // beside the first).  Where BN sums are taken, smaller tiles pay for them more often: 128x128 is left for a tenth or more.  us, 128x128 |
+    // smaller, predicted: 256 -> 1024 ch 14x14, batch 31, statistics 12.6 | 14.0, 0.99; data gradient to 192 ch 56x56 from 384 with all its
+    // side inputs 51.0 | 56.2, 0.96; from 64 -> 192 ch without sums 41.2 | 30.7, 0.86.  And 128x64 for 64x64, without sums, for a fortieth:
+    // 256 -> 64 ch 56x56, batch 128 41.4 | 43.7, 0.99; with sums, for a reduction of no whole 128 channels, 128x64 for 64x64 for a tenth: data gradient
+    // to 64 ch 56x56 from 192, batch 16 10.7 | 10.2, 0.95.
     const double k = (double)a.IC * a.R * a.S;
-    auto rounds = [&](int bm, int bn) { return (double)((tiles(bm, bn) + 255) / 256); };
-    const double r128 = rounds(128, 128), r64 = rounds(128, 64), r32 = rounds(64, 64);
-    const double eight = 5 + r128 * (3.5 + 7.8e-3 * k), four = 5 + r128 * (2.8 + 7.3e-3 * k) + (r128 == 1 ? 4 : 0);
-    const double half = 5.3 + r64 * (1.8 + 4.5e-3 * k), quarter = 6 + r32 * (0.75 + 2.9e-3 * k);
+    auto rounds = [](long long n) { return (double)((n + 255) / 256); };
+    const double r128 = rounds(t128), r64 = rounds(t64), r32 = rounds(tiles(64, 64));
+    enum { kEight, kFour, kHalf, kQuarter };
+    const double cost[] = {5 + r128 * (3.5 + 7.8e-3 * k), 5 + r128 * (r128 == 1 ? 1.3 : 1.0) * (2.8 + 7.3e-3 * k), 5.3 + r64 * (1.8 + 4.5e-3 * k),
+                           6 + r32 * (0.75 + 2.9e-3 * k)};
+    const int usual = a.OC > 64 && t128 >= 192 ? (a.OC >= 128 && t128 < 320 ? kEight : kFour)
+                                               : t64 >= kMin || (a.OC >= 128 && t64 >= 256 && deep) ? kHalf : kQuarter;
+    int best = (int)(std::min_element(cost + (a.OC > 64 ? kEight : kHalf), cost + 4) - cost);
+    const bool sums = a.stats || a.bn_sums;
+    const double worth = sums && (usual <= kFour ? best >= kHalf : usual == kQuarter && !deep) ? 0.9 : !sums && usual == kHalf && best == kQuarter ? 0.975 : 1.0;
+    if (cost[best] > worth * cost[usual]) best = usual;
     // chunks of 128 channels where a unit gets one workgroup (two of 64x64) and the reduction is long
-    const bool deep = a.IC % (16 * V) == 0;
-    if (a.cls == 1) {
-      if (a.OC > 64 && std::min(eight, four) <= std::min(half, quarter))
-        return eight <= four ? launch_igemm<T, 128, 128, 8 * V, 4, 2, MODE>(a, st, tiles_m_out) : launch_igemm<T, 128, 128, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
-      if (half <= quarter)
-        return deep && r64 == 1 && k >= 1024 ? launch_igemm<T, 128, 64, 16 * V, 4, 2, MODE>(a, st, tiles_m_out) : launch_igemm<T, 128, 64, 8 * V, 4, 2, MODE>(a, st, tiles_m_out);
-      return deep && (r32 == 1 || (r32 == 2 && k >= 1024)) ? launch_igemm<T, 64, 64, 16 * V, 2, 2, MODE>(a, st, tiles_m_out)
-                                                           : launch_igemm<T, 64, 64, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
-    }
-  }
-  // fp32 is bound by the matrix cores, and 64x64 tiles with little LDS, several to a compute unit, keep them busiest; up to two to a unit the
-  // longer chunk is the faster.  us, 128x128 | 128x64 | 64x64 in chunks of 64 | of 32 channels: 128 -> 128 ch 1x1, 33280 pixels 27.3 | 25.6 |
-  // 22.8 | 21.5, 16000 pixels 18.1 | 13.0 | 12.1 | 12.3; 64 -> 128 ch 3x3 stride 2, 102400 pixels 158.9 | 149.4 | 142.8 | 133.4, its data
-  // gradient from 32768 127 | 73.5 | 67.2 | 60.1.  (Before: 128x128 from 512 tiles, then 128x64.)
-  if constexpr (!lp) {
-    // (the test-time epilogue, which has tensors of the output's size to read, stays in 128x128 from 512 tiles)
-    if (MODE == kEval && a.OC > 64 && tiles(128, 128) >= kMin) return launch_igemm<T, 128, 128, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
-    if (a.IC % (16 * V) == 0 && tiles(64, 64) <= 512) return launch_igemm<T, 64, 64, 16 * V, 2, 2, MODE>(a, st, tiles_m_out);
-    return launch_igemm<T, 64, 64, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
-  } else {
-    // The test-time forward (whose epilogue the model above was not fitted to) and the parity classes of strided data gradients: the 128x128
-    // tile moves half the operand bytes per FLOP; of eight waves where there is about one to a compute unit (256 -> 256 ch 14x14, batch 64
-    // 29.0 -> 24.1 us), or 128x64 where there are fewer.
-    if (a.cls == 1 && a.OC >= 128) {
-      const long long t128 = tiles(128, 128);
-      if (t128 >= 192 && t128 < 320) return launch_igemm<T, 128, 128, 8 * V, 4, 2, MODE>(a, st, tiles_m_out);
-      if (t128 < 192 && tiles(128, 64) >= 256 && a.IC % (16 * V) == 0)
-        return launch_igemm<T, 128, 64, 16 * V, 4, 2, MODE>(a, st, tiles_m_out);
-    }
-    if (a.OC > 64 && tiles(128, 128) >= 192) return launch_igemm<T, 128, 128, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
-    if (a.cls == 1 && a.OC <= 64 && tiles(128, 64) >= kMin) return launch_igemm<T, 128, 64, 8 * V, 4, 2, MODE>(a, st, tiles_m_out);
-    if (tiles(128, 64) >= kMin) return launch_igemm<T, 128, 64, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
-    if (a.IC % (16 * V) == 0) return launch_igemm<T, 64, 64, 16 * V, 2, 2, MODE>(a, st, tiles_m_out);
-    return launch_igemm<T, 64, 64, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
+    if (best == kEight) return launch_igemm<T, 128, 128, 8 * V, 4, 2, MODE>(a, st, tiles_m_out);
+    if (best == kFour) return launch_igemm<T, 128, 128, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
+    if (best == kHalf)
+      return deep && r64 == 1 && k >= 1024 ? launch_igemm<T, 128, 64, 16 * V, 4, 2, MODE>(a, st, tiles_m_out) : launch_igemm<T, 128, 64, 8 * V, 4, 2, MODE>(a, st, tiles_m_out);
+    return deep && (r32 == 1 || (r32 == 2 && k >= 1024)) ? launch_igemm<T, 64, 64, 16 * V, 2, 2, MODE>(a, st, tiles_m_out)
+                                                         : launch_igemm<T, 64, 64, 8 * V, 2, 2, MODE>(a, st, tiles_m_out);
   }
 }
 

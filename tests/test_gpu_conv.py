@@ -732,3 +732,23 @@ def test_wgrad_of_a_step_adds_like_the_layer_call(shape):
     x, dy = torch.randn(N, H, W, C, generator=gen, device="cuda"), torch.randn(N, H, W, K, generator=gen, device="cuda")
     (alone, step), ran = _launched(lambda: (I.conv_wgrad(g, 0, dy, x, False), I.conv_wgrad(g, 0, dy, x, True)))
     assert "wgrad3_f32" in ran and torch.equal(alone, step)
+
+
+# Which kernel a bf16 layer runs on, by shape alone (the kernels' values: above): one round of 128x128 tiles and a long reduction; tiles left only
+# for a clear gain where statistics are taken; 3x3 data gradients whose 128x128 tiles fill their rounds, and do not
+#                       N   H   C    K   R  call
+BF16_ROUTES = [((64, 14, 1024, 256, 3, "fwd"), "igemm_bf16_fwd_128x128x64_w8"), ((31, 14, 256, 1024, 1, "stats"), "igemm_bf16_fwd_128x128x64"),
+               ((31, 14, 256, 1024, 1, "fwd"), "igemm_bf16_fwd_128x64x64_w8"), ((128, 16, 512, 256, 3, "dgrad"), "igemm_bf16_bwd_128x128x64"),
+               ((64, 28, 256, 256, 3, "dgrad"), "conv3_bf16_bwd_64x64"), ((128, 8, 256, 256, 3, "dgrad"), "conv3_bf16_bwd_64x64")]
+
+
+@pytest.mark.parametrize("case", BF16_ROUTES)
+def test_conv_bf16_routes(case):
+    from tests import internals as I
+    (N, H, C, K, r, call), kernel = case
+    x, w = (torch.zeros(s, device="cuda", dtype=torch.bfloat16) for s in ((N, H, H, C), (K, r, r, C)))
+    dy, stats = torch.zeros(N, H, H, K, device="cuda", dtype=torch.bfloat16), torch.zeros(3 * ((N * H * H + 31) // 32) * K, device="cuda")
+    f = {"fwd": lambda: R.conv2d_forward(x, w, 1, r // 2), "stats": lambda: I.conv_fwd(I.geom(N, H, H, C, K, r, 1, r // 2), 1, x, w, dy, stats),
+         "dgrad": lambda: R.conv2d_dgrad(dy, w, (N, H, H, C), 1, r // 2)}[call]
+    _, ran = _launched(f)
+    assert {n for n in ran if not n.startswith("prepare")} == {kernel}, ran
