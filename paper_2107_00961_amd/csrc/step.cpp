@@ -17,7 +17,11 @@ inline double geom_flops(const ConvGeom &g) { return 2.0 * g.N * g.P * g.Q * g.K
 // chain data gradient -> BN backward -> next layer, whose short kernels then overlap with them.  A
 // weight gradient starts once its output gradient is complete (fork), and a buffer it reads is not
 // overwritten before it has finished (before_write).
+// Steps of less convolution work than this, about 20 GFLOP, are bound by launch latency, and the event calls of the second stream cost more than
+// the overlap returns: everything stays on the caller's stream, and two buffers serve for the output gradients.
+constexpr double kSideFlops = 2e10;
 constexpr int kDyRing = 6;
+inline int dy_buffers(double flops) { return flops >= kSideFlops ? kDyRing : 2; }
 struct WgradSide {
   SideStream side;
   int dt;
@@ -31,10 +35,9 @@ struct WgradSide {
   int launched = 0, waited = 0;
   std::vector<std::pair<const void *, int>> readers;   // buffer -> its last reader
   std::vector<std::pair<int, hipEvent_t>> marks;       // events behind weight gradients, ascending
-  // `flops`: convolution work of the step.  Below ~20 GFLOP a step is bound by launch latency and the
-  // event calls of the second stream cost more than the overlap returns: everything stays on `main`.
-  WgradSide(hipStream_t main, int dt_, float *splitk_, double flops)
-      : side(main, overlap_mode() == 2 || (overlap_mode() == 1 && flops >= 2e10)), dt(dt_), splitk(splitk_) {}
+  // flops: convolution work of the step; dys: its dy_buffers(flops) output-gradient buffers
+  WgradSide(hipStream_t main, int dt_, float *splitk_, double flops, void *const *dys_)
+      : side(main, overlap_mode() == 2 || (overlap_mode() == 1 && flops >= kSideFlops)), dt(dt_), splitk(splitk_), dys(dys_), ndy(dy_buffers(flops)) {}
   hipStream_t stream() const { return side.stream(); }
   int mark() {
     hipEvent_t e = nullptr;
@@ -78,11 +81,11 @@ struct WgradSide {
     return RESIST_OK;
   }
   // output gradients take turns in a ring of buffers
-  void *const *dys = nullptr;
-  int next_dy = 0;
+  void *const *dys;
+  int ndy, next_dy = 0;
   int take_dy(void **buf) {
     *buf = dys[next_dy];
-    next_dy = (next_dy + 1) % kDyRing;
+    next_dy = (next_dy + 1) % ndy;
     return before_write(*buf);
   }
   // Filters as the convolutions read them.  What the forward pass multiplies is made first, on the caller's stream; in fp32 mode
@@ -193,6 +196,7 @@ struct StepPlan {
   int feat_hw = 0;
   // shared scratch
   void *gbuf[2] = {nullptr, nullptr}, *gm = nullptr, *dys[kDyRing] = {}, *da = nullptr;
+  double flops = 0;                   // convolution work of the step
   float *splitk = nullptr;
   float *stats = nullptr;             // per-tile column sums left by a forward convolution
   double *bn_scratch = nullptr;
@@ -277,6 +281,7 @@ int build_plan(const resist_model_desc *desc, const int32_t *blocks, int32_t nbl
     max_act = std::max<int64_t>(max_act, (int64_t)c.g.N * c.g.H * c.g.W * c.g.C);
     (void)needs_dgrad;
     max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(c.g, net.d.compute_dtype, true));
+    P->flops += 3.0 * geom_flops(c.g);
     max_c = std::max(max_c, c.g.K);
   };
 
@@ -368,7 +373,7 @@ int build_plan(const resist_model_desc *desc, const int32_t *blocks, int32_t nbl
   P->gbuf[0] = A.take_act(max_act, es);
   P->gbuf[1] = A.take_act(max_act, es);
   P->gm = A.take_act(max_act, es);
-  for (void *&p : P->dys) p = A.take_act(max_act, es);
+  for (int i = 0; i < dy_buffers(P->flops); ++i) P->dys[i] = A.take_act(max_act, es);
   P->da = A.take_act(max_act, es);
   P->splitk = A.take<float>(max_splitk);
   P->stats = A.take<float>(max_stats);
@@ -540,6 +545,7 @@ struct PrePlan {
   const void *feat_in = nullptr;
   int feat_hw = 0;
   void *gbuf[2] = {nullptr, nullptr}, *sc = nullptr, *dsgrad = nullptr, *dys[kDyRing] = {}, *da = nullptr;
+  double flops = 0;                   // convolution work of the step
   float *splitk = nullptr, *stats = nullptr;
   double *bn_scratch = nullptr;
   std::vector<float *> own_grads;
@@ -565,6 +571,7 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
     max_act = std::max<int64_t>(max_act, (int64_t)g.N * g.P * g.Q * g.K);
     max_act = std::max<int64_t>(max_act, (int64_t)g.N * g.H * g.W * g.C);
     max_splitk = std::max<int64_t>(max_splitk, wgrad_scratch_floats(g, net.d.compute_dtype, true));
+    P->flops += 3.0 * geom_flops(g);
     if (stats) max_stats = std::max<int64_t>(max_stats, conv_stats_floats(g));
     max_c = std::max(max_c, std::max(g.K, g.C));
   };
@@ -650,7 +657,7 @@ int build_preact_plan(const resist_model_desc *desc, const int32_t *blocks, int3
   P->gbuf[1] = A.take_act(max_act, es);
   P->sc = A.take_act(max_act, es);
   P->dsgrad = A.take_act(max_act, es);
-  for (void *&p : P->dys) p = A.take_act(max_act, es);
+  for (int i = 0; i < dy_buffers(P->flops); ++i) P->dys[i] = A.take_act(max_act, es);
   P->da = A.take_act(max_act, es);
   P->splitk = A.take<float>(max_splitk);
   P->stats = A.take<float>(max_stats);
@@ -685,12 +692,7 @@ int local_step_preact(const resist_model_desc *desc, const int32_t *blocks, int3
   const float eps = net.d.bn_eps, bnm = net.d.bn_momentum;
   auto params = [&](int slot) { return (float *)block_params[slot]; };
   auto grads = [&](int slot) { return block_grads ? (float *)block_grads[slot] : P.own_grads[slot]; };
-  double step_flops = 0;
-  for (PreBlock &pb : P.blocks) {
-    for (PreUnit &un : pb.units) step_flops += 3.0 * geom_flops(un.g);
-    if (pb.has_ds) step_flops += 3.0 * geom_flops(pb.dsg);
-  }
-  WgradSide wg(st, dt, P.splitk, step_flops);
+  WgradSide wg(st, dt, P.splitk, P.flops, P.dys);
   {
     std::vector<FilterPrep> prep;
     for (PreBlock &pb : P.blocks) {
@@ -745,7 +747,6 @@ int local_step_preact(const resist_model_desc *desc, const int32_t *blocks, int3
   RESIST_TRY(avgpool_bwd(dt, P.dpooled, nullptr, P.da, N, P.feat_hw, CH, st));
   int gi = 0;
   RESIST_TRY(wg.filters_ready());
-  wg.dys = P.dys;
   hipEvent_t ready = wg.side.kernel_event();   // carried by the last kernel that writes what the next weight gradient reads
   RESIST_TRY(bn_backward(dt, P.da, true, P.feat_in, P.head_rows, CH, hb, P.gbuf[gi], nullptr, P.bn_scratch, st, nullptr, StatParts{}, ready));
   for (int bi = (int)P.blocks.size() - 1; bi >= 0; --bi) {
@@ -864,14 +865,9 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
   auto grads = [&](int slot) { return block_grads ? (float *)block_grads[slot] : P.own_grads[slot]; };
 
   const int dt = net.d.compute_dtype;
-  double step_flops = 0;
-  for (BlockPlan &bp : P.blocks) {
-    for (ConvLayer &c : bp.convs) step_flops += 3.0 * geom_flops(c.g);
-    if (bp.has_ds) step_flops += 3.0 * geom_flops(bp.ds.g);
-  }
-  WgradSide wg(st, dt, P.splitk, step_flops);
-  // every filter once, up front: the transpose the data gradient reads and, in bf16 mode, the copy
-  // the forward convolution multiplies with (fp32 mode multiplies the master itself)
+  WgradSide wg(st, dt, P.splitk, P.flops, P.dys);
+  // every filter once, up front, as the convolutions read it (Prepared): in matrix fragments, fp32 3x3 layers of stride 1 in three parts,
+  // 6 bytes a value; else in rows, for a data gradient transposed and in bf16 a copy (fp32 reads the master itself)
   {
     std::vector<FilterPrep> prep;
     for (BlockPlan &bp : P.blocks) {
@@ -961,7 +957,6 @@ extern "C" int resist_local_step(const resist_model_desc *desc, const int32_t *b
   const bool fuse_bn = bn_fusion_mode() == 2 || (bn_fusion_mode() == 1 && dt == DT_BF16);
   StatParts pre{};        // P.stats holds the first pass for the BN that ends the block below
   bool have_pre = false;
-  wg.dys = P.dys;
   int gi = 0;
   void *G = P.gbuf[gi];
   RESIST_TRY(avgpool_bwd(dt, P.dpooled, P.feat, G, N, P.feat_hw, CH, st));

@@ -347,12 +347,13 @@ def test_second_stream_changes_no_bit(name, bf16):
 
 @pytest.mark.parametrize("bf16", [False, True])
 def test_second_stream_changes_no_bit_when_a_step_takes_more_events_than_the_ring_holds(bf16):
-    """The events that order the two streams come from a ring of 256 per device.  A step of a 90-block
-    network records about 370 of them, so the ring wraps inside a step; every event that is still to be
+    """The events that order the two streams come from a ring of 256 per device.  A step of a 130-block
+    network takes about 400 of them (one a BN backward, one behind every second weight gradient, a few forks),
+    so the ring wraps inside a step; every event that is still to be
     waited for must have been waited for by then.  Same check as above: bit-identical to one stream."""
     basic = get_config("cfg1")["model"]
-    model = dict(basic, widths=[16, 32], blocks=[45, 45], in_h=8, in_w=8, num_classes=10, compute_dtype=1 if bf16 else 0)
-    blocks, batch = list(range(90)), 8
+    model = dict(basic, widths=[16, 32], blocks=[65, 65], in_h=8, in_w=8, num_classes=10, compute_dtype=1 if bf16 else 0)
+    blocks, batch = list(range(130)), 8
     params = make_params(model, 9, perturb_bn=True)
     outs = []
     try:

@@ -87,6 +87,16 @@ def test_conv_weight_layout_is_krsc():
     assert flat[((k * 3 + r) * 3 + s) * 16 + c] == w[k, c, r, s]
 
 
+@pytest.mark.parametrize("kind", [0, 2])
+def test_workspace_of_a_step_too_small_for_the_second_stream(kind):
+    """Below 20 GFLOP a step gets along with two output-gradient buffers: 16 tensors of the activations' size in all, where from there
+    up there are four more (1416 images of 14.1 MFLOP)."""
+    model = dict(get_config("cfg1")["model"], block_kind=kind)
+    act = lambda batch: 4 * batch * 16 * 16 * 16
+    small, large = R.workspace_bytes(model, [0, 1], 1410) / act(1410), R.workspace_bytes(model, [0, 1], 1420) / act(1420)
+    assert small < 16.5 and 3.9 < large - small < 4.1
+
+
 def test_workspace_and_step_argument_errors():
     model = get_config("cfg2")["model"]
     with pytest.raises(R.ResistError, match="first block"):
