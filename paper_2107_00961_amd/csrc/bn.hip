@@ -438,7 +438,7 @@ unsigned apply_grid_x(int64_t M, const ColMap &m, int rows_per_thread) {
 
 inline int vec_of(int dt) { return dt == DT_BF16 ? 8 : 4; }
 
-// thread rows and parts in flight by the length of the list: every part of a list of up to 1024 in flight at once
+// thread rows and parts in flight by the length of the list: every part of a list of up to 512 in flight at once, of a longer one 512
 template <typename S>
 void launch_final(const S *sums, int parts, int C, const BnBufs &b, hipStream_t st) {
   if (parts <= 32) hipLaunchKernelGGL((bn_bwd_final_kernel<S, 16, 2>), dim3(C / 16), dim3(256), 0, st, sums, parts, C, b.dgamma, b.dbeta);

@@ -667,8 +667,7 @@ def test_conv_f32_tiles(case):
     assert_close(y.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_fwd(x, w, st, r // 2), f"fwd {case}")
     if back:
         dx, ran = _launched(lambda: R.conv2d_dgrad(dyd, wd, (N, H, W, C), st, r // 2))
-        if K % 64 == 0 or back == "64x64x32":
-            assert {n for n in ran if n.startswith("igemm")} == {f"igemm_f32_bwd_{back}"}, ran
+        assert {n for n in ran if n.startswith("igemm")} == {f"igemm_f32_bwd_{back}"}, ran
         assert_close(dx.cpu().numpy().transpose(0, 3, 1, 2), L.conv2d_dgrad(dy, w, x.shape, st, r // 2), f"dgrad {case}")
 
 
@@ -752,3 +751,51 @@ def test_conv_bf16_routes(case):
          "dgrad": lambda: R.conv2d_dgrad(dy, w, (N, H, H, C), 1, r // 2)}[call]
     _, ran = _launched(f)
     assert {n for n in ran if not n.startswith("prepare")} == {kernel}, ran
+
+
+# Streamed 1x1 layers as a step calls them: statistics of the outputs, and data gradients with an addend (which may be the output), a mask and
+# the sums for a BN, each there or not.  Sums are compared with those of the values as stored: 12 roundings as above, of the sum of magnitudes.
+#                        N    H   W   C    K
+CONV1_SIDE_CASES = [(66, 9, 7, 64, 128), (1, 67, 71, 8, 136), (50, 29, 31, 72, 200), (18, 23, 23, 136, 1000), (35, 23, 23, 256, 512), (4097, 1, 1, 16, 152)]
+
+
+@pytest.mark.parametrize("case", CONV1_SIDE_CASES)
+def test_conv_streamed_1x1_in_a_step(case):
+    from tests import internals as I
+    print("case", case, flush=True)
+    N, H, W, C, K = case
+    M, bound = N * H * W, 12 * 2.0 ** -24
+    gen = torch.Generator(device="cuda").manual_seed(55)
+    T = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16)
+    x, w = T(M, C), (T(K, C).float() / C ** 0.5).to(torch.bfloat16)
+    prod = x.double() @ w.double().t()
+    y, stats = torch.empty(M, K, device="cuda", dtype=torch.bfloat16), torch.zeros(3 * ((M + 63) // 64) * K, device="cuda")
+    (parts, rows), ran = _launched(lambda: I.conv_fwd(I.geom(N, H, W, C, K, 1, 1, 0), 1, x, w, y, stats))
+    assert any(n.startswith("conv1_bf16_fwd") for n in ran), ran
+    assert bool(((y.double() - prod).abs() <= 2.0 ** -8 * prod.abs() + 1e-5).all())
+    k, s1, s2 = (t.double() for t in stats[:3 * parts * K].view(3, parts, K))
+    for p in range(parts):
+        d = y[p * rows:(p + 1) * rows].double() - k[p]
+        assert bool(((s1[p] - d.sum(0)).abs() <= bound * d.abs().sum(0)).all()) and bool(((s2[p] - d.square().sum(0)).abs() <= bound * d.square().sum(0)).all())
+    g = I.geom(N, H, W, K, C, 1, 1, 0)
+    add, mask, by = T(M, K), T(M, K), T(M, K)
+    mask[0], mask[1, ::2] = 0, float("nan")   # neither is larger than zero
+    mean, invstd = (torch.rand(K, generator=gen, device="cuda") + 0.5 for _ in range(2))
+    for addend in ("none", "own", "out"):
+        for masked in (False, True):
+            for sums in (False, True):
+                dx = add.clone() if addend == "out" else torch.empty_like(add)
+                bn = dict(y=by, mean=mean, invstd=invstd, scale=mean, shift=mean, self=False, sums=torch.zeros(2 * ((M + 63) // 64) * K, device="cuda")) if sums else None
+                (parts, rows), ran = _launched(lambda: I.conv_dgrad(g, 1, x, w, dx, dx if addend == "out" else add if addend == "own" else None,
+                                                                    mask if masked else None, bn))
+                assert any(n.startswith("conv1_bf16_bwd") for n in ran), ran
+                want = prod + (add.double() if addend != "none" else 0.0)
+                if masked:
+                    want = torch.where(mask > 0, want, torch.zeros_like(want))
+                assert bool(((dx.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all()), (addend, masked, sums)
+                if sums:
+                    s1, s2 = (t.double() for t in bn["sums"][:2 * parts * K].view(2, parts, K))
+                    for p in range(parts):
+                        gm, c = dx[p * rows:(p + 1) * rows].double(), (by[p * rows:(p + 1) * rows].double() - mean.double()) * invstd.double()
+                        assert bool(((s1[p] - gm.sum(0)).abs() <= bound * gm.abs().sum(0)).all()), (addend, masked, p)
+                        assert bool(((s2[p] - (gm * c).sum(0)).abs() <= bound * (gm * c).abs().sum(0)).all()), (addend, masked, p)

@@ -97,10 +97,11 @@ def test_local_step_small_bn_first_pass_from_the_data_gradient(name):
 
 
 # Lists of per-tile sums around the lengths at which the kernels that add them change their shape (32 and 128 tiles of 32 rows,
-# the last one ragged or not), forward and, taken by the data gradient, backward.  Forward quantities to the element; the last
+# the last one ragged or not) or go round once more (512 of 64 rows), forward and, taken by the data gradient, backward.  Forward quantities to the element; the last
 # block's BN gradients, behind one ReLU, as tensors (7e4 decisions, each within 1e-6 of a tie: at most one falls the other way,
 # a few 1e-3 of the norm).
-@pytest.mark.parametrize("hw,batch", [((16, 16), 4), ((12, 12), 8), ((12, 20), 17), ((16, 16), 16), ((12, 20), 18), ((16, 16), 17)])
+@pytest.mark.parametrize("hw,batch", [((16, 16), 4), ((12, 12), 8), ((12, 20), 17), ((16, 16), 16), ((12, 20), 18), ((16, 16), 17), ((16, 16), 128),
+                                      ((16, 16), 129), ((12, 20), 138)])
 @pytest.mark.parametrize("fusion", [1, 2])
 def test_bn_sums_of_many_tiles(hw, batch, fusion):
     model = dict(get_config("cfg1")["model"], in_h=hw[0], in_w=hw[1], blocks=[1])
@@ -343,6 +344,67 @@ def test_second_stream_changes_no_bit(name, bf16):
     for other in outs[1:]:
         for a, b in zip(outs[0], other):
             assert a.tobytes() == b.tobytes()
+
+
+@pytest.mark.parametrize("kind,bf16", [(0, False), (0, True), (1, True), (2, False), (3, True)])
+def test_second_stream_changes_no_bit_in_a_large_step(kind, bf16):
+    """Above 20 GFLOP a step has six output-gradient buffers and takes the second stream by default: steps that nothing waits
+    between, with another worker's in between, against the same on one stream, one at a time."""
+    basic = get_config("cfg1")["model"]
+    model = dict(basic, block_kind=kind, widths=[64, 128], blocks=[5, 4], in_h=32, in_w=32, compute_dtype=1 if bf16 else 0)
+    blocks, batch = list(range(9)), 32
+    params = make_params(model, 9, perturb_bn=True)
+    batches = [to_device_batch(*make_batch(model, batch, 80 + it)) for it in range(3)]
+    outs = []
+    try:
+        for overlap in (0, 1):
+            R.set_overlap(overlap)
+            sub, other = SubResNet(model, blocks, params, batch), SubResNet(model, blocks, params, batch)
+            for xd, yd in batches:
+                sub.step(xd, yd, 0.01, 0.9, 1e-4)
+                if overlap:
+                    other.step(yd.float().view(-1, 1, 1, 1) * xd, yd, 0.01, 0.9, 1e-4)
+                else:
+                    torch.cuda.synchronize()
+            torch.cuda.synchronize()
+            outs.append([t.cpu().numpy().copy() for t in sub.params + sub.momentum + sub.grads] + [sub.loss.cpu().numpy().copy()])
+    finally:
+        R.set_overlap(True)
+    assert np.isfinite(outs[0][-1]).all()
+    for a, b in zip(*outs):
+        assert a.tobytes() == b.tobytes()
+
+
+@pytest.mark.parametrize("name", ["strided_sub", "bottleneck_sub", "preact_full"])
+@pytest.mark.parametrize("bf16,overlap", [(False, 0), (False, 2), (True, 2)])
+def test_captured_step(name, bf16, overlap):
+    """A step captured into a graph, on one stream and with the second one: every replay, with other work and waits in between, gives
+    the bits of a step that is launched."""
+    model, blocks, batch = _small_models()[name]
+    model = dict(model, compute_dtype=1 if bf16 else 0)
+    params = make_params(model, 5, perturb_bn=True)
+    xd, yd = to_device_batch(*make_batch(model, batch, 40))
+    try:
+        R.set_overlap(overlap)
+        warm, sub, ref = (SubResNet(model, blocks, params, batch) for _ in range(3))
+        for _ in range(16):   # the second stream and its events are made on first use
+            warm.step(xd, yd, 0.05, 0.9, 1e-4)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            sub.step(xd, yd, 0.05, 0.9, 1e-4)
+        for it in range(4):
+            print(name, bf16, overlap, "replay", it, flush=True)
+            graph.replay()
+            if it % 2:
+                torch.cuda.synchronize()
+            ref.step(xd, yd, 0.05, 0.9, 1e-4)
+            warm.step(xd, yd, 0.05, 0.9, 1e-4)
+            torch.cuda.synchronize()
+            for a, b in zip(sub.params + sub.momentum + sub.grads + [sub.loss], ref.params + ref.momentum + ref.grads + [ref.loss]):
+                assert a.cpu().numpy().tobytes() == b.cpu().numpy().tobytes(), it
+    finally:
+        R.set_overlap(True)
 
 
 @pytest.mark.parametrize("bf16", [False, True])
