@@ -167,7 +167,9 @@ __global__ __launch_bounds__(kNT, NP == 3 ? 2 : 4) void conv3_kernel(Conv3Args<M
 #pragma unroll
   for (int t = 0; t < kRing; ++t) fetch_b(t, t, 0);
   // Three taps of bf16 products are over before a line arrives from beyond the L2, and all workgroups of an XCD walk the filter
-  // in step.  So those that share it ask for a part each, up front.
+  // in step.  So those that share it ask for a part each, up front.  us a layer of a step, without -> with: 256 ch 8x8 and 512 ch
+  // 4x4 (the mean of a network's 50), batch 64 16.5 -> 14.8, batch 128 20.7 -> 20.2, 512 ch 7x7 with 256 ch 14x14, batch 16
+  // 19.3 -> 17.9, batch 64 29.4 -> 28.5.
   f32x4 ahead[NP == 1 ? kAhead : 1];
   if constexpr (NP == 1) {
     const int first = (tm % a.share) * a.ahead * kNT * 16 + tid * 16;
